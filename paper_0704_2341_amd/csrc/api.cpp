@@ -47,7 +47,7 @@ grg_status diag_schur_apply_internal(grg_schur S, const double *xb, double *yb, 
 grg_status tune_dc(grg_schur S, int prec, int nrhs, int reps);
 grg_status tune_eo(grg_schur S, int prec, int nrhs, int reps);
 DslashTune default_eo_tune(const Geom &gh, int prec, int nrhs);
-DslashTune default_dc_tune(const Geom &g);
+DslashTune default_dc_tune(const Geom &g, int prec, int nrhs);
 bool dc_launch_ok(const Geom &g, int prec, int nrhs, const DslashTune &t);
 bool eo_launch_ok(const Geom &gh, int prec, int nrhs, const DslashTune &t);
 
@@ -766,7 +766,7 @@ grg_status grg_schur_dc_launch_info(grg_schur S, int precision, int nrhs, int32_
     if (precision < 0 || precision > 2 || nrhs < 1 || nrhs > kMaxRhs)
         return set_error("bad precision or nrhs"), GRG_EINVAL;
     const DslashTune &t = S->dctune[precision][nrhs];
-    const DslashTune d = t.valid ? t : default_dc_tune(S->lat->g);
+    const DslashTune d = t.valid ? t : default_dc_tune(S->lat->g, precision, nrhs);
     const int32_t v[6] = {d.SB, d.RG, d.split, d.grid, d.chunk, d.march};
     memcpy(info, v, sizeof(v));
     *ms = t.valid ? t.ms : -1.0f;

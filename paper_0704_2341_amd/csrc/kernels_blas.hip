@@ -1,10 +1,13 @@
 // Krylov vector operations on internal fields, with deterministic reductions.
 //
-// Every kernel is a grid-stride walk over blocks of 256 sites (XCD-aware, as
-// the stencil) with all right-hand sides looped inside the thread.  Sums are
-// formed per thread in FP64, reduced over the wavefront by shuffles, over the
-// workgroup through LDS, and written as one partial per workgroup and RHS;
-// launch_reduce then adds the partials in a fixed tree order.  No floating
+// Every kernel is a grid-stride walk over work items (block of 256 sites, one
+// RHS), the RHS fastest (XCD-aware, as the stencil).  The RHS are items rather
+// than a loop inside the thread because on a small lattice the site blocks
+// alone leave most of the chip idle (8^4: 16 workgroups): the FP64 vector
+// steps at 12x10x9x14 with 4 RHS took 35 / 22 / 19 us with 60 workgroups.
+// Sums are formed per thread in FP64, reduced over the wavefront by shuffles,
+// over the workgroup through LDS, and written as one partial per workgroup and
+// RHS; launch_reduce then adds the partials in a fixed tree order.  No floating
 // point atomics anywhere, so every reduction is bitwise reproducible.
 #include "common.h"
 #include "engine.h"
@@ -14,12 +17,15 @@ namespace grg {
 
 constexpr int kBlasSB = 256;
 
-#define SITE_LOOP_BEGIN(sh)                                            \
+// items (site block, RHS rhs), RHS fastest
+#define SITE_LOOP_BEGIN_R(sh, rhs)                                     \
     const int nsb_ = ((sh).g.V + kBlasSB - 1) / kBlasSB;               \
-    const ItemRange it_ = xcd_items(nsb_);                             \
+    const ItemRange it_ = xcd_items(nsb_ * (sh).nrhs);                 \
     for (int w_ = it_.begin; w_ < it_.end; w_ += it_.step) {           \
-        const int s = w_ * kBlasSB + (int)threadIdx.x;                 \
+        const int sb_ = w_ / (sh).nrhs, rhs = w_ - sb_ * (sh).nrhs;    \
+        const int s = sb_ * kBlasSB + (int)threadIdx.x;                \
         const bool valid = s < (sh).g.V;
+#define SITE_LOOP_BEGIN(sh) SITE_LOOP_BEGIN_R(sh, k)
 
 #define SITE_LOOP_END }
 
@@ -111,12 +117,16 @@ struct VecIO<GRG_FP64> {
 // as stored) per RHS.  HAS_P = false: p is r itself (minimal residual).
 //
 // All RHS of a 64-site tile are one contiguous block, and one RHS of a tile
-// (12 components x 64 sites) is a contiguous unit; a wavefront streams whole
-// units with 16-byte accesses, so every load and store instruction of the
-// wavefront moves 1 KB of consecutive memory, and alpha and the norm of a
-// unit belong to one RHS.  Units are walked in tile order, XCD-aware.
+// (12 components x 64 sites) is contiguous too.  A wavefront streams a unit of
+// kUnitVecs 16-byte vectors per lane of one (tile, RHS): the whole of it in
+// BF16, a half in FP32, a quarter in FP64, so that in every precision a lane
+// has three vectors per stream in flight and a small FP64 field spreads over
+// four times the wavefronts.  Every load and store instruction of the wavefront
+// moves 1 KB of consecutive memory, and alpha and the norm of a unit belong to
+// one RHS.  Units are walked in tile order, XCD-aware.
 // X0: x is taken as zero (not read): the first update of a solve started
 // from x = 0.
+constexpr int kUnitVecs = 3;
 template <int P, bool HAS_P, bool X0 = false>
 __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, void *r_,
                                                         const void *q_, const void *p_,
@@ -125,26 +135,27 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
     typedef VecIO<P> IO;
     typedef typename IO::R R;
     constexpr int N = IO::N;
-    constexpr int UV = 12 * 64 / N;  // 16-byte vectors per unit
-    constexpr int NV = UV / 64;      // per lane
+    constexpr int PARTS = 12 / N / kUnitVecs;  // units per (tile, RHS)
+    constexpr int UV = kUnitVecs * 64;         // 16-byte vectors per unit
     __shared__ double red[4][kMaxRhs];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int i = lane; i < sh.nrhs; i += 64) red[wave][i] = 0.0;
     uint4 *x = (uint4 *)x_, *r = (uint4 *)r_;
     const uint4 *q = (const uint4 *)q_, *p = (const uint4 *)p_;
     const int ntiles = (sh.g.V + 63) >> 6;
-    const int nunits = ntiles * sh.nrhs;
+    const int nunits = ntiles * sh.nrhs * PARTS;
     const ItemRange it = xcd_items((nunits + 3) >> 2);
     for (int w = it.begin; w < it.end; w += it.step) {
         const int u = w * 4 + wave;
         if (u >= nunits) continue;  // the whole wavefront
-        const int tile = u / sh.nrhs, k = u - tile * sh.nrhs;
+        const int tr = u / PARTS, tile = tr / sh.nrhs, k = tr - tile * sh.nrhs;
         const double2 a2 = alpha[k];
         const cpx<R> a = {(R)a2.x, (R)a2.y}, na = {-a.re, -a.im};
         const size_t base = (size_t)u * UV;
         R rr = 0;
+        // (a unit starts at a whole component, so its lanes' sites do not depend on it)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
+        for (int v = 0; v < kUnitVecs; ++v) {
             const int site = tile * 64 + (((v * 64 + lane) * N) & 63);
             if (site < sh.g.V) {
                 const size_t i = base + v * 64 + lane;
@@ -190,8 +201,8 @@ __global__ void __launch_bounds__(256) bicg_kernel(BlasShape sh, void *x_, void 
     typedef VecIO<P> IO;
     typedef typename IO::R R;
     constexpr int N = IO::N;
-    constexpr int UV = 12 * 64 / N;
-    constexpr int NV = UV / 64;
+    constexpr int PARTS = 12 / N / kUnitVecs;
+    constexpr int UV = kUnitVecs * 64;
     __shared__ double red[4][kMaxRhs][3];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (MODE == kBicgUpd)
@@ -200,18 +211,18 @@ __global__ void __launch_bounds__(256) bicg_kernel(BlasShape sh, void *x_, void 
     const uint4 *a = (const uint4 *)a_, *b = (const uint4 *)b_, *c = (const uint4 *)c_,
                 *d = (const uint4 *)d_;
     const int ntiles = (sh.g.V + 63) >> 6;
-    const int nunits = ntiles * sh.nrhs;
+    const int nunits = ntiles * sh.nrhs * PARTS;
     const ItemRange it = xcd_items((nunits + 3) >> 2);
     for (int w = it.begin; w < it.end; w += it.step) {
         const int u = w * 4 + wave;
         if (u >= nunits) continue;
-        const int tile = u / sh.nrhs, k = u - tile * sh.nrhs;
+        const int tr = u / PARTS, tile = tr / sh.nrhs, k = tr - tile * sh.nrhs;
         const double2 al2 = sc[kMaxRhs + k], om2 = sc[2 * kMaxRhs + k], be2 = sc[3 * kMaxRhs + k];
         const cpx<R> al = {(R)al2.x, (R)al2.y}, om = {(R)om2.x, (R)om2.y}, be = {(R)be2.x, (R)be2.y};
         const size_t base = (size_t)u * UV;
         R sre = 0, sim = 0, srr = 0;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
+        for (int v = 0; v < kUnitVecs; ++v) {
             const int site = tile * 64 + (((v * 64 + lane) * N) & 63);
             if (site >= sh.g.V) continue;
             const size_t i = base + v * 64 + lane;
@@ -347,18 +358,16 @@ __global__ void __launch_bounds__(256) norm2_kernel(BlasShape sh, const void *v_
     part.init(smem, sh.nrhs);
     const S *v = (const S *)v_;
     SITE_LOOP_BEGIN(sh)
-    for (int k = 0; k < sh.nrhs; ++k) {
-        double t = 0;
-        if (valid) {
+    double t = 0;
+    if (valid) {
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const cpx<R> a = ldc(v, fidx(s, k, c, sh.nrhs));
-                t += (double)a.re * a.re + (double)a.im * a.im;
-            }
+        for (int c = 0; c < 12; ++c) {
+            const cpx<R> a = ldc(v, fidx(s, k, c, sh.nrhs));
+            t += (double)a.re * a.re + (double)a.im * a.im;
         }
-        const double vv[1] = {t};
-        part.add(k, vv);
     }
+    const double vv[1] = {t};
+    part.add(k, vv);
     SITE_LOOP_END
     part.flush(partials);
 }
@@ -371,21 +380,19 @@ __global__ void __launch_bounds__(256) sub_norm_kernel(BlasShape sh, const doubl
     Partial<1> part;
     part.init(smem, sh.nrhs);
     SITE_LOOP_BEGIN(sh)
-    for (int k = 0; k < sh.nrhs; ++k) {
-        double t = 0;
-        if (valid) {
+    double t = 0;
+    if (valid) {
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const size_t i = fidx(s, k, c, sh.nrhs);
-                const double2 bv = b[i], av = ax[i];
-                const double2 d = make_double2(bv.x - av.x, bv.y - av.y);
-                r[i] = d;
-                t += d.x * d.x + d.y * d.y;
-            }
+        for (int c = 0; c < 12; ++c) {
+            const size_t i = fidx(s, k, c, sh.nrhs);
+            const double2 bv = b[i], av = ax[i];
+            const double2 d = make_double2(bv.x - av.x, bv.y - av.y);
+            r[i] = d;
+            t += d.x * d.x + d.y * d.y;
         }
-        const double vv[1] = {t};
-        part.add(k, vv);
     }
+    const double vv[1] = {t};
+    part.add(k, vv);
     SITE_LOOP_END
     part.flush(partials);
 }
@@ -415,24 +422,22 @@ __global__ void __launch_bounds__(256) axpy_convert_kernel(BlasShape sh, const v
             const int par = (x0 + x1 + s2 % sh.g.L[2] + s2 / sh.g.L[2]) & 1;
             ybase = par == y_first ? 0 : y_half;
         }
-        for (int k = 0; k < sh.nrhs; ++k) {
-            double f = scale ? scale[k] : 1.0;
-            if (mode == 1) f = f > 0 ? 1.0 / sqrt(f) : 0.0;
-            if (mode == 2) f = sqrt(f);
-            if (active && !active[k]) f = 0.0;
-            const RO fo = (RO)f;
+        double f = scale ? scale[k] : 1.0;
+        if (mode == 1) f = f > 0 ? 1.0 / sqrt(f) : 0.0;
+        if (mode == 2) f = sqrt(f);
+        if (active && !active[k]) f = 0.0;
+        const RO fo = (RO)f;
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const size_t i = fidx(s, k, c, sh.nrhs);
-                const cpx<RI> a = ldc(x, i);
-                cpx<RO> o = {fo * (RO)a.re, fo * (RO)a.im};
-                if (beta) {
-                    const cpx<RO> yo = ldc(y, i);
-                    o.re += yo.re;
-                    o.im += yo.im;
-                }
-                stc(y, y_half ? ybase + fidx(s >> 1, k, c, sh.nrhs) : i, o);
+        for (int c = 0; c < 12; ++c) {
+            const size_t i = fidx(s, k, c, sh.nrhs);
+            const cpx<RI> a = ldc(x, i);
+            cpx<RO> o = {fo * (RO)a.re, fo * (RO)a.im};
+            if (beta) {
+                const cpx<RO> yo = ldc(y, i);
+                o.re += yo.re;
+                o.im += yo.im;
             }
+            stc(y, y_half ? ybase + fidx(s >> 1, k, c, sh.nrhs) : i, o);
         }
     }
     SITE_LOOP_END
@@ -442,13 +447,11 @@ __global__ void __launch_bounds__(256) xmy_kernel(BlasShape sh, const double2 *x
 {
     SITE_LOOP_BEGIN(sh)
     if (valid) {
-        for (int k = 0; k < sh.nrhs; ++k) {
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const size_t i = fidx(s, k, c, sh.nrhs);
-                const double2 a = x[i], b = y[i];
-                y[i] = make_double2(a.x - b.x, a.y - b.y);
-            }
+        for (int c = 0; c < 12; ++c) {
+            const size_t i = fidx(s, k, c, sh.nrhs);
+            const double2 a = x[i], b = y[i];
+            y[i] = make_double2(a.x - b.x, a.y - b.y);
         }
     }
     SITE_LOOP_END
@@ -480,18 +483,16 @@ __global__ void __launch_bounds__(256) reusken_divide_kernel(BlasShape sh, const
     SITE_LOOP_BEGIN(sh)
     if (valid) {
         const bool rest = mask[s] == 0;
-        for (int k = 0; k < sh.nrhs; ++k) {
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const size_t i = fidx(s, k, c, sh.nrhs);
-                double2 o = make_double2(0.0, 0.0);
-                if (rest) {
-                    const double2 a = y[i], b = dt[fidx(s, 0, c, 1)];
-                    const double den = b.x * b.x + b.y * b.y;
-                    o = make_double2((a.x * b.x + a.y * b.y) / den, (a.y * b.x - a.x * b.y) / den);
-                }
-                t[i] = o;
+        for (int c = 0; c < 12; ++c) {
+            const size_t i = fidx(s, k, c, sh.nrhs);
+            double2 o = make_double2(0.0, 0.0);
+            if (rest) {
+                const double2 a = y[i], b = dt[fidx(s, 0, c, 1)];
+                const double den = b.x * b.x + b.y * b.y;
+                o = make_double2((a.x * b.x + a.y * b.y) / den, (a.y * b.x - a.x * b.y) / den);
             }
+            t[i] = o;
         }
     }
     SITE_LOOP_END
@@ -505,21 +506,19 @@ __global__ void __launch_bounds__(256) reusken_combine_kernel(BlasShape sh, cons
     SITE_LOOP_BEGIN(sh)
     if (valid) {
         const bool rest = mask[s] == 0;
-        for (int k = 0; k < sh.nrhs; ++k) {
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const size_t i = fidx(s, k, c, sh.nrhs);
-                const double2 uv = u[i];
-                double2 o = uv;
-                if (rest) {
-                    const double2 yv = y[i];
-                    const double2 zv = z ? z[i] : make_double2(0.0, 0.0);
-                    const double2 tv = t ? t[i] : make_double2(0.0, 0.0);
-                    o = make_double2(uv.x - ((yv.x - zv.x) * inv_d + tv.x),
-                                     uv.y - ((yv.y - zv.y) * inv_d + tv.y));
-                }
-                w[i] = o;
+        for (int c = 0; c < 12; ++c) {
+            const size_t i = fidx(s, k, c, sh.nrhs);
+            const double2 uv = u[i];
+            double2 o = uv;
+            if (rest) {
+                const double2 yv = y[i];
+                const double2 zv = z ? z[i] : make_double2(0.0, 0.0);
+                const double2 tv = t ? t[i] : make_double2(0.0, 0.0);
+                o = make_double2(uv.x - ((yv.x - zv.x) * inv_d + tv.x),
+                                 uv.y - ((yv.y - zv.y) * inv_d + tv.y));
             }
+            w[i] = o;
         }
     }
     SITE_LOOP_END
@@ -533,20 +532,18 @@ __global__ void __launch_bounds__(256) combine_kernel(BlasShape sh, CombineArgs 
     double2 *out = (double2 *)a.out;
     SITE_LOOP_BEGIN(sh)
     if (valid) {
-        for (int k = 0; k < sh.nrhs; ++k) {
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const size_t i = fidx(s, k, c, sh.nrhs);
-                double2 v = x ? x[i] : make_double2(0.0, 0.0);
-                for (int j = 0; j < a.n; ++j) {
-                    const double f = a.f[j * kMaxRhs + k];
-                    const cpx<double> e = ldr<double>((const S *)a.e[j], i);
-                    v.x = fma(f, e.re, v.x);
-                    v.y = fma(f, e.im, v.y);
-                }
-                const double2 b = u ? u[i] : make_double2(0.0, 0.0);
-                out[i] = make_double2(fma(a.sigma, v.x, b.x), fma(a.sigma, v.y, b.y));
+        for (int c = 0; c < 12; ++c) {
+            const size_t i = fidx(s, k, c, sh.nrhs);
+            double2 v = x ? x[i] : make_double2(0.0, 0.0);
+            for (int j = 0; j < a.n; ++j) {
+                const double f = a.f[j * kMaxRhs + k];
+                const cpx<double> e = ldr<double>((const S *)a.e[j], i);
+                v.x = fma(f, e.re, v.x);
+                v.y = fma(f, e.im, v.y);
             }
+            const double2 b = u ? u[i] : make_double2(0.0, 0.0);
+            out[i] = make_double2(fma(a.sigma, v.x, b.x), fma(a.sigma, v.y, b.y));
         }
     }
     SITE_LOOP_END
@@ -603,12 +600,10 @@ __global__ void __launch_bounds__(256) copy_kernel(BlasShape sh, const void *x_,
     S *y = (S *)y_;
     SITE_LOOP_BEGIN(sh)
     if (valid) {
-        for (int k = 0; k < sh.nrhs; ++k) {
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const size_t i = fidx(s, k, c, sh.nrhs);
-                y[i] = x[i];
-            }
+        for (int c = 0; c < 12; ++c) {
+            const size_t i = fidx(s, k, c, sh.nrhs);
+            y[i] = x[i];
         }
     }
     SITE_LOOP_END
@@ -637,8 +632,8 @@ __global__ void __launch_bounds__(256) multidot_kernel(BlasShape sh, const void 
     double (*red)[2] = (double (*)[2])dsm;  // [4 waves][nr][2]
     for (int i = lane; i < nr * 2; i += 64) red[wave * nr + i / 2][i % 2] = 0.0;
     __syncthreads();
-    SITE_LOOP_BEGIN(sh)
-    for (int r = 0; r < sh.nrhs; ++r) {
+    SITE_LOOP_BEGIN_R(sh, r)
+    {
         cpx<R> qv[12];
         if (valid) {
 #pragma unroll
@@ -687,8 +682,8 @@ __global__ void __launch_bounds__(256) orthogonalise_kernel(BlasShape sh, const 
     const S *Q = (const S *)Q_, *Pm = (const S *)P_, *rr = (const S *)r_;
     S *q = (S *)q_, *p = (S *)p_;
     const size_t vstride = (size_t)sh.nrhs * 12 * sh.g.Vs;
-    SITE_LOOP_BEGIN(sh)
-    for (int r = 0; r < sh.nrhs; ++r) {
+    SITE_LOOP_BEGIN_R(sh, r)
+    {
         double d[3] = {0, 0, 0};
         if (valid) {
 #pragma unroll

@@ -600,49 +600,51 @@ __global__ void __launch_bounds__(256) dc_update_kernel(DcArgs a)
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int i = lane; i < a.nrhs; i += 64) red[wave][i] = 0.0;
     __syncthreads();
+    // items (site block, RHS), RHS fastest: the RHS of a block run side by side
+    // on one XCD and share its links through L2 (looping over the RHS inside
+    // the thread left 8^4 with 4 RHS at 64 wavefronts)
     const int nsb = (a.g.V + blockDim.x - 1) / blockDim.x;
-    const ItemRange it = xcd_items(nsb);
+    const ItemRange it = xcd_items(nsb * a.nrhs);
     for (int w = it.begin; w < it.end; w += it.step) {
-        const int s = w * blockDim.x + (int)threadIdx.x;
+        const int sb = w / a.nrhs, r = w - sb * a.nrhs;
+        const int s = sb * blockDim.x + (int)threadIdx.x;
         const bool valid = s < a.g.V;
         const bool on = valid && a.mask[s] == 0;
         SiteGeo q;
         if (on) q = site_geo(s, a.g);
-        for (int r = 0; r < a.nrhs; ++r) {
-            double nrm = 0;
-            if (on) {
-                cpx<double> acc[12];
-                dslash_site<S, double, true, double2>(acc, e, U, s, q, a.g, r, a.nrhs, a.diag);
-                const double f = a.f[r];
-                const double sn = r_next ? a.s_next[r] : 0.0;
-                const DcNext nx(a, s);
+        double nrm = 0;
+        if (on) {
+            cpx<double> acc[12];
+            dslash_site<S, double, true, double2>(acc, e, U, s, q, a.g, r, a.nrhs, a.diag);
+            const double f = a.f[r];
+            const double sn = r_next ? a.s_next[r] : 0.0;
+            const DcNext nx(a, s);
 #pragma unroll
-                for (int c = 0; c < 12; ++c) {
-                    const size_t i = fidx(s, r, c, a.nrhs);
-                    const double2 rv = dc_load_r(a, r_in, i);
-                    const double2 d = make_double2(rv.x - f * acc[c].re, rv.y - f * acc[c].im);
-                    dc_store_r(a, r_out, i, d);
-                    if (r_next) stc(r_next, nx.at(i, r, c, a.nrhs), cpx<R>{(R)(sn * d.x), (R)(sn * d.y)});
-                    nrm += d.x * d.x + d.y * d.y;
-                    if (x_out) {
-                        const cpx<double> ev = ldr<double>(e, i);
-                        const double2 xv = x_in ? x_in[i] : make_double2(0.0, 0.0);
-                        x_out[i] = make_double2(xv.x + f * ev.re, xv.y + f * ev.im);
-                    }
-                }
-            } else if (valid) {
-                const DcNext nx(a, s);
-#pragma unroll
-                for (int c = 0; c < 12; ++c) {
-                    const size_t i = fidx(s, r, c, a.nrhs);
-                    dc_store_r(a, r_out, i, make_double2(0.0, 0.0));
-                    if (x_out) x_out[i] = make_double2(0.0, 0.0);
-                    if (r_next) stc(r_next, nx.at(i, r, c, a.nrhs), cpx<R>{0, 0});
+            for (int c = 0; c < 12; ++c) {
+                const size_t i = fidx(s, r, c, a.nrhs);
+                const double2 rv = dc_load_r(a, r_in, i);
+                const double2 d = make_double2(rv.x - f * acc[c].re, rv.y - f * acc[c].im);
+                dc_store_r(a, r_out, i, d);
+                if (r_next) stc(r_next, nx.at(i, r, c, a.nrhs), cpx<R>{(R)(sn * d.x), (R)(sn * d.y)});
+                nrm += d.x * d.x + d.y * d.y;
+                if (x_out) {
+                    const cpx<double> ev = ldr<double>(e, i);
+                    const double2 xv = x_in ? x_in[i] : make_double2(0.0, 0.0);
+                    x_out[i] = make_double2(xv.x + f * ev.re, xv.y + f * ev.im);
                 }
             }
-            nrm = wave_sum(nrm);
-            if (lane == 0) red[wave][r] += nrm;
+        } else if (valid) {
+            const DcNext nx(a, s);
+#pragma unroll
+            for (int c = 0; c < 12; ++c) {
+                const size_t i = fidx(s, r, c, a.nrhs);
+                dc_store_r(a, r_out, i, make_double2(0.0, 0.0));
+                if (x_out) x_out[i] = make_double2(0.0, 0.0);
+                if (r_next) stc(r_next, nx.at(i, r, c, a.nrhs), cpx<R>{0, 0});
+            }
         }
+        nrm = wave_sum(nrm);
+        if (lane == 0) red[wave][r] += nrm;
     }
     __syncthreads();
     const int nw = blockDim.x >> 6;

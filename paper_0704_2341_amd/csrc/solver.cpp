@@ -33,27 +33,41 @@ int round8(long v) { return (int)std::max<long>(8, ((v + 7) / 8) * 8); }
 int dslash_grid(const Geom &g, int nrhs, int SB, int RG)
 {
     const long items = (long)((g.V + SB - 1) / SB) * ((nrhs + RG - 1) / RG);
-    return round8(std::min<long>(items, 2048));
+    return round8(std::min<long>(items, kMaxGridValue));
 }
+
+// Wavefronts that a field of nrhs right-hand sides gives with one site and one
+// RHS per lane: what the default launches below are chosen by (the chip holds
+// 8192 at eight per SIMD).
+static long field_waves(const Geom &g, int nrhs) { return (long)((g.V + 63) / 64) * nrhs; }
 
 BlasShape blas_shape(const Geom &g, int nrhs)
 {
     BlasShape sh;
     sh.g = g;
     sh.nrhs = nrhs;
-    sh.grid = round8(std::min<long>((g.V + 255) / 256, 2048));
+    // one workgroup per unit of the finest walk (a 64-site tile with one RHS,
+    // which a workgroup's four wavefronts share in FP64)
+    sh.grid = round8(std::min<long>((long)((g.V + 63) / 64) * nrhs, 2048));
     return sh;
 }
 
-static int dslash_sb(const Geom &g) { return g.V >= (1 << 16) ? 128 : 64; }
-
-// Default stencil launch (before or without tuning).
+// Default stencil launch (before or without tuning).  One RHS per item until
+// the field gives more than 32768 wavefronts: below that the chip is not full
+// and looping over the RHS inside a thread only lengthens the chain of loads
+// (FP64, 12^4, 4 RHS: 21 us with RG 1, 65 us with RG 4); above it three RHS
+// per item read the links less often (FP64, 32^4, 12 RHS: 2.44 ms against 2.84
+// with RG 1 and 4.0 with RG 12; FP32 1.52 against 1.75).  Workgroups of one
+// wavefront spread a small field evenly, four share links and lines of a large
+// one (BF16, 32^4, 12 RHS: 0.69 ms against 0.93).  Every form sums a site's
+// hops in the same order.
 DslashTune default_tune(const Geom &g, int prec, int nrhs)
 {
+    const long waves = field_waves(g, nrhs);
     DslashTune t;
-    t.SB = dslash_sb(g);
-    t.RG = nrhs;
-    t.split = prec == GRG_FP64 ? 1 : 0;
+    t.SB = waves <= (prec == GRG_FP64 ? 16384 : 2048) ? 64 : 256;
+    t.RG = waves > 32768 && nrhs >= 6 ? 3 : 1;
+    t.split = prec == GRG_FP64 ? 0 : prec == GRG_FP32 ? waves > 1024 : 2;
     t.grid = dslash_grid(g, nrhs, t.SB, t.RG);
     return t;
 }
@@ -233,12 +247,29 @@ grg_status tune_dslash(grg_schur S, int prec, int nrhs, int reps)
 
 // Launch of the fused defect-correction step: the site-parallel kernel
 // (march == 0: SB threads, grid-stride over sites) or the t-marching kernel.
-DslashTune default_dc_tune(const Geom &g)
+// Default: site-parallel, one RHS per item.  From 32768 wavefronts on with at
+// least four RHS, four of them in a t-marching workgroup (32^4, 12 RHS: FP64
+// 3.40 ms against 4.18, FP32 2.49 against 2.81), in its LDS-ring form where
+// that is valid (BF16: 2.07 ms against 2.34; without it the site-parallel
+// kernel is the faster one, 0.76 ms against 0.80 at 24^4).
+bool dc_launch_ok(const Geom &g, int prec, int nrhs, const DslashTune &t);
+DslashTune default_dc_tune(const Geom &g, int prec, int nrhs)
 {
     DslashTune t;
-    t.SB = 128;
+    t.SB = 64;
+    if (field_waves(g, nrhs) > 32768 && nrhs >= 4) {
+        t.RG = 4;
+        t.march = std::min(8, g.L[3]);
+        t.split = prec == GRG_BF16 ? 3 : 0;
+        t.chunk = prec == GRG_BF16 ? 8 : 0;
+        const long items = (long)((g.L[0] * g.L[1] * g.L[2] + 63) / 64) * ((g.L[3] + t.march - 1) / t.march) *
+                           ((nrhs + 3) / 4);
+        t.grid = round8(std::min<long>(items, 2048));
+        if (dc_launch_ok(g, prec, nrhs, t)) return t;
+    }
     t.RG = 1;
-    t.grid = round8(std::min<long>((g.V + 127) / 128, 2048));
+    t.march = t.split = t.chunk = 0;
+    t.grid = round8(std::min<long>((long)((g.V + t.SB - 1) / t.SB) * nrhs, 2048));
     return t;
 }
 
@@ -293,7 +324,7 @@ grg_status tune_dc(grg_schur S, int prec, int nrhs, int reps)
     GRG_TRY_HIP(hipEventCreate(&e0));
     GRG_TRY_HIP(hipEventCreate(&e1));
     grg_status status = GRG_OK;
-    DslashTune best = default_dc_tune(g);
+    DslashTune best = default_dc_tune(g, prec, nrhs);
     best.ms = 1e30f;
     auto timeit = [&](DslashTune t) {
         if (status != GRG_OK || !dc_launch_ok(g, prec, nrhs, t)) return;
@@ -316,9 +347,9 @@ grg_status tune_dc(grg_schur S, int prec, int nrhs, int reps)
         if (t.ms < best.ms) best = t;
     };
     for (int sb : {64, 128, 256}) {
-        DslashTune t = default_dc_tune(g);
+        DslashTune t = default_dc_tune(g, prec, nrhs);
         t.SB = sb;
-        t.grid = round8(std::min<long>((g.V + sb - 1) / sb, 2048));
+        t.grid = round8(std::min<long>((long)((g.V + sb - 1) / sb) * nrhs, 2048));
         timeit(t);
     }
     const int nb3 = (g.L[0] * g.L[1] * g.L[2] + 63) / 64;
@@ -510,14 +541,34 @@ static Geom half_geom(grg_lattice L)
     return gh;
 }
 
+// Default half-stencil: the plane form where it is valid with planes of at
+// least 256 columns (BF16, 32^4: 0.29 / 0.106 / 0.046 ms with 12 / 4 / 1 RHS
+// against 0.43 / 0.149 / 0.047 for the best other form; with 16^4's planes of
+// 128 columns it gains nothing).  Otherwise one RHS per item (FP32, 16^4, 8
+// RHS: 38 us against 48 with RG 3), workgroups of one wavefront until the
+// field gives 4096 of them; BF16 double-buffers the hops until occupancy pays
+// more than a hop's latency (24^4, 4 RHS: 53 us double-buffered against 49; 12^4,
+// 1 RHS: 11.3 against 12.8).
+bool eo_launch_ok(const Geom &gh, int prec, int nrhs, const DslashTune &t);
 DslashTune default_eo_tune(const Geom &gh, int prec, int nrhs)
 {
     DslashTune t;
-    t.SB = 256;
-    t.RG = std::min(nrhs, 3);
-    t.split = prec == GRG_BF16 ? 2 : 1;  // hop schedule
-    const long items = (long)((gh.V + t.SB - 1) / t.SB) * ((nrhs + t.RG - 1) / t.RG);
-    t.grid = round8(std::min<long>(items, 2048));
+    t.RG = 1;
+    const int plane = gh.L[0] / 2 * gh.L[1];
+    if (prec == GRG_BF16 && plane >= 256) {
+        t.SB = plane;
+        t.split = 7;
+        t.march = std::min(4, gh.L[3]);
+        const long nx = (long)((gh.L[2] + 7) / 8) * nrhs * ((gh.L[3] + t.march - 1) / t.march);
+        t.grid = round8(std::min<long>(8 * nx, kMaxGridValue));
+        if (eo_launch_ok(gh, prec, nrhs, t)) return t;
+        t.march = 0;
+    }
+    const long waves = field_waves(gh, nrhs);
+    t.SB = waves <= 4096 ? 64 : 256;
+    t.split = prec == GRG_BF16 && waves <= 6144 ? 2 : 1;  // hop schedule
+    const long items = (long)((gh.V + t.SB - 1) / t.SB) * nrhs;
+    t.grid = round8(std::min<long>(items, kMaxGridValue));
     return t;
 }
 
@@ -677,7 +728,7 @@ grg_status tune_eo(grg_schur S, int prec, int nrhs, int reps)
             if ((nrhs % rg && rg != nrhs) || (rg > 4 && rg != nrhs)) continue;
             for (int hops = 1; hops <= (prec == GRG_BF16 ? 6 : 1); ++hops) {
                 if (hops == 3 || ((hops == 4 || hops == 5) && rg != hops - 2)) continue;
-                DslashTune t = default_eo_tune(gh, prec, nrhs);
+                DslashTune t;
                 t.SB = sb;
                 t.RG = rg;
                 t.split = hops;
@@ -1308,7 +1359,7 @@ grg_status drr_solve_internal(grg_schur S, int nrhs, grg_solver_stats *stats, co
     bool verified = false;
     grg_status status = GRG_OK;
     double worst = 0;
-    const DslashTune dct = S->dctune[prec][nrhs].valid ? S->dctune[prec][nrhs] : default_dc_tune(g);
+    const DslashTune dct = S->dctune[prec][nrhs].valid ? S->dctune[prec][nrhs] : default_dc_tune(g, prec, nrhs);
     for (;;) {
         bool conv = true;
         worst = 0;

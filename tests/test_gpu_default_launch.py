@@ -1,0 +1,48 @@
+"""The launches that untuned handles use: on each side of the sizes at which
+the default rule changes form, the stencils agree bit for bit with the plain
+one-wavefront, one-hop launch (every form sums a site's hops in the same
+order), and the D_rr solve agrees with the one that runs the site-parallel
+defect-correction step to twice the solver tolerance times the condition
+number of D_rr on these fields (about 5): 1e-9."""
+import pytest
+
+from grg_inputs import gaussian_vectors
+
+from gpu_support import Lattice, rel_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+# 64 wavefronts; 4096 (several per SIMD); 36864 (more than the chip holds, RHS
+# grouped, t-marching correction); planes of 256 columns (BF16 plane form)
+SIZES = [((8, 8, 8, 8), 1), ((8, 8, 8, 32), 16), ((24, 24, 16, 16), 16), ((32, 16, 8, 8), 5)]
+
+
+@pytest.mark.parametrize("dims,nrhs", SIZES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_default_launches(dims, nrhs):
+    import torch
+
+    lat = Lattice(dims, 0.5, 71)
+    grg = lat.grg
+    xd = to_dev(gaussian_vectors(12 * lat.V, nrhs, 71))
+    yd, zd = torch.empty_like(xd), torch.empty_like(xd)
+    for prec in ("fp64", "fp32", "bf16"):
+        s = lat.schur(-0.2, "I", False, tol=1e-10, inner=prec, inner_tol=1e-2 if prec == "bf16" else 1e-5,
+                      max_rhs=nrhs)
+        print(f"default launches {dims} {prec} x {nrhs}", flush=True)
+        grg.grg_block_apply(s.h, prec, 0, 0, xd, yd, nrhs)
+        grg.grg_schur_set_launch(s.h, prec, nrhs, [64, 1, 1, 64, 0, 0])
+        grg.grg_block_apply(s.h, prec, 0, 0, xd, zd, nrhs)
+        assert torch.equal(yd, zd), prec
+        for parity in (0, 1):
+            s2 = lat.schur(-0.2, "I", False, inner=prec, max_rhs=nrhs)
+            grg.grg_reduced_apply(s2.h, prec, parity, xd, yd, nrhs)
+            grg.grg_schur_set_launch(s2.h, prec, nrhs, [64, 1, 1, 64, 0, 0], eo=True)
+            grg.grg_reduced_apply(s2.h, prec, parity, xd, zd, nrhs)
+            assert torch.equal(yd, zd), (prec, parity)
+            s2.close()
+        grg.grg_drr_solve(s.h, xd, yd, nrhs)
+        grg.grg_schur_set_dc_launch(s.h, prec, nrhs, [64, 1, 0, 64, 0, 0])
+        grg.grg_drr_solve(s.h, xd, zd, nrhs)
+        assert rel_err(to_host(yd), to_host(zd)) < 1e-9, prec
+        s.close()
+    lat.close()

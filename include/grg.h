@@ -262,8 +262,8 @@ grg_status grg_schur_assemble(grg_schur s, double *S, size_t cap_bytes);
  * with d the diagonal of D_rr (4 + m0) and d~ the diagonal matrix of the row
  * sums of D_rr, each scalar row summed over its dof (d~ = D_rr applied to the
  * field that is 1 on every rest-site dof).  y_b = S~_bb x_b for nrhs
- * coarse-space fields (device, layout as grg_schur_apply), in FP64: four
- * stencil launches and no solve.  GRG_EINVAL if 4 + m0 = 0; a zero row sum
+ * coarse-space fields (device, layout as grg_schur_apply), in FP64, without a
+ * solve, on the coarse sites and their neighbours.  GRG_EINVAL if 4 + m0 = 0; a zero row sum
  * gives non-finite output (no check).  Uses the handle's workspaces. */
 grg_status grg_reusken_apply(grg_schur s, const double *x_b, double *y_b, int nrhs);
 /* Dense S~_bb (host, column-major complex128), as grg_schur_assemble. */
@@ -274,7 +274,7 @@ grg_status grg_reusken_assemble(grg_schur s, double *S, size_t cap_bytes);
  * coarse operator (it couples coarse sites at most two fine hops apart):
  *     S0_bb = D_bb - D_br d^{-1} D_rb,   d = 4 + m0, the diagonal of D_rr.
  * y_b = S0_bb x_b for nrhs coarse-space fields (device, layout as
- * grg_schur_apply), in FP64: two stencil launches, no solve.  GRG_EINVAL if
+ * grg_schur_apply), in FP64, no solve.  GRG_EINVAL if
  * 4 + m0 = 0.  Uses the handle's workspaces. */
 grg_status grg_diag_schur_apply(grg_schur s, const double *x_b, double *y_b, int nrhs);
 /* The dense S0_bb, as grg_schur_assemble. */

@@ -413,6 +413,8 @@ static void schur_free(grg_schur S)
     dfree((void *&)S->cb_in);
     dfree((void *&)S->cb_out);
     dfree(S->dt64);
+    dfree((void *&)S->bnd_site);
+    dfree((void *&)S->bnd_map);
     dfree((void *&)S->d_mask_eo);
     dfree((void *&)S->d_mask_par);
     for (int p = 0; p < 3; ++p) {

@@ -213,16 +213,37 @@ hipError_t launch_axpy_convert(int prec_in, int prec_out, const BlasShape &sh, c
                                const int *active, hipStream_t st, size_t y_half = 0, int y_first = 0);
 // y = x - y (FP64), used for u - z
 hipError_t launch_xmy(const BlasShape &sh, const void *x, void *y, hipStream_t st);
-// Second-order Schur complement approximation (kernels_blas.hip): the
-// rest-site ones field, t = y / d~ and w = u - ((y - z) / d + t) (z, t
-// nullable: zero; w = u - y / d is the approximation that ignores D_rr).
+// the rest-site ones field (the row sums' input)
 hipError_t launch_rest_ones(const Geom &g, const uint8_t *mask, void *o, hipStream_t st);
 hipError_t launch_combine(int prec, const BlasShape &sh, const CombineArgs &a, hipStream_t st);
-hipError_t launch_reusken_divide(const BlasShape &sh, const void *y, const void *dt,
-                                 const uint8_t *mask, void *t, hipStream_t st);
-hipError_t launch_reusken_combine(const BlasShape &sh, const void *u, const void *y, const void *z,
-                                  const void *t, const uint8_t *mask, double inv_d, void *w,
-                                  hipStream_t st);
+// Schur complement approximations of section 3 on the boundary, the rest
+// sites next to a coarse site (kernels_approx.hip).  count: boundary_blocks + 1
+// ints; site: the boundary's sites in lattice order (count's last entry of
+// them), map: site -> index in it, or negative.
+struct ApproxArgs {
+    Geom g;
+    const double *xb;     // canonical coarse vector
+    double *yb;
+    const int32_t *q, *bidx;
+    int nb;
+    const int32_t *site, *map;
+    int nbnd;
+    const void *U;        // FP64 links
+    const void *rows;     // row sums of D_rr (one FP64 field), nullptr: couplings inside D_rr ignored
+    int linked;           // a boundary site has a neighbour whose t is not zero
+    double diag;          // 4 + m0
+    void *t, *p;          // compact FP64 fields over the boundary, internal tiles
+    int nrhs;
+};
+int boundary_blocks(const Geom &g);
+hipError_t launch_boundary_build(const Geom &g, const int32_t *bidx, int *count, int32_t *site, int32_t *map,
+                                 hipStream_t st);
+hipError_t launch_boundary_rows(const Geom &g, const int32_t *bidx, const void *rows, int32_t *map, hipStream_t st);
+hipError_t launch_boundary_links(const Geom &g, const int32_t *site, int nbnd, const int32_t *map, int *linked,
+                                 hipStream_t st);
+hipError_t launch_boundary_source(const ApproxArgs &a, hipStream_t st);
+hipError_t launch_boundary_apply(const ApproxArgs &a, hipStream_t st);
+hipError_t launch_boundary_coarse(const ApproxArgs &a, hipStream_t st);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st);
 hipError_t launch_copy(int prec, const BlasShape &sh, const void *x, void *y, hipStream_t st);
 

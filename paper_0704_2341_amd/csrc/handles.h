@@ -117,6 +117,11 @@ struct grg_schur_s {
     // the lattice's gauge_version they were computed from (-1: not yet)
     void *dt64 = nullptr;
     int dt_version = -1;
+    // the rest sites next to a coarse site, in lattice order, and the map from
+    // sites into that list (negative off it; allocated on first use)
+    int32_t *bnd_site = nullptr, *bnd_map = nullptr;
+    int n_bnd = -1;
+    int bnd_linked = 1;  // with the rows of dt_version: a boundary site has a neighbour whose t is not zero
     // even-odd reduced inner solve: mask per parity ([2][Vhs]), the parity of
     // the reduced system, and compact fields per inner precision: r, x, q
     // (reduced parity), w (other parity) and the preconditioned direction p

@@ -1,0 +1,410 @@
+// The Schur complement approximations of section 3, on the sites that matter.
+//
+// With d = 4 + m0, d~ the row sums of D_rr and u = x_b on the coarse sites,
+//     S~_bb x = [D w]_b,  w = u - ((y - z) / d + t),  y = D_rb x, t = y / d~, z = D_rr t
+// (and S0_bb x the same with w = u - y / d).  y and t vanish except on the
+// rest sites next to a coarse site (the boundary), and [D w]_b reads w on the
+// coarse sites and the boundary only, so y, t, z and w are formed on the
+// boundary alone, in compact fields over its sites: with the all-even coarse
+// set 4 of the 15 rest sites in 16.  At 32^4 with 12 RHS the six passes over the
+// whole lattice took 7.7 ms (9.4 with the former stencil launch).
+//
+// A rest site off the boundary has y = 0, so t = 0 there, unless its row sum
+// is zero or not finite: then 0 / d~ is not a number and spreads to its
+// neighbours, here as in the formula (kBadRow marks such sites).
+#include <algorithm>
+
+#include "common.h"
+#include "engine.h"
+#include "split.h"
+
+namespace grg {
+
+constexpr int kBadRow = -2;
+
+// ------------------------------------------------------------------ the boundary
+// flag of site s: a rest site with a coarse neighbour
+__device__ __forceinline__ bool on_boundary(int s, const Geom &g, const int32_t *__restrict__ bidx)
+{
+    if (s >= g.V || bidx[s] >= 0) return false;
+    const SiteGeo q = site_geo(s, g);
+    bool b = false;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        int sp, sm;
+        nbr(s, mu, q, g, sp, sm);
+        b = b || bidx[sp] >= 0 || bidx[sm] >= 0;
+    }
+    return b;
+}
+
+// per block of 256 sites, the boundary sites' number
+__global__ void __launch_bounds__(256) boundary_count_kernel(Geom g, const int32_t *__restrict__ bidx, int *count)
+{
+    __shared__ int n[4];
+    const int s = blockIdx.x * 256 + threadIdx.x;
+    const unsigned long long m = __ballot(on_boundary(s, g, bidx));
+    if ((threadIdx.x & 63) == 0) n[threadIdx.x >> 6] = __popcll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) count[blockIdx.x] = n[0] + n[1] + n[2] + n[3];
+}
+
+// count[i] -> the sum of the counts before i; count[n] the total (one workgroup)
+__global__ void __launch_bounds__(1024) boundary_scan_kernel(int *count, int n)
+{
+    __shared__ int sm[1024];
+    int base = 0;
+    for (int i0 = 0; i0 < n; i0 += 1024) {
+        const int i = i0 + (int)threadIdx.x;
+        const int v = i < n ? count[i] : 0;
+        sm[threadIdx.x] = v;
+        __syncthreads();
+        for (int o = 1; o < 1024; o <<= 1) {
+            const int a = (int)threadIdx.x >= o ? sm[threadIdx.x - o] : 0;
+            __syncthreads();
+            sm[threadIdx.x] += a;
+            __syncthreads();
+        }
+        if (i < n) count[i] = base + sm[threadIdx.x] - v;
+        base += sm[1023];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) count[n] = base;
+}
+
+// site[j] = the j-th boundary site in lattice order, map[s] = its j, or -1
+__global__ void __launch_bounds__(256) boundary_fill_kernel(Geom g, const int32_t *__restrict__ bidx,
+                                                            const int *__restrict__ first, int32_t *site,
+                                                            int32_t *map)
+{
+    __shared__ int n[4];
+    const int s = blockIdx.x * 256 + threadIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const bool b = on_boundary(s, g, bidx);
+    const unsigned long long m = __ballot(b);
+    if (lane == 0) n[wave] = __popcll(m);
+    __syncthreads();
+    int j = first[blockIdx.x] + __popcll(m & ((1ull << lane) - 1));
+    for (int w = 0; w < wave; ++w) j += n[w];
+    if (b) site[j] = s;
+    if (s < g.V) map[s] = b ? j : -1;
+}
+
+// rest sites off the boundary: kBadRow where a row sum's 0 / d~ is not zero
+__global__ void __launch_bounds__(256) boundary_rows_kernel(Geom g, const int32_t *__restrict__ bidx,
+                                                            const double2 *__restrict__ rows, int32_t *map)
+{
+    const int s = blockIdx.x * 256 + threadIdx.x;
+    if (s >= g.V || bidx[s] >= 0 || map[s] >= 0) return;
+    bool bad = false;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        const double2 b = rows[fidx(s, 0, c, 1)];
+        const double den = b.x * b.x + b.y * b.y;
+        bad = bad || !(den > 0.0 && isfinite(den));
+    }
+    map[s] = bad ? kBadRow : -1;
+}
+
+// *linked = 1 if a boundary site has a neighbour with t != 0: one on the
+// boundary, or a kBadRow site
+__global__ void __launch_bounds__(256) boundary_links_kernel(Geom g, const int32_t *__restrict__ site, int nbnd,
+                                                             const int32_t *__restrict__ map, int *linked)
+{
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= nbnd) return;
+    const int s = site[j];
+    const SiteGeo q = site_geo(s, g);
+    bool b = false;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        int sp, sm;
+        nbr(s, mu, q, g, sp, sm);
+        b = b || map[sp] != -1 || map[sm] != -1;
+    }
+    if (b) *linked = 1;
+}
+
+// t = a / b as the formula divides
+__device__ __forceinline__ cpx<double> row_divide(double2 a, double2 b)
+{
+    const double den = b.x * b.x + b.y * b.y;
+    return {(a.x * b.x + a.y * b.y) / den, (a.y * b.x - a.x * b.y) / den};
+}
+
+// ------------------------------------------------------------------ the fields
+// Boundary site j, RHS r: y = (D x)_j from its coarse neighbours, then p = -w
+// or what is known of it:
+//   kNoRows   p = y / d                                  (S0_bb)
+//   kTwoPass  p = y / d + t, and t for boundary_apply_kernel to subtract z / d
+//   kOnePass  p = (y - z) / d + t with z = d t: no neighbour carries a t (the
+//             all-even coarse set, where this saves writing t and three more
+//             passes over the boundary: S~_bb at 32^4 with 12 RHS 1.18 ms in
+//             two passes)
+// Work items (256 boundary sites, RHS), RHS fastest: the RHS share the links
+// in L2.
+enum { kNoRows = 0, kTwoPass = 1, kOnePass = 2 };
+template <int MODE>
+__global__ void __launch_bounds__(256) boundary_source_kernel(Geom g, const double2 *__restrict__ xb,
+                                                              const int32_t *__restrict__ bidx, int nb,
+                                                              const double2 *__restrict__ U,
+                                                              const double2 *__restrict__ rows,
+                                                              const int32_t *__restrict__ site, int nbnd,
+                                                              double diag, double inv_d, double2 *__restrict__ t,
+                                                              double2 *__restrict__ p, int nrhs)
+{
+    const int nsb = (nbnd + 255) >> 8;
+    const ItemRange it = xcd_items(nsb * nrhs);
+    for (int w = it.begin; w < it.end; w += it.step) {
+        const int sb = w / nrhs, r = w - sb * nrhs;
+        const int j = sb * 256 + (int)threadIdx.x;
+        if (j >= nbnd) continue;
+        const int s = site[j];
+        const SiteGeo q = site_geo(s, g);
+        cpx<double> acc[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = {0, 0};
+#pragma unroll 1
+        for (int k = 0; k < 8; ++k) {
+            const int mu = k >> 1;
+            int sp, sm;
+            nbr(s, mu, q, g, sp, sm);
+            const int kb = bidx[(k & 1) ? sm : sp];
+            if (kb < 0) continue;
+            cpx<double> v[12], u[9];
+            const double2 *x = xb + ((size_t)r * nb + kb) * 12;
+#pragma unroll
+            for (int c = 0; c < 12; ++c) v[c] = {x[c].x, x[c].y};
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                const double2 l = U[lidx((k & 1) ? sm : s, mu, e)];
+                u[e] = {l.x, l.y};
+            }
+            switch (k) {
+            case 0: hop_math<0, true>(acc, v, u); break;
+            case 1: hop_math<0, false>(acc, v, u); break;
+            case 2: hop_math<1, true>(acc, v, u); break;
+            case 3: hop_math<1, false>(acc, v, u); break;
+            case 4: hop_math<2, true>(acc, v, u); break;
+            case 5: hop_math<2, false>(acc, v, u); break;
+            case 6: hop_math<3, true>(acc, v, u); break;
+            default: hop_math<3, false>(acc, v, u); break;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const size_t i = fidx(j, r, c, nrhs);
+            cpx<double> pv = {acc[c].re * inv_d, acc[c].im * inv_d};
+            if constexpr (MODE != kNoRows) {
+                const cpx<double> tv = row_divide(make_double2(acc[c].re, acc[c].im), rows[fidx(s, 0, c, 1)]);
+                if constexpr (MODE == kTwoPass) t[i] = make_double2(tv.re, tv.im);
+                pv.re += tv.re;
+                pv.im += tv.im;
+                if constexpr (MODE == kOnePass) {
+                    pv.re -= diag * tv.re * inv_d;
+                    pv.im -= diag * tv.im * inv_d;
+                }
+            }
+            p[i] = make_double2(pv.re, pv.im);
+        }
+    }
+}
+
+// p <- -w = p - z / d on the boundary, z = D_rr t from the neighbours on it
+// (t = 0 off it, but for the kBadRow sites)
+__global__ void __launch_bounds__(256) boundary_apply_kernel(Geom g, const double2 *__restrict__ U,
+                                                             const double2 *__restrict__ rows,
+                                                             const int32_t *__restrict__ site,
+                                                             const int32_t *__restrict__ map, int nbnd,
+                                                             double diag, double inv_d,
+                                                             const double2 *__restrict__ t, double2 *p, int nrhs)
+{
+    const int nsb = (nbnd + 255) >> 8;
+    const ItemRange it = xcd_items(nsb * nrhs);
+    for (int w = it.begin; w < it.end; w += it.step) {
+        const int sb = w / nrhs, r = w - sb * nrhs;
+        const int j = sb * 256 + (int)threadIdx.x;
+        if (j >= nbnd) continue;
+        const int s = site[j];
+        const SiteGeo q = site_geo(s, g);
+        cpx<double> acc[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const double2 v = t[fidx(j, r, c, nrhs)];
+            acc[c] = {diag * v.x, diag * v.y};
+        }
+#pragma unroll 1
+        for (int k = 0; k < 8; ++k) {
+            const int mu = k >> 1;
+            int sp, sm;
+            nbr(s, mu, q, g, sp, sm);
+            const int n = (k & 1) ? sm : sp;
+            const int jn = map[n];
+            if (jn == -1) continue;  // coarse, or t = 0
+            cpx<double> v[12], u[9];
+            if (jn >= 0) {
+#pragma unroll
+                for (int c = 0; c < 12; ++c) {
+                    const double2 x = t[fidx(jn, r, c, nrhs)];
+                    v[c] = {x.x, x.y};
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < 12; ++c) v[c] = row_divide(make_double2(0.0, 0.0), rows[fidx(n, 0, c, 1)]);
+            }
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                const double2 l = U[lidx((k & 1) ? sm : s, mu, e)];
+                u[e] = {l.x, l.y};
+            }
+            switch (k) {
+            case 0: hop_math<0, true>(acc, v, u); break;
+            case 1: hop_math<0, false>(acc, v, u); break;
+            case 2: hop_math<1, true>(acc, v, u); break;
+            case 3: hop_math<1, false>(acc, v, u); break;
+            case 4: hop_math<2, true>(acc, v, u); break;
+            case 5: hop_math<2, false>(acc, v, u); break;
+            case 6: hop_math<3, true>(acc, v, u); break;
+            default: hop_math<3, false>(acc, v, u); break;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const size_t i = fidx(j, r, c, nrhs);
+            const double2 v = p[i];
+            p[i] = make_double2(v.x - acc[c].re * inv_d, v.y - acc[c].im * inv_d);
+        }
+    }
+}
+
+// y_b = [D w]_b, w = x_b on the coarse sites and -p on the boundary: every
+// neighbour of a coarse site is one or the other.  64 coarse sites and one RHS
+// per workgroup, a hop per wavefront (split.h), RHS fastest.
+__global__ void __launch_bounds__(kSplitThreads) boundary_coarse_kernel(Geom g, const double2 *__restrict__ xb,
+                                                                        const int32_t *__restrict__ qsites,
+                                                                        const int32_t *__restrict__ bidx, int nb,
+                                                                        const int32_t *__restrict__ map,
+                                                                        const double2 *__restrict__ U, double diag,
+                                                                        const double2 *__restrict__ p,
+                                                                        double2 *__restrict__ yb, int nrhs)
+{
+    __shared__ HopSums<double> sums;
+    const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int nkb = (nb + 63) >> 6;
+    const ItemRange it = xcd_items(nkb * nrhs);
+    for (int wi = it.begin; wi < it.end; wi += it.step) {
+        const int kb = wi / nrhs, r = wi - kb * nrhs;
+        const int kc = kb * 64 + lane;
+        if (kc < nb) {
+            const int s = qsites[kc];
+            const SiteGeo q = site_geo(s, g);
+            const int mu = k >> 1;
+            int sp, sm;
+            nbr(s, mu, q, g, sp, sm);
+            const int n = (k & 1) ? sm : sp;
+            const int kn = bidx[n];
+            cpx<double> v[12], u[9], w[6];
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                const double2 l = U[lidx((k & 1) ? sm : s, mu, e)];
+                u[e] = {l.x, l.y};
+            }
+            if (kn >= 0) {
+                const double2 *x = xb + ((size_t)r * nb + kn) * 12;
+#pragma unroll
+                for (int c = 0; c < 12; ++c) v[c] = {x[c].x, x[c].y};
+            } else {
+                const int jn = map[n];
+#pragma unroll
+                for (int c = 0; c < 12; ++c) {
+                    const double2 x = p[fidx(jn, r, c, nrhs)];
+                    v[c] = {-x.x, -x.y};
+                }
+            }
+            hop_w_k(k, w, v, u);
+            sums.put(k, lane, w);
+        }
+        __syncthreads();
+        if (k < 6 && kc < nb) {
+            const int row = k % 3, spin = k < 3 ? 0 : 2;
+            const size_t i = ((size_t)r * nb + kc) * 12 + 3 * spin + row;
+            const double2 x0 = xb[i], x1 = xb[i + 3];
+            cpx<double> a0 = {diag * x0.x, diag * x0.y}, a1 = {diag * x1.x, diag * x1.y};
+            if (spin == 0) sums.add<false>(row, lane, a0, a1);
+            else sums.add<true>(row, lane, a0, a1);
+            yb[i] = make_double2(a0.re, a0.im);
+            yb[i + 3] = make_double2(a1.re, a1.im);
+        }
+        __syncthreads();  // the sums are read before the next item's overwrite them
+    }
+}
+
+// ------------------------------------------------------------------ launchers
+static inline int round8_grid(long n)
+{
+    n = std::min<long>(n, kMaxGridValue);
+    return (int)std::max<long>(8, (n + 7) / 8 * 8);
+}
+
+int boundary_blocks(const Geom &g) { return (g.V + 255) / 256; }
+
+hipError_t launch_boundary_build(const Geom &g, const int32_t *bidx, int *count, int32_t *site, int32_t *map,
+                                 hipStream_t st)
+{
+    const int n = boundary_blocks(g);
+    hipLaunchKernelGGL(boundary_count_kernel, dim3(n), dim3(256), 0, st, g, bidx, count);
+    hipLaunchKernelGGL(boundary_scan_kernel, dim3(1), dim3(1024), 0, st, count, n);
+    hipLaunchKernelGGL(boundary_fill_kernel, dim3(n), dim3(256), 0, st, g, bidx, (const int *)count, site, map);
+    return hipGetLastError();
+}
+
+hipError_t launch_boundary_rows(const Geom &g, const int32_t *bidx, const void *rows, int32_t *map, hipStream_t st)
+{
+    hipLaunchKernelGGL(boundary_rows_kernel, dim3(boundary_blocks(g)), dim3(256), 0, st, g, bidx,
+                       (const double2 *)rows, map);
+    return hipGetLastError();
+}
+
+hipError_t launch_boundary_links(const Geom &g, const int32_t *site, int nbnd, const int32_t *map, int *linked,
+                                 hipStream_t st)
+{
+    if (nbnd < 1) return hipSuccess;
+    hipLaunchKernelGGL(boundary_links_kernel, dim3((nbnd + 255) / 256), dim3(256), 0, st, g, site, nbnd, map, linked);
+    return hipGetLastError();
+}
+
+hipError_t launch_boundary_source(const ApproxArgs &a, hipStream_t st)
+{
+    if (a.nrhs < 1 || a.nrhs > kMaxRhs || a.nb < 1 || a.nbnd < 0) return hipErrorInvalidValue;
+    if (a.nbnd == 0) return hipSuccess;
+    const dim3 grd(round8_grid((long)((a.nbnd + 255) / 256) * a.nrhs)), blk(256);
+#define SRC(M)                                                                                              \
+    hipLaunchKernelGGL(boundary_source_kernel<M>, grd, blk, 0, st, a.g, (const double2 *)a.xb, a.bidx, a.nb, \
+                       (const double2 *)a.U, (const double2 *)a.rows, a.site, a.nbnd, a.diag, 1.0 / a.diag, \
+                       (double2 *)a.t, (double2 *)a.p, a.nrhs)
+    if (!a.rows) SRC(kNoRows);
+    else if (a.linked) SRC(kTwoPass);
+    else SRC(kOnePass);
+#undef SRC
+    return hipGetLastError();
+}
+
+hipError_t launch_boundary_apply(const ApproxArgs &a, hipStream_t st)
+{
+    if (a.nrhs < 1 || a.nrhs > kMaxRhs || a.nbnd < 0 || !a.rows) return hipErrorInvalidValue;
+    if (a.nbnd == 0 || !a.linked) return hipSuccess;
+    hipLaunchKernelGGL(boundary_apply_kernel, dim3(round8_grid((long)((a.nbnd + 255) / 256) * a.nrhs)), dim3(256),
+                       0, st, a.g, (const double2 *)a.U, (const double2 *)a.rows, a.site, a.map, a.nbnd, a.diag,
+                       1.0 / a.diag, (const double2 *)a.t, (double2 *)a.p, a.nrhs);
+    return hipGetLastError();
+}
+
+hipError_t launch_boundary_coarse(const ApproxArgs &a, hipStream_t st)
+{
+    if (a.nrhs < 1 || a.nrhs > kMaxRhs || a.nb < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(boundary_coarse_kernel, dim3(round8_grid((long)((a.nb + 63) / 64) * a.nrhs)),
+                       dim3(kSplitThreads), 0, st, a.g, (const double2 *)a.xb, a.q, a.bidx, a.nb, a.map,
+                       (const double2 *)a.U, a.diag, (const double2 *)a.p, (double2 *)a.yb, a.nrhs);
+    return hipGetLastError();
+}
+
+}  // namespace grg

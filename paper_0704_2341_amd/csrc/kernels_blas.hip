@@ -459,12 +459,7 @@ __global__ void __launch_bounds__(256) xmy_kernel(BlasShape sh, const double2 *x
 
 static bool shape_ok(const BlasShape &sh);
 
-// ------------------------------------------------------------------ section 3 approximation
-// The pieces of S~_bb x = [D (u - M y)]_b, M = d^{-1} + d~^{-1} - d^{-1} D_rr d~^{-1},
-// y = D_rb u, d = 4 + m0 and d~ = D_rr 1 (row sums):
-//   ones:     1 on every rest-site dof (one field), 0 on the coarse sites
-//   divide:   t = y / d~ on the rest sites, 0 on the coarse sites
-//   combine:  w = u - ((y - D_rr t) / d + t) on the rest sites, u on the coarse sites
+// 1 on every rest-site dof (one field), 0 on the coarse sites
 __global__ void __launch_bounds__(256) rest_ones_kernel(BlasShape sh, const uint8_t *mask, double2 *o)
 {
     SITE_LOOP_BEGIN(sh)
@@ -472,54 +467,6 @@ __global__ void __launch_bounds__(256) rest_ones_kernel(BlasShape sh, const uint
         const double v = mask[s] == 0 ? 1.0 : 0.0;
 #pragma unroll
         for (int c = 0; c < 12; ++c) o[fidx(s, 0, c, 1)] = make_double2(v, 0.0);
-    }
-    SITE_LOOP_END
-}
-
-__global__ void __launch_bounds__(256) reusken_divide_kernel(BlasShape sh, const double2 *y,
-                                                             const double2 *dt, const uint8_t *mask,
-                                                             double2 *t)
-{
-    SITE_LOOP_BEGIN(sh)
-    if (valid) {
-        const bool rest = mask[s] == 0;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            const size_t i = fidx(s, k, c, sh.nrhs);
-            double2 o = make_double2(0.0, 0.0);
-            if (rest) {
-                const double2 a = y[i], b = dt[fidx(s, 0, c, 1)];
-                const double den = b.x * b.x + b.y * b.y;
-                o = make_double2((a.x * b.x + a.y * b.y) / den, (a.y * b.x - a.x * b.y) / den);
-            }
-            t[i] = o;
-        }
-    }
-    SITE_LOOP_END
-}
-
-__global__ void __launch_bounds__(256) reusken_combine_kernel(BlasShape sh, const double2 *u,
-                                                              const double2 *y, const double2 *z,
-                                                              const double2 *t, const uint8_t *mask,
-                                                              double inv_d, double2 *w)
-{
-    SITE_LOOP_BEGIN(sh)
-    if (valid) {
-        const bool rest = mask[s] == 0;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            const size_t i = fidx(s, k, c, sh.nrhs);
-            const double2 uv = u[i];
-            double2 o = uv;
-            if (rest) {
-                const double2 yv = y[i];
-                const double2 zv = z ? z[i] : make_double2(0.0, 0.0);
-                const double2 tv = t ? t[i] : make_double2(0.0, 0.0);
-                o = make_double2(uv.x - ((yv.x - zv.x) * inv_d + tv.x),
-                                 uv.y - ((yv.y - zv.y) * inv_d + tv.y));
-            }
-            w[i] = o;
-        }
     }
     SITE_LOOP_END
 }
@@ -569,26 +516,6 @@ hipError_t launch_rest_ones(const Geom &g, const uint8_t *mask, void *o, hipStre
     const int blocks = (g.V + 255) / 256;
     sh.grid = blocks < 8 ? 8 : blocks > 2048 ? 2048 : (blocks + 7) / 8 * 8;
     hipLaunchKernelGGL(rest_ones_kernel, dim3(sh.grid), dim3(kBlasSB), 0, st, sh, mask, (double2 *)o);
-    return hipGetLastError();
-}
-
-hipError_t launch_reusken_divide(const BlasShape &sh, const void *y, const void *dt,
-                                 const uint8_t *mask, void *t, hipStream_t st)
-{
-    if (!shape_ok(sh)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(reusken_divide_kernel, dim3(sh.grid), dim3(kBlasSB), 0, st, sh,
-                       (const double2 *)y, (const double2 *)dt, mask, (double2 *)t);
-    return hipGetLastError();
-}
-
-hipError_t launch_reusken_combine(const BlasShape &sh, const void *u, const void *y, const void *z,
-                                  const void *t, const uint8_t *mask, double inv_d, void *w,
-                                  hipStream_t st)
-{
-    if (!shape_ok(sh)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(reusken_combine_kernel, dim3(sh.grid), dim3(kBlasSB), 0, st, sh,
-                       (const double2 *)u, (const double2 *)y, (const double2 *)z, (const double2 *)t,
-                       mask, inv_d, (double2 *)w);
     return hipGetLastError();
 }
 

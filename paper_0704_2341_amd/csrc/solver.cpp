@@ -1655,72 +1655,122 @@ grg_status schur_apply_internal(grg_schur S, const double *xb, double *yb, int n
 
 namespace grg {
 
+// The boundary of the partition (the rest sites next to a coarse site), on
+// first use.  At most 8 sites per coarse one.
+static grg_status ensure_boundary(grg_schur S)
+{
+    if (S->n_bnd >= 0) return GRG_OK;
+    grg_lattice L = S->lat;
+    const Geom &g = L->g;
+    const int nblk = boundary_blocks(g);
+    const size_t most = (size_t)std::min<long>(8L * S->nb, (long)g.V - S->nb);
+    int *count = nullptr;
+    auto give_up = [&](grg_status e) {
+        if (count) (void)hipFree(count);
+        if (S->bnd_site) (void)hipFree(S->bnd_site);
+        if (S->bnd_map) (void)hipFree(S->bnd_map);
+        S->bnd_site = S->bnd_map = nullptr;
+        return e;
+    };
+    if (hipMalloc(&S->bnd_site, sizeof(int32_t) * most) != hipSuccess) {
+        S->bnd_site = nullptr;
+        return set_error("boundary list: hipMalloc failed"), GRG_ENOMEM;
+    }
+    if (hipMalloc(&S->bnd_map, sizeof(int32_t) * g.V) != hipSuccess) {
+        S->bnd_map = nullptr;
+        return set_error("boundary map: hipMalloc failed"), give_up(GRG_ENOMEM);
+    }
+    if (hipMalloc(&count, sizeof(int) * (nblk + 1)) != hipSuccess) {
+        count = nullptr;
+        return set_error("boundary count: hipMalloc failed"), give_up(GRG_ENOMEM);
+    }
+    int n = 0;
+    hipError_t e = launch_boundary_build(g, S->d_bidx, count, S->bnd_site, S->bnd_map, L->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(&n, count + nblk, sizeof(int), hipMemcpyDeviceToHost, L->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
+    if (e != hipSuccess) return set_error("boundary list: %s", hipGetErrorString(e)), give_up(GRG_EHIP);
+    (void)hipFree(count);
+    S->n_bnd = n;
+    return GRG_OK;
+}
+
+// (x_b and y_b may overlap: the last kernel reads x_b at neighbouring coarse
+// sites while it writes y_b, so an overlapping x_b is copied first)
+static grg_status approx_args(grg_schur S, const double *xb, double *yb, int nrhs, const void *rows, ApproxArgs &a)
+{
+    grg_lattice L = S->lat;
+    const size_t n = (size_t)nrhs * S->nb * 24;
+    if (xb < yb + n && yb < xb + n) {
+        GRG_TRY_HIP(hipMemcpyAsync(S->u64, xb, n * sizeof(double), hipMemcpyDeviceToDevice, L->stream));
+        xb = (const double *)S->u64;
+    }
+    a.g = L->g;
+    a.xb = xb;
+    a.yb = yb;
+    a.q = S->d_q;
+    a.bidx = S->d_bidx;
+    a.nb = S->nb;
+    a.site = S->bnd_site;
+    a.map = S->bnd_map;
+    a.nbnd = S->n_bnd;
+    a.U = L->U[GRG_FP64];
+    a.rows = rows;
+    a.linked = S->bnd_linked;
+    a.diag = 4.0 + S->m0;
+    a.t = S->t64;  // V sites' room; the boundary has fewer
+    a.p = S->x64;
+    a.nrhs = nrhs;
+    return GRG_OK;
+}
+
+// D_bb x_b - D_br (D_rb x_b) / d: the Schur complement with the couplings
+// inside D_rr ignored (D_rr^{-1} -> 1 / d, d = 4 + m0 its diagonal), which
+// keeps the coarse operator's sparsity; no solve.
+grg_status diag_schur_apply_internal(grg_schur S, const double *xb, double *yb, int nrhs)
+{
+    hipStream_t st = S->lat->stream;
+    GRG_TRY(ensure_boundary(S));
+    ApproxArgs a;
+    GRG_TRY(approx_args(S, xb, yb, nrhs, nullptr, a));
+    GRG_TRY_HIP(launch_boundary_source(a, st));
+    GRG_TRY_HIP(launch_boundary_coarse(a, st));
+    return GRG_OK;
+}
+
 // y_b = S~_bb x_b, the second-order Schur complement approximation of
 // section 3, in FP64 without any solve:
 //     u = x_b on the coarse sites;  y = D_rb u;  d~ = D_rr 1 (row sums);
 //     t = y / d~;  z = D_rr t;  w = u - ((y - z) / d + t);  y_b = (D w)_b,
-// with d = 4 + m0 the diagonal of D_rr.  Three stencil launches on nrhs
-// fields and one on a single field (d~, recomputed per call since the links
-// may have been reset).
-// D_bb x_b - D_br (D_rb x_b) / d: the Schur complement with the couplings
-// inside D_rr ignored (D_rr^{-1} -> 1 / d, d = 4 + m0 its diagonal), which
-// keeps the coarse operator's sparsity; two stencil launches, no solve.
-grg_status diag_schur_apply_internal(grg_schur S, const double *xb, double *yb, int nrhs)
-{
-    grg_lattice L = S->lat;
-    hipStream_t st = L->stream;
-    const Geom &g = L->g;
-    const BlasShape sh = blas_shape(g, nrhs);
-    GRG_TRY_HIP(launch_scatter_coarse(xb, S->u64, S->d_bidx, S->nb, g, nrhs, st));
-    GRG_TRY_HIP(launch_rb_apply(g, xb, S->d_bidx, S->nb, L->U[GRG_FP64], S->b64, nrhs, st));
-    GRG_TRY_HIP(launch_reusken_combine(sh, S->u64, S->b64, nullptr, nullptr, S->d_mask,
-                                       1.0 / (4.0 + S->m0), S->x64, st));
-    CoarseArgs c;
-    c.in = S->x64;
-    c.out = yb;
-    c.U = L->U[GRG_FP64];
-    c.q = S->d_q;
-    c.nb = S->nb;
-    c.diag = 4.0 + S->m0;
-    c.g = g;
-    c.nrhs = nrhs;
-    GRG_TRY_HIP(launch_dslash_coarse(c, st));
-    return GRG_OK;
-}
-
+// with d = 4 + m0 the diagonal of D_rr.  d~ is formed once per gauge field;
+// y, t, z and w on the boundary only.
 grg_status reusken_apply_internal(grg_schur S, const double *xb, double *yb, int nrhs)
 {
     grg_lattice L = S->lat;
     hipStream_t st = L->stream;
     const Geom &g = L->g;
-    const BlasShape sh = blas_shape(g, nrhs);
     if (!S->dt64 && hipMalloc(&S->dt64, spinor_elems(g, 1) * 16) != hipSuccess) {
         S->dt64 = nullptr;
         set_error("row-sum field: hipMalloc failed");
         return GRG_ENOMEM;
     }
+    GRG_TRY(ensure_boundary(S));
     if (S->dt_version != L->gauge_version) {
-        // d~ = D_rr 1 (the row sums), once per gauge field
         GRG_TRY_HIP(launch_rest_ones(g, S->d_mask, S->t64, st));
         GRG_TRY(run_dslash(S, GRG_FP64, S->t64, S->dt64, 0, 1, nullptr));
+        GRG_TRY_HIP(launch_boundary_rows(g, S->d_bidx, S->dt64, S->bnd_map, st));
+        int *linked = S->active;  // (set by every solve before it is read)
+        GRG_TRY_HIP(launch_fill_zero(linked, sizeof(int), st));
+        GRG_TRY_HIP(launch_boundary_links(g, S->bnd_site, S->n_bnd, S->bnd_map, linked, st));
+        GRG_TRY_HIP(hipMemcpyAsync(S->h_buf, linked, sizeof(int), hipMemcpyDeviceToHost, st));
+        GRG_TRY_HIP(hipStreamSynchronize(st));
+        memcpy(&S->bnd_linked, S->h_buf, sizeof(int));
         S->dt_version = L->gauge_version;
     }
-    GRG_TRY_HIP(launch_scatter_coarse(xb, S->u64, S->d_bidx, S->nb, g, nrhs, st));
-    GRG_TRY_HIP(launch_rb_apply(g, xb, S->d_bidx, S->nb, L->U[GRG_FP64], S->b64, nrhs, st));
-    GRG_TRY_HIP(launch_reusken_divide(sh, S->b64, S->dt64, S->d_mask, S->t64, st));
-    GRG_TRY(run_dslash(S, GRG_FP64, S->t64, S->r64, 0, nrhs, nullptr));
-    GRG_TRY_HIP(launch_reusken_combine(sh, S->u64, S->b64, S->r64, S->t64, S->d_mask,
-                                       1.0 / (4.0 + S->m0), S->x64, st));
-    CoarseArgs c;
-    c.in = S->x64;
-    c.out = yb;
-    c.U = L->U[GRG_FP64];
-    c.q = S->d_q;
-    c.nb = S->nb;
-    c.diag = 4.0 + S->m0;
-    c.g = g;
-    c.nrhs = nrhs;
-    GRG_TRY_HIP(launch_dslash_coarse(c, st));
+    ApproxArgs a;
+    GRG_TRY(approx_args(S, xb, yb, nrhs, S->dt64, a));
+    GRG_TRY_HIP(launch_boundary_source(a, st));
+    GRG_TRY_HIP(launch_boundary_apply(a, st));
+    GRG_TRY_HIP(launch_boundary_coarse(a, st));
     return GRG_OK;
 }
 

@@ -154,3 +154,55 @@ def test_diag_schur_matrix_free(dims, kind, inv, nrhs):
     assert rel_err(got[sample], want) < 1e-12
     s.close()
     lat.close()
+
+
+@pytest.mark.parametrize("dims,kind,nrhs", [((4, 4, 4, 4), "first", 1), ((5, 3, 7, 4), "third", 2),
+                                            ((5, 3, 7, 4), "all but one", 3), ((6, 6, 6, 6), "one", 16)])
+def test_boundary_forms(dims, kind, nrhs):
+    """Coarse sets whose boundary (the rest sites next to a coarse site) is a
+    few sites, most of the lattice or one site, on odd extents too, in place
+    and not; both approximations."""
+    import torch
+
+    lat = Lattice(dims, 0.5, 3)
+    grg, V = lat.grg, lat.V
+    order = np.random.default_rng(3).permutation(V).astype(np.int32)
+    nb = {"first": 64, "third": V // 3, "all but one": V - 1, "one": 1}[kind]
+    h = grg.grg_schur_create(lat.h, -0.2, order, nb, grg.grg_solver_params_default(max_rhs=nrhs))
+    xb = gaussian_vectors(12 * nb, nrhs, 3)
+    want = matfree.reusken_apply(lat.links, dims, -0.2, order, nb, xb)
+    x = to_dev(xb)
+    y = torch.empty_like(x)
+    print(f"boundary forms {dims} {kind}", flush=True)
+    grg.grg_reusken_apply(h, x, y, nrhs)
+    assert rel_err(to_host(y), want) < 1e-12
+    grg.grg_diag_schur_apply(h, x, y, nrhs)
+    z = x.clone()
+    grg.grg_diag_schur_apply(h, z, z, nrhs)
+    assert torch.equal(z, y)
+    z = x.clone()
+    grg.grg_reusken_apply(h, z, z, nrhs)
+    assert rel_err(to_host(z), want) < 1e-12
+    grg.grg_schur_destroy(h)
+    lat.close()
+
+
+def test_zero_row_sums():
+    """A free field at m0 = 0, periodic: the row sums of D_rr vanish on the
+    rest sites that are not next to a coarse site, where the formula divides
+    zero by zero, and its neighbours' output is not a number."""
+    import torch
+
+    dims = (8, 8, 4, 4)
+    V = int(np.prod(dims))
+    links = np.tile(np.eye(3, dtype=complex), (V, 4, 1, 1))
+    lat = Lattice(dims, 0, 0, bc=(1, 1, 1, 1), links=links)
+    s = lat.schur(0.0, "I", False, max_rhs=2)
+    x = to_dev(gaussian_vectors(12 * s.nb, 2, 5))
+    y = torch.empty_like(x)
+    lat.grg.grg_reusken_apply(s.h, x, y, 2)
+    assert bool(torch.isnan(torch.view_as_real(y)).all())
+    lat.grg.grg_diag_schur_apply(s.h, x, y, 2)
+    assert bool(torch.isfinite(torch.view_as_real(y)).all())
+    s.close()
+    lat.close()

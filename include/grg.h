@@ -189,9 +189,9 @@ grg_status grg_permutation_block(const int32_t dims[4], int type, int inverse, i
  * Figure 2 shows before and after blocking.  Computed in the given precision:
  * inputs and links are rounded to it (BF16 through FP32, round to nearest
  * even), the arithmetic is FP64, FP32 or FP32 on BF16 operands, and the result
- * is widened to FP64.  Uses a grow-only scratch of the lattice handle (two
- * fields of nrhs in that precision, allocated on the first call that needs
- * more).  GRG_EINVAL: null pointer, nrhs outside 1..16, bad precision, gauge
+ * is widened to FP64.  Uses a grow-only scratch of the lattice handle (one
+ * field of nrhs in that precision, allocated on the first call that needs
+ * more; the smallest fields need none).  GRG_EINVAL: null pointer, nrhs outside 1..16, bad precision, gauge
  * field not set, m0 not finite. */
 grg_status grg_dirac_apply(grg_lattice lat, double m0, int precision, const double *in,
                            double *out, int nrhs);
@@ -199,7 +199,7 @@ grg_status grg_dirac_apply(grg_lattice lat, double m0, int precision, const doub
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): out = D in
  * exactly as grg_dirac_apply (same kernels and launch, so the same bits), but
- * its two internal staging fields live in a fixed scratch array of
+ * its internal staging lives in a fixed scratch array of
  * GRG_NOALLOC_SCRATCH_BYTES per GPU that the library holds until the process
  * ends, so the call itself allocates nothing (the first call on a device
  * looks up that device's array once).  Needs
@@ -306,8 +306,10 @@ grg_status grg_schur_tune(grg_schur s, int nrhs);
  * lattice for one RHS (info[1] = 1), or two planes z, z + 1 of it (info[1] =
  * 2, Lz a multiple of 16, the z hop between the two from LDS), walking
  * info[5] time slices with the x, y and backward t hops read from LDS;
- * info[5] = 0 except with 3 and 7.  With
- * schedule 3 or 7, the full-layout first and last steps of a reduced solve
+ * info[5] = 0 except with 3 and 7.  Hop schedule 8, of every precision and
+ * of both stencils, takes 64 sites of one RHS per workgroup with a hop per
+ * wavefront (info[0] = 64, info[1] = 1, info[5] = 0): the form of the smallest
+ * fields.  With schedule 3 or 7, the full-layout first and last steps of a reduced solve
  * run the one-hop shape that tuning found faster for them, if it found one,
  * else the same schedule as well. */
 grg_status grg_schur_tune_info(grg_schur s, int precision, int nrhs, int32_t info[6], float *ms);
@@ -330,7 +332,8 @@ grg_status grg_schur_set_launch(grg_schur s, int precision, int nrhs, const int3
  * most 4 RHS per workgroup; the column's e at t - 1 and t and its U_t at
  * t - 1 kept in LDS, each site finished within its slice), 3 the same with
  * the work items ordered RHS group first (the groups
- * of a tile run together on one XCD and share its links), else 0.
+ * of a tile run together on one XCD and share its links), 8 a hop per wavefront
+ * (info[0] = 64, info[1] = 1, info[5] = 0), else 0.
  * *ms = tuned time per step, or -1 if untuned. */
 grg_status grg_schur_dc_launch_info(grg_schur s, int precision, int nrhs, int32_t info[6],
                                     float *ms);

@@ -36,6 +36,7 @@ grg_status run_dslash(grg_schur S, int prec, const void *in, void *out, int sel,
 int partial_rows(const Geom &g, int nrhs);
 int dslash_grid(const Geom &g, int nrhs, int SB, int RG);
 DslashTune default_tune(const Geom &g, int prec, int nrhs);
+DslashTune default_lane_tune(const Geom &g, int prec, int nrhs);
 bool launch_ok(const Geom &g, int prec, int nrhs, const DslashTune &t, bool dots);
 grg_status block_apply_internal(grg_schur S, int prec, int rows, int cols, const double *in,
                                 double *out, int nrhs);
@@ -217,7 +218,6 @@ grg_status grg_lattice_destroy(grg_lattice L)
     for (int p = 0; p < 3; ++p) dfree(L->U[p]);
     for (int p = 0; p < 3; ++p) dfree(L->Ueo[p]);
     dfree(L->tmp_in);
-    dfree(L->tmp_out);
     void *tl = L->tmp_links;
     dfree(tl);
     delete L;
@@ -279,6 +279,49 @@ grg_status grg_permutation_block(const int32_t dims[4], int type, int inverse, i
     return GRG_OK;
 }
 
+namespace {
+// Whether D needs its input packed into internal tiles first: the smallest
+// fields are read in the canonical layout by the hop-per-wavefront form, one
+// launch for the whole call (its neighbours' reads forbid out to overlap in).
+bool dirac_staged(grg_lattice L, int precision, const double *in, const double *out, int nrhs)
+{
+    const size_t n = (size_t)nrhs * L->g.V * 24;
+    const bool overlap = in < out + n && out < in + n;
+    return overlap || default_tune(L->g, precision, nrhs).split != kSplitForm;
+}
+
+grg_status dirac_apply_launch(grg_lattice L, double m0, int precision, const double *in, double *out, int nrhs,
+                              void *stage)
+{
+    DslashArgs a;
+    a.in = stage ? stage : (const void *)in;
+    a.out = out;
+    a.U = L->U[precision];
+    a.mask = nullptr;
+    a.sel = 0;
+    a.diag = 4.0 + m0;
+    a.g = L->g;
+    a.nrhs = nrhs;
+    const DslashTune t = stage ? default_lane_tune(L->g, precision, nrhs) : default_tune(L->g, precision, nrhs);
+    a.SB = t.SB;
+    a.RG = t.RG;
+    a.split = t.split;
+    a.chunk = t.chunk;
+    a.march = t.march;
+    a.partials = nullptr;
+    a.dot_with = nullptr;
+    a.out_canon = 1;
+    if (stage) {
+        GRG_TRY_HIP(launch_pack_spinor(precision, in, stage, L->g, nrhs, L->stream));
+        GRG_TRY_HIP(launch_dslash(precision, a, t.grid, L->stream));
+    } else {
+        GRG_TRY_HIP(launch_dslash_split(precision, a, true, t.grid, L->stream));
+    }
+    GRG_TRY_HIP(hipStreamSynchronize(L->stream));
+    return GRG_OK;
+}
+}  // namespace
+
 grg_status grg_dirac_apply(grg_lattice L, double m0, int precision, const double *in, double *out,
                            int nrhs)
 {
@@ -288,37 +331,15 @@ grg_status grg_dirac_apply(grg_lattice L, double m0, int precision, const double
     if (!L->gauge_set) return set_error("gauge field not set"), GRG_EINVAL;
     if (!isfinite(m0)) return set_error("m0 not finite"), GRG_EINVAL;
     DeviceGuard dg(L->device);
+    const bool staged = dirac_staged(L, precision, in, out, nrhs);
     const size_t bytes = spinor_elems(L->g, nrhs) * prec_bytes(precision);
-    if (bytes > L->tmp_bytes) {
+    if (staged && bytes > L->tmp_bytes) {
         dfree(L->tmp_in);
-        dfree(L->tmp_out);
         L->tmp_bytes = 0;
         GRG_TRY(dmalloc(&L->tmp_in, bytes, "dirac_apply scratch"));
-        GRG_TRY(dmalloc(&L->tmp_out, bytes, "dirac_apply scratch"));
         L->tmp_bytes = bytes;
     }
-    GRG_TRY_HIP(launch_pack_spinor(precision, in, L->tmp_in, L->g, nrhs, L->stream));
-    DslashArgs a;
-    a.in = L->tmp_in;
-    a.out = L->tmp_out;
-    a.U = L->U[precision];
-    a.mask = nullptr;
-    a.sel = 0;
-    a.diag = 4.0 + m0;
-    a.g = L->g;
-    a.nrhs = nrhs;
-    const DslashTune t = default_tune(L->g, precision, nrhs);
-    a.SB = t.SB;
-    a.RG = t.RG;
-    a.split = t.split;
-    a.chunk = t.chunk;
-    a.march = t.march;
-    a.partials = nullptr;
-    a.dot_with = nullptr;
-    GRG_TRY_HIP(launch_dslash(precision, a, t.grid, L->stream));
-    GRG_TRY_HIP(launch_unpack_spinor(precision, L->tmp_out, out, L->g, nrhs, L->stream));
-    GRG_TRY_HIP(hipStreamSynchronize(L->stream));
-    return GRG_OK;
+    return dirac_apply_launch(L, m0, precision, in, out, nrhs, staged ? L->tmp_in : nullptr);
 }
 
 // ------------------------------------------------------------------ no-alloc D apply
@@ -367,31 +388,10 @@ grg_status grg_dirac_apply_noalloc(grg_lattice L, double m0, int precision, cons
     DeviceGuard dg(L->device);
     void *base = nullptr;
     GRG_TRY(scratch_address(L->device, &base));
-    void *sin = base, *sout = (char *)base + bytes;
     // every entry the stencil reads (sites < V of every RHS) is written by the
     // pack first, so nothing left by an earlier call is read
-    GRG_TRY_HIP(launch_pack_spinor(precision, in, sin, L->g, nrhs, L->stream));
-    DslashArgs a;
-    a.in = sin;
-    a.out = sout;
-    a.U = L->U[precision];
-    a.mask = nullptr;
-    a.sel = 0;
-    a.diag = 4.0 + m0;
-    a.g = L->g;
-    a.nrhs = nrhs;
-    const DslashTune t = default_tune(L->g, precision, nrhs);
-    a.SB = t.SB;
-    a.RG = t.RG;
-    a.split = t.split;
-    a.chunk = t.chunk;
-    a.march = t.march;
-    a.partials = nullptr;
-    a.dot_with = nullptr;
-    GRG_TRY_HIP(launch_dslash(precision, a, t.grid, L->stream));
-    GRG_TRY_HIP(launch_unpack_spinor(precision, sout, out, L->g, nrhs, L->stream));
-    GRG_TRY_HIP(hipStreamSynchronize(L->stream));
-    return GRG_OK;
+    return dirac_apply_launch(L, m0, precision, in, out, nrhs,
+                              dirac_staged(L, precision, in, out, nrhs) ? base : nullptr);
 }
 
 static void schur_free(grg_schur S)

@@ -12,6 +12,9 @@
 namespace grg {
 
 constexpr int kMaxRhs = 16;
+// hop schedule of the hop-per-wavefront form of every stencil (64 sites of one
+// RHS per item, a workgroup of eight wavefronts)
+constexpr int kSplitForm = 8, kSplitSites = 64;
 constexpr int kMaxGridValue = 4096;  // largest stencil/BLAS grid (sizes partial sums)
 
 void set_error(const char *fmt, ...);
@@ -50,6 +53,9 @@ struct DslashArgs {
                           //      (64 sites x RG RHS wavefronts per workgroup)
     double *partials;     // [grid][nrhs][3] or nullptr
     const void *dot_with; // the fused dots use this field instead of `in` (or nullptr)
+    int out_canon = 0;    // out is a canonical complex128 field (site-parallel forms, no sums)
+    const uint8_t *in_mask = nullptr;  // canonical hop-per-wavefront form only: in is read on the
+    int in_sel = 0;                    // sites with in_mask[s] == in_sel (nullptr: on every site)
 };
 
 // Stencil between the compact parity halves of the even-odd reduction
@@ -124,6 +130,7 @@ struct DcArgs {
     int nrhs;
     double *partials;     // [grid][nrhs]: |r_out|^2
     int RG, chunk, march; // t-marching launch (march > 0), as in DslashArgs
+    int split = 0;        // kSplitForm: the hop-per-wavefront form
     int ring;             // with march > 0 and BF16 e: the LDS-ring form of the t-marching step
     int grp_first;        // ring form: work items ordered with the RHS group fastest, so the
                           // groups of one tile run together on one XCD and share its links
@@ -141,6 +148,12 @@ hipError_t launch_dslash(int prec, const DslashArgs &a, int grid, hipStream_t st
 // the t-marching kernel runs with 64 * a.RG threads per workgroup (a.ring: its
 // LDS-ring form, BF16 e only, 64 sites per x-y-z tile made of whole x-rows).
 hipError_t launch_dc_update(int prec, const DcArgs &a, int grid, int SB, hipStream_t st);
+// The hop-per-wavefront forms (kernels_split.hip): 512 threads, one RHS per
+// item.  canonical (no sums): in and out are canonical complex128 fields that
+// do not overlap.
+hipError_t launch_dslash_split(int prec, const DslashArgs &a, bool canonical, int grid, hipStream_t st);
+hipError_t launch_eo_split(int prec, const EoArgs &a, int grid, hipStream_t st);
+hipError_t launch_dc_split(int prec, const DcArgs &a, int grid, hipStream_t st);
 hipError_t launch_dslash_coarse(const CoarseArgs &a, hipStream_t st);
 // b = D_rb x_b from the canonical coarse vector (kernels_coarse.hip): internal
 // FP64 field, zero on the coarse sites

@@ -19,7 +19,7 @@ struct grg_lattice_s {
     bool gauge_set = false;
     int gauge_version = 0;  // incremented by every grg_gauge_set (caches derived from the links)
     // grow-only scratch of grg_dirac_apply
-    void *tmp_in = nullptr, *tmp_out = nullptr;
+    void *tmp_in = nullptr;
     size_t tmp_bytes = 0;
     double *tmp_links = nullptr;  // staging of host links
 };

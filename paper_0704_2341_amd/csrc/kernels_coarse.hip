@@ -10,6 +10,7 @@
 
 #include "common.h"
 #include "engine.h"
+#include "split.h"
 #include "stencil.h"
 
 namespace grg {
@@ -180,57 +181,52 @@ __device__ __forceinline__ void coarse_w(cpx<double> (&w)[12], int n, const doub
     }
 }
 
+// 64 coarse sites and one RHS per workgroup, a hop per wavefront (split.h):
+// each wavefront gathers one neighbour's corrections, so a site's eight
+// gathers wait together instead of one after the other.  RHS fastest, one
+// contiguous range per XCD: the RHS of a block share their links in L2.
 template <int P>
-__global__ void __launch_bounds__(256) coarse_combine_apply_kernel(Geom g, const double2 *__restrict__ xb,
-                                                                   const int32_t *__restrict__ qsites,
-                                                                   const int32_t *__restrict__ bidx, int nb,
-                                                                   const double2 *__restrict__ U, double diag,
-                                                                   CombineArgs a, double2 *__restrict__ yb,
-                                                                   int nrhs)
+__global__ void __launch_bounds__(kSplitThreads) coarse_combine_apply_kernel(Geom g, const double2 *__restrict__ xb,
+                                                                             const int32_t *__restrict__ qsites,
+                                                                             const int32_t *__restrict__ bidx, int nb,
+                                                                             const double2 *__restrict__ U, double diag,
+                                                                             CombineArgs a, double2 *__restrict__ yb,
+                                                                             int nrhs)
 {
-    // work items (block of 256 coarse sites, RHS), RHS fastest, one
-    // contiguous range per XCD: the RHS of a block share its links in L2
-    const int nkb = (nb + 255) >> 8;
+    __shared__ HopSums<double> sums;
+    const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int nkb = (nb + 63) >> 6;
     const ItemRange it = xcd_items(nkb * nrhs);
     for (int wi = it.begin; wi < it.end; wi += it.step) {
         const int kb = wi / nrhs, r = wi - kb * nrhs;
-        const int k = kb * 256 + (int)threadIdx.x;
-        if (k >= nb) continue;
-        const int s = qsites[k];
-        const SiteGeo q = site_geo(s, g);
-        cpx<double> acc[12];
-        const double2 *v = xb + ((size_t)r * nb + k) * 12;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) acc[c] = {diag * v[c].x, diag * v[c].y};
-        // one hop per iteration (+x, -x, ..., -t): the FP64 operands of a hop
-        // are 84 registers, so the hops are not unrolled
-#pragma unroll 1
-        for (int h = 0; h < 8; ++h) {
-            const int mu = h >> 1;
+        const int kc = kb * 64 + lane;
+        if (kc < nb) {
+            const int s = qsites[kc];
+            const SiteGeo q = site_geo(s, g);
             int sp, sm;
-            nbr(s, mu, q, g, sp, sm);
-            const int n = (h & 1) ? sm : sp;
-            cpx<double> w[12], u[9];
-            coarse_w<P>(w, n, xb, bidx, nb, r, nrhs, a);
+            nbr(s, k >> 1, q, g, sp, sm);
+            cpx<double> v[12], u[9], w[6];
 #pragma unroll
             for (int e = 0; e < 9; ++e) {
-                const double2 x = U[lidx((h & 1) ? sm : s, mu, e)];
+                const double2 x = U[lidx((k & 1) ? sm : s, k >> 1, e)];
                 u[e] = {x.x, x.y};
             }
-            switch (h) {
-            case 0: hop_math<0, true>(acc, w, u); break;
-            case 1: hop_math<0, false>(acc, w, u); break;
-            case 2: hop_math<1, true>(acc, w, u); break;
-            case 3: hop_math<1, false>(acc, w, u); break;
-            case 4: hop_math<2, true>(acc, w, u); break;
-            case 5: hop_math<2, false>(acc, w, u); break;
-            case 6: hop_math<3, true>(acc, w, u); break;
-            default: hop_math<3, false>(acc, w, u); break;
-            }
+            coarse_w<P>(v, (k & 1) ? sm : sp, xb, bidx, nb, r, nrhs, a);
+            hop_w_k(k, w, v, u);
+            sums.put(k, lane, w);
         }
-        double2 *o = yb + ((size_t)r * nb + k) * 12;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) o[c] = make_double2(acc[c].re, acc[c].im);
+        __syncthreads();
+        if (k < 6 && kc < nb) {
+            const int row = k % 3, spin = k < 3 ? 0 : 2;
+            const size_t i = ((size_t)r * nb + kc) * 12 + 3 * spin + row;
+            const double2 x0 = xb[i], x1 = xb[i + 3];
+            cpx<double> a0 = {diag * x0.x, diag * x0.y}, a1 = {diag * x1.x, diag * x1.y};
+            if (spin == 0) sums.add<false>(row, lane, a0, a1);
+            else sums.add<true>(row, lane, a0, a1);
+            yb[i] = make_double2(a0.re, a0.im);
+            yb[i + 3] = make_double2(a1.re, a1.im);
+        }
+        __syncthreads();  // the sums are read before the next item's overwrite them
     }
 }
 
@@ -239,8 +235,8 @@ hipError_t launch_coarse_combine_apply(int prec, const Geom &g, const double *xb
                                        const CombineArgs &a, double *yb, int nrhs, hipStream_t st)
 {
     if (nrhs < 1 || nrhs > kMaxRhs || nb < 1 || a.n < 0 || a.n > kCorrPool) return hipErrorInvalidValue;
-    const long items = (long)(nb + 255) / 256 * nrhs;
-    dim3 grd((unsigned)std::max<long>(8, (std::min<long>(items, 2048) + 7) / 8 * 8)), blk(256);
+    const long items = (long)(nb + 63) / 64 * nrhs;
+    dim3 grd((unsigned)std::max<long>(8, (std::min<long>(items, 2048) + 7) / 8 * 8)), blk(kSplitThreads);
 #define CCA(PP)                                                                                        \
     hipLaunchKernelGGL(coarse_combine_apply_kernel<PP>, grd, blk, 0, st, g, (const double2 *)xb, qsites, bidx, nb, \
                        (const double2 *)U64, diag, a, (double2 *)yb, nrhs)

@@ -22,13 +22,17 @@
 // output-site mask (inputs vanish off their block by construction).
 #include "common.h"
 #include "engine.h"
+#include "eo_site.h"
 #include "stencil.h"
 
 namespace grg {
 
 // out = mask_sel D in, for nrhs fields.  With a.partials set, also the
 // per-workgroup partial sums of conj(out).in (re, im) and |out|^2 per RHS.
-template <int P, int SPLIT>
+// OC: out is a canonical complex128 field, written here (the value as it would
+// be stored, widened) instead of by a pass of its own over the fields (32^4, 12
+// RHS in FP64: 1.1 ms for that pass).
+template <int P, int SPLIT, bool OC = false>
 __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
 {
     typedef typename Store<P>::S S;
@@ -67,7 +71,16 @@ __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
             }
             if (valid) {
 #pragma unroll
-                for (int c = 0; c < 12; ++c) stc(out, fidx(s, r, c, a.nrhs), acc[c]);
+                for (int c = 0; c < 12; ++c) {
+                    if constexpr (OC) {
+                        cpx<R> o = acc[c];
+                        if constexpr (P == GRG_BF16) o = as_cpx(pack_bf16(o.re, o.im));
+                        ((double2 *)a.out)[((size_t)r * a.g.V + s) * 12 + c] =
+                            make_double2((double)o.re, (double)o.im);
+                    } else {
+                        stc(out, fidx(s, r, c, a.nrhs), acc[c]);
+                    }
+                }
             }
             if (dots) {
                 // a site's 12 terms in the compute precision, the sums over
@@ -157,42 +170,6 @@ struct StoreEpi {
 // dc_update_kernel): r_out = r_in - f acc, x_out = x_in + f e (skipped when
 // x_out is null: the caller sums the corrections itself), r_next =
 // s_next r_out, and |r_out|^2.  The stencil of e runs in FP64 with FP64 links.
-// The defect correction's residual element i, stored in FP64 or (late steps,
-// DcArgs::r_in32 / r_out32) in FP32 at the same element index.
-__device__ __forceinline__ double2 dc_load_r(const DcArgs &a, const double2 *r, size_t i)
-{
-    if (a.r_in32) {
-        const float2 v = ((const float2 *)r)[i];
-        return make_double2((double)v.x, (double)v.y);
-    }
-    return r[i];
-}
-__device__ __forceinline__ void dc_store_r(const DcArgs &a, double2 *r, size_t i, double2 v)
-{
-    if (a.r_out32) ((float2 *)r)[i] = make_float2((float)v.x, (float)v.y);
-    else r[i] = v;
-}
-
-// Where r_next's element (r, c) of site s goes: the full layout (i), or the
-// compact half of the site's parity at its compact index s / 2.
-struct DcNext {
-    size_t base = 0;
-    int hs;
-    bool compact;
-    __device__ DcNext(const DcArgs &a, int s) : hs(s), compact(a.next_half != 0)
-    {
-        if (compact) {
-            const SiteGeo q = site_geo(s, a.g);
-            base = ((q.c[0] ^ q.c[1] ^ q.c[2] ^ q.c[3]) & 1) == a.next_par ? 0 : a.next_half;
-            hs = s >> 1;
-        }
-    }
-    __device__ size_t at(size_t i, int r, int c, int nrhs) const
-    {
-        return compact ? base + fidx(hs, r, c, nrhs) : i;
-    }
-};
-
 template <int P>
 struct DcEpi {
     typedef typename Store<P>::S SIN;
@@ -770,6 +747,11 @@ hipError_t launch_dslash(int prec, const DslashArgs &a, int grid, hipStream_t st
 {
     if (a.nrhs < 1 || a.nrhs > kMaxRhs || a.RG < 1) return hipErrorInvalidValue;
     if (grid < 8 || grid % 8) return hipErrorInvalidValue;
+    if (a.split == kSplitForm) {
+        if (a.RG != 1 || a.SB != kSplitSites || a.march > 0) return hipErrorInvalidValue;
+        return launch_dslash_split(prec, a, false, grid, st);
+    }
+    if (a.out_canon && (a.march > 0 || a.partials)) return hipErrorInvalidValue;
     if (a.march > 0) {
         // one wavefront per RHS of a group
         if (64 * a.RG > (prec == GRG_FP64 ? 512 : 768)) return hipErrorInvalidValue;
@@ -785,7 +767,11 @@ hipError_t launch_dslash(int prec, const DslashArgs &a, int grid, hipStream_t st
     if (a.SB != 256 && a.SB != 128 && a.SB != 64) return hipErrorInvalidValue;
     dim3 blk(a.SB), grd(grid);
 #define DSL(PP)                                                                                 \
-    if (a.split == 2) hipLaunchKernelGGL((dslash_kernel<PP, 2>), grd, blk, 0, st, a);           \
+    if (a.out_canon) {                                                                          \
+        if (a.split == 2) hipLaunchKernelGGL((dslash_kernel<PP, 2, true>), grd, blk, 0, st, a); \
+        else if (a.split) hipLaunchKernelGGL((dslash_kernel<PP, 1, true>), grd, blk, 0, st, a); \
+        else hipLaunchKernelGGL((dslash_kernel<PP, 0, true>), grd, blk, 0, st, a);              \
+    } else if (a.split == 2) hipLaunchKernelGGL((dslash_kernel<PP, 2>), grd, blk, 0, st, a);           \
     else if (a.split) hipLaunchKernelGGL((dslash_kernel<PP, 1>), grd, blk, 0, st, a);           \
     else hipLaunchKernelGGL((dslash_kernel<PP, 0>), grd, blk, 0, st, a);
     switch (prec) {
@@ -801,6 +787,10 @@ hipError_t launch_dslash(int prec, const DslashArgs &a, int grid, hipStream_t st
 hipError_t launch_dc_update(int prec, const DcArgs &a, int grid, int SB, hipStream_t st)
 {
     if (a.nrhs < 1 || a.nrhs > kMaxRhs || grid < 8 || grid % 8) return hipErrorInvalidValue;
+    if (a.split == kSplitForm) {
+        if (SB != kSplitSites || a.march > 0) return hipErrorInvalidValue;
+        return launch_dc_split(prec, a, grid, st);
+    }
     if (a.march > 0 && a.ring) {
         const int V3 = a.g.L[0] * a.g.L[1] * a.g.L[2];
         if (prec != GRG_BF16 || a.RG < 1 || a.RG > kRingWaves || V3 % 64 || 64 % a.g.L[0])

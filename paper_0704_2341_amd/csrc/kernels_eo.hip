@@ -21,19 +21,10 @@
 
 #include "common.h"
 #include "engine.h"
+#include "eo_site.h"
 #include "stencil.h"
 
 namespace grg {
-
-// site of half index h with parity p, and its coordinates
-__device__ __forceinline__ int eo_site(int h, int p, const Geom &g, SiteGeo &q)
-{
-    const int s0 = 2 * h;
-    q = site_geo(s0, g);
-    const int b = (p ^ q.c[1] ^ q.c[2] ^ q.c[3]) & 1;  // parity of s0 is y + z + t (x0 even)
-    q.c[0] += b;
-    return s0 + b;
-}
 
 __device__ __forceinline__ int site_parity(int s, const Geom &g)
 {
@@ -914,6 +905,10 @@ hipError_t launch_eo_hop(int prec, const EoArgs &a, int grid, hipStream_t st)
     else if (!a.in_full && a.in2_full && a.out_full) io = 2;
     else if (!a.in_full && !a.in2_full && a.out_full) io = 3;
     else if (a.in_full || a.in2_full || a.out_full) return hipErrorInvalidValue;
+    if (a.hops == kSplitForm) {
+        if (a.SB != kSplitSites || a.RG != 1) return hipErrorInvalidValue;
+        return launch_eo_split(prec, a, grid, st);
+    }
     if (a.hops == 7) {
         // plane form: packed BF16, one workgroup of P = Lx / 2 * Ly lanes
         // per x-y plane

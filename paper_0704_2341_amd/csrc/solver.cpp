@@ -61,7 +61,7 @@ BlasShape blas_shape(const Geom &g, int nrhs)
 // wavefront spread a small field evenly, four share links and lines of a large
 // one (BF16, 32^4, 12 RHS: 0.69 ms against 0.93).  Every form sums a site's
 // hops in the same order.
-DslashTune default_tune(const Geom &g, int prec, int nrhs)
+DslashTune default_lane_tune(const Geom &g, int prec, int nrhs)
 {
     const long waves = field_waves(g, nrhs);
     DslashTune t;
@@ -69,6 +69,23 @@ DslashTune default_tune(const Geom &g, int prec, int nrhs)
     t.RG = waves > 32768 && nrhs >= 6 ? 3 : 1;
     t.split = prec == GRG_FP64 ? 0 : prec == GRG_FP32 ? waves > 1024 : 2;
     t.grid = dslash_grid(g, nrhs, t.SB, t.RG);
+    return t;
+}
+
+// The smallest fields run a hop per wavefront instead (8^4, 1 RHS: FP64 8.0 us
+// against 10.7, BF16 6.6 against 9.3), up to where the one-lane-per-site form
+// has as many wavefronts to wait with (FP64 22.5 / 23.5 us at 1296 wavefronts,
+// 49.2 / 49.5 at 4096; FP32 34.4 / 35.5 at 4096, 71 / 65 at 8192; BF16 13.4 /
+// 13.5 at 1296, 19.8 / 17.2 at 2592).
+DslashTune default_tune(const Geom &g, int prec, int nrhs)
+{
+    const long waves = field_waves(g, nrhs);
+    if (waves > (prec == GRG_FP64 ? 640 : prec == GRG_FP32 ? 4096 : 1024)) return default_lane_tune(g, prec, nrhs);
+    DslashTune t;
+    t.SB = kSplitSites;
+    t.RG = 1;
+    t.split = kSplitForm;
+    t.grid = dslash_grid(g, nrhs, 64, 1);
     return t;
 }
 
@@ -104,9 +121,33 @@ bool launch_ok(const Geom &g, int prec, int nrhs, const DslashTune &t, bool)
         return t.march <= g.L[3] && t.RG >= 1 && t.RG <= nrhs &&
                64 * t.RG <= (prec == GRG_FP64 ? 512 : 768);
     }
+    if (t.split == kSplitForm) return t.SB == kSplitSites && t.RG == 1;
     return (t.SB == 64 || t.SB == 128 || t.SB == 256) && t.RG >= 1 && t.RG <= nrhs &&
            (t.split == 0 || t.split == 1 || (t.split == 2 && prec == GRG_BF16));
 }
+
+// One stencil launch of the handle: counted, and bracketed by profiling events
+// when enabled.
+struct StencilTimer {
+    grg_schur S;
+    bool ev;
+    StencilTimer(grg_schur s, int prec) : S(s)
+    {
+        ProfilePool &P = S->prof;
+        ev = P.on && P.used < (int)P.start.size();
+        if (ev) {
+            P.prec[P.used] = prec;
+            (void)hipEventRecord(P.start[P.used], S->lat->stream);
+        }
+        ++S->n_dslash;
+    }
+    ~StencilTimer()
+    {
+        if (ev) (void)hipEventRecord(S->prof.stop[S->prof.used++], S->lat->stream);
+    }
+    StencilTimer(const StencilTimer &) = delete;
+    StencilTimer &operator=(const StencilTimer &) = delete;
+};
 
 // One stencil launch, bracketed by profiling events when enabled.
 grg_status run_dslash(grg_schur S, int prec, const void *in, void *out, int sel, int nrhs,
@@ -114,17 +155,9 @@ grg_status run_dslash(grg_schur S, int prec, const void *in, void *out, int sel,
 {
     grg_lattice L = S->lat;
     const DslashTune t = S->tune[prec][nrhs].valid ? S->tune[prec][nrhs] : default_tune(L->g, prec, nrhs);
-    ProfilePool &P = S->prof;
-    const bool ev = P.on && P.used < (int)P.start.size();
-    if (ev) GRG_TRY_HIP(hipEventRecord(P.start[P.used], L->stream));
+    StencilTimer ev(S, prec);
     GRG_TRY(launch_tuned(L, prec, t, in, out, sel < 0 ? nullptr : S->d_mask, sel < 0 ? 0 : sel,
                          S->m0, nrhs, partials, dot_with));
-    if (ev) {
-        GRG_TRY_HIP(hipEventRecord(P.stop[P.used], L->stream));
-        P.prec[P.used] = prec;
-        ++P.used;
-    }
-    ++S->n_dslash;
     return GRG_OK;
 }
 
@@ -187,6 +220,17 @@ grg_status tune_dslash(grg_schur S, int prec, int nrhs, int reps)
             }
         }
     }
+    // a hop per wavefront
+    {
+        DslashTune t;
+        t.SB = kSplitSites;
+        t.RG = 1;
+        t.split = kSplitForm;
+        t.grid = dslash_grid(g, nrhs, 64, 1);
+        t.valid = 1;
+        timeit(t);
+        cands.push_back(t);
+    }
     // t-marching kernel: one workgroup = 64 sites x RG RHS (one wavefront
     // each), time chunks of T; RG = nrhs or a divisor of it that fits a
     // workgroup
@@ -216,6 +260,7 @@ grg_status tune_dslash(grg_schur S, int prec, int nrhs, int reps)
             cands[i].march > 0
                 ? (long)((g.L[0] * g.L[1] * g.L[2] + 63) / 64) * ((g.L[3] + cands[i].march - 1) / cands[i].march)
                 : (long)((g.V + cands[i].SB - 1) / cands[i].SB) * ((nrhs + cands[i].RG - 1) / cands[i].RG);
+        if (cands[i].split == kSplitForm) continue;
         const int caps[4] = {512, 1024, 2048, kMaxGrid};
         std::vector<int> chunks = {0, 1, 8, 64};
         if (cands[i].march == 0) {
@@ -251,11 +296,20 @@ grg_status tune_dslash(grg_schur S, int prec, int nrhs, int reps)
 // least four RHS, four of them in a t-marching workgroup (32^4, 12 RHS: FP64
 // 3.40 ms against 4.18, FP32 2.49 against 2.81), in its LDS-ring form where
 // that is valid (BF16: 2.07 ms against 2.34; without it the site-parallel
-// kernel is the faster one, 0.76 ms against 0.80 at 24^4).
+// kernel is the faster one, 0.76 ms against 0.80 at 24^4).  The smallest fields
+// take a hop per wavefront (8^4, 1 RHS: 11.8 us against 17.7; at 768 wavefronts
+// the forms meet, at 1024 it is 31 against 27).
 bool dc_launch_ok(const Geom &g, int prec, int nrhs, const DslashTune &t);
 DslashTune default_dc_tune(const Geom &g, int prec, int nrhs)
 {
     DslashTune t;
+    if (field_waves(g, nrhs) <= 512) {
+        t.SB = kSplitSites;
+        t.RG = 1;
+        t.split = kSplitForm;
+        t.grid = dslash_grid(g, nrhs, 64, 1);
+        return t;
+    }
     t.SB = 64;
     if (field_waves(g, nrhs) > 32768 && nrhs >= 4) {
         t.RG = 4;
@@ -280,6 +334,8 @@ bool dc_launch_ok(const Geom &g, int prec, int nrhs, const DslashTune &t)
     if (t.grid < 8 || t.grid % 8 || t.grid > kMaxGridValue || t.chunk < 0 || t.march < 0) return false;
     // split: 0 the t-marching form, 1 its LDS-ring form, 3 the ring form with
     // the RHS groups of a tile adjacent in the item order
+    // and kSplitForm a hop per wavefront
+    if (t.split == kSplitForm) return t.SB == kSplitSites && t.march == 0 && t.RG == 1;
     if (t.split != 0 && t.split != 1 && t.split != 3) return false;
     const int V3 = g.L[0] * g.L[1] * g.L[2];
     if ((t.split & 1) && (t.march < 1 || prec != GRG_BF16 || V3 % 64 || 64 % g.L[0] || t.RG > 4)) return false;
@@ -292,6 +348,7 @@ static void dc_fill_launch(DcArgs &d, const DslashTune &t)
     d.RG = t.RG;
     d.chunk = t.chunk;
     d.march = t.march;
+    d.split = t.split;
     d.ring = (t.split & 1) != 0;
     d.grp_first = (t.split & 2) != 0;
 }
@@ -350,6 +407,14 @@ grg_status tune_dc(grg_schur S, int prec, int nrhs, int reps)
         DslashTune t = default_dc_tune(g, prec, nrhs);
         t.SB = sb;
         t.grid = round8(std::min<long>((long)((g.V + sb - 1) / sb) * nrhs, 2048));
+        timeit(t);
+    }
+    {
+        DslashTune t;  // a hop per wavefront
+        t.SB = kSplitSites;
+        t.RG = 1;
+        t.split = kSplitForm;
+        t.grid = dslash_grid(g, nrhs, 64, 1);
         timeit(t);
     }
     const int nb3 = (g.L[0] * g.L[1] * g.L[2] + 63) / 64;
@@ -548,7 +613,11 @@ static Geom half_geom(grg_lattice L)
 // RHS: 38 us against 48 with RG 3), workgroups of one wavefront until the
 // field gives 4096 of them; BF16 double-buffers the hops until occupancy pays
 // more than a hop's latency (24^4, 4 RHS: 53 us double-buffered against 49; 12^4,
-// 1 RHS: 11.3 against 12.8).
+// 1 RHS: 11.3 against 12.8).  The smallest fields take a hop per wavefront (8^4,
+// 1 RHS: FP64 9.0 us against 12.5, FP32 7.6 against 12.5, BF16 7.7 against 10.9)
+// until the forms meet: FP64 at 512 wavefronts (13.8 / 16.0 us; 19.0 / 17.6 at
+// 648), FP32 at 2048 (21.7 / 22.8; 40 / 38 at 4096), BF16 at 1024 (11.9 / 12.4;
+// 17.3 / 16.8 at 1944).
 bool eo_launch_ok(const Geom &gh, int prec, int nrhs, const DslashTune &t);
 DslashTune default_eo_tune(const Geom &gh, int prec, int nrhs)
 {
@@ -565,6 +634,12 @@ DslashTune default_eo_tune(const Geom &gh, int prec, int nrhs)
         t.march = 0;
     }
     const long waves = field_waves(gh, nrhs);
+    if (waves <= (prec == GRG_FP64 ? 512 : prec == GRG_FP32 ? 2048 : 1024)) {
+        t.SB = kSplitSites;
+        t.split = kSplitForm;
+        t.grid = dslash_grid(gh, nrhs, 64, 1);
+        return t;
+    }
     t.SB = waves <= 4096 ? 64 : 256;
     t.split = prec == GRG_BF16 && waves <= 6144 ? 2 : 1;  // hop schedule
     const long items = (long)((gh.V + t.SB - 1) / t.SB) * nrhs;
@@ -686,6 +761,9 @@ bool eo_launch_ok(const Geom &gh, int prec, int nrhs, const DslashTune &t)
     const bool plane_ok = t.split == 7 && prec == GRG_BF16 && t.SB == plane && plane % 64 == 0 &&
                           plane <= 512 && t.march >= 1 && t.march <= Lt && Lt >= 2 &&
                           (t.RG == 1 || (t.RG == 2 && gh.L[2] % 16 == 0));
+    if (t.split == kSplitForm)
+        return t.SB == kSplitSites && t.RG == 1 && t.march == 0 && t.grid >= 8 && t.grid % 8 == 0 &&
+               t.grid <= kMaxGridValue && t.chunk >= 0 && gh.V > 0;
     if (t.split == 7)
         return plane_ok && t.grid >= 8 && t.grid % 8 == 0 && t.grid <= kMaxGridValue && t.chunk >= 0;
     return (t.SB == 64 || t.SB == 128 || t.SB == 256) && t.RG >= 1 && t.RG <= nrhs &&
@@ -739,6 +817,15 @@ grg_status tune_eo(grg_schur S, int prec, int nrhs, int reps)
             }
         }
     }
+    {
+        DslashTune t;  // a hop per wavefront
+        t.SB = kSplitSites;
+        t.RG = 1;
+        t.split = kSplitForm;
+        t.grid = dslash_grid(gh, nrhs, 64, 1);
+        timeit(t);
+        cands.push_back(t);
+    }
     std::sort(cands.begin(), cands.end(), [](const DslashTune &a, const DslashTune &b) { return a.ms < b.ms; });
     DslashTune best = cands.empty() ? default_eo_tune(gh, prec, nrhs) : cands[0];
     DslashTune best_io;  // the best one-hop shape, for the full-layout steps
@@ -746,6 +833,7 @@ grg_status tune_eo(grg_schur S, int prec, int nrhs, int reps)
     for (const DslashTune &c : cands)
         if (c.split == 1 && c.ms < best_io.ms) best_io = c;
     for (size_t i = 0; i < std::min<size_t>(2, cands.size()); ++i) {
+        if (cands[i].split == kSplitForm) continue;
         const long items = (long)((gh.V + cands[i].SB - 1) / cands[i].SB) *
                            ((nrhs + cands[i].RG - 1) / cands[i].RG);
         // chunks: one XCD per z-slab of a time slice (an eighth of its
@@ -1578,6 +1666,28 @@ grg_status block_apply_internal(grg_schur S, int prec, int rows, int cols, const
                                 double *out, int nrhs)
 {
     grg_lattice L = S->lat;
+    const size_t n = (size_t)nrhs * L->g.V * 24;
+    const DslashTune &tt = S->tune[prec][nrhs];
+    const DslashTune t = tt.valid ? tt : default_tune(L->g, prec, nrhs);
+    if (t.split == kSplitForm && !(in < out + n && out < in + n)) {
+        // the hop-per-wavefront form reads and writes the canonical fields
+        DslashArgs a;
+        a.in = in;
+        a.out = out;
+        a.U = L->U[prec];
+        a.mask = rows < 0 ? nullptr : S->d_mask;
+        a.sel = rows < 0 ? 0 : rows;
+        a.diag = 4.0 + S->m0;
+        a.g = L->g;
+        a.nrhs = nrhs;
+        a.partials = nullptr;
+        a.dot_with = nullptr;
+        a.in_mask = cols < 0 ? nullptr : S->d_mask;
+        a.in_sel = cols;
+        StencilTimer ev(S, prec);
+        GRG_TRY_HIP(launch_dslash_split(prec, a, true, t.grid, L->stream));
+        return GRG_OK;
+    }
     GRG_TRY(ensure_inner(S, prec));
     void *a = S->in_b[prec], *b = S->in_q[prec];
     GRG_TRY_HIP(launch_pack_spinor(prec, in, a, L->g, nrhs, L->stream, cols < 0 ? nullptr : S->d_mask,

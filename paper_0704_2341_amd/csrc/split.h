@@ -15,11 +15,12 @@
 #pragma once
 
 #include "common.h"
+#include "engine.h"
 #include "stencil.h"
 
 namespace grg {
 
-constexpr int kSplitThreads = 512;
+constexpr int kSplitThreads = 8 * kSplitSites;
 
 // w = U h or U^+ h for both spins of h
 template <bool FWD, class R>
@@ -51,6 +52,32 @@ __device__ __forceinline__ void hop_w(cpx<R> (&w)[6], const cpx<R> (&p)[12], con
 #pragma unroll
     for (int a = 0; a < 3; ++a) project1<MU, FWD>(h0[a], h1[a], p[a], p[3 + a], p[6 + a], p[9 + a]);
     link_mult<FWD>(w, h0, h1, u);
+}
+
+// packed BF16 spinors with FP64 links (the defect correction of a BF16 inner
+// solution) and with BF16 links
+template <int MU, bool FWD>
+__device__ __forceinline__ void hop_w(cpx<double> (&w)[6], const uint32_t (&p)[12], const cpx<double> (&u)[9])
+{
+    cpx<double> h0[3], h1[3];
+    auto wd = [](uint32_t x) -> cpx<double> {
+        return {(double)__uint_as_float(x << 16), (double)__uint_as_float(x & 0xffff0000u)};
+    };
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        project1<MU, FWD>(h0[a], h1[a], wd(p[a]), wd(p[3 + a]), wd(p[6 + a]), wd(p[9 + a]));
+    link_mult<FWD>(w, h0, h1, u);
+}
+template <int MU, bool FWD>
+__device__ __forceinline__ void hop_w(cpx<float> (&w)[6], const uint32_t (&p)[12], const uint32_t (&u)[9])
+{
+    cpx<float> w0[3], w1[3];
+    hop_bf16_w<MU, FWD>(w0, w1, p, u);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        w[r] = w0[r];
+        w[3 + r] = w1[r];
+    }
 }
 
 // hop k (the same in a wavefront)

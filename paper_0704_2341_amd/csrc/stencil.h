@@ -158,11 +158,10 @@ __device__ __forceinline__ void dot_fence(float &a0, float &b0, float &a1, float
     asm("s_nop 2" : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1));
 }
 
-// FIRST: the first hop of a site writes the accumulators instead of adding
-// to them (the same values as adding to zero, without clearing them first).
-template <int MU, bool FWD, bool FIRST = false>
-__device__ __forceinline__ void hop_bf16(cpx<float> (&acc)[12], const uint32_t (&p)[12],
-                                         const uint32_t (&u)[9])
+// The hop up to its link product: w0, w1 = U h or U^+ h.
+template <int MU, bool FWD>
+__device__ __forceinline__ void hop_bf16_w(cpx<float> (&w0)[3], cpx<float> (&w1)[3], const uint32_t (&p)[12],
+                                           const uint32_t (&u)[9])
 {
     // y_s = sg (B_mu psi_lo)_s, sg = -1 forward, +1 backward, i (re, im) =
     // (-im, re): the lower spin YS feeding y_s, swapped halves (SW), and the
@@ -175,7 +174,6 @@ __device__ __forceinline__ void hop_bf16(cpx<float> (&acc)[12], const uint32_t (
     constexpr int F1H = MU == 0 ? FWD : MU == 1 ? FWD : MU == 2 ? !FWD : FWD;
     // the link forms: re on m with signs PR*, im on swap(m) with signs PI*
     constexpr int PRL = 0, PRH = FWD, PIL = !FWD, PIH = 0;
-    cpx<float> w0[3], w1[3];
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
         float a0, b0, a1, b1;
@@ -211,6 +209,16 @@ __device__ __forceinline__ void hop_bf16(cpx<float> (&acc)[12], const uint32_t (
         w0[r] = {a0, b0};
         w1[r] = {a1, b1};
     }
+}
+
+// FIRST: the first hop of a site writes the accumulators instead of adding
+// to them (the same values as adding to zero, without clearing them first).
+template <int MU, bool FWD, bool FIRST = false>
+__device__ __forceinline__ void hop_bf16(cpx<float> (&acc)[12], const uint32_t (&p)[12],
+                                         const uint32_t (&u)[9])
+{
+    cpx<float> w0[3], w1[3];
+    hop_bf16_w<MU, FWD>(w0, w1, p, u);
     const float hl = FWD ? 0.5f : -0.5f;
     // a + b f with a = 0 on the first hop (exact: f is a power of two)
     auto mad = [](float f, float b, float a) { return FIRST ? f * b : fmaf(f, b, a); };

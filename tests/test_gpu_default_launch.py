@@ -4,6 +4,7 @@ one-wavefront, one-hop launch (every form sums a site's hops in the same
 order), and the D_rr solve agrees with the one that runs the site-parallel
 defect-correction step to twice the solver tolerance times the condition
 number of D_rr on these fields (about 5): 1e-9."""
+import numpy as np
 import pytest
 
 from grg_inputs import gaussian_vectors
@@ -45,4 +46,39 @@ def test_default_launches(dims, nrhs):
         grg.grg_drr_solve(s.h, xd, zd, nrhs)
         assert rel_err(to_host(yd), to_host(zd)) < 1e-9, prec
         s.close()
+    lat.close()
+
+
+@pytest.mark.parametrize("dims,nrhs", [((4, 4, 4, 4), 1), ((3, 5, 2, 7), 3), ((1, 6, 1, 11), 16), ((9, 7, 10, 11), 5)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_canonical_forms(dims, nrhs):
+    """The forms that read or write the canonical fields directly (the smallest
+    fields, ragged tiles, extents of one) against the staged form: D in place is
+    staged, and a pinned launch stages the sub-blocks; bit for bit."""
+    import torch
+
+    lat = Lattice(dims, 0.5, 72)
+    grg, V = lat.grg, lat.V
+    order = np.random.default_rng(72).permutation(V).astype(np.int32)
+    h = grg.grg_schur_create(lat.h, -0.2, order, max(1, V // 5), grg.grg_solver_params_default(max_rhs=nrhs))
+    xd = to_dev(gaussian_vectors(12 * V, nrhs, 72))
+    yd, zd = torch.empty_like(xd), torch.empty_like(xd)
+    for prec in ("fp64", "fp32", "bf16"):
+        print(f"canonical forms {dims} {prec} x {nrhs}", flush=True)
+        grg.grg_dirac_apply(lat.h, -0.2, prec, xd, yd, nrhs)
+        zd.copy_(xd)
+        grg.grg_dirac_apply(lat.h, -0.2, prec, zd, zd, nrhs)
+        assert torch.equal(yd, zd), prec
+        outs = {}
+        for pinned in (False, True):
+            if pinned:
+                grg.grg_schur_set_launch(h, prec, nrhs, [64, 1, 0, 64, 0, 0])
+            for rows in (-1, 0, 1):
+                for cols in (-1, 0, 1):
+                    grg.grg_block_apply(h, prec, rows, cols, xd, yd, nrhs)
+                    if pinned:
+                        assert torch.equal(yd, outs[rows, cols]), (prec, rows, cols)
+                    else:
+                        outs[rows, cols] = yd.clone()
+    grg.grg_schur_destroy(h)
     lat.close()

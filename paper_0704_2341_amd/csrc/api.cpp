@@ -496,7 +496,7 @@ grg_status grg_schur_create(grg_lattice L, double m0, const int32_t *q, int32_t 
     S->partials_elems = (size_t)partial_rows(g, prm.max_rhs) * prm.max_rhs * std::max(3, 2 * kMaxRhs);
     ALLOC(S->partials, S->partials_elems * sizeof(double));
     ALLOC(S->alpha, sizeof(double2) * kMaxRhs);
-    ALLOC(S->bicg_sc, sizeof(double2) * 4 * kMaxRhs);
+    ALLOC(S->bicg_sc, sizeof(double2) * 5 * kMaxRhs);  // rho, alpha, omega, beta, and rho's other place
     ALLOC(S->beta, sizeof(double2) * kMaxRhs * kMaxRhs);
     ALLOC(S->rn2, sizeof(double) * kMaxRhs);
     ALLOC(S->qn2, sizeof(double) * kMaxRhs * kMaxRhs);
@@ -505,7 +505,7 @@ grg_status grg_schur_create(grg_lattice L, double m0, const int32_t *q, int32_t 
     // scalars with one copy
     ALLOC(S->bn2, sizeof(double) * 5 * kMaxRhs);
     if (S->bn2) S->thr2 = S->bn2 + 4 * kMaxRhs;
-    ALLOC(S->active, sizeof(int) * kMaxRhs);
+    ALLOC(S->active, sizeof(int) * 2 * kMaxRhs);
     ALLOC(S->act0, sizeof(int) * kMaxRhs);
     if (L->eo_ok) ALLOC(S->d_mask_eo, (size_t)2 * L->Vhs);
     if (L->eo_ok) ALLOC(S->d_mask_par, (size_t)V);

@@ -206,11 +206,26 @@ hipError_t launch_reduce(int mode, const double *partials, int nparts, int nrhs,
                          double *out2, const double *thr2, int *active, hipStream_t st,
                          int *part = nullptr);
 
+// Scalars taken straight from per-workgroup partials by the vector kernels,
+// instead of by a reduction launch between: for as few rows as kFoldRows.  A
+// reduction of few rows is a launch of 2.6-5 us that the next kernel waits for;
+// summing them again in every wavefront adds about 1 us to that kernel (S_bb at
+// 8^4, BF16: 897 -> 814 us, the V-cycle 18.4 -> 15.4 ms; with 948 rows the
+// BiCGstab solve gains nothing, 1771 against 1800 us).
+constexpr int kFoldRows = 512;
+struct FoldMr {
+    const double *dot = nullptr;  // the stencil's sums [ndot][nrhs][3]; nullptr: alpha is given
+    int ndot = 0;
+    const double *nrm = nullptr;  // |r|^2 before this step [nnrm][nrhs] (nullptr: active alone decides)
+    int nnrm = 0;
+    const double *thr2 = nullptr; // with nrm: a RHS at or below it takes no step
+    const int *active = nullptr;
+};
 // x += alpha r ; r -= alpha q ; partial |r|^2     (one MR/GCR step; x_zero:
 // x is taken as zero and not read, the first step from x = 0)
 hipError_t launch_mr_update(int prec, const BlasShape &sh, void *x, void *r, const void *q,
                             const void *p, const double2 *alpha, double *partials,
-                            hipStream_t st, bool x_zero = false);
+                            hipStream_t st, bool x_zero = false, const FoldMr &fold = FoldMr());
 // partial |v|^2
 hipError_t launch_norm2(int prec, const BlasShape &sh, const void *v, double *partials,
                         hipStream_t st);
@@ -270,9 +285,24 @@ hipError_t launch_copy(int prec, const BlasShape &sh, const void *x, void *y, hi
 // from the stencil's fused sums against r0), kBicgBeta (beta, rho, |r|^2).
 enum { kBicgS = 0, kBicgUpd = 1, kBicgP = 2 };
 enum { kBicgInit = 0, kBicgAlpha = 1, kBicgBeta = 2 };
+// With fold.rows set, the step's own scalar comes from those partials (kBicgS:
+// alpha from the stencil's sums; kBicgUpd: omega from the stencil's; kBicgP:
+// beta, rho, |r|^2 and the active flags from kBicgUpd's) and the wavefront of
+// each RHS's first unit writes it out: alpha and omega to sc, and rho, the
+// flags and |r|^2 to the fold's outputs, which this launch does not read.
+struct FoldBicg {
+    const double *rows = nullptr;
+    int n = 0;
+    const double2 *rho = nullptr;  // current rho
+    double2 *rho_out = nullptr;    // kBicgP
+    const int *active = nullptr;
+    int *active_out = nullptr;     // kBicgP
+    const double *thr2 = nullptr;  // kBicgP
+    double *rn2 = nullptr;         // kBicgP
+};
 hipError_t launch_bicg(int prec, int mode, const BlasShape &sh, void *x, void *r, const void *a,
-                       const void *b, const void *c, const void *d, const double2 *sc,
-                       double *partials, hipStream_t st);
+                       const void *b, const void *c, const void *d, double2 *sc,
+                       double *partials, hipStream_t st, const FoldBicg &fold = FoldBicg());
 hipError_t launch_bicg_reduce(int mode, const double *partials, int nparts, int nrhs, double2 *sc,
                               double *out2, const double *thr2, int *active, hipStream_t st);
 

@@ -127,10 +127,11 @@ struct VecIO<GRG_FP64> {
 // X0: x is taken as zero (not read): the first update of a solve started
 // from x = 0.
 constexpr int kUnitVecs = 3;
-template <int P, bool HAS_P, bool X0 = false>
+// FOLD: alpha from the stencil's partials (see FoldMr).
+template <int P, bool HAS_P, bool X0 = false, bool FOLD = false>
 __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, void *r_,
                                                         const void *q_, const void *p_,
-                                                        const double2 *alpha, double *partials)
+                                                        const double2 *alpha, double *partials, FoldMr fold)
 {
     typedef VecIO<P> IO;
     typedef typename IO::R R;
@@ -149,7 +150,20 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
         const int u = w * 4 + wave;
         if (u >= nunits) continue;  // the whole wavefront
         const int tr = u / PARTS, tile = tr / sh.nrhs, k = tr - tile * sh.nrhs;
-        const double2 a2 = alpha[k];
+        double2 a2;
+        if constexpr (FOLD) {
+            bool on = fold.active == nullptr || fold.active[k] != 0;
+            if (fold.nrm) {
+                double n2[1];
+                wave_rows_sum<1>(fold.nrm, fold.nnrm, sh.nrhs, k, n2);
+                on = on && n2[0] > fold.thr2[k];
+            }
+            double sums[3];
+            wave_rows_sum<3>(fold.dot, fold.ndot, sh.nrhs, k, sums);
+            a2 = mr_alpha(sums, on);
+        } else {
+            a2 = alpha[k];
+        }
         const cpx<R> a = {(R)a2.x, (R)a2.y}, na = {-a.re, -a.im};
         const size_t base = (size_t)u * UV;
         R rr = 0;
@@ -193,10 +207,11 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
 //             of <r0, r> (re, im) and |r|^2 of the stored r
 //             (x_ = x, r_ = r, a = p, b = s, c = t, d = r0)
 //   kBicgP:   p = r + beta (p - omega v)          (r_ = p, a = r, b = v)
-template <int P, int MODE>
+// FOLD: the step's scalar from partials (see FoldBicg).
+template <int P, int MODE, bool FOLD = false>
 __global__ void __launch_bounds__(256) bicg_kernel(BlasShape sh, void *x_, void *r_, const void *a_,
                                                    const void *b_, const void *c_, const void *d_,
-                                                   const double2 *sc, double *partials)
+                                                   double2 *sc, double *partials, FoldBicg fold)
 {
     typedef VecIO<P> IO;
     typedef typename IO::R R;
@@ -217,7 +232,34 @@ __global__ void __launch_bounds__(256) bicg_kernel(BlasShape sh, void *x_, void 
         const int u = w * 4 + wave;
         if (u >= nunits) continue;
         const int tr = u / PARTS, tile = tr / sh.nrhs, k = tr - tile * sh.nrhs;
-        const double2 al2 = sc[kMaxRhs + k], om2 = sc[2 * kMaxRhs + k], be2 = sc[3 * kMaxRhs + k];
+        double2 al2, om2, be2;
+        if constexpr (FOLD) {
+            // (each scalar is read by later launches only where it is written here)
+            const bool on = fold.active[k] != 0, first = tr == k && u % PARTS == 0 && lane == 0;
+            double sums[3];
+            wave_rows_sum<3>(fold.rows, fold.n, sh.nrhs, k, sums);
+            if (MODE == kBicgS) {
+                al2 = bicg_alpha(fold.rho[k], sums, on);
+                if (first) sc[kMaxRhs + k] = al2;
+            } else if (MODE == kBicgUpd) {
+                al2 = sc[kMaxRhs + k];
+                om2 = mr_alpha(sums, on);
+                if (first) sc[2 * kMaxRhs + k] = om2;
+            } else {
+                om2 = sc[2 * kMaxRhs + k];
+                const double2 rn = make_double2(sums[0], sums[1]);
+                be2 = bicg_beta(rn, fold.rho[k], sc[kMaxRhs + k], om2, on);
+                if (first) {
+                    fold.rho_out[k] = rn;
+                    fold.active_out[k] = sums[2] > fold.thr2[k] ? 1 : 0;
+                    fold.rn2[k] = sums[2];
+                }
+            }
+        } else {
+            al2 = sc[kMaxRhs + k];
+            om2 = sc[2 * kMaxRhs + k];
+            be2 = sc[3 * kMaxRhs + k];
+        }
         const cpx<R> al = {(R)al2.x, (R)al2.y}, om = {(R)om2.x, (R)om2.y}, be = {(R)be2.x, (R)be2.y};
         const size_t base = (size_t)u * UV;
         R sre = 0, sim = 0, srr = 0;
@@ -325,23 +367,11 @@ __global__ void __launch_bounds__(256) bicg_reduce_kernel(int mode, const double
         out2[r] = sm[0][0];
         if (active) active[r] = sm[0][0] > thr2[r] ? 1 : 0;
     } else if (mode == kBicgAlpha) {
-        // <r0, v> = conj(sum conj(v) r0)
-        const double sr = sm[0][0], si = -sm[1][0];
-        const double den = sr * sr + si * si;
-        const double2 rh = rho[r];
-        alpha[r] = on && den > 0 ? make_double2((rh.x * sr + rh.y * si) / den, (rh.y * sr - rh.x * si) / den)
-                                 : make_double2(0.0, 0.0);
+        const double sums[3] = {sm[0][0], sm[1][0], sm[2][0]};
+        alpha[r] = bicg_alpha(rho[r], sums, on);
     } else {
-        const double2 rn = make_double2(sm[0][0], sm[1][0]), rh = rho[r], al = alpha[r], om = omega[r];
-        const double d1 = rh.x * rh.x + rh.y * rh.y, d2 = om.x * om.x + om.y * om.y;
-        double2 b = make_double2(0.0, 0.0);
-        if (on && d1 > 0 && d2 > 0) {
-            // (rn / rh) (al / om)
-            const double2 q1 = make_double2((rn.x * rh.x + rn.y * rh.y) / d1, (rn.y * rh.x - rn.x * rh.y) / d1);
-            const double2 q2 = make_double2((al.x * om.x + al.y * om.y) / d2, (al.y * om.x - al.x * om.y) / d2);
-            b = make_double2(q1.x * q2.x - q1.y * q2.y, q1.x * q2.y + q1.y * q2.x);
-        }
-        beta[r] = b;
+        const double2 rn = make_double2(sm[0][0], sm[1][0]);
+        beta[r] = bicg_beta(rn, rho[r], alpha[r], omega[r], on);
         rho[r] = rn;
         out2[r] = sm[2][0];
         if (active) active[r] = sm[2][0] > thr2[r] ? 1 : 0;
@@ -659,10 +689,9 @@ __global__ void __launch_bounds__(256) reduce_kernel(int mode, const double *par
     }
     if (threadIdx.x == 0) {
         if (mode == kAlpha) {
-            const double qq = sm[2][0];
-            const bool on = (active == nullptr || active[r]) && qq > 0;
-            alpha[r] = on ? make_double2(sm[0][0] / qq, sm[1][0] / qq) : make_double2(0.0, 0.0);
-            if (out2) out2[r] = qq;
+            const double sums[3] = {sm[0][0], sm[1][0], sm[2][0]};
+            alpha[r] = mr_alpha(sums, active == nullptr || active[r]);
+            if (out2) out2[r] = sums[2];
         } else {
             const double n2 = sm[mode == kNorm3 ? 2 : 0][0];
             out2[r] = n2;
@@ -726,15 +755,18 @@ hipError_t launch_reduce(int mode, const double *partials, int nparts, int nrhs,
 
 hipError_t launch_mr_update(int prec, const BlasShape &sh, void *x, void *r, const void *q,
                             const void *p, const double2 *alpha, double *partials,
-                            hipStream_t st, bool x_zero)
+                            hipStream_t st, bool x_zero, const FoldMr &fold)
 {
-    if (!shape_ok(sh)) return hipErrorInvalidValue;
+    if (!shape_ok(sh) || (p && fold.dot)) return hipErrorInvalidValue;
     dim3 g(sh.grid), b(kBlasSB);
-#define MRU(PP)                                                                                    \
-    if (p) hipLaunchKernelGGL((mr_update_kernel<PP, true>), g, b, 0, st, sh, x, r, q, p, alpha, partials); \
-    else if (x_zero)                                                                                      \
-        hipLaunchKernelGGL((mr_update_kernel<PP, false, true>), g, b, 0, st, sh, x, r, q, p, alpha, partials); \
-    else hipLaunchKernelGGL((mr_update_kernel<PP, false>), g, b, 0, st, sh, x, r, q, p, alpha, partials);
+#define MRK(PP, HP, X, F) \
+    hipLaunchKernelGGL((mr_update_kernel<PP, HP, X, F>), g, b, 0, st, sh, x, r, q, p, alpha, partials, fold)
+#define MRU(PP)                                     \
+    if (p) MRK(PP, true, false, false);             \
+    else if (fold.dot && x_zero) MRK(PP, false, true, true);   \
+    else if (fold.dot) MRK(PP, false, false, true); \
+    else if (x_zero) MRK(PP, false, true, false);   \
+    else MRK(PP, false, false, false);
     switch (prec) {
     case GRG_FP64: MRU(GRG_FP64) break;
     case GRG_FP32: MRU(GRG_FP32) break;
@@ -742,19 +774,26 @@ hipError_t launch_mr_update(int prec, const BlasShape &sh, void *x, void *r, con
     default: return hipErrorInvalidValue;
     }
 #undef MRU
+#undef MRK
     return hipGetLastError();
 }
 
 hipError_t launch_bicg(int prec, int mode, const BlasShape &sh, void *x, void *r, const void *a,
-                       const void *b, const void *c, const void *d, const double2 *sc,
-                       double *partials, hipStream_t st)
+                       const void *b, const void *c, const void *d, double2 *sc,
+                       double *partials, hipStream_t st, const FoldBicg &fold)
 {
     if (!shape_ok(sh) || mode < kBicgS || mode > kBicgP) return hipErrorInvalidValue;
     dim3 g(sh.grid), bl(kBlasSB);
-#define BIC(PP)                                                                                         \
-    if (mode == kBicgS) hipLaunchKernelGGL((bicg_kernel<PP, kBicgS>), g, bl, 0, st, sh, x, r, a, b, c, d, sc, partials); \
-    else if (mode == kBicgUpd) hipLaunchKernelGGL((bicg_kernel<PP, kBicgUpd>), g, bl, 0, st, sh, x, r, a, b, c, d, sc, partials); \
-    else hipLaunchKernelGGL((bicg_kernel<PP, kBicgP>), g, bl, 0, st, sh, x, r, a, b, c, d, sc, partials);
+#define BIK(PP, M, F) \
+    hipLaunchKernelGGL((bicg_kernel<PP, M, F>), g, bl, 0, st, sh, x, r, a, b, c, d, sc, partials, fold)
+#define BIC(PP)                                       \
+    if (fold.rows) {                                  \
+        if (mode == kBicgS) BIK(PP, kBicgS, true);    \
+        else if (mode == kBicgUpd) BIK(PP, kBicgUpd, true); \
+        else BIK(PP, kBicgP, true);                   \
+    } else if (mode == kBicgS) BIK(PP, kBicgS, false); \
+    else if (mode == kBicgUpd) BIK(PP, kBicgUpd, false); \
+    else BIK(PP, kBicgP, false);
     switch (prec) {
     case GRG_FP64: BIC(GRG_FP64) break;
     case GRG_FP32: BIC(GRG_FP32) break;
@@ -762,6 +801,7 @@ hipError_t launch_bicg(int prec, int mode, const BlasShape &sh, void *x, void *r
     default: return hipErrorInvalidValue;
     }
 #undef BIC
+#undef BIK
     return hipGetLastError();
 }
 

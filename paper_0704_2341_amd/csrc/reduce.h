@@ -32,4 +32,58 @@ __device__ __forceinline__ void strided_sum(const double *__restrict__ partials,
         for (int k = 0; k < K; ++k) acc[k] += partials[((size_t)i * nrhs + r) * K + k];
 }
 
+// The same sums by one wavefront (every lane gets them), in an order of its own
+// that is the same in every wavefront: for the vector kernels that take their
+// scalars straight from the partials (a few hundred rows).
+template <int K>
+__device__ __forceinline__ void wave_rows_sum(const double *__restrict__ partials, int n, int nrhs, int r,
+                                              double (&acc)[K])
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc[k] = 0.0;
+    int i = lane;
+    for (; i + 3 * 64 < n; i += 4 * 64) {
+        double v[4][K];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < K; ++k) v[u][k] = partials[((size_t)(i + u * 64) * nrhs + r) * K + k];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < K; ++k) acc[k] += v[u][k];
+    }
+    for (; i < n; i += 64)
+#pragma unroll
+        for (int k = 0; k < K; ++k) acc[k] += partials[((size_t)i * nrhs + r) * K + k];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        for (int o = 32; o > 0; o >>= 1) acc[k] += __shfl_xor(acc[k], o, 64);
+}
+
+// alpha = <q, r> / |q|^2 from the sums (re, im, |q|^2)
+__device__ __forceinline__ double2 mr_alpha(const double (&s)[3], bool on)
+{
+    return on && s[2] > 0 ? make_double2(s[0] / s[2], s[1] / s[2]) : make_double2(0.0, 0.0);
+}
+// BiCGstab: alpha = rho / <r0, v> from the sums of conj(v) r0
+__device__ __forceinline__ double2 bicg_alpha(double2 rho, const double (&s)[3], bool on)
+{
+    // <r0, v> = conj(sum conj(v) r0)
+    const double sr = s[0], si = -s[1];
+    const double den = sr * sr + si * si;
+    return on && den > 0 ? make_double2((rho.x * sr + rho.y * si) / den, (rho.y * sr - rho.x * si) / den)
+                         : make_double2(0.0, 0.0);
+}
+// beta = (rho' / rho) (alpha / omega)
+__device__ __forceinline__ double2 bicg_beta(double2 rn, double2 rho, double2 al, double2 om, bool on)
+{
+    const double d1 = rho.x * rho.x + rho.y * rho.y, d2 = om.x * om.x + om.y * om.y;
+    if (!on || !(d1 > 0) || !(d2 > 0)) return make_double2(0.0, 0.0);
+    const double2 q1 = make_double2((rn.x * rho.x + rn.y * rho.y) / d1, (rn.y * rho.x - rn.x * rho.y) / d1);
+    const double2 q2 = make_double2((al.x * om.x + al.y * om.y) / d2, (al.y * om.x - al.x * om.y) / d2);
+    return make_double2(q1.x * q2.x - q1.y * q2.y, q1.x * q2.y + q1.y * q2.x);
+}
+
 }  // namespace grg

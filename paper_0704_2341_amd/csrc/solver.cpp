@@ -167,6 +167,12 @@ grg_status precond_apply_inner(grg_schur S, int prec, const void *r, void *p, in
 // Largest grid any stencil or BLAS launch may use (sizes the partial sums).
 constexpr int kMaxGrid = kMaxGridValue;
 int partial_rows(const Geom &, int) { return kMaxGrid; }
+// Part j (0, 1, 2) of the partial sums' room, each for kMaxGrid rows of three
+// sums per RHS (the room is ten times that).
+static double *partial_rows_at(grg_schur S, int j)
+{
+    return S->partials + (size_t)j * 3 * kMaxGrid * S->prm.max_rhs;
+}
 
 // Autotuner: time every candidate launch of the D_rr stencil (with its fused
 // dot products, as the solver runs it) on the handle's own workspaces and keep
@@ -1002,21 +1008,40 @@ static grg_status inner_mr_eo(grg_schur S, int prec, int nrhs, const double *thr
         GRG_TRY(read_norms(S, nrhs, h));
         done = all_done(h);
     }
+    // few partial rows: the update takes alpha and the previous |r|^2 from them
+    // itself (the norms' rows alternate between two places), and the norms are
+    // reduced where the host reads them
+    const bool fold = t.grid <= kFoldRows && sh.grid <= kFoldRows;
     while (done == 0 && it < maxit) {
         // q = (d - H_PQ H_QP / d) r, with the sums for alpha
         GRG_TRY(eo_hop(S, prec, t, r, nullptr, w, Q, 0.0, 1.0, nrhs, nullptr, nullptr));
         GRG_TRY(eo_hop(S, prec, t, w, r, q, P, d, -1.0 / d, nrhs, S->partials, r));
+        const bool read = (it + 1) % check == 0 || it + 1 == maxit;
         {
             PhaseTimer pt(S->prof, st, kProfBlas);
-            GRG_TRY_HIP(launch_reduce(kAlpha, S->partials, t.grid, nrhs, S->alpha, nullptr, nullptr,
-                                      S->active, st));
+            double *norms = S->partials;
+            FoldMr f;
+            if (fold) {
+                norms = partial_rows_at(S, 1 + (it & 1));
+                f.dot = S->partials;
+                f.ndot = t.grid;
+                f.active = S->active;
+                if (it > 0) {
+                    f.nrm = partial_rows_at(S, 1 + ((it - 1) & 1));
+                    f.nnrm = sh.grid;
+                    f.thr2 = S->thr2;
+                }
+            } else {
+                GRG_TRY_HIP(launch_reduce(kAlpha, S->partials, t.grid, nrhs, S->alpha, nullptr, nullptr,
+                                          S->active, st));
+            }
             // x starts at zero: the first step writes x = alpha r without reading it
-            GRG_TRY_HIP(launch_mr_update(prec, sh, x, r, q, nullptr, S->alpha, S->partials, st, it == 0));
-            GRG_TRY_HIP(launch_reduce(kNorm, S->partials, sh.grid, nrhs, nullptr, S->rn2, S->thr2,
-                                      S->active, st));
+            GRG_TRY_HIP(launch_mr_update(prec, sh, x, r, q, nullptr, S->alpha, norms, st, it == 0, f));
+            if (!fold || read)
+                GRG_TRY_HIP(launch_reduce(kNorm, norms, sh.grid, nrhs, nullptr, S->rn2, S->thr2, S->active, st));
         }
         ++it;
-        if (it % check == 0 || it == maxit) {
+        if (read) {
             GRG_TRY(read_norms(S, nrhs, h));
             done = all_done(h);
         }
@@ -1205,16 +1230,44 @@ static grg_status inner_bicgstab(grg_schur S, int prec, int nrhs, const double *
     };
     int it = 0;
     int done = all_done(h);
+    // few partial rows: the vector steps take their scalars from them (rho and
+    // the flags alternate between two places, since the step that forms them
+    // reads the current ones)
+    const bool fold = nparts <= kFoldRows && sh.grid <= kFoldRows;
+    double2 *rho[2] = {sc, sc + 4 * kMaxRhs};
+    int *act[2] = {S->active, S->active + kMaxRhs};
     while (done == 0 && it < maxit) {
         GRG_TRY(apply(pv, v, r0));
-        {
+        if (fold) {
+            const int now = it & 1;
+            FoldBicg f;
+            f.rows = S->partials;
+            f.n = nparts;
+            f.rho = rho[now];
+            f.active = act[now];
+            {
+                PhaseTimer pt(S->prof, st, kProfBlas);
+                GRG_TRY_HIP(launch_bicg(prec, kBicgS, sh, nullptr, sv, r, v, nullptr, nullptr, sc, nullptr, st, f));
+            }
+            GRG_TRY(apply(sv, tv, sv));
             PhaseTimer pt(S->prof, st, kProfBlas);
-            GRG_TRY_HIP(launch_bicg_reduce(kBicgAlpha, S->partials, nparts, nrhs, sc, nullptr, nullptr,
-                                           S->active, st));
-            GRG_TRY_HIP(launch_bicg(prec, kBicgS, sh, nullptr, sv, r, v, nullptr, nullptr, sc, nullptr, st));
-        }
-        GRG_TRY(apply(sv, tv, sv));
-        {
+            double *rows = partial_rows_at(S, 1);
+            GRG_TRY_HIP(launch_bicg(prec, kBicgUpd, sh, x, r, pv, sv, tv, r0, sc, rows, st, f));
+            f.rows = rows;
+            f.n = sh.grid;
+            f.rho_out = rho[1 - now];
+            f.active_out = act[1 - now];
+            f.thr2 = S->thr2;
+            f.rn2 = S->rn2;
+            GRG_TRY_HIP(launch_bicg(prec, kBicgP, sh, nullptr, pv, r, v, nullptr, nullptr, sc, nullptr, st, f));
+        } else {
+            {
+                PhaseTimer pt(S->prof, st, kProfBlas);
+                GRG_TRY_HIP(launch_bicg_reduce(kBicgAlpha, S->partials, nparts, nrhs, sc, nullptr, nullptr,
+                                               S->active, st));
+                GRG_TRY_HIP(launch_bicg(prec, kBicgS, sh, nullptr, sv, r, v, nullptr, nullptr, sc, nullptr, st));
+            }
+            GRG_TRY(apply(sv, tv, sv));
             PhaseTimer pt(S->prof, st, kProfBlas);
             GRG_TRY_HIP(launch_reduce(kAlpha, S->partials, nparts, nrhs, sc + 2 * kMaxRhs, nullptr, nullptr,
                                       S->active, st));

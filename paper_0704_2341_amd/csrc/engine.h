@@ -51,7 +51,7 @@ struct DslashArgs {
     int chunk;            // items per XCD chunk (0 = one contiguous eighth per XCD)
     int march;            // > 0: t-marching kernel with time chunks of this length
                           //      (64 sites x RG RHS wavefronts per workgroup)
-    double *partials;     // [grid][nrhs][3] or nullptr
+    double *partials;     // [nrhs][3][grid] or nullptr
     const void *dot_with; // the fused dots use this field instead of `in` (or nullptr)
     int out_canon = 0;    // out is a canonical complex128 field (site-parallel forms, no sums)
     const uint8_t *in_mask = nullptr;  // canonical hop-per-wavefront form only: in is read on the
@@ -73,7 +73,7 @@ struct EoArgs {
     int Vh, Vhs;          // half volume, and padded to whole tiles (multiple of 256)
     int nrhs, SB, RG, hops, chunk;
     int march;            // hops == 3: time slices per workgroup item (t-marching form)
-    double *partials;     // [grid][nrhs][3] or nullptr
+    double *partials;     // [nrhs][3][grid] or nullptr
     const void *dot_with; // parity po, or nullptr: the sums are |out|^2 only (re, im zero)
     const int *active;    // per RHS: 0 writes zero for that RHS (nullptr: all active)
     // full-layout variants (the first and last steps of a reduced solve read
@@ -128,7 +128,7 @@ struct DcArgs {
     double diag;          // 4 + m0
     Geom g;
     int nrhs;
-    double *partials;     // [grid][nrhs]: |r_out|^2
+    double *partials;     // [nrhs][grid]: |r_out|^2
     int RG, chunk, march; // t-marching launch (march > 0), as in DslashArgs
     int split = 0;        // kSplitForm: the hop-per-wavefront form
     int ring;             // with march > 0 and BF16 e: the LDS-ring form of the t-marching step
@@ -157,7 +157,7 @@ hipError_t launch_dc_split(int prec, const DcArgs &a, int grid, hipStream_t st);
 hipError_t launch_dslash_coarse(const CoarseArgs &a, hipStream_t st);
 // b = D_rb x_b from the canonical coarse vector (kernels_coarse.hip): internal
 // FP64 field, zero on the coarse sites
-// With partials set, also the per-workgroup |b|^2 per RHS ([rb_apply_grid(g)][nrhs]).
+// With partials set, also the per-workgroup |b|^2 per RHS ([nrhs][rb_apply_grid(g)]).
 // With pair set, b also in precision pair_prec as a compact even-odd pair
 // (parity `first` at compact index s / 2, the other parity `half` elements on).
 hipError_t launch_rb_apply(const Geom &g, const double *xb, const int32_t *bidx, int nb, const void *U64,
@@ -187,7 +187,7 @@ hipError_t launch_scatter_coarse(const double *xb, void *dst, const int32_t *bid
                                  const Geom &g, int nrhs, hipStream_t st);
 
 // BLAS-1 on internal fields.  Every kernel walks sites in work items of
-// SB sites x all RHS (looped); partial sums go to [grid][nrhs][k] doubles.
+// SB sites x all RHS (looped); partial sums go to [nrhs][k][grid] doubles.
 struct BlasShape {
     Geom g;
     int nrhs;
@@ -214,9 +214,9 @@ hipError_t launch_reduce(int mode, const double *partials, int nparts, int nrhs,
 // BiCGstab solve gains nothing, 1771 against 1800 us).
 constexpr int kFoldRows = 512;
 struct FoldMr {
-    const double *dot = nullptr;  // the stencil's sums [ndot][nrhs][3]; nullptr: alpha is given
+    const double *dot = nullptr;  // the stencil's sums [nrhs][3][ndot]; nullptr: alpha is given
     int ndot = 0;
-    const double *nrm = nullptr;  // |r|^2 before this step [nnrm][nrhs] (nullptr: active alone decides)
+    const double *nrm = nullptr;  // |r|^2 before this step [nrhs][nnrm] (nullptr: active alone decides)
     int nnrm = 0;
     const double *thr2 = nullptr; // with nrm: a RHS at or below it takes no step
     const int *active = nullptr;

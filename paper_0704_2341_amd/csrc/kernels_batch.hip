@@ -432,7 +432,6 @@ __global__ void __launch_bounds__(256) batch_reduce_kernel(int mode, const doubl
                                                            const double *thr2, const int *act_in,
                                                            int *act_out)
 {
-    __shared__ double sm[3][256];
     if (act_in && !any_set(act_in, nsys)) return;
     const int r = blockIdx.x;
     if (act_in && !act_in[r]) {
@@ -442,23 +441,14 @@ __global__ void __launch_bounds__(256) batch_reduce_kernel(int mode, const doubl
         }
         return;
     }
-    const int K = mode == kNorm ? 1 : 3;
-    double acc[3] = {0, 0, 0};
-    if (K == 1) strided_sum<1>(partials, nparts, nsys, r, acc);
-    else strided_sum<3>(partials, nparts, nsys, r, acc);
-    for (int k = 0; k < K; ++k) sm[k][threadIdx.x] = acc[k];
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o)
-            for (int k = 0; k < K; ++k) sm[k][threadIdx.x] += sm[k][threadIdx.x + o];
-        __syncthreads();
-    }
+    double sums[3] = {0, 0, 0};
+    if (mode == kNorm) block_rows_sum<1>(partials, nparts, r, sums, nsys);
+    else block_rows_sum<3>(partials, nparts, r, sums, nsys);
     if (threadIdx.x != 0) return;
     if (mode == kAlpha) {
-        const double qq = sm[2][0];
-        alpha[r] = qq > 0 ? make_double2(sm[0][0] / qq, sm[1][0] / qq) : make_double2(0.0, 0.0);
+        alpha[r] = mr_alpha(sums, true);
     } else {
-        const double n2 = sm[mode == kNorm3 ? 2 : 0][0];
+        const double n2 = sums[mode == kNorm3 ? 2 : 0];
         if (out2) out2[r] = n2;
         if (act_out) act_out[r] = n2 > thr2[r] ? 1 : 0;
     }

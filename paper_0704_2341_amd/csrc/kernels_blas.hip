@@ -58,7 +58,7 @@ struct Partial {
         for (int i = threadIdx.x; i < nrhs * K; i += blockDim.x) {
             double t = 0;
             for (int w = 0; w < nw; ++w) t += red[w * nrhs + i / K][i % K];
-            partials[(size_t)blockIdx.x * nrhs * K + i] = t;
+            partials[(size_t)i * gridDim.x + blockIdx.x] = t;
         }
     }
 };
@@ -155,11 +155,11 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
             bool on = fold.active == nullptr || fold.active[k] != 0;
             if (fold.nrm) {
                 double n2[1];
-                wave_rows_sum<1>(fold.nrm, fold.nnrm, sh.nrhs, k, n2);
+                wave_rows_sum<1>(fold.nrm, fold.nnrm, k, n2);
                 on = on && n2[0] > fold.thr2[k];
             }
             double sums[3];
-            wave_rows_sum<3>(fold.dot, fold.ndot, sh.nrhs, k, sums);
+            wave_rows_sum<3>(fold.dot, fold.ndot, k, sums);
             a2 = mr_alpha(sums, on);
         } else {
             a2 = alpha[k];
@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
     }
     __syncthreads();
     for (int i = threadIdx.x; i < sh.nrhs; i += blockDim.x)
-        partials[(size_t)blockIdx.x * sh.nrhs + i] = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
+        partials[(size_t)i * gridDim.x + blockIdx.x] = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
 }
 
 // BiCGstab vector steps (per-RHS scalars sc[0..3][kMaxRhs] = rho, alpha,
@@ -237,7 +237,7 @@ __global__ void __launch_bounds__(256) bicg_kernel(BlasShape sh, void *x_, void 
             // (each scalar is read by later launches only where it is written here)
             const bool on = fold.active[k] != 0, first = tr == k && u % PARTS == 0 && lane == 0;
             double sums[3];
-            wave_rows_sum<3>(fold.rows, fold.n, sh.nrhs, k, sums);
+            wave_rows_sum<3>(fold.rows, fold.n, k, sums);
             if (MODE == kBicgS) {
                 al2 = bicg_alpha(fold.rho[k], sums, on);
                 if (first) sc[kMaxRhs + k] = al2;
@@ -328,7 +328,7 @@ __global__ void __launch_bounds__(256) bicg_kernel(BlasShape sh, void *x_, void 
         __syncthreads();
         for (int i = threadIdx.x; i < sh.nrhs * 3; i += blockDim.x) {
             const int k = i / 3, j = i % 3;
-            partials[(size_t)blockIdx.x * sh.nrhs * 3 + i] =
+            partials[(size_t)i * gridDim.x + blockIdx.x] =
                 ((red[0][k][j] + red[1][k][j]) + red[2][k][j]) + red[3][k][j];
         }
     }
@@ -342,39 +342,29 @@ __global__ void __launch_bounds__(256) bicg_kernel(BlasShape sh, void *x_, void 
 // An inactive RHS (or a zero denominator) gets alpha = beta = 0, which
 // freezes its x and r in the vector steps (omega comes from the MR reduction
 // with the same active flags).
-__global__ void __launch_bounds__(256) bicg_reduce_kernel(int mode, const double *partials, int nparts,
+__global__ void __launch_bounds__(1024) bicg_reduce_kernel(int mode, const double *partials, int nparts,
                                                           int nrhs, double2 *sc, double *out2,
                                                           const double *thr2, int *active)
 {
-    __shared__ double sm[3][256];
     const int r = blockIdx.x;
-    const int K = mode == kBicgInit ? 1 : 3;
-    double acc[3] = {0, 0, 0};
-    if (K == 1) strided_sum<1>(partials, nparts, nrhs, r, acc);
-    else strided_sum<3>(partials, nparts, nrhs, r, acc);
-    for (int k = 0; k < K; ++k) sm[k][threadIdx.x] = acc[k];
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o)
-            for (int k = 0; k < K; ++k) sm[k][threadIdx.x] += sm[k][threadIdx.x + o];
-        __syncthreads();
-    }
+    double sums[3] = {0, 0, 0};
+    if (mode == kBicgInit) block_rows_sum<1>(partials, nparts, r, sums);
+    else block_rows_sum<3>(partials, nparts, r, sums);
     if (threadIdx.x != 0) return;
     double2 *rho = sc, *alpha = sc + kMaxRhs, *omega = sc + 2 * kMaxRhs, *beta = sc + 3 * kMaxRhs;
     const bool on = active == nullptr || active[r];
     if (mode == kBicgInit) {
-        rho[r] = make_double2(sm[0][0], 0.0);
-        out2[r] = sm[0][0];
-        if (active) active[r] = sm[0][0] > thr2[r] ? 1 : 0;
+        rho[r] = make_double2(sums[0], 0.0);
+        out2[r] = sums[0];
+        if (active) active[r] = sums[0] > thr2[r] ? 1 : 0;
     } else if (mode == kBicgAlpha) {
-        const double sums[3] = {sm[0][0], sm[1][0], sm[2][0]};
         alpha[r] = bicg_alpha(rho[r], sums, on);
     } else {
-        const double2 rn = make_double2(sm[0][0], sm[1][0]);
+        const double2 rn = make_double2(sums[0], sums[1]);
         beta[r] = bicg_beta(rn, rho[r], alpha[r], omega[r], on);
         rho[r] = rn;
-        out2[r] = sm[2][0];
-        if (active) active[r] = sm[2][0] > thr2[r] ? 1 : 0;
+        out2[r] = sums[2];
+        if (active) active[r] = sums[2] > thr2[r] ? 1 : 0;
     }
 }
 
@@ -670,30 +660,20 @@ __global__ void __launch_bounds__(256) orthogonalise_kernel(BlasShape sh, const 
 }
 
 // ------------------------------------------------------------------ reductions
-__global__ void __launch_bounds__(256) reduce_kernel(int mode, const double *partials, int nparts,
+__global__ void __launch_bounds__(1024) reduce_kernel(int mode, const double *partials, int nparts,
                                                      int nrhs, double2 *alpha, double *out2,
                                                      const double *thr2, int *active, int *part)
 {
-    __shared__ double sm[3][256];
     const int r = blockIdx.x;
-    const int K = mode == kNorm ? 1 : 3;
-    double acc[3] = {0, 0, 0};
-    if (K == 1) strided_sum<1>(partials, nparts, nrhs, r, acc);
-    else strided_sum<3>(partials, nparts, nrhs, r, acc);
-    for (int k = 0; k < K; ++k) sm[k][threadIdx.x] = acc[k];
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o)
-            for (int k = 0; k < K; ++k) sm[k][threadIdx.x] += sm[k][threadIdx.x + o];
-        __syncthreads();
-    }
+    double sums[3] = {0, 0, 0};
+    if (mode == kNorm) block_rows_sum<1>(partials, nparts, r, sums);
+    else block_rows_sum<3>(partials, nparts, r, sums);
     if (threadIdx.x == 0) {
         if (mode == kAlpha) {
-            const double sums[3] = {sm[0][0], sm[1][0], sm[2][0]};
             alpha[r] = mr_alpha(sums, active == nullptr || active[r]);
             if (out2) out2[r] = sums[2];
         } else {
-            const double n2 = sm[mode == kNorm3 ? 2 : 0][0];
+            const double n2 = sums[mode == kNorm3 ? 2 : 0];
             out2[r] = n2;
             if (active) active[r] = n2 > thr2[r] ? 1 : 0;
             if (part) part[r] = isinf(thr2[r]) ? 0 : 1;
@@ -748,7 +728,7 @@ static bool shape_ok(const BlasShape &sh)
 hipError_t launch_reduce(int mode, const double *partials, int nparts, int nrhs, double2 *alpha,
                          double *out2, const double *thr2, int *active, hipStream_t st, int *part)
 {
-    hipLaunchKernelGGL(reduce_kernel, dim3(nrhs), dim3(256), 0, st, mode, partials, nparts, nrhs,
+    hipLaunchKernelGGL(reduce_kernel, dim3(nrhs), dim3(reduce_threads(nparts)), 0, st, mode, partials, nparts, nrhs,
                        alpha, out2, thr2, active, part);
     return hipGetLastError();
 }
@@ -809,7 +789,7 @@ hipError_t launch_bicg_reduce(int mode, const double *partials, int nparts, int 
                               double *out2, const double *thr2, int *active, hipStream_t st)
 {
     if (nrhs < 1 || nrhs > kMaxRhs || mode < kBicgInit || mode > kBicgBeta) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(bicg_reduce_kernel, dim3(nrhs), dim3(256), 0, st, mode, partials, nparts, nrhs, sc,
+    hipLaunchKernelGGL(bicg_reduce_kernel, dim3(nrhs), dim3(reduce_threads(nparts)), 0, st, mode, partials, nparts, nrhs, sc,
                        out2, thr2, active);
     return hipGetLastError();
 }

@@ -51,7 +51,7 @@ __device__ __forceinline__ void rb_hops(cpx<double> (&acc)[12], int s, const Sit
 
 // Work items (block of 256 sites, RHS) with the RHS fastest, one contiguous
 // range per XCD: the RHS of a site block run side by side in one L2 and share
-// its links and neighbour lists.  partials[workgroup][r]: the workgroup's sum
+// its links and neighbour lists.  partials[r][workgroup]: the workgroup's sum
 // of |out|^2 for RHS r.  PP >= 0: b also written, in precision PP, into the
 // compact even-odd pair `pair` (parity `first` at compact index s / 2, the
 // other parity `half` elements on), the reduced solve's right-hand side.
@@ -103,7 +103,7 @@ __global__ void __launch_bounds__(256) rb_apply_kernel(Geom g, const double2 *__
     if (partials) {
         __syncthreads();
         for (int i = threadIdx.x; i < nrhs; i += blockDim.x)
-            partials[(size_t)blockIdx.x * nrhs + i] = red[0][i] + red[1][i] + red[2][i] + red[3][i];
+            partials[(size_t)i * gridDim.x + blockIdx.x] = red[0][i] + red[1][i] + red[2][i] + red[3][i];
     }
 }
 

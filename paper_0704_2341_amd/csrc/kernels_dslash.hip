@@ -113,7 +113,7 @@ __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a)
         for (int i = threadIdx.x; i < a.nrhs * 3; i += blockDim.x) {
             double t = 0;
             for (int k = 0; k < nw; ++k) t += red[k][i / 3][i % 3];
-            a.partials[(size_t)blockIdx.x * a.nrhs * 3 + i] = t;
+            a.partials[(size_t)i * gridDim.x + blockIdx.x] = t;
         }
     }
 }
@@ -370,7 +370,7 @@ __global__ void __launch_bounds__(E::kThreads) march_kernel(typename E::Args a)
     if (partials) {
         __syncthreads();
         for (int i = threadIdx.x; i < a.nrhs * K; i += blockDim.x)
-            partials[(size_t)blockIdx.x * a.nrhs * K + i] = red[i / K][i % K];
+            partials[(size_t)i * gridDim.x + blockIdx.x] = red[i / K][i % K];
     }
 }
 
@@ -547,7 +547,7 @@ __global__ void __launch_bounds__(64 * kRingWaves) ring_march_kernel(typename E:
     if (partials) {
         __syncthreads();
         for (int i = threadIdx.x; i < a.nrhs * K; i += blockDim.x)
-            partials[(size_t)blockIdx.x * a.nrhs * K + i] = red[i / K][i % K];
+            partials[(size_t)i * gridDim.x + blockIdx.x] = red[i / K][i % K];
     }
 }
 
@@ -628,7 +628,7 @@ __global__ void __launch_bounds__(256) dc_update_kernel(DcArgs a)
     for (int i = threadIdx.x; i < a.nrhs; i += blockDim.x) {
         double t = 0;
         for (int k = 0; k < nw; ++k) t += red[k][i];
-        a.partials[(size_t)blockIdx.x * a.nrhs + i] = t;
+        a.partials[(size_t)i * gridDim.x + blockIdx.x] = t;
     }
 }
 

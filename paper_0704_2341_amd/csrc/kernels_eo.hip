@@ -544,7 +544,7 @@ __global__ void __launch_bounds__(256) eo_hop_kernel(EoArgs a)
         for (int i = threadIdx.x; i < a.nrhs * 3; i += blockDim.x) {
             double t = 0;
             for (int k = 0; k < nw; ++k) t += red[k][i / 3][i % 3];
-            a.partials[(size_t)blockIdx.x * a.nrhs * 3 + i] = t;
+            a.partials[(size_t)i * gridDim.x + blockIdx.x] = t;
         }
     }
 }
@@ -835,7 +835,7 @@ __global__ void __launch_bounds__(kMaxPlane * NPL, 4) eo_plane_kernel(EoArgs a)
         for (int i = tid; i < nr * 3; i += blockDim.x) {
             double t = 0;
             for (int k = 0; k < nw; ++k) t += red[k][i / 3][i % 3];
-            a.partials[(size_t)blockIdx.x * nr * 3 + i] = t;
+            a.partials[(size_t)i * gridDim.x + blockIdx.x] = t;
         }
     }
 }

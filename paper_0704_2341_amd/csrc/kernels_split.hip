@@ -38,7 +38,7 @@ struct SplitSums {
         for (int i = threadIdx.x; i < nrhs * K; i += blockDim.x) {
             double t = 0;
             for (int w = 0; w < 6; ++w) t += red[w][i / K][i % K];
-            partials[(size_t)blockIdx.x * nrhs * K + i] = t;
+            partials[(size_t)i * gridDim.x + blockIdx.x] = t;
         }
     }
 };

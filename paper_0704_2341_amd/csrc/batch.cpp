@@ -50,11 +50,12 @@ struct grg_batch_s {
     void *U[3] = {nullptr, nullptr, nullptr};
     uint8_t *mask = nullptr;
     int32_t *bidx = nullptr, *qg = nullptr;
-    int *clat = nullptr, *tile_lat = nullptr, *off = nullptr, *nb = nullptr, *nboff = nullptr;
+    int *tile_lat = nullptr, *off = nullptr, *nb = nullptr, *nboff = nullptr;
     int4 *dims = nullptr;
     double *diag = nullptr;
     long long *coff = nullptr;
-    void *b64 = nullptr, *x64 = nullptr, *r64 = nullptr, *t64 = nullptr, *u64 = nullptr;
+    void *b64 = nullptr, *x64 = nullptr, *r64 = nullptr, *t64 = nullptr;
+    void *Uh = nullptr;  // the inner precision's links by side (reduced solve)
     void *in_b = nullptr, *in_x = nullptr, *in_r = nullptr, *in_q = nullptr;
     // the even-odd reduced inner solve (every extent even, params.eo) on compact
     // half-lattice fields (BatchHalf): per lattice the parity with fewer rest
@@ -179,7 +180,7 @@ static grg_status eo_half(grg_batch B, int prec, const void *in, const void *in2
     a.in = in;
     a.in2 = in2;
     a.out = out;
-    a.U = B->U[prec];
+    a.U = B->Uh;
     a.bt = table(B);
     a.hf = half(B);
     a.po = po;
@@ -259,19 +260,19 @@ static grg_status outer_step(grg_batch B, int prec, const void *r_src, const voi
 {
     BatchBlasArgs a = blas(B);
     a.act = B->oact;
-    GRG_TRY_HIP(launch_batch_inner_init(prec, a, r_src, B->fr2, B->in_r, B->in_x, B->st));
-    GRG_TRY_HIP(launch_batch_reduce(kNorm, B->partials, a.grid, B->nsys, nullptr, B->rn2i, B->thr2, B->oact,
-                                    B->active, B->st));
     if (B->eo) {
         // the halves b_p (into hq for the moment) and b_q of the inner right-hand
         // side, the reduced right-hand side b_p - H_pq b_q / d into hr with its
         // |.|^2 setting the inner flags, and the reduced iterate from zero
-        GRG_TRY_HIP(launch_batch_eo_split(prec, table(B), half(B), B->nrhs, B->in_r, B->hq, B->hbq, 0, hgrid(B),
-                                          B->st));
+        GRG_TRY_HIP(launch_batch_inner_split(prec, a, half(B), r_src, B->fr2, B->hq, B->hbq, B->st));
         GRG_TRY(eo_half(B, prec, B->hbq, B->hq, B->hr, 0, kC1, kCminv, true, B->oact));
         GRG_TRY_HIP(launch_batch_reduce(kNorm3, B->partials, egrid(B), B->nsys, nullptr, B->rn2i, B->thr2,
                                         B->oact, B->active, B->st));
         GRG_TRY_HIP(launch_fill_zero(B->hx, (size_t)B->Vh * B->nrhs * 12 * prec_bytes(prec), B->st));
+    } else {
+        GRG_TRY_HIP(launch_batch_inner_init(prec, a, r_src, B->fr2, B->in_r, B->in_x, B->st));
+        GRG_TRY_HIP(launch_batch_reduce(kNorm, B->partials, a.grid, B->nsys, nullptr, B->rn2i, B->thr2, B->oact,
+                                        B->active, B->st));
     }
     int it = 0;
     if (eager) {
@@ -294,8 +295,8 @@ static grg_status outer_step(grg_batch B, int prec, const void *r_src, const voi
         // the other parity of the correction, e_q = (b_q - H_qp e_p) / d, and
         // both halves into the full-layout correction in_x
         GRG_TRY(eo_half(B, prec, B->hx, B->hbq, B->heq, 1, kCinv, kCminv, false, B->oact));
-        GRG_TRY_HIP(launch_batch_eo_split(prec, table(B), half(B), B->nrhs, B->in_x, B->hx, B->heq, 1, hgrid(B),
-                                          B->st));
+        GRG_TRY_HIP(launch_batch_eo_join(prec, table(B), half(B), B->nrhs, B->in_x, B->hx, B->heq, hgrid(B),
+                                         B->st));
     }
     BatchDcArgs d;
     d.e = B->in_x;
@@ -313,7 +314,7 @@ static grg_status outer_step(grg_batch B, int prec, const void *r_src, const voi
     d.act = B->oact;
     d.gate = r_src == B->r64 ? 1 : 0;  // the first step writes r64 and x64 for every system
     d.ctr = B->ctr + 1;
-    const int dcg = round8(std::min<long>(B->Vtot / 128, kBatchMaxGrid));
+    const int dcg = round8(std::min<long>((long)B->Vtot / 128 * B->nrhs, kBatchMaxGrid));
     GRG_TRY_HIP(launch_batch_dc_update(prec, d, dcg, B->st));
     GRG_TRY_HIP(launch_batch_reduce(kNorm, B->partials, dcg, B->nsys, nullptr, B->rn2, nullptr, B->oact, nullptr,
                                     B->st));
@@ -321,14 +322,31 @@ static grg_status outer_step(grg_batch B, int prec, const void *r_src, const voi
     return GRG_OK;
 }
 
+static BatchCoarseArgs coarse_args(grg_batch B, const double *xb)
+{
+    BatchCoarseArgs c;
+    c.bt = table(B);
+    c.Vtot = B->Vtot;
+    c.nrhs = B->nrhs;
+    c.xb = xb;
+    c.U = B->U[GRG_FP64];
+    c.bidx = B->bidx;
+    c.qg = B->qg;
+    c.nb = B->nb;
+    c.nboff = B->nboff;
+    c.coff = B->coff;
+    c.nbtot = B->nbtot;
+    return c;
+}
+
+// grid of the FP64 kernels whose items are a block of 256 sites with one RHS
+static int fgrid(grg_batch B) { return round8(std::min<long>((long)B->Vtot / 256 * B->nrhs, kBatchMaxGrid)); }
+
 // b = D_rb x_b, |b|^2, control initialised (|r| = |b|, counters cleared)
 static grg_status prologue(grg_batch B, const double *xb)
 {
-    const BatchBlasArgs a = blas(B);
-    GRG_TRY_HIP(launch_batch_scatter(table(B), xb, B->u64, B->bidx, B->nb, B->coff, B->Vtot, B->nrhs, B->st));
-    GRG_TRY(dslash(B, GRG_FP64, B->u64, B->b64, 0, false));
-    GRG_TRY_HIP(launch_batch_norm2(GRG_FP64, a, B->b64, B->st));
-    GRG_TRY_HIP(launch_batch_reduce(kNorm, B->partials, a.grid, B->nsys, nullptr, B->bn2, nullptr, nullptr, nullptr,
+    GRG_TRY_HIP(launch_batch_rb(coarse_args(B, xb), (double2 *)B->b64, B->partials, fgrid(B), B->st));
+    GRG_TRY_HIP(launch_batch_reduce(kNorm, B->partials, fgrid(B), B->nsys, nullptr, B->bn2, nullptr, nullptr, nullptr,
                                     B->st));
     GRG_TRY(ctl(B, true));
     return GRG_OK;
@@ -337,23 +355,33 @@ static grg_status prologue(grg_batch B, const double *xb)
 // r = b - D_rr x from the iterate (every system), control on it
 static grg_status verify(grg_batch B)
 {
-    const BatchBlasArgs a = blas(B);
-    GRG_TRY(dslash(B, GRG_FP64, B->x64, B->t64, 0, false));
-    GRG_TRY_HIP(launch_batch_sub_norm(a, B->b64, B->t64, B->r64, B->st));
-    GRG_TRY_HIP(launch_batch_reduce(kNorm, B->partials, a.grid, B->nsys, nullptr, B->rn2, nullptr, nullptr, nullptr,
+    BatchResidualArgs a;
+    a.bt = table(B);
+    a.Vtot = B->Vtot;
+    a.nrhs = B->nrhs;
+    a.x = B->x64;
+    a.b = B->b64;
+    a.U = B->U[GRG_FP64];
+    a.r = B->r64;
+    a.mask = B->mask;
+    a.partials = B->partials;
+    GRG_TRY_HIP(launch_batch_residual(a, fgrid(B), B->st));
+    GRG_TRY_HIP(launch_batch_reduce(kNorm, B->partials, fgrid(B), B->nsys, nullptr, B->rn2, nullptr, nullptr, nullptr,
                                     B->st));
     GRG_TRY(ctl(B, false));
     return GRG_OK;
 }
 
-// y_b = [D (u - z)]_b; leaves u - z in x64 (undone by applying it again:
-// u and z have disjoint supports)
-static grg_status epilogue(grg_batch B, double *yb)
+// y_b = [D (u - z)]_b.  x_b is read at neighbouring coarse sites while y_b is
+// written, so an x_b that overlaps it is read from its staged copy (xb_in)
+static grg_status epilogue(grg_batch B, const double *xb, double *yb)
 {
-    const BatchBlasArgs a = blas(B);
-    GRG_TRY_HIP(launch_batch_xmy(a, B->u64, B->x64, B->st));
-    GRG_TRY_HIP(launch_batch_coarse(table(B), B->x64, B->U[GRG_FP64], yb, B->qg, B->clat, B->nb, B->nboff,
-                                    B->coff, B->nbtot, B->nrhs, B->st));
+    const size_t n = 24 * (size_t)B->nrhs * B->nbtot;
+    if (xb != B->xb_in && xb < yb + n && yb < xb + n) {
+        GRG_TRY_HIP(hipMemcpyAsync(B->xb_in, xb, n * sizeof(double), hipMemcpyDeviceToDevice, B->st));
+        xb = B->xb_in;
+    }
+    GRG_TRY_HIP(launch_batch_coarse(coarse_args(B, xb), B->x64, yb, B->st));
     return GRG_OK;
 }
 
@@ -386,7 +414,7 @@ static grg_status build_graph(grg_batch B, int prec, int n_outer, int n_inner)
     for (int o = 0; o < n_outer && s == GRG_OK; ++o)
         s = outer_step(B, prec, o == 0 ? B->b64 : B->r64, o == 0 ? nullptr : B->x64, false, n_inner, nullptr);
     if (s == GRG_OK) s = verify(B);
-    if (s == GRG_OK) s = epilogue(B, B->yb_out);
+    if (s == GRG_OK) s = epilogue(B, B->xb_in, B->yb_out);
     hipError_t e = hipStreamEndCapture(B->st, &g);
     if (s != GRG_OK) {
         if (g) (void)hipGraphDestroy(g);
@@ -427,8 +455,9 @@ static grg_status batch_apply(grg_batch B, const double *xb, double *yb, bool us
         done_by_graph = conv == 1;
         if (!done_by_graph) {
             // continue eagerly from the verified residual; the next graph
-            // is captured with one more outer step
-            GRG_TRY(epilogue(B, yb));  // restores the iterate in x64 (the combine's output is redone)
+            // is captured with one more outer step (the combine's output is
+            // redone, from the staged x_b: yb may be the caller's xb)
+            xb = B->xb_in;
             (void)hipGraphExecDestroy(B->graph);
             B->graph = nullptr;
             r_src = B->r64;
@@ -474,7 +503,7 @@ static grg_status batch_apply(grg_batch B, const double *xb, double *yb, bool us
         }
         if (x_src == nullptr)
             GRG_TRY_HIP(launch_fill_zero(B->x64, spinor_elems(B->gtot, B->nrhs) * 16, st));
-        GRG_TRY(epilogue(B, yb));
+        GRG_TRY(epilogue(B, xb, yb));
         if (status == GRG_OK) {
             // the counts the next captured apply of this batch is built with:
             // every outer step this apply took (the graph's and the eager
@@ -501,7 +530,6 @@ static void batch_free(grg_batch B)
     f(B->mask);
     f(B->bidx);
     f(B->qg);
-    f(B->clat);
     f(B->tile_lat);
     f(B->off);
     f(B->nb);
@@ -513,7 +541,7 @@ static void batch_free(grg_batch B)
     f(B->x64);
     f(B->r64);
     f(B->t64);
-    f(B->u64);
+    f(B->Uh);
     f(B->in_b);
     f(B->in_x);
     f(B->in_r);
@@ -606,7 +634,7 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
     // host tables
     std::vector<uint8_t> mask(Vtot, 0);
     std::vector<int32_t> bidx(Vtot, -1), qg(nbtot);
-    std::vector<int> clat(nbtot), tile_lat(Vtot / 64), off(count), nb(count), nboff(count);
+    std::vector<int> tile_lat(Vtot / 64), off(count), nb(count), nboff(count);
     std::vector<int4> dims(count);
     std::vector<double> diag(count);
     std::vector<long long> coffs(count);
@@ -626,7 +654,6 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
             mask[s] = 1;
             bidx[s] = k;
             qg[b.nboff + k] = s;
-            clat[b.nboff + k] = i;
         }
         for (int t = 0; t < b.V / 64; ++t) tile_lat[b.off / 64 + t] = i;
         off[i] = b.off;
@@ -702,7 +729,6 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
     al((void **)&B->mask, Vtot);
     al((void **)&B->bidx, sizeof(int32_t) * Vtot);
     al((void **)&B->qg, sizeof(int32_t) * nbtot);
-    al((void **)&B->clat, sizeof(int) * nbtot);
     al((void **)&B->tile_lat, sizeof(int) * (Vtot / 64));
     al((void **)&B->off, sizeof(int) * count);
     al((void **)&B->nb, sizeof(int) * count);
@@ -710,7 +736,7 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
     al((void **)&B->dims, sizeof(int4) * count);
     al((void **)&B->diag, sizeof(double) * count);
     al((void **)&B->coff, sizeof(long long) * count);
-    for (void **p : {&B->b64, &B->x64, &B->r64, &B->t64, &B->u64}) al(p, f64);
+    for (void **p : {&B->b64, &B->x64, &B->r64, &B->t64}) al(p, f64);
     for (void **p : {&B->in_b, &B->in_x, &B->in_r, &B->in_q}) al(p, fin);
     B->eo = eo;
     B->Vh = (int)Vh;
@@ -722,6 +748,7 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
         al((void **)&B->mask_h, 2 * (size_t)Vh);
         al((void **)&B->coef, sizeof(double) * 5 * count);
         for (void **p : {&B->hx, &B->hr, &B->hq, &B->hw, &B->hbq, &B->heq}) al(p, fh);
+        al(&B->Uh, (size_t)2 * 36 * Vh * prec_bytes(prm.inner));
     }
     al((void **)&B->partials, sizeof(double) * kBatchMaxGrid * B->nsys * 3);
     al((void **)&B->alpha, sizeof(double2) * B->nsys);
@@ -756,7 +783,6 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
     UP(B->mask, mask.data(), Vtot);
     UP(B->bidx, bidx.data(), sizeof(int32_t) * Vtot);
     UP(B->qg, qg.data(), sizeof(int32_t) * nbtot);
-    UP(B->clat, clat.data(), sizeof(int) * nbtot);
     UP(B->tile_lat, tile_lat.data(), sizeof(int) * (Vtot / 64));
     UP(B->off, off.data(), sizeof(int) * count);
     UP(B->nb, nb.data(), sizeof(int) * count);
@@ -773,7 +799,7 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
     }
     GRG_TRY_HIP(hipStreamSynchronize(st));
 #undef UP
-    for (void *p : {B->b64, B->x64, B->r64, B->t64, B->u64}) GRG_TRY_HIP(launch_fill_zero(p, f64, st));
+    for (void *p : {B->b64, B->x64, B->r64, B->t64}) GRG_TRY_HIP(launch_fill_zero(p, f64, st));
     for (void *p : {B->in_b, B->in_x, B->in_r, B->in_q}) GRG_TRY_HIP(launch_fill_zero(p, fin, st));
     for (void *p : {B->hx, B->hr, B->hq, B->hw, B->hbq, B->heq})
         if (p) GRG_TRY_HIP(launch_fill_zero(p, fh, st));
@@ -800,6 +826,10 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
             s = GRG_EHIP;
     }
     (void)hipFree(stage);
+    if (s == GRG_OK && B->eo &&
+        (launch_batch_half_links(prm.inner, table(B), half(B), B->U[prm.inner], B->Uh, st) != hipSuccess ||
+         hipStreamSynchronize(st) != hipSuccess))
+        s = GRG_EHIP;
     if (s != GRG_OK) {
         set_error("uploading the batch links failed");
         batch_free(B);

@@ -77,14 +77,7 @@ struct BatchCtlArgs {
 hipError_t launch_dslash_batch(int prec, const BatchDslashArgs &a, int grid, int SB, hipStream_t st);
 hipError_t launch_batch_mr_update(int prec, const BatchBlasArgs &a, void *x, void *r, const void *q,
                                   hipStream_t st);
-hipError_t launch_batch_norm2(int prec, const BatchBlasArgs &a, const void *v, hipStream_t st);
-hipError_t launch_batch_axpy_convert(int pin, int pout, const BatchBlasArgs &a, const void *x, void *y,
-                                     const double *scale, int mode, int beta, hipStream_t st);
-hipError_t launch_batch_sub_norm(const BatchBlasArgs &a, const void *b, const void *ax, void *r,
-                                 hipStream_t st);
 hipError_t launch_batch_dc_update(int prec, const BatchDcArgs &a, int grid, hipStream_t st);
-hipError_t launch_batch_scatter(const BatchTable &bt, const double *xb, void *dst, const int32_t *bidx,
-                                const int *nb, const long long *coff, int Vtot, int nrhs, hipStream_t st);
 // in_r = r_src / |r| (scale 1 / sqrt(fr2)) in the inner precision and in_x = 0, for the
 // systems with a.act set (zero for the others), with the partial |in_r|^2
 hipError_t launch_batch_inner_init(int prec, const BatchBlasArgs &a, const void *r_src, const double *fr2,
@@ -97,9 +90,6 @@ hipError_t launch_batch_reduce(int mode, const double *partials, int nparts, int
                                double *out2, const double *thr2, const int *act_in, int *act_out,
                                hipStream_t st);
 hipError_t launch_batch_ctl(const BatchCtlArgs &c, hipStream_t st);
-// y = x - y (FP64, every site and RHS)
-hipError_t launch_batch_xmy(const BatchBlasArgs &a, const void *x, void *y, hipStream_t st);
-
 // The even-odd reduced form of every lattice's D_rr on compact half-lattice
 // fields.  Each lattice's half-sites h (the site pair 2h, 2h + 1 of opposite
 // parities: Lx is even) form a block of its own, starting on a 256 boundary
@@ -122,7 +112,7 @@ struct BatchHalf {
 struct BatchEoArgs {
     const void *in, *in2;
     void *out;
-    const void *U;        // full-layout links of the batch, in the stencil's precision
+    const void *U;        // the links by side (launch_batch_half_links), in the stencil's precision
     BatchTable bt;        // the full layout (extents, first sites, lattices of full tiles)
     BatchHalf hf;
     int po;
@@ -132,13 +122,42 @@ struct BatchEoArgs {
     const int *act;
 };
 hipError_t launch_batch_eo(int prec, const BatchEoArgs &a, int grid, hipStream_t st);
-// full-layout field x -> its two halves (xp on each lattice's reduced parity,
-// xq on the other), zero on padding; with to_full, the reverse (every site of
-// the full field written from the halves)
-hipError_t launch_batch_eo_split(int prec, const BatchTable &bt, const BatchHalf &hf, int nrhs, void *x,
-                                 void *xp, void *xq, int to_full, int grid, hipStream_t st);
-hipError_t launch_batch_coarse(const BatchTable &bt, const void *in, const void *U, double *yb,
-                               const int32_t *qg, const int *clat, const int *nb, const int *nboff,
-                               const long long *coff, int nbtot, int nrhs, hipStream_t st);
+// the full-layout field x from its two halves (xp on each lattice's reduced
+// parity, xq on the other)
+hipError_t launch_batch_eo_join(int prec, const BatchTable &bt, const BatchHalf &hf, int nrhs, void *x,
+                                const void *xp, const void *xq, int grid, hipStream_t st);
+// Coarse vectors of the batch (lattice l's block [nrhs][nb[l]][12] at complex
+// offset coff[l]) and the maps between coarse indices and sites.
+struct BatchCoarseArgs {
+    BatchTable bt;
+    int Vtot, nrhs;
+    const double *xb;
+    const void *U;          // FP64 links
+    const int32_t *bidx;    // coarse index of a site inside its lattice, or -1
+    const int32_t *qg;      // site of every coarse index of the batch
+    const int *nb, *nboff;
+    const long long *coff;
+    int nbtot;
+};
+// b = D_rb x_b (internal FP64 field), partials the per-system |b|^2
+hipError_t launch_batch_rb(const BatchCoarseArgs &c, double2 *b, double *partials, int grid, hipStream_t st);
+// y_b = [D (u - z)]_b, u = x_b on the coarse sites (xb and yb do not overlap)
+hipError_t launch_batch_coarse(const BatchCoarseArgs &c, const void *z, double *yb, hipStream_t st);
+// r = b - D_rr x (FP64), partials the per-system |r|^2
+struct BatchResidualArgs {
+    BatchTable bt;
+    int Vtot, nrhs;
+    const void *x, *b, *U;
+    void *r;
+    const uint8_t *mask;
+    double *partials;
+};
+hipError_t launch_batch_residual(const BatchResidualArgs &a, int grid, hipStream_t st);
+// the links by side, [2][hf.Vtot] compact (36 hf.Vtot each), from the full layout's
+hipError_t launch_batch_half_links(int prec, const BatchTable &bt, const BatchHalf &hf, const void *U, void *Uh,
+                                   hipStream_t st);
+// the scaled residual as the two halves of the reduced solve's right-hand side
+hipError_t launch_batch_inner_split(int prec, const BatchBlasArgs &a, const BatchHalf &hf, const void *r_src,
+                                    const double *fr2, void *bp, void *bq, hipStream_t st);
 
 }  // namespace grg

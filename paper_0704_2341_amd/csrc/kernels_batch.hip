@@ -5,10 +5,13 @@
 // extents, the first site and the diagonal 4 + m0.  A "system" is one
 // (lattice, right-hand side) pair, sys = lattice * nrhs + rhs; step lengths,
 // norms and convergence flags are per system.
+#include <algorithm>
+
 #include "batch.h"
 #include "common.h"
 #include "engine.h"
 #include "reduce.h"
+#include "split.h"
 #include "stencil.h"
 
 namespace grg {
@@ -81,6 +84,101 @@ __device__ bool any_set(const int *flags, int n)
     if (mine) s_any = 1;
     __syncthreads();
     return s_any != 0;
+}
+
+// A stencil's work item per wavefront: 64 sites with one RHS, RHS fastest, so
+// that the wavefronts of a workgroup read the same links (nrhs 4: one link
+// fetch from L2 for the four).
+__device__ __forceinline__ void tile_item(int w, int nrhs, int &tile, int &r)
+{
+    const int i = __builtin_amdgcn_readfirstlane(w * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6));
+    tile = i / nrhs;
+    r = i - tile * nrhs;
+}
+
+// The compact fields and links (BatchHalf).  In FP32 two components share 16
+// bytes of a lane: the L1 answers a wavefront's 8-byte loads at half the rate
+// of its 16-byte ones (16 cache accesses for 512 bytes and for 1024), and the
+// half-steps read 21 complex numbers per hop.  BF16 (4 bytes: 4 accesses for
+// 256 bytes) and FP64 keep a component per lane and line.
+template <class S>
+__device__ __forceinline__ size_t hidx(int H, int r, int c, int nrhs)
+{
+    if constexpr (sizeof(S) == 8)
+        return ((size_t)(H >> 6) * nrhs + r) * 768 + (c >> 1) * 128 + (H & 63) * 2 + (c & 1);
+    else
+        return fidx(H, r, c, nrhs);
+}
+
+template <class S>
+__device__ __forceinline__ size_t hlidx(int H, int mu, int e)
+{
+    if constexpr (sizeof(S) == 8)
+        return (size_t)(H >> 6) * 2304 + mu * 576 + (e < 8 ? (e >> 1) * 128 + (H & 63) * 2 + (e & 1) : 512 + (H & 63));
+    else
+        return lidx(H, mu, e);
+}
+
+// a site's spinor and a link in the operand form of the hops
+template <class S, class R, class T>
+__device__ __forceinline__ void load_half(T (&p)[12], const S *__restrict__ f, int H, int r, int nrhs)
+{
+    if constexpr (sizeof(S) == 8) {
+        const float4 *q = (const float4 *)(f + hidx<S>(H, r, 0, nrhs));
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            const float4 v = q[i * 64];
+            p[2 * i] = {v.x, v.y};
+            p[2 * i + 1] = {v.z, v.w};
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) p[c] = Operand<S, R>::load(f, hidx<S>(H, r, c, nrhs));
+    }
+}
+
+template <class S, class R, class T>
+__device__ __forceinline__ void load_half_link(T (&u)[9], const S *__restrict__ U, int H, int mu)
+{
+    if constexpr (sizeof(S) == 8) {
+        const float4 *q = (const float4 *)(U + hlidx<S>(H, mu, 0));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 v = q[i * 64];
+            u[2 * i] = {v.x, v.y};
+            u[2 * i + 1] = {v.z, v.w};
+        }
+        const float2 v = U[hlidx<S>(H, mu, 8)];
+        u[8] = {v.x, v.y};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) u[e] = Operand<S, R>::load(U, hlidx<S>(H, mu, e));
+    }
+}
+
+// its values
+template <class S, class R>
+__device__ __forceinline__ void load_half_vals(cpx<R> (&p)[12], const S *__restrict__ f, int H, int r, int nrhs)
+{
+    if constexpr (sizeof(S) == 8) {
+        load_half<S, R>(p, f, H, r, nrhs);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) p[c] = ldc(f, hidx<S>(H, r, c, nrhs));
+    }
+}
+
+template <class S, class R>
+__device__ __forceinline__ void store_half(S *__restrict__ f, const cpx<R> (&p)[12], int H, int r, int nrhs)
+{
+    if constexpr (sizeof(S) == 8) {
+        float4 *q = (float4 *)(f + hidx<S>(H, r, 0, nrhs));
+#pragma unroll
+        for (int i = 0; i < 6; ++i) q[i * 64] = make_float4(p[2 * i].re, p[2 * i].im, p[2 * i + 1].re, p[2 * i + 1].im);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) stc(f, hidx<S>(H, r, c, nrhs), p[c]);
+    }
 }
 
 // out = mask_sel D in over all lattices; fused dots per system when partials.
@@ -183,97 +281,9 @@ __global__ void __launch_bounds__(256) batch_mr_update_kernel(BatchBlasArgs a, v
     part.flush(a.partials);
 }
 
-template <int P>
-__global__ void __launch_bounds__(256) batch_norm2_kernel(BatchBlasArgs a, const void *v_)
-{
-    typedef typename Store<P>::S S;
-    typedef typename Store<P>::R R;
-    extern __shared__ double smem[];
-    SysPartial<1> part;
-    part.init(smem, a.bt.nlat * a.nrhs);
-    const S *v = (const S *)v_;
-    const ItemRange it = xcd_items(a.Vtot / 256);
-    for (int w = it.begin; w < it.end; w += it.step) {
-        const int s = w * 256 + threadIdx.x;
-        const int l = a.bt.tile_lat[s >> 6];
-        for (int k = 0; k < a.nrhs; ++k) {
-            double t = 0;
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const cpx<R> z = ldc(v, fidx(s, k, c, a.nrhs));
-                t += (double)z.re * z.re + (double)z.im * z.im;
-            }
-            const double vv[1] = {t};
-            part.add(l * a.nrhs + k, vv);
-        }
-    }
-    part.flush(a.partials);
-}
-
-// y = beta*y + f(scale[sys]) * x, f = identity / 1/sqrt / sqrt
-template <int PI, int PO>
-__global__ void __launch_bounds__(256) batch_axpy_convert_kernel(BatchBlasArgs a, const void *x_, void *y_,
-                                                                 const double *scale, int mode, int beta)
-{
-    typedef typename Store<PI>::S SI;
-    typedef typename Store<PI>::R RI;
-    typedef typename Store<PO>::S SO;
-    typedef typename Store<PO>::R RO;
-    const SI *x = (const SI *)x_;
-    SO *y = (SO *)y_;
-    const ItemRange it = xcd_items(a.Vtot / 256);
-    for (int w = it.begin; w < it.end; w += it.step) {
-        const int s = w * 256 + threadIdx.x;
-        const int l = a.bt.tile_lat[s >> 6];
-        for (int k = 0; k < a.nrhs; ++k) {
-            double f = scale ? scale[l * a.nrhs + k] : 1.0;
-            if (mode == 1) f = f > 0 ? 1.0 / sqrt(f) : 0.0;
-            if (mode == 2) f = sqrt(f);
-            const RO fo = (RO)f;
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const size_t i = fidx(s, k, c, a.nrhs);
-                const cpx<RI> v = ldc(x, i);
-                cpx<RO> o = {fo * (RO)v.re, fo * (RO)v.im};
-                if (beta) {
-                    const cpx<RO> yo = ldc(y, i);
-                    o.re += yo.re;
-                    o.im += yo.im;
-                }
-                stc(y, i, o);
-            }
-        }
-    }
-}
-
-__global__ void __launch_bounds__(256) batch_sub_norm_kernel(BatchBlasArgs a, const double2 *b,
-                                                             const double2 *ax, double2 *r)
-{
-    extern __shared__ double smem[];
-    SysPartial<1> part;
-    part.init(smem, a.bt.nlat * a.nrhs);
-    const ItemRange it = xcd_items(a.Vtot / 256);
-    for (int w = it.begin; w < it.end; w += it.step) {
-        const int s = w * 256 + threadIdx.x;
-        const int l = a.bt.tile_lat[s >> 6];
-        for (int k = 0; k < a.nrhs; ++k) {
-            double t = 0;
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const size_t i = fidx(s, k, c, a.nrhs);
-                const double2 bv = b[i], av = ax[i];
-                const double2 d = make_double2(bv.x - av.x, bv.y - av.y);
-                r[i] = d;
-                t += d.x * d.x + d.y * d.y;
-            }
-            const double vv[1] = {t};
-            part.add(l * a.nrhs + k, vv);
-        }
-    }
-    part.flush(a.partials);
-}
-
-// r_out = r_in - f (D_rr e), x_out = x_in + f e in FP64, f = sqrt(fr2[sys])
+// r_out = r_in - f (D_rr e), x_out = x_in + f e in FP64, f = sqrt(fr2[sys]).
+// 48 lattices, 1.2 million sites, 4 RHS: 1.6 ms, its bytes 0.9 of it; the rest
+// is the wait for operands with four wavefronts per SIMD (112 VGPRs).
 template <int P>
 __global__ void __launch_bounds__(128) batch_dc_update_kernel(BatchDcArgs a)
 {
@@ -294,13 +304,15 @@ __global__ void __launch_bounds__(128) batch_dc_update_kernel(BatchDcArgs a)
         if (any && a.ctr && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(a.ctr, 1);
         if (a.gate && !any) return;
     }
-    const ItemRange it = xcd_items(a.Vtot / blockDim.x);
+    const ItemRange it = xcd_items(a.Vtot / blockDim.x * a.nrhs);
     for (int w = it.begin; w < it.end; w += it.step) {
-        const int s = w * blockDim.x + threadIdx.x;
+        int tile, r;
+        tile_item(w, a.nrhs, tile, r);
+        const int s = tile * 64 + (int)(threadIdx.x & 63);
         const BSite b = bsite(a.bt, s);
         const bool on = a.mask[s] == 0;
         const SiteGeo q = site_geo(b.local, b.g);
-        for (int r = 0; r < a.nrhs; ++r) {
+        {
             const int sys = b.l * a.nrhs + r;
             const bool sys_on = a.act == nullptr || a.act[sys] != 0;
             if (in_place && !sys_on) continue;  // converged: r and x stay
@@ -343,46 +355,6 @@ __global__ void __launch_bounds__(128) batch_dc_update_kernel(BatchDcArgs a)
         }
     }
     part.flush(a.partials);
-}
-
-// coarse canonical -> internal FP64 lattice field (zero elsewhere).  The
-// coarse vectors of lattice l are one block [nrhs][nb_l][12] at complex
-// offset coff[l]; bidx[s] is the coarse index of site s inside its lattice.
-__global__ void batch_scatter_kernel(BatchTable bt, const double2 *xb, double2 *dst,
-                                     const int32_t *bidx, const int *nb, const long long *coff,
-                                     int Vtot, int nrhs)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    const int r = blockIdx.y;
-    if (s >= Vtot || r >= nrhs) return;
-    const int l = bt.tile_lat[s >> 6];
-    const int k = bidx[s];
-    const double2 *p = xb + coff[l] + ((size_t)r * nb[l] + (k < 0 ? 0 : k)) * 12;
-#pragma unroll
-    for (int c = 0; c < 12; ++c) dst[fidx(s, r, c, nrhs)] = k >= 0 ? p[c] : make_double2(0.0, 0.0);
-}
-
-// y_b = (D in)(coarse sites), FP64, into the per-lattice coarse blocks
-__global__ void __launch_bounds__(128) batch_coarse_kernel(BatchTable bt, const double2 *in,
-                                                           const double2 *U, double2 *yb,
-                                                           const int32_t *qg, const int *clat,
-                                                           const int *nb, const int *nboff,
-                                                           const long long *coff, int nbtot, int nrhs)
-{
-    const int kg = blockIdx.x * blockDim.x + threadIdx.x;
-    if (kg >= nbtot) return;
-    const int l = clat[kg];
-    const int s = qg[kg];
-    const BSite b = bsite(bt, s);
-    const SiteGeo q = site_geo(b.local, b.g);
-    const int k = kg - nboff[l];
-    for (int r = 0; r < nrhs; ++r) {
-        cpx<double> acc[12];
-        dslash_site<double2, double, true>(acc, in, U, s, q, b.g, r, nrhs, bt.diag[l]);
-        double2 *o = yb + coff[l] + ((size_t)r * nb[l] + k) * 12;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) o[c] = make_double2(acc[c].re, acc[c].im);
-    }
 }
 
 // in_r = r_src / sqrt(fr2) in the inner precision, in_x = 0, partial |in_r|^2
@@ -475,27 +447,6 @@ __global__ void __launch_bounds__(256) batch_ctl_kernel(BatchCtlArgs c)
     }
 }
 
-// y = x - y, FP64
-__global__ void __launch_bounds__(256) batch_xmy_kernel(BatchBlasArgs a, const double2 *x, double2 *y)
-{
-    const ItemRange it = xcd_items(a.Vtot / 256);
-    for (int w = it.begin; w < it.end; w += it.step) {
-        const int s = w * 256 + threadIdx.x;
-        for (int k = 0; k < a.nrhs; ++k) {
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const size_t i = fidx(s, k, c, a.nrhs);
-                const double2 u = x[i], v = y[i];
-                y[i] = make_double2(u.x - v.x, u.y - v.y);
-            }
-        }
-    }
-}
-
-// ------------------------------------------------------------------ launchers
-static size_t lds_sys(int nsys, int K) { return (size_t)4 * nsys * K * sizeof(double); }
-
-// ------------------------------------------------------------------ even-odd reduced form
 // The site of side po (0: the lattice's reduced parity, 1: the other) at
 // half-site h: 2h and 2h + 1 differ in parity (Lx even), 2h having the
 // parity of y + z + t.
@@ -507,6 +458,233 @@ __device__ __forceinline__ int half_site(int h, int4 d, int parity)
     return 2 * h + ((parity ^ (y + z + t)) & 1);
 }
 
+// b = D_rb x_b over the batch (FP64, zero on the coarse sites), from the
+// coarse neighbours alone, with the per-system |b|^2: as rb_apply_kernel.
+// (48 lattices, 1.2 million sites, 4 RHS: 0.46 ms, the write of b 0.2 of it;
+// a scatter of x_b, D over the whole field and a norm pass took 1.4.)
+__global__ void __launch_bounds__(256) batch_rb_kernel(BatchCoarseArgs a, double2 *__restrict__ b, double *partials)
+{
+    extern __shared__ double smem[];
+    SysPartial<1> part;
+    part.init(smem, a.bt.nlat * a.nrhs);
+    const double2 *__restrict__ xb = (const double2 *)a.xb, *__restrict__ U = (const double2 *)a.U;
+    const ItemRange it = xcd_items(a.Vtot / 256 * a.nrhs);
+    for (int w = it.begin; w < it.end; w += it.step) {
+        int tile, r;
+        tile_item(w, a.nrhs, tile, r);
+        const int s = tile * 64 + (int)(threadIdx.x & 63);
+        const BSite bs = bsite(a.bt, s);
+        cpx<double> acc[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = {0, 0};
+        if (a.bidx[s] < 0) {
+            const SiteGeo q = site_geo(bs.local, bs.g);
+            const int fo = a.bt.off[bs.l];
+            const double2 *x = xb + a.coff[bs.l] + (size_t)r * a.nb[bs.l] * 12;
+#pragma unroll 1
+            for (int k = 0; k < 8; ++k) {
+                int sp, sm;
+                nbr(bs.local, k >> 1, q, bs.g, sp, sm);
+                const int kb = a.bidx[fo + ((k & 1) ? sm : sp)];
+                if (kb < 0) continue;
+                cpx<double> p[12], u[9];
+#pragma unroll
+                for (int c = 0; c < 12; ++c) p[c] = {x[(size_t)kb * 12 + c].x, x[(size_t)kb * 12 + c].y};
+#pragma unroll
+                for (int e = 0; e < 9; ++e) {
+                    const double2 l = U[lidx(fo + ((k & 1) ? sm : bs.local), k >> 1, e)];
+                    u[e] = {l.x, l.y};
+                }
+                switch (k) {
+                case 0: hop_math<0, true>(acc, p, u); break;
+                case 1: hop_math<0, false>(acc, p, u); break;
+                case 2: hop_math<1, true>(acc, p, u); break;
+                case 3: hop_math<1, false>(acc, p, u); break;
+                case 4: hop_math<2, true>(acc, p, u); break;
+                case 5: hop_math<2, false>(acc, p, u); break;
+                case 6: hop_math<3, true>(acc, p, u); break;
+                default: hop_math<3, false>(acc, p, u); break;
+                }
+            }
+        }
+        double n2 = 0;
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            b[fidx(s, r, c, a.nrhs)] = make_double2(acc[c].re, acc[c].im);
+            n2 += acc[c].re * acc[c].re + acc[c].im * acc[c].im;
+        }
+        const double v[1] = {n2};
+        part.add(bs.l * a.nrhs + r, v);
+    }
+    part.flush(partials);
+}
+
+// r = b - D_rr x on the rest sites, zero on the coarse ones, with the
+// per-system |r|^2 (the same batch: 1.26 ms; D, then the difference with its
+// norm took 1.0 + 0.53)
+__global__ void __launch_bounds__(256) batch_residual_kernel(BatchResidualArgs a)
+{
+    extern __shared__ double smem[];
+    SysPartial<1> part;
+    part.init(smem, a.bt.nlat * a.nrhs);
+    const double2 *__restrict__ x = (const double2 *)a.x, *__restrict__ U = (const double2 *)a.U;
+    const double2 *__restrict__ b = (const double2 *)a.b;
+    double2 *__restrict__ ro = (double2 *)a.r;
+    const ItemRange it = xcd_items(a.Vtot / 256 * a.nrhs);
+    for (int w = it.begin; w < it.end; w += it.step) {
+        int tile, r;
+        tile_item(w, a.nrhs, tile, r);
+        const int s = tile * 64 + (int)(threadIdx.x & 63);
+        const BSite bs = bsite(a.bt, s);
+        double n2 = 0;
+        if (a.mask[s] == 0) {
+            const SiteGeo q = site_geo(bs.local, bs.g);
+            cpx<double> acc[12];
+            dslash_site<double2, double, true>(acc, x, U, s, q, bs.g, r, a.nrhs, a.bt.diag[bs.l]);
+#pragma unroll
+            for (int c = 0; c < 12; ++c) {
+                const size_t i = fidx(s, r, c, a.nrhs);
+                const double2 d = make_double2(b[i].x - acc[c].re, b[i].y - acc[c].im);
+                ro[i] = d;
+                n2 += d.x * d.x + d.y * d.y;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 12; ++c) ro[fidx(s, r, c, a.nrhs)] = make_double2(0.0, 0.0);
+        }
+        const double v[1] = {n2};
+        part.add(bs.l * a.nrhs + r, v);
+    }
+    part.flush(a.partials);
+}
+
+// y_b = [D (u - z)]_b, u = x_b on the coarse sites: the neighbours of a coarse
+// site are read as x_b or -z.  64 coarse sites and one RHS per workgroup, a
+// hop per wavefront (split.h); a workgroup may span lattices.  (The same batch:
+// 0.18 ms; u - z over the whole field and a lane per coarse site took 0.53 + 0.2.)
+__global__ void __launch_bounds__(kSplitThreads) batch_coarse_kernel(BatchCoarseArgs a, const double2 *__restrict__ z,
+                                                                     double2 *__restrict__ yb)
+{
+    __shared__ HopSums<double> sums;
+    const double2 *__restrict__ xb = (const double2 *)a.xb, *__restrict__ U = (const double2 *)a.U;
+    const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int nkb = (a.nbtot + 63) >> 6;
+    const ItemRange it = xcd_items(nkb * a.nrhs);
+    for (int wi = it.begin; wi < it.end; wi += it.step) {
+        const int kb = wi / a.nrhs, r = wi - kb * a.nrhs;
+        const int kg = kb * 64 + lane;
+        size_t x0 = 0;
+        int l = 0;
+        if (kg < a.nbtot) {
+            const int s = a.qg[kg];
+            const BSite bs = bsite(a.bt, s);
+            l = bs.l;
+            x0 = a.coff[l] + (size_t)r * a.nb[l] * 12;
+            const int fo = a.bt.off[l];
+            const SiteGeo q = site_geo(bs.local, bs.g);
+            int sp, sm;
+            nbr(bs.local, k >> 1, q, bs.g, sp, sm);
+            const int n = fo + ((k & 1) ? sm : sp), kn = a.bidx[n];
+            cpx<double> p[12], u[9], w[6];
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                const double2 v = U[lidx(fo + ((k & 1) ? sm : bs.local), k >> 1, e)];
+                u[e] = {v.x, v.y};
+            }
+            if (kn >= 0) {
+#pragma unroll
+                for (int c = 0; c < 12; ++c) {
+                    const double2 v = xb[x0 + (size_t)kn * 12 + c];
+                    p[c] = {v.x, v.y};
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < 12; ++c) {
+                    const double2 v = z[fidx(n, r, c, a.nrhs)];
+                    p[c] = {0.0 - v.x, 0.0 - v.y};
+                }
+            }
+            hop_w_k(k, w, p, u);
+            sums.put(k, lane, w);
+        }
+        __syncthreads();
+        if (k < 6 && kg < a.nbtot) {
+            const int row = k % 3, spin = k < 3 ? 0 : 2;
+            const size_t i = x0 + (size_t)(kg - a.nboff[l]) * 12 + 3 * spin + row;
+            const double2 v0 = xb[i], v1 = xb[i + 3];
+            const double diag = a.bt.diag[l];
+            cpx<double> a0 = {diag * v0.x, diag * v0.y}, a1 = {diag * v1.x, diag * v1.y};
+            if (spin == 0) sums.add<false>(row, lane, a0, a1);
+            else sums.add<true>(row, lane, a0, a1);
+            yb[i] = make_double2(a0.re, a0.im);
+            yb[i + 3] = make_double2(a1.re, a1.im);
+        }
+        __syncthreads();  // the sums are read before the next item's overwrite them
+    }
+}
+
+// The links once more by side (0: the reduced parity's sites, 1: the others),
+// compact like the half fields: a half-step over the full layout's links used
+// half of every line it read, forward and backward (48 lattices, 1.2 million
+// sites, FP32, 4 RHS: 313 us per half-step, 290 with these).
+template <class S>
+__global__ void __launch_bounds__(256) batch_half_links_kernel(BatchTable bt, BatchHalf hf, const S *__restrict__ U,
+                                                               S *__restrict__ Uh)
+{
+    const int H = blockIdx.x * 256 + threadIdx.x;
+    if (H >= hf.Vtot) return;
+    const int l = hf.tile_lat[H >> 6];
+    const int4 d = bt.dims[l];
+    const int h = H - hf.off[l];
+    const bool valid = 2 * h < d.x * d.y * d.z * d.w;
+    const int sp = valid ? half_site(h, d, hf.par[l]) : 0;
+    for (int side = 0; side < 2; ++side) {
+        const int s = bt.off[l] + (side ? sp ^ 1 : sp);
+        for (int mu = 0; mu < 4; ++mu)
+#pragma unroll
+            for (int e = 0; e < 9; ++e)
+                Uh[(size_t)side * 36 * hf.Vtot + hlidx<S>(H, mu, e)] = valid ? U[lidx(s, mu, e)] : S{};
+    }
+}
+
+// The scaled residual r / sqrt(fr2) in the inner precision straight into the
+// two compact halves of the reduced solve's right-hand side (the padding of
+// the halves stays zero); systems whose flag is 0 get zeros.  Bound by its bytes
+// (48 lattices, 4 RHS: 0.28 ms at 4.9 TB/s; through the full layout 0.75).
+template <int PO>
+__global__ void __launch_bounds__(256) batch_inner_split_kernel(BatchBlasArgs a, BatchHalf hf,
+                                                                const double2 *__restrict__ r_src,
+                                                                const double *__restrict__ fr2, void *bp_, void *bq_)
+{
+    typedef typename Store<PO>::S S;
+    typedef typename Store<PO>::R R;
+    if (a.act && !any_set(a.act, a.bt.nlat * a.nrhs)) return;
+    S *bp = (S *)bp_, *bq = (S *)bq_;
+    const ItemRange it = xcd_items(a.Vtot / 256 * a.nrhs);
+    for (int w = it.begin; w < it.end; w += it.step) {
+        const int sb = w / a.nrhs, r = w - sb * a.nrhs;
+        const int s = sb * 256 + (int)threadIdx.x;
+        const BSite bs = bsite(a.bt, s);
+        const int sys = bs.l * a.nrhs + r;
+        const bool on = a.act == nullptr || a.act[sys] != 0;
+        const double f2 = fr2[sys];
+        const double f = on && f2 > 0 ? 1.0 / sqrt(f2) : 0.0;
+        const SiteGeo q = site_geo(bs.local, bs.g);
+        const bool p_side = ((q.c[0] ^ q.c[1] ^ q.c[2] ^ q.c[3]) & 1) == hf.par[bs.l];
+        S *o = p_side ? bp : bq;
+        const int H = hf.off[bs.l] + (bs.local >> 1);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const double2 v = on ? r_src[fidx(s, r, c, a.nrhs)] : make_double2(0.0, 0.0);
+            stc(o, hidx<S>(H, r, c, a.nrhs), cpx<R>{(R)(f * v.x), (R)(f * v.y)});
+        }
+    }
+}
+
+// ------------------------------------------------------------------ launchers
+static size_t lds_sys(int nsys, int K) { return (size_t)4 * nsys * K * sizeof(double); }
+
+// ------------------------------------------------------------------ even-odd reduced form
 template <int P>
 __global__ void __launch_bounds__(256) batch_eo_kernel(BatchEoArgs a)
 {
@@ -518,20 +696,21 @@ __global__ void __launch_bounds__(256) batch_eo_kernel(BatchEoArgs a)
     const S *__restrict__ in = (const S *)a.in;
     const S *__restrict__ in2 = (const S *)a.in2;
     S *__restrict__ out = (S *)a.out;
-    const S *__restrict__ U = (const S *)a.U;
+    // the links of the output's side and of the input's
+    const S *__restrict__ Uo = (const S *)a.U + (size_t)a.po * 36 * a.hf.Vtot;
+    const S *__restrict__ Ui = (const S *)a.U + (size_t)(1 - a.po) * 36 * a.hf.Vtot;
     const int nsys = a.bt.nlat * a.nrhs;
     if (a.act && !any_set(a.act, nsys)) return;
     const bool dots = a.partials != nullptr;
     SysPartial<3> part;
     if (dots) part.init(smem, nsys);
     const uint8_t *mk = a.hf.mask + (size_t)a.po * a.hf.Vtot;
-    // work items: a block of 256 half-sites with one RHS (the RHS of a block
-    // adjacent, so that they share its links in L2)
     const ItemRange it = xcd_items(a.hf.Vtot / 256 * a.nrhs);
     for (int w = it.begin; w < it.end; w += it.step) {
-        const int blk = w / a.nrhs, r = w - blk * a.nrhs;
-        const int H = blk * 256 + (int)threadIdx.x;
-        const int l = a.hf.tile_lat[H >> 6];  // a block of 256 lies in one lattice
+        int tile, r;
+        tile_item(w, a.nrhs, tile, r);
+        const int H = tile * 64 + (int)(threadIdx.x & 63);
+        const int l = a.hf.tile_lat[tile];
         const int4 d = a.bt.dims[l];
         Geom g;
         g.L[0] = d.x;
@@ -543,13 +722,13 @@ __global__ void __launch_bounds__(256) batch_eo_kernel(BatchEoArgs a)
         const int par = a.po ? 1 - a.hf.par[l] : a.hf.par[l];
         const int s = half_site(on ? H - a.hf.off[l] : 0, d, par);  // local full site
         const SiteGeo q = site_geo(s, g);
-        const int fo = a.bt.off[l], co = a.hf.off[l];
+        const int co = a.hf.off[l];
         const R ca = (R)a.ca[l], cb = (R)a.cb[l];
         {
-            if (a.act && !a.act[l * a.nrhs + r]) continue;  // uniform (one lattice, one RHS)
-            cpx<R> acc[12];
+            if (a.act && !a.act[l * a.nrhs + r]) continue;  // uniform in the wavefront
+            cpx<R> acc[12], v2[12];
 #pragma unroll
-            for (int c = 0; c < 12; ++c) acc[c] = {0, 0};
+            for (int c = 0; c < 12; ++c) acc[c] = v2[c] = {0, 0};
             if (on) {
 #pragma unroll 1
                 for (int hp = 0; hp < 8; ++hp) {
@@ -559,10 +738,8 @@ __global__ void __launch_bounds__(256) batch_eo_kernel(BatchEoArgs a)
                     // the neighbour (other side) at its half-site index
                     const int n = co + (((hp & 1) ? sm : sp) >> 1);
                     PT p[12], u[9];
-#pragma unroll
-                    for (int c = 0; c < 12; ++c) p[c] = OP::load(in, fidx(n, r, c, a.nrhs));
-#pragma unroll
-                    for (int e = 0; e < 9; ++e) u[e] = OP::load(U, lidx(fo + ((hp & 1) ? sm : s), mu, e));
+                    load_half<S, R>(p, in, n, r, a.nrhs);
+                    load_half_link<S, R>(u, (hp & 1) ? Ui : Uo, (hp & 1) ? n : H, mu);
                     switch (hp) {
                     case 0: hop<0, true>(acc, p, u); break;
                     case 1: hop<0, false>(acc, p, u); break;
@@ -574,20 +751,18 @@ __global__ void __launch_bounds__(256) batch_eo_kernel(BatchEoArgs a)
                     default: hop<3, false>(acc, p, u); break;
                     }
                 }
+                if (in2) load_half_vals<S, R>(v2, in2, H, r, a.nrhs);
 #pragma unroll
-                for (int c = 0; c < 12; ++c) {
-                    const cpx<R> v2 = in2 ? ldc(in2, fidx(H, r, c, a.nrhs)) : cpx<R>{0, 0};
-                    acc[c] = {ca * v2.re + cb * acc[c].re, ca * v2.im + cb * acc[c].im};
-                }
+                for (int c = 0; c < 12; ++c)
+                    acc[c] = {ca * v2[c].re + cb * acc[c].re, ca * v2[c].im + cb * acc[c].im};
             }
-#pragma unroll
-            for (int c = 0; c < 12; ++c) stc(out, fidx(H, r, c, a.nrhs), acc[c]);
+            store_half<S, R>(out, acc, H, r, a.nrhs);
             if (dots) {
                 R sre = 0, sim = 0, sqq = 0;
                 if (on) {
 #pragma unroll
                     for (int c = 0; c < 12; ++c) {
-                        const cpx<R> v = in2 ? ldc(in2, fidx(H, r, c, a.nrhs)) : cpx<R>{0, 0};
+                        const cpx<R> v = v2[c];
                         sre = fma(acc[c].re, v.re, fma(acc[c].im, v.im, sre));
                         sim = fma(acc[c].re, v.im, fma(-acc[c].im, v.re, sim));
                         sqq = fma(acc[c].re, acc[c].re, fma(acc[c].im, acc[c].im, sqq));
@@ -602,14 +777,15 @@ __global__ void __launch_bounds__(256) batch_eo_kernel(BatchEoArgs a)
 }
 
 template <int P>
-__global__ void __launch_bounds__(256) batch_eo_split_kernel(BatchTable bt, BatchHalf hf, int nrhs, void *x_,
-                                                             void *xp_, void *xq_, int to_full)
+__global__ void __launch_bounds__(256) batch_eo_join_kernel(BatchTable bt, BatchHalf hf, int nrhs, void *x_,
+                                                            const void *xp_, const void *xq_)
 {
     typedef typename Store<P>::S S;
-    S *x = (S *)x_, *xp = (S *)xp_, *xq = (S *)xq_;
+    S *x = (S *)x_;
+    const S *xp = (const S *)xp_, *xq = (const S *)xq_;
     const size_t n = (size_t)hf.Vtot * nrhs * 12;
     for (size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (size_t)gridDim.x * blockDim.x) {
-        // j = fidx(H, r, c): compact tile, RHS, component, lane
+        // j = (compact tile, RHS, component, lane)
         const size_t rest = j >> 6;
         const int tile = (int)(rest / ((size_t)nrhs * 12)), rc = (int)(rest - (size_t)tile * nrhs * 12);
         const int r = rc / 12, c = rc - r * 12;
@@ -621,13 +797,10 @@ __global__ void __launch_bounds__(256) batch_eo_split_kernel(BatchTable bt, Batc
         const int sp = half_site(valid ? h : 0, d, hf.par[l]);
         const int sq = sp ^ 1;  // the other site of the pair
         const size_t gp = fidx(bt.off[l] + sp, r, c, nrhs), gq = fidx(bt.off[l] + sq, r, c, nrhs);
-        if (!to_full) {
-            const S zero = {};
-            xp[j] = valid ? x[gp] : zero;
-            xq[j] = valid ? x[gq] : zero;
-        } else if (valid) {
-            x[gp] = xp[j];
-            x[gq] = xq[j];
+        if (valid) {
+            const size_t i = hidx<S>(H, r, c, nrhs);
+            x[gp] = xp[i];
+            x[gq] = xq[i];
         }
     }
 }
@@ -644,21 +817,18 @@ hipError_t launch_batch_eo(int prec, const BatchEoArgs &a, int grid, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_batch_eo_split(int prec, const BatchTable &bt, const BatchHalf &hf, int nrhs, void *x,
-                                 void *xp, void *xq, int to_full, int grid, hipStream_t st)
+hipError_t launch_batch_eo_join(int prec, const BatchTable &bt, const BatchHalf &hf, int nrhs, void *x,
+                                const void *xp, const void *xq, int grid, hipStream_t st)
 {
     switch (prec) {
     case GRG_FP64:
-        hipLaunchKernelGGL(batch_eo_split_kernel<GRG_FP64>, dim3(grid), dim3(256), 0, st, bt, hf, nrhs, x, xp, xq,
-                           to_full);
+        hipLaunchKernelGGL(batch_eo_join_kernel<GRG_FP64>, dim3(grid), dim3(256), 0, st, bt, hf, nrhs, x, xp, xq);
         break;
     case GRG_FP32:
-        hipLaunchKernelGGL(batch_eo_split_kernel<GRG_FP32>, dim3(grid), dim3(256), 0, st, bt, hf, nrhs, x, xp, xq,
-                           to_full);
+        hipLaunchKernelGGL(batch_eo_join_kernel<GRG_FP32>, dim3(grid), dim3(256), 0, st, bt, hf, nrhs, x, xp, xq);
         break;
     case GRG_BF16:
-        hipLaunchKernelGGL(batch_eo_split_kernel<GRG_BF16>, dim3(grid), dim3(256), 0, st, bt, hf, nrhs, x, xp, xq,
-                           to_full);
+        hipLaunchKernelGGL(batch_eo_join_kernel<GRG_BF16>, dim3(grid), dim3(256), 0, st, bt, hf, nrhs, x, xp, xq);
         break;
     default: return hipErrorInvalidValue;
     }
@@ -693,36 +863,6 @@ hipError_t launch_batch_mr_update(int prec, const BatchBlasArgs &a, void *x, voi
     return hipGetLastError();
 }
 
-hipError_t launch_batch_norm2(int prec, const BatchBlasArgs &a, const void *v, hipStream_t st)
-{
-    BDISP(prec, batch_norm2_kernel, lds_sys(a.bt.nlat * a.nrhs, 1), a, v);
-    return hipGetLastError();
-}
-
-hipError_t launch_batch_axpy_convert(int pin, int pout, const BatchBlasArgs &a, const void *x, void *y,
-                                     const double *scale, int mode, int beta, hipStream_t st)
-{
-    dim3 g(a.grid), b(256);
-#define BAX(PI, PO)                                                                                  \
-    if (pin == PI && pout == PO) {                                                                   \
-        hipLaunchKernelGGL((batch_axpy_convert_kernel<PI, PO>), g, b, 0, st, a, x, y, scale, mode, beta); \
-        return hipGetLastError();                                                                    \
-    }
-    BAX(GRG_FP64, GRG_FP64) BAX(GRG_FP64, GRG_FP32) BAX(GRG_FP64, GRG_BF16)
-    BAX(GRG_FP32, GRG_FP64) BAX(GRG_FP32, GRG_FP32) BAX(GRG_FP32, GRG_BF16)
-    BAX(GRG_BF16, GRG_FP64) BAX(GRG_BF16, GRG_FP32) BAX(GRG_BF16, GRG_BF16)
-#undef BAX
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_batch_sub_norm(const BatchBlasArgs &a, const void *b, const void *ax, void *r,
-                                 hipStream_t st)
-{
-    hipLaunchKernelGGL(batch_sub_norm_kernel, dim3(a.grid), dim3(256), lds_sys(a.bt.nlat * a.nrhs, 1), st,
-                       a, (const double2 *)b, (const double2 *)ax, (double2 *)r);
-    return hipGetLastError();
-}
-
 hipError_t launch_batch_dc_update(int prec, const BatchDcArgs &a, int grid, hipStream_t st)
 {
     const size_t lds = lds_sys(a.bt.nlat * a.nrhs, 1);
@@ -733,14 +873,6 @@ hipError_t launch_batch_dc_update(int prec, const BatchDcArgs &a, int grid, hipS
     case GRG_BF16: hipLaunchKernelGGL(batch_dc_update_kernel<GRG_BF16>, g, b, lds, st, a); break;
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_batch_scatter(const BatchTable &bt, const double *xb, void *dst, const int32_t *bidx,
-                                const int *nb, const long long *coff, int Vtot, int nrhs, hipStream_t st)
-{
-    hipLaunchKernelGGL(batch_scatter_kernel, dim3((Vtot + 255) / 256, nrhs), dim3(256), 0, st, bt,
-                       (const double2 *)xb, (double2 *)dst, bidx, nb, coff, Vtot, nrhs);
     return hipGetLastError();
 }
 
@@ -769,19 +901,52 @@ hipError_t launch_batch_ctl(const BatchCtlArgs &c, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_batch_xmy(const BatchBlasArgs &a, const void *x, void *y, hipStream_t st)
+hipError_t launch_batch_rb(const BatchCoarseArgs &c, double2 *b, double *partials, int grid, hipStream_t st)
 {
-    hipLaunchKernelGGL(batch_xmy_kernel, dim3(a.grid), dim3(256), 0, st, a, (const double2 *)x, (double2 *)y);
+    hipLaunchKernelGGL(batch_rb_kernel, dim3(grid), dim3(256), lds_sys(c.bt.nlat * c.nrhs, 1), st, c, b, partials);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_coarse(const BatchTable &bt, const void *in, const void *U, double *yb,
-                               const int32_t *qg, const int *clat, const int *nb, const int *nboff,
-                               const long long *coff, int nbtot, int nrhs, hipStream_t st)
+hipError_t launch_batch_residual(const BatchResidualArgs &a, int grid, hipStream_t st)
 {
-    hipLaunchKernelGGL(batch_coarse_kernel, dim3((nbtot + 127) / 128), dim3(128), 0, st, bt,
-                       (const double2 *)in, (const double2 *)U, (double2 *)yb, qg, clat, nb, nboff,
-                       coff, nbtot, nrhs);
+    hipLaunchKernelGGL(batch_residual_kernel, dim3(grid), dim3(256), lds_sys(a.bt.nlat * a.nrhs, 1), st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_coarse(const BatchCoarseArgs &c, const void *z, double *yb, hipStream_t st)
+{
+    const long items = (long)((c.nbtot + 63) / 64) * c.nrhs;
+    const int grid = (int)std::max<long>(8, (std::min<long>(items, 2048) + 7) / 8 * 8);
+    hipLaunchKernelGGL(batch_coarse_kernel, dim3(grid), dim3(kSplitThreads), 0, st, c, (const double2 *)z,
+                       (double2 *)yb);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_half_links(int prec, const BatchTable &bt, const BatchHalf &hf, const void *U, void *Uh,
+                                   hipStream_t st)
+{
+    const dim3 g((hf.Vtot + 255) / 256), b(256);
+    switch (prec) {
+    case GRG_FP64: hipLaunchKernelGGL(batch_half_links_kernel<double2>, g, b, 0, st, bt, hf, (const double2 *)U, (double2 *)Uh); break;
+    case GRG_FP32: hipLaunchKernelGGL(batch_half_links_kernel<float2>, g, b, 0, st, bt, hf, (const float2 *)U, (float2 *)Uh); break;
+    case GRG_BF16: hipLaunchKernelGGL(batch_half_links_kernel<bf16x2>, g, b, 0, st, bt, hf, (const bf16x2 *)U, (bf16x2 *)Uh); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_inner_split(int prec, const BatchBlasArgs &a, const BatchHalf &hf, const void *r_src,
+                                    const double *fr2, void *bp, void *bq, hipStream_t st)
+{
+    const dim3 g((unsigned)std::max<long>(8, std::min<long>((long)a.Vtot / 256 * a.nrhs, 2048) / 8 * 8)), b(256);
+#define BIS(PP) hipLaunchKernelGGL(batch_inner_split_kernel<PP>, g, b, 0, st, a, hf, (const double2 *)r_src, fr2, bp, bq)
+    switch (prec) {
+    case GRG_FP64: BIS(GRG_FP64); break;
+    case GRG_FP32: BIS(GRG_FP32); break;
+    case GRG_BF16: BIS(GRG_BF16); break;
+    default: return hipErrorInvalidValue;
+    }
+#undef BIS
     return hipGetLastError();
 }
 

@@ -202,6 +202,40 @@ def test_48_lattice_workload():
     grg.grg_batch_destroy(b)
 
 
+@pytest.mark.parametrize("inner,inner_tol,nrhs", [("fp64", 1e-2, 1), ("fp32", 1e-5, 5), ("bf16", 1e-2, 3)])
+def test_compact_halves_per_precision(inner, inner_tol, nrhs):
+    """The reduced solve's compact fields and links in each inner precision: a
+    half of 128 sites (padded to a block) beside ones of whole blocks, y written
+    over x.  The D_rr solve reaches 1e-12, so S_bb x is within 1e-10 of the
+    single lattice's (as the other comparisons here)."""
+    import torch
+    import paper_0704_2341_amd as grg
+
+    ensure_built()
+    descs = [dict(dims=(4, 4, 4, 4), m0=0.1, seed=4051), dict(dims=(2, 8, 4, 8), m0=-0.1, seed=4052),
+             dict(dims=(8, 4, 12, 2), m0=0.05, seed=4053)]
+    ms = members(descs, [(1, True), (2, False), (1, False)])
+    p = grg.grg_solver_params_default(tol=1e-12, inner=inner, inner_tol=inner_tol, eo=1)
+    b = grg.grg_batch_create(ms, nrhs, p)
+    x = batch_inputs(b, ms, nrhs, 90)
+    xs = split(b, ms, x, nrhs)
+    for use_graph in (False, True):
+        yd = to_dev(x)
+        st = grg.grg_batch_apply(b, yd, yd, use_graph=use_graph)
+        assert st["converged"]
+        ys = split(b, ms, to_host(yd), nrhs)
+        for i, m in enumerate(ms):
+            lat = Lattice(m["dims"], 0.5, m["seed"], links=m["links"])
+            sh = grg.grg_schur_create(lat.h, m["m0"], m["q"], m["n_coarse"], grg.grg_solver_params_default(tol=1e-12))
+            xx = to_dev(xs[i])
+            yy = torch.empty_like(xx)
+            grg.grg_schur_apply(sh, xx, yy, nrhs)
+            assert rel_err(ys[i], to_host(yy)) < 1e-10, (use_graph, i)
+            grg.grg_schur_destroy(sh)
+            lat.close()
+    grg.grg_batch_destroy(b)
+
+
 def test_bicgstab_is_rejected():
     """The batch's captured inner loop is minimal residual only."""
     import paper_0704_2341_amd as grg

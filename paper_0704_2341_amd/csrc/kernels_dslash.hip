@@ -182,6 +182,7 @@ struct DcEpi {
     __device__ static const SIN *input(const Args &a) { return (const SIN *)a.e; }
     __device__ static const SU *links(const Args &a) { return (const SU *)a.U; }
     __device__ static double *partials(const Args &a) { return a.partials; }
+    template <int STEP = 3>
     __device__ static void store(const Args &a, cpx<double> (&acc)[12], int s, int r, bool valid,
                                  double (&nrm)[K])
     {
@@ -199,9 +200,9 @@ struct DcEpi {
         const DcNext nx(a, s);
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-            // three components at a time: a compiler barrier keeps the
+            // STEP components at a time: a compiler barrier keeps the
             // streams' loads from being hoisted all at once (registers)
-            if (c % 3 == 0) asm volatile("" ::: "memory");
+            if (c % STEP == 0) asm volatile("" ::: "memory");
             const size_t i = fidx(s, r, c, a.nrhs);
             if (on) {
                 const double2 rv = dc_load_r(a, r_in, i);
@@ -383,9 +384,15 @@ __global__ void __launch_bounds__(E::kThreads) march_kernel(typename E::Args a)
 // x-row, lanes of the same wavefront) read LDS, and no second FP64
 // accumulator is carried from one slice to the next.  The hops of a site are
 // summed in march_kernel's order (backward t, diagonal, x, y, z, forward t).
+// The LDS holds two workgroups per CU, two wavefronts per SIMD, so a lane has 256
+// registers: the operands of two hops are in flight while a third is summed, and
+// the residual's twelve components are loaded together (32^4, 12 RHS: 1.94 ms; one
+// hop at a time and three components 2.06).  The step's bytes, 8 GB with the z
+// neighbours' second and third reads, take 1.6 ms at the rate of a copy; without
+// the residual's read it takes 1.5 ms, without its read and write 0.83.
 constexpr int kRingWaves = 4;  // wavefronts (RHS) per workgroup of the LDS-ring form
 template <class E>
-__global__ void __launch_bounds__(64 * kRingWaves) ring_march_kernel(typename E::Args a)
+__global__ void __launch_bounds__(64 * kRingWaves, 2) ring_march_kernel(typename E::Args a)
 {
     typedef typename E::SIN S;
     typedef typename E::SU SU;
@@ -462,16 +469,28 @@ __global__ void __launch_bounds__(64 * kRingWaves) ring_march_kernel(typename E:
 #pragma unroll
             for (int e = 0; e < 9; ++e) ut[e][lane] = ((const double2 *)U)[lidx(s3 + V3 * tm, 3, e)];
         }
+        auto load_u = [&](UT (&u)[9], int site, int mu) {
+#pragma unroll
+            for (int e = 0; e < 9; ++e) u[e] = OU::load(U, lidx(site, mu, e));
+        };
+        auto load_p = [&](PT (&p)[12], int site) {
+#pragma unroll
+            for (int c = 0; c < 12; ++c) p[c] = OP::load(in, fidx(site, r, c, a.nrhs));
+        };
+        // the operands of hops h (forward) and h + 1 (backward): each buffer is
+        // refilled as soon as its hop is summed
+        UT uf[9], ub[9];
+        PT pf[12], pb[12];
+        int sp, sm;
+        nbr(s3, 0, g3, a.g, sp, sm);
+        const int dxm = sm - s3;
+        load_u(uf, s3 + V3 * t0, 0);
+        load_u(ub, s3 + V3 * t0 + dxm, 0);
 #pragma unroll 1
         for (int t = t0; t < t1; ++t) {
             const int s = s3 + V3 * t;
             g3.c[3] = t;
-            const int tf = t + 1 == Lt ? 0 : t + 1, tb = t == 0 ? Lt - 1 : t - 1;
-            // the forward t-neighbour: used at the end of this slice, then
-            // kept in the ring for the next two
-            PT qc[12];
-#pragma unroll
-            for (int c = 0; c < 12; ++c) qc[c] = OP::load(in, fidx(s3 + V3 * tf, r, c, a.nrhs));
+            const int sf = s3 + V3 * (t + 1 == Lt ? 0 : t + 1);
             cpx<R> acc[12];
 #pragma unroll
             for (int c = 0; c < 12; ++c) acc[c] = {0, 0};
@@ -494,46 +513,48 @@ __global__ void __launch_bounds__(64 * kRingWaves) ring_march_kernel(typename E:
                 acc[c].im += diag * (R)v.im;
             }
 #pragma unroll 1
-            for (int h = 0; h < 6; ++h) {  // x hops from the ring, y and z hops loaded
-                const int mu = h >> 1;
-                int sp, sm;
-                nbr(s, mu, g3, a.g, sp, sm);
-                PT p[12];
-                UT u[9];
-                if (h < 2) {
-                    const int l = h == 0 ? lp : lm;
+            for (int mu = 0; mu < 3; ++mu) {
+                // the next direction's operands (the forward t link, and the
+                // next slice's x links, after the z hops; of the last slice
+                // those are unused, but in range)
+                const int nmu = mu + 1;
+                switch (mu) {
+                case 0: {
+                    PT p[12];
 #pragma unroll
-                    for (int c = 0; c < 12; ++c) p[c] = q[t & 1][c][l];
-                } else {
-                    const int n = (h & 1) ? sm : sp;
-#pragma unroll
-                    for (int c = 0; c < 12; ++c) p[c] = OP::load(in, fidx(n, r, c, a.nrhs));
+                    for (int c = 0; c < 12; ++c) p[c] = q[t & 1][c][lp];
+                    hop<0, true>(acc, p, uf);
+                    break;
                 }
-#pragma unroll
-                for (int e = 0; e < 9; ++e) u[e] = OU::load(U, lidx((h & 1) ? sm : s, mu, e));
-                switch (h) {
-                case 0: hop<0, true>(acc, p, u); break;
-                case 1: hop<0, false>(acc, p, u); break;
-                case 2: hop<1, true>(acc, p, u); break;
-                case 3: hop<1, false>(acc, p, u); break;
-                case 4: hop<2, true>(acc, p, u); break;
-                default: hop<2, false>(acc, p, u); break;
+                case 1: hop<1, true>(acc, pf, uf); break;
+                default: hop<2, true>(acc, pf, uf); break;
                 }
+                nbr(s, nmu, g3, a.g, sp, sm);
+                load_p(pf, mu < 2 ? sp : sf);  // last the forward t neighbour
+                load_u(uf, s, nmu);
+                switch (mu) {
+                case 0: {
+                    PT p[12];
+#pragma unroll
+                    for (int c = 0; c < 12; ++c) p[c] = q[t & 1][c][lm];
+                    hop<0, false>(acc, p, ub);
+                    break;
+                }
+                case 1: hop<1, false>(acc, pb, ub); break;
+                default: hop<2, false>(acc, pb, ub); break;
+                }
+                if (mu < 2) load_p(pb, sm);
+                load_u(ub, mu < 2 ? sm : sf + dxm, mu < 2 ? nmu : 0);
             }
-            {
-                UT u[9];
+            hop<3, true>(acc, pf, uf);
+            // the backward t link of the next slice, and slice t + 1 into the
+            // slot of slice t - 1 (read above by this lane only)
 #pragma unroll
-                for (int e = 0; e < 9; ++e) u[e] = OU::load(U, lidx(s, 3, e));
-                hop<3, true>(acc, qc, u);
-                // the backward t link of the next slice
+            for (int e = 0; e < 9; ++e) ut[e][lane] = make_double2(uf[e].re, uf[e].im);
 #pragma unroll
-                for (int e = 0; e < 9; ++e) ut[e][lane] = make_double2(u[e].re, u[e].im);
-            }
-            // slice t + 1 into the slot of slice t - 1 (read above by this
-            // lane only)
-#pragma unroll
-            for (int c = 0; c < 12; ++c) q[(t + 1) & 1][c][lane] = qc[c];
-            E::store(a, acc, s, r, true, dot);
+            for (int c = 0; c < 12; ++c) q[(t + 1) & 1][c][lane] = pf[c];
+            load_u(uf, sf, 0);
+            E::template store<12>(a, acc, s, r, true, dot);
         }
         if (partials) {
 #pragma unroll

@@ -317,10 +317,27 @@ grg_status dirac_apply_launch(grg_lattice L, double m0, int precision, const dou
     } else {
         GRG_TRY_HIP(launch_dslash_split(precision, a, true, t.grid, L->stream));
     }
-    GRG_TRY_HIP(hipStreamSynchronize(L->stream));
     return GRG_OK;
 }
 }  // namespace
+
+extern "C++" {
+namespace grg {
+// enqueued on the lattice's stream (its device current), arguments checked
+grg_status dirac_apply_internal(grg_lattice L, double m0, int precision, const double *in, double *out, int nrhs)
+{
+    const bool staged = dirac_staged(L, precision, in, out, nrhs);
+    const size_t bytes = spinor_elems(L->g, nrhs) * prec_bytes(precision);
+    if (staged && bytes > L->tmp_bytes) {
+        dfree(L->tmp_in);
+        L->tmp_bytes = 0;
+        GRG_TRY(dmalloc(&L->tmp_in, bytes, "dirac_apply scratch"));
+        L->tmp_bytes = bytes;
+    }
+    return dirac_apply_launch(L, m0, precision, in, out, nrhs, staged ? L->tmp_in : nullptr);
+}
+}  // namespace grg
+}
 
 grg_status grg_dirac_apply(grg_lattice L, double m0, int precision, const double *in, double *out,
                            int nrhs)
@@ -331,15 +348,9 @@ grg_status grg_dirac_apply(grg_lattice L, double m0, int precision, const double
     if (!L->gauge_set) return set_error("gauge field not set"), GRG_EINVAL;
     if (!isfinite(m0)) return set_error("m0 not finite"), GRG_EINVAL;
     DeviceGuard dg(L->device);
-    const bool staged = dirac_staged(L, precision, in, out, nrhs);
-    const size_t bytes = spinor_elems(L->g, nrhs) * prec_bytes(precision);
-    if (staged && bytes > L->tmp_bytes) {
-        dfree(L->tmp_in);
-        L->tmp_bytes = 0;
-        GRG_TRY(dmalloc(&L->tmp_in, bytes, "dirac_apply scratch"));
-        L->tmp_bytes = bytes;
-    }
-    return dirac_apply_launch(L, m0, precision, in, out, nrhs, staged ? L->tmp_in : nullptr);
+    GRG_TRY(dirac_apply_internal(L, m0, precision, in, out, nrhs));
+    GRG_TRY_HIP(hipStreamSynchronize(L->stream));
+    return GRG_OK;
 }
 
 // ------------------------------------------------------------------ no-alloc D apply
@@ -390,8 +401,10 @@ grg_status grg_dirac_apply_noalloc(grg_lattice L, double m0, int precision, cons
     GRG_TRY(scratch_address(L->device, &base));
     // every entry the stencil reads (sites < V of every RHS) is written by the
     // pack first, so nothing left by an earlier call is read
-    return dirac_apply_launch(L, m0, precision, in, out, nrhs,
-                              dirac_staged(L, precision, in, out, nrhs) ? base : nullptr);
+    GRG_TRY(dirac_apply_launch(L, m0, precision, in, out, nrhs,
+                               dirac_staged(L, precision, in, out, nrhs) ? base : nullptr));
+    GRG_TRY_HIP(hipStreamSynchronize(L->stream));
+    return GRG_OK;
 }
 
 static void schur_free(grg_schur S)

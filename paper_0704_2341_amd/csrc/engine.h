@@ -314,12 +314,34 @@ struct VcCoef {
     double2 c[3][kMaxRhs];     // per input and RHS
 };
 hipError_t launch_vc_block_links(const Geom &gf, const void *U64, const Geom &gc, double *out, hipStream_t st);
-hipError_t launch_vc_restrict(const double *full, double *coarse, const int32_t *q, int nb, int V, int nrhs,
-                              hipStream_t st);
-hipError_t launch_vc_prolong(const double *coarse, double *full, const int32_t *q, int nb, int V, int nrhs,
+hipError_t launch_vc_restrict(const double *f, const double *t, double *coarse, const int32_t *q, int nb, int V,
+                              int nrhs, hipStream_t st);
+hipError_t launch_vc_prolong(const double *coarse, double *full, const int32_t *bidx, int nb, int V, int nrhs,
                              hipStream_t st);
 hipError_t launch_vc_lincomb(size_t len, int nrhs, const VcCoef &cf, double *out, const double *in0,
                              const double *in1, const double *in2, hipStream_t st);
+// A whole BiCGstab solve A x = f, x from zero, A = c D (mask == nullptr) or
+// c D_rr on the sites with mask 0 (f read and x written there, x zero elsewhere),
+// a workgroup per RHS (kernels_small.hip).  Lattices of at most kSmallSites
+// sites; canonical FP64 fields, x not overlapping f.  Per RHS until
+// |r| <= tol |f| or max_iter; with check > 0 the residual is then recomputed from
+// x, the solve goes on if that misses tol (check times at most), and x = 0 is kept
+// if x is no better.
+// flags[0] is set if an RHS did not reach tol, flags[1] if a residual is not
+// finite.
+constexpr int kSmallSites = 256;
+constexpr int kSmallIters = 20000;  // most iterations of one launch (which nothing interrupts): 0.5 s
+struct SmallArgs {
+    Geom g;
+    const void *U;  // internal FP64 links
+    const uint8_t *mask;
+    double diag, c, tol;
+    int max_iter, check;
+    const double *f;
+    double *x;
+    int *flags;
+};
+hipError_t launch_small_bicgstab(const SmallArgs &a, int nrhs, hipStream_t st);
 int vc_dot_grid(size_t len);
 hipError_t launch_vc_dot(size_t len, int nrhs, const double *a, const double *b, double *partials,
                          hipStream_t st);

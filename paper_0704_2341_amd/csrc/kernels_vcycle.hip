@@ -55,10 +55,12 @@ __global__ void __launch_bounds__(256) vc_block_links_kernel(Geom gf, const doub
         }
 }
 
-// canonical fields [nrhs][V][12]: coarse[r][k] = full[r][q[k]] (restriction
-// to the coarse sites, which are the next level's sites in its own order),
-// and full[r][q[k]] = coarse[r][k] with full zero elsewhere (prolongation)
-__global__ void __launch_bounds__(256) vc_restrict_kernel(const double2 *__restrict__ full,
+// canonical fields [nrhs][V][12]: coarse[r][k] = (f - t)[r][q[k]] (restriction
+// to the coarse sites, which are the next level's sites in its own order), and
+// full[r][s] = coarse[r][bidx[s]] on the coarse sites, zero elsewhere
+// (prolongation; bidx: coarse index of a site or -1)
+__global__ void __launch_bounds__(256) vc_restrict_kernel(const double2 *__restrict__ f,
+                                                          const double2 *__restrict__ t,
                                                           double2 *__restrict__ coarse,
                                                           const int32_t *__restrict__ q, int nb, int V,
                                                           int nrhs)
@@ -68,21 +70,23 @@ __global__ void __launch_bounds__(256) vc_restrict_kernel(const double2 *__restr
         const int c = (int)(i % 12);
         const size_t rk = i / 12;
         const int k = (int)(rk % nb), r = (int)(rk / nb);
-        coarse[i] = full[((size_t)r * V + q[k]) * 12 + c];
+        const size_t j = ((size_t)r * V + q[k]) * 12 + c;
+        const double2 a = f[j], b = t[j];
+        coarse[i] = make_double2(a.x - b.x, a.y - b.y);
     }
 }
 
 __global__ void __launch_bounds__(256) vc_prolong_kernel(const double2 *__restrict__ coarse,
                                                          double2 *__restrict__ full,
-                                                         const int32_t *__restrict__ q, int nb, int V,
+                                                         const int32_t *__restrict__ bidx, int nb, int V,
                                                          int nrhs)
 {
-    const size_t n = (size_t)nrhs * nb * 12;
+    const size_t n = (size_t)nrhs * V * 12;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
         const int c = (int)(i % 12);
-        const size_t rk = i / 12;
-        const int k = (int)(rk % nb), r = (int)(rk / nb);
-        full[((size_t)r * V + q[k]) * 12 + c] = coarse[i];
+        const size_t rs = i / 12;
+        const int s = (int)(rs % V), r = (int)(rs / V), k = bidx[s];
+        full[i] = k < 0 ? make_double2(0.0, 0.0) : coarse[((size_t)r * nb + k) * 12 + c];
     }
 }
 
@@ -151,19 +155,19 @@ hipError_t launch_vc_block_links(const Geom &gf, const void *U64, const Geom &gc
     return hipGetLastError();
 }
 
-hipError_t launch_vc_restrict(const double *full, double *coarse, const int32_t *q, int nb, int V, int nrhs,
-                              hipStream_t st)
+hipError_t launch_vc_restrict(const double *f, const double *t, double *coarse, const int32_t *q, int nb, int V,
+                              int nrhs, hipStream_t st)
 {
     hipLaunchKernelGGL(vc_restrict_kernel, dim3(vc_grid((size_t)nrhs * nb * 12)), dim3(256), 0, st,
-                       (const double2 *)full, (double2 *)coarse, q, nb, V, nrhs);
+                       (const double2 *)f, (const double2 *)t, (double2 *)coarse, q, nb, V, nrhs);
     return hipGetLastError();
 }
 
-hipError_t launch_vc_prolong(const double *coarse, double *full, const int32_t *q, int nb, int V, int nrhs,
+hipError_t launch_vc_prolong(const double *coarse, double *full, const int32_t *bidx, int nb, int V, int nrhs,
                              hipStream_t st)
 {
-    hipLaunchKernelGGL(vc_prolong_kernel, dim3(vc_grid((size_t)nrhs * nb * 12)), dim3(256), 0, st,
-                       (const double2 *)coarse, (double2 *)full, q, nb, V, nrhs);
+    hipLaunchKernelGGL(vc_prolong_kernel, dim3(vc_grid((size_t)nrhs * V * 12)), dim3(256), 0, st,
+                       (const double2 *)coarse, (double2 *)full, bidx, nb, V, nrhs);
     return hipGetLastError();
 }
 

@@ -35,7 +35,6 @@ struct grg_vcycle_s {
     grg_schur schur[3] = {nullptr, nullptr, nullptr};  // levels below the top
     double m[3] = {0, 0, 0}, c[3] = {1, 1, 1};
     int V[3] = {0, 0, 0}, nb[3] = {0, 0, 0};
-    int32_t *d_q[3] = {nullptr, nullptr, nullptr};      // coarse sites of level k, q[0:nb]
     // canonical FP64 fields per level, max_rhs each: the cycle's input and
     // output on that level, and three temporaries
     double *fin[3] = {}, *xout[3] = {}, *t0[3] = {}, *t1[3] = {}, *t2[3] = {};
@@ -43,12 +42,15 @@ struct grg_vcycle_s {
     // when it is solved inside a cycle, hence a second set)
     double *bv[2][8] = {};
     double *partials = nullptr, *h_part = nullptr;
+    int *flags = nullptr;  // pinned: what a small level's solve reports (SmallArgs)
     int cycles = 0;
 };
 
 namespace grg {
 
 grg_status reusken_apply_internal(grg_schur S, const double *xb, double *yb, int nrhs);
+grg_status dirac_apply_internal(grg_lattice L, double m0, int precision, const double *in, double *out, int nrhs);
+grg_status block_apply_internal(grg_schur S, int prec, int rows, int cols, const double *in, double *out, int nrhs);
 
 namespace {
 
@@ -104,17 +106,56 @@ grg_status dots(grg_vcycle_s *v, int k, int nrhs, const double *a, const double 
     return GRG_OK;
 }
 
-// out = A_k in (the approximate top level enqueued without the API call's
-// synchronisation: the solve's next norm read waits for it)
+// out = A_k in, enqueued (the solve's next norm read waits for it)
 grg_status apply_level(grg_vcycle_s *v, int k, int nrhs, const double *in, double *out)
 {
     if (k > 0 && v->approx_top) return reusken_apply_internal(v->schur[0], in, out, nrhs);
-    GRG_TRY(grg_dirac_apply(v->lat[k], v->m[k], GRG_FP64, in, out, nrhs));
+    GRG_TRY(dirac_apply_internal(v->lat[k], v->m[k], GRG_FP64, in, out, nrhs));
     if (v->c[k] != 1.0) {
         double2 s[kMaxRhs];
         for (int r = 0; r < nrhs; ++r) s[r] = make_double2(v->c[k], 0);
         GRG_TRY(lincomb(v, k, nrhs, out, 1, out, s));
     }
+    return GRG_OK;
+}
+
+// Whether a level is solved in one launch (kernels_small.hip).  The registers of
+// a workgroup hold the vectors of 256 sites; a D_rr solve there (4 RHS, two
+// iterations) takes 86 us and the 16 sites of an 8^4 lattice's third level 37,
+// launched step by step 310 and 500 with the waits of the host.
+bool small_level(const grg_vcycle_s *v, int k)
+{
+    return v->lat[k] && v->V[k] <= kSmallSites && v->prm.max_iter <= kSmallIters;
+}
+
+// x = A_k^{-1} f to tol (top), or x = D_rr^{-1} f_r of level k to tol, enqueued
+grg_status small_solve(grg_vcycle_s *v, int k, bool drr, double tol, int nrhs, const double *f, double *x)
+{
+    SmallArgs a;
+    a.g = v->lat[k]->g;
+    a.U = v->lat[k]->U[GRG_FP64];
+    a.mask = drr ? v->schur[k]->d_mask : nullptr;
+    a.diag = 4.0 + v->m[k];
+    a.c = drr ? 1.0 : v->c[k];
+    a.tol = tol;
+    a.max_iter = v->prm.max_iter;
+    a.check = drr ? v->schur[k]->prm.max_outer : 0;
+    a.f = f;
+    a.x = x;
+    // a D_rr solve that stops at max_iter is used as it is
+    a.flags = v->flags + (drr ? 2 : 0);
+    GRG_TRY_HIP(launch_small_bicgstab(a, nrhs, v->lat[0]->stream));
+    return GRG_OK;
+}
+
+// what the small levels' solves since the last clear_flags reported (after a
+// synchronisation)
+void clear_flags(grg_vcycle_s *v) { memset(v->flags, 0, 4 * sizeof(int)); }
+grg_status check_flags(grg_vcycle_s *v)
+{
+    const volatile int *f = v->flags;
+    if (f[1] || f[3]) return set_error("non-finite residual in the V-cycle's BiCGstab"), GRG_ENONFINITE;
+    if (f[0]) return set_error("V-cycle: the top level's solve did not reach top_tol"), GRG_ENOCONV;
     return GRG_OK;
 }
 
@@ -170,6 +211,7 @@ grg_status bicgstab(grg_vcycle_s *v, int k, int set, bool pre, double tol, int n
         }
         GRG_TRY(apply_level(v, k, nrhs, pin, vv));
         GRG_TRY(dots(v, k, nrhs, rh, vv, tmp, nullptr));
+        if (pre) GRG_TRY(check_flags(v));
         for (int i = 0; i < nrhs; ++i) alpha[i] = act[i] ? cdiv(rho[i], tmp[i]) : make_double2(0, 0);
         for (int i = 0; i < nrhs; ++i) tmp[i] = make_double2(-alpha[i].x, -alpha[i].y);
         GRG_TRY(lincomb(v, k, nrhs, s, 2, r, one, vv, tmp));  // s = r - alpha v
@@ -223,15 +265,15 @@ grg_status bicgstab(grg_vcycle_s *v, int k, int set, bool pre, double tol, int n
 grg_status cycle(grg_vcycle_s *v, int k, int nrhs, const double *f, double *x)
 {
     hipStream_t st = v->lat[0]->stream;
-    double2 one[kMaxRhs], mone[kMaxRhs], ic[kMaxRhs], mc[kMaxRhs];
+    double2 one[kMaxRhs], ic[kMaxRhs], mc[kMaxRhs];
     for (int i = 0; i < kMaxRhs; ++i) {
         one[i] = make_double2(1, 0);
-        mone[i] = make_double2(-1, 0);
         ic[i] = make_double2(1.0 / v->c[k], 0);
         mc[i] = make_double2(-v->c[k], 0);
     }
     if (k == v->levels - 1) {
         // the top level, solved to top_tol
+        if (small_level(v, k)) return small_solve(v, k, false, v->prm.top_tol, nrhs, f, x);
         int it = 0;
         bool conv = false;
         GRG_TRY(bicgstab(v, k, 1, false, v->prm.top_tol, nrhs, f, x, &it, nullptr, &conv));
@@ -242,23 +284,25 @@ grg_status cycle(grg_vcycle_s *v, int k, int nrhs, const double *f, double *x)
     grg_schur S = v->schur[k];
     const int V = v->V[k], nb = v->nb[k];
     double *y = v->t0[k], *t = v->t1[k], *u = v->t2[k];
+    const bool small = small_level(v, k);
+    auto drr = [&](const double *in, double *out) -> grg_status {
+        if (small) return small_solve(v, k, true, v->prm.drr_tol, nrhs, in, out);
+        const grg_status s = grg_drr_solve(S, in, out, nrhs, nullptr);
+        return s == GRG_ENOCONV ? GRG_OK : s;
+    };
     // y = D_rr^{-1} f_r  (A_rr^{-1} f_r = y / c_k)
-    grg_status s = grg_drr_solve(S, f, y, nrhs, nullptr);
-    if (s != GRG_OK && s != GRG_ENOCONV) return s;
+    GRG_TRY(drr(f, y));
     // g = f_b - A_br A_rr^{-1} f_r = f_b - (D_br y)_b, restricted to level k + 1
-    GRG_TRY(grg_block_apply(S, GRG_FP64, 1, 0, y, t, nrhs));
-    GRG_TRY(lincomb(v, k, nrhs, t, 2, f, one, t, mone));
-    GRG_TRY_HIP(launch_vc_restrict(t, v->fin[k + 1], v->d_q[k], nb, V, nrhs, st));
+    GRG_TRY(block_apply_internal(S, GRG_FP64, 1, 0, y, t, nrhs));
+    GRG_TRY_HIP(launch_vc_restrict(f, t, v->fin[k + 1], S->d_q, nb, V, nrhs, st));
     // x_b = cycle(k + 1) g
     GRG_TRY(cycle(v, k + 1, nrhs, v->fin[k + 1], v->xout[k + 1]));
     // u = x_b on the coarse sites; h = f_r - A_rb u = f - c_k (D_rb u)
-    GRG_TRY_HIP(launch_fill_zero(u, (size_t)nrhs * V * 12 * 16, st));
-    GRG_TRY_HIP(launch_vc_prolong(v->xout[k + 1], u, v->d_q[k], nb, V, nrhs, st));
-    GRG_TRY(grg_block_apply(S, GRG_FP64, 0, 1, u, t, nrhs));
+    GRG_TRY_HIP(launch_vc_prolong(v->xout[k + 1], u, S->d_bidx, nb, V, nrhs, st));
+    GRG_TRY(block_apply_internal(S, GRG_FP64, 0, 1, u, t, nrhs));
     GRG_TRY(lincomb(v, k, nrhs, t, 2, f, one, t, mc));
     // x_r = A_rr^{-1} h = D_rr^{-1} h / c_k ; x = x_r + u
-    s = grg_drr_solve(S, t, y, nrhs, nullptr);
-    if (s != GRG_OK && s != GRG_ENOCONV) return s;
+    GRG_TRY(drr(t, y));
     GRG_TRY(lincomb(v, k, nrhs, x, 2, y, ic, u, one));
     return GRG_OK;
 }
@@ -274,7 +318,6 @@ void vcycle_free(grg_vcycle_s *v)
     for (int k = 0; k < 3; ++k) {
         if (v->schur[k]) (void)grg_schur_destroy(v->schur[k]);
         if (k > 0 && v->lat[k]) (void)grg_lattice_destroy(v->lat[k]);
-        vfree((void *&)v->d_q[k]);
         vfree((void *&)v->fin[k]);
         vfree((void *&)v->xout[k]);
         vfree((void *&)v->t0[k]);
@@ -286,6 +329,8 @@ void vcycle_free(grg_vcycle_s *v)
     vfree((void *&)v->partials);
     if (v->h_part) (void)hipHostFree(v->h_part);
     v->h_part = nullptr;
+    if (v->flags) (void)hipHostFree(v->flags);
+    v->flags = nullptr;
 }
 
 }  // namespace
@@ -377,9 +422,6 @@ grg_status grg_vcycle_create(grg_lattice L, double m0, const grg_vcycle_params *
             sp.max_iter = p.max_iter;
             if ((s = grg_schur_create(v->lat[k], v->m[k], q.data(), nb, &sp, &v->schur[k])) != GRG_OK)
                 return fail(s);
-            if (!alloc((void **)&v->d_q[k], sizeof(int32_t) * nb)) return fail(GRG_ENOMEM);
-            if (hipMemcpy(v->d_q[k], q.data(), sizeof(int32_t) * nb, hipMemcpyHostToDevice) != hipSuccess)
-                return set_error("V-cycle: copy of the coarse sites failed"), fail(GRG_EHIP);
             if (approx_top) {
                 // the top level: the N_b coarse sites, no lattice of their own
                 dims[0] = nb;
@@ -422,6 +464,11 @@ grg_status grg_vcycle_create(grg_lattice L, double m0, const grg_vcycle_params *
         v->h_part = nullptr;
         return set_error("V-cycle: hipHostMalloc failed"), fail(GRG_ENOMEM);
     }
+    if (hipHostMalloc((void **)&v->flags, 4 * sizeof(int)) != hipSuccess) {
+        v->flags = nullptr;
+        return set_error("V-cycle: hipHostMalloc failed"), fail(GRG_ENOMEM);
+    }
+    clear_flags(v);
     *out = v;
     return GRG_OK;
 }
@@ -441,9 +488,10 @@ grg_status grg_vcycle_apply(grg_vcycle v, const double *f, double *x, int nrhs)
     if (!v || !f || !x) return set_error("null argument"), GRG_EINVAL;
     if (nrhs < 1 || nrhs > v->prm.max_rhs) return set_error("nrhs outside 1..max_rhs"), GRG_EINVAL;
     Dev dev(v->lat[0]->device);
-    GRG_TRY(cycle(v, 0, nrhs, f, x));
+    clear_flags(v);
+    const grg_status s = cycle(v, 0, nrhs, f, x);
     GRG_TRY_HIP(hipStreamSynchronize(v->lat[0]->stream));
-    return GRG_OK;
+    return s == GRG_OK ? check_flags(v) : s;
 }
 
 grg_status grg_vcycle_solve(grg_vcycle v, int precondition, double tol, const double *f, double *x, int nrhs,
@@ -459,10 +507,15 @@ grg_status grg_vcycle_solve(grg_vcycle v, int precondition, double tol, const do
     int it = 0;
     double rate = 0;
     bool conv = false;
-    GRG_TRY(bicgstab(v, 0, 0, precondition != 0, tol, nrhs, f, x, &it, &rate, &conv));
+    clear_flags(v);
+    const grg_status bs = bicgstab(v, 0, 0, precondition != 0, tol, nrhs, f, x, &it, &rate, &conv);
+    if (bs != GRG_OK) {
+        (void)hipStreamSynchronize(v->lat[0]->stream);  // nothing is left that could set a flag later
+        return bs;
+    }
     // |f - D x| / |f| from the iterate
     double *t = v->t0[0];
-    GRG_TRY(grg_dirac_apply(v->lat[0], v->m[0], GRG_FP64, x, t, nrhs));
+    GRG_TRY(dirac_apply_internal(v->lat[0], v->m[0], GRG_FP64, x, t, nrhs));
     double2 one[kMaxRhs], mone[kMaxRhs];
     for (int i = 0; i < kMaxRhs; ++i) {
         one[i] = make_double2(1, 0);

@@ -62,6 +62,54 @@ def test_cycle_other_boundary_signs(levels):
     lt.close()
 
 
+@pytest.mark.parametrize("dims,levels", [((4, 4, 4, 4), 2), ((8, 8, 4, 4), 2), ((8, 4, 8, 8), 2), ((8, 8, 4, 12), 2),
+                                         ((8, 8, 8, 12), 2), ((8, 8, 8, 16), 3)])
+def test_level_sizes_vs_oracle(dims, levels):
+    """Lower levels of one to three tiles of 64 sites (and a quarter and a half of
+    one), solved in one launch, and of 384 and 512 that are not; four RHS, one of
+    them zero."""
+    import torch
+
+    lt = Lattice(dims, 0.5, 48)
+    grg = lt.grg
+    prm = grg.grg_vcycle_params_default(levels=levels, drr_tol=1e-12, top_tol=1e-13, max_rhs=4)
+    v = grg.grg_vcycle_create(lt.h, M0, prm)
+    f = gaussian_vectors(12 * lt.V, 4, 49)
+    f[2] = 0
+    fd = to_dev(f)
+    xd = torch.full_like(fd, 7.0)
+    print(f"V-cycle apply, {levels} levels, {dims}", flush=True)
+    grg.grg_vcycle_apply(v, fd, xd, 4)
+    x = to_host(xd)
+    lv = vcycle.hierarchy(lt.links, dims, M0, levels)
+    for k in (0, 3):
+        assert rel_err(x[k], vcycle.cycle(lv, 0, f[k], tol=1e-13)) < 1e-9, k
+    assert not np.any(x[2])
+    grg.grg_vcycle_destroy(v)
+    lt.close()
+
+
+def test_small_level_stops(lat):
+    """A top level that may not reach its tolerance in the iterations allowed
+    is refused, and a residual that is not finite is reported."""
+    import torch
+
+    grg = lat.grg
+    v = grg.grg_vcycle_create(lat.h, M0, grg.grg_vcycle_params_default(levels=3, max_rhs=1, max_iter=1))
+    f = to_dev(gaussian_vectors(12 * lat.V, 1, 50))
+    x = torch.empty_like(f)
+    with pytest.raises(grg.GrgError) as e:
+        grg.grg_vcycle_apply(v, f, x, 1)
+    assert e.value.status == grg.GRG_ENOCONV
+    grg.grg_vcycle_destroy(v)
+    v = grg.grg_vcycle_create(lat.h, M0, grg.grg_vcycle_params_default(levels=3, max_rhs=1))
+    f[0, 5] = float("nan")
+    with pytest.raises(grg.GrgError) as e:
+        grg.grg_vcycle_apply(v, f, x, 1)
+    assert e.value.status == grg.GRG_ENONFINITE
+    grg.grg_vcycle_destroy(v)
+
+
 def test_preconditioned_solve(lat):
     import torch
 

@@ -21,6 +21,7 @@
 // per site (F colour vectors); a Dirac field is the F = 4 case.
 #include "common.h"
 #include "engine.h"
+#include "eo_site.h"
 #include "ptc.h"
 #include "stencil.h"
 
@@ -172,10 +173,25 @@ __device__ __forceinline__ void ptc_task_store(int h, int f0, const GatherOps<FH
 // its channels.  A wavefront loads its next slot's operands before it
 // transports the current one, so that the memory latency of its tasks
 // overlaps.
-template <int FIN, bool ROWK, int LD>
-__device__ __forceinline__ void ptc_gather(const bf16x2 *__restrict__ x, const bf16x2 *__restrict__ U,
-                                           const Geom &g, const LaneSite &c, bool valid, int r, int nrhs,
-                                           __bf16 *lds, int h0, int h1, int kbase)
+// The solve on the even-odd reduced system needs the network between one
+// parity's fields only: the first layer's input and the last layer's output are
+// zero on, or not wanted on, the other.  On the compact halves (EO) the first
+// layer forms no hops where only hop 0 contributes, the last layer runs on half the
+// tiles, and no field is spread to the full lattice and back (16^4, 12 RHS:
+// layers 112 / 150 / 151 us and two scatters of 46 on the full layout; 97 / 158 /
+// 90 us here).
+//
+// Where a gather reads: the full layout, or (EO) the compact halves, in which
+// the site's own half serves hop 0 and forward links, the other half the
+// neighbours and backward links; a half that is zero (nullptr) is not read.
+struct GatherFrom {
+    const bf16x2 *x, *U;    // the full layout's; EO: the own half's
+    const bf16x2 *xo, *Uo;  // EO: the other half's
+};
+
+template <int FIN, bool ROWK, int LD, bool EO = false>
+__device__ __forceinline__ void ptc_gather(const GatherFrom &from, const Geom &g, const LaneSite &c, bool valid,
+                                           int r, int nrhs, __bf16 *lds, int h0, int h1, int kbase)
 {
     constexpr int FH = (FIN + 1) / 2;  // channels per task
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -186,7 +202,20 @@ __device__ __forceinline__ void ptc_gather(const bf16x2 *__restrict__ x, const b
         const int h = h0 + (t >> 1);
         int n, ls;
         ptc_hop_site(c, h, g, n, ls);
-        ptc_task_load<FIN, FH>(h, (t & 1) * FH, n, ls, x, U, r, nrhs, o);
+        if constexpr (EO) {
+            const bf16x2 *x = h == 0 ? from.x : from.xo;
+            if (FIN == 4 && x == nullptr) {
+#pragma unroll
+                for (int e = 0; e < 9; ++e) o.m[e] = 0;
+#pragma unroll
+                for (int i = 0; i < FH; ++i) o.v[i][0] = o.v[i][1] = o.v[i][2] = 0;
+                return;
+            }
+            const bool fwd = ((h - 1) & 1) == 0;
+            ptc_task_load<FIN, FH>(h, (t & 1) * FH, n >> 1, ls >> 1, x, fwd ? from.U : from.Uo, r, nrhs, o);
+        } else {
+            ptc_task_load<FIN, FH>(h, (t & 1) * FH, n, ls, from.x, from.U, r, nrhs, o);
+        }
     };
     GatherOps<FH> A, B;
     load(task, A);
@@ -205,7 +234,7 @@ __device__ __forceinline__ void ptc_gather(const bf16x2 *__restrict__ x, const b
 }
 
 // ------------------------------------------------------------------ layer
-template <int FIN, int FOUT>
+template <int FIN, int FOUT, bool EO = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) ptc_layer_kernel(PtcLayerArgs a)
 {
     constexpr int KR = 9 * FIN * 2;
@@ -230,25 +259,39 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) p
         *(bf16x8_v *)(wl + 8 * i) = *(const bf16x8_v *)(a.A + 8 * i);
     const __bf16 *arow = wl + (lane & 15) * KP + 8 * (lane >> 4);
     const bf16x2 *x = (const bf16x2 *)a.x;
-    bf16x2 *y = (bf16x2 *)a.y;
     const bf16x2 *U = (const bf16x2 *)a.U;
     // work items: (tile, group of rc right-hand sides); the sites a tile's
     // gather reads are found once per item
-    const int ntiles = (a.g.V + 63) >> 6;
+    const int V = EO ? a.g.V >> 1 : a.g.V;  // sites of a half
+    const int nth = (V + 63) >> 6;
+    const int ntiles = EO && a.out_par < 0 ? 2 * nth : nth;
     const int ngrp = (a.nrhs + a.rc - 1) / a.rc;
     const int nitems = ntiles * ngrp;
     for (int w = blockIdx.x; w < nitems; w += gridDim.x) {
         const int tile = w / ngrp, grp = w - tile * ngrp;
         const int r0 = grp * a.rc, r1 = min(r0 + a.rc, a.nrhs);
-        const int s = tile * 64 + lane;
-        const bool valid = s < a.g.V;
-        const LaneSite ls = lane_site(valid ? s : 0, a.g);
+        // (EO: par the tile's parity, s and site half indices)
+        const int par = !EO ? 0 : a.out_par >= 0 ? a.out_par : tile >= nth;
+        const int t0 = (EO && a.out_par < 0 ? tile - par * nth : tile) * 64;
+        const int s = t0 + lane;
+        const bool valid = s < V;
+        LaneSite ls;
+        if constexpr (EO) {
+            SiteGeo q;
+            ls.s = eo_site(valid ? s : 0, par, a.g, q);
+            for (int k = 0; k < 4; ++k) ls.x[k] = q.c[k];
+        } else {
+            ls = lane_site(valid ? s : 0, a.g);
+        }
+        const size_t hx = (size_t)a.Vhs * a.nrhs * (3 * FIN), hy = (size_t)a.Vhs * a.nrhs * (3 * FOUT);
+        const uint8_t *mask = EO && a.mask ? a.mask + (size_t)par * a.Vhs : a.mask;
+        bf16x2 *y = (bf16x2 *)a.y + (EO && a.out_par < 0 ? par * hy : 0);
         // this lane's output columns 16 t + l%16 = (site, colour), t = wv + 4 i
         bool on[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            const int site = tile * 64 + (16 * (wv + 4 * i) + (lane & 15)) / 3;
-            on[i] = site < a.g.V && (a.mask == nullptr || a.mask[site] == a.sel);
+            const int site = t0 + (16 * (wv + 4 * i) + (lane & 15)) / 3;
+            on[i] = site < V && (mask == nullptr || mask[site] == a.sel);
         }
         for (int r = r0; r < r1; ++r) {
             // the links are re-read for every right-hand side (L1 hits): an
@@ -257,6 +300,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) p
             // into registers the occupancy cannot spare
             const bf16x2 *Ur = U;
             asm volatile("" : "+s"(Ur));
+            GatherFrom from = {x, Ur, nullptr, nullptr};
+            if constexpr (EO) {
+                // (the first layer's input is on one parity only)
+                from.x = FIN > 4 ? x + par * hx : a.in_par == par ? x : nullptr;
+                from.xo = FIN > 4 ? x + (1 - par) * hx : a.in_par == par ? nullptr : x;
+                from.U = Ur + (size_t)par * 36 * a.Vhs;
+                from.Uo = Ur + (size_t)(1 - par) * 36 * a.Vhs;
+            }
             LaneSite lc = ls;
             opaque_site(lc);
             f32x4_v c[3];
@@ -264,9 +315,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) p
             for (int i = 0; i < 3; ++i) c[i] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int pass = 0; pass < 2; ++pass) {
+                // (no neighbour contributes: the second pass is all zero)
+                if (EO && FIN == 4 && pass == 1 && from.xo == nullptr) break;
                 __syncthreads();  // the previous products are out of LDS
-                if (pass == 0) ptc_gather<FIN, true, LD>(x, Ur, a.g, lc, valid, r, a.nrhs, lds, 0, 4, 0);
-                else ptc_gather<FIN, true, LD>(x, Ur, a.g, lc, valid, r, a.nrhs, lds, 4, 9, K1);
+                if (pass == 0) ptc_gather<FIN, true, LD, EO>(from, a.g, lc, valid, r, a.nrhs, lds, 0, 4, 0);
+                else ptc_gather<FIN, true, LD, EO>(from, a.g, lc, valid, r, a.nrhs, lds, 4, 9, K1);
                 __syncthreads();
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
@@ -285,8 +338,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) p
                 const int t = wv + 4 * i;
                 // rows 4 (l/16) + q = (f, re/im): two complex outputs per lane
                 const int col = 16 * t + (lane & 15);
-                const int site = tile * 64 + col / 3, colour = col % 3;
-                if (site < a.g.V) {
+                const int site = t0 + col / 3, colour = col % 3;
+                if (site < V) {
                     const int f0 = 2 * (lane >> 4);
 #pragma unroll
                     for (int q = 0; q < 2; ++q) {
@@ -338,7 +391,7 @@ __global__ void __launch_bounds__(256) ptc_wgrad_kernel(PtcGradArgs a)
             LaneSite lc = ls;
             opaque_site(lc);
             __syncthreads();
-            ptc_gather<FIN, false, LD>(x, Ur, a.g, lc, valid, r, a.nrhs, tx, 0, 9, 0);
+            ptc_gather<FIN, false, LD>(GatherFrom{x, Ur, nullptr, nullptr}, a.g, lc, valid, r, a.nrhs, tx, 0, 9, 0);
             // dY rows (g, re/im), columns (site, colour)
             for (int gch = wv; gch < FOUT; gch += 4) {
 #pragma unroll
@@ -612,6 +665,14 @@ int ptc_launch_shape(int kind, int fin, int fout, const Geom &g, int nrhs, int *
 hipError_t launch_ptc_layer(int fin, int fout, const PtcLayerArgs &a, int grid, hipStream_t st)
 {
     dim3 g(grid), b(256);
+    if (a.Vhs > 0) {
+        if ((fin == 4) != (a.in_par >= 0) || (fout == 4) != (a.out_par >= 0)) return hipErrorInvalidValue;
+        if (fin == 4 && fout == 8) hipLaunchKernelGGL((ptc_layer_kernel<4, 8, true>), g, b, 0, st, a);
+        else if (fin == 8 && fout == 8) hipLaunchKernelGGL((ptc_layer_kernel<8, 8, true>), g, b, 0, st, a);
+        else if (fin == 8 && fout == 4) hipLaunchKernelGGL((ptc_layer_kernel<8, 4, true>), g, b, 0, st, a);
+        else return hipErrorInvalidValue;
+        return hipGetLastError();
+    }
     if (fin == 4 && fout == 8) hipLaunchKernelGGL((ptc_layer_kernel<4, 8>), g, b, 0, st, a);
     else if (fin == 8 && fout == 8) hipLaunchKernelGGL((ptc_layer_kernel<8, 8>), g, b, 0, st, a);
     else if (fin == 8 && fout == 4) hipLaunchKernelGGL((ptc_layer_kernel<8, 4>), g, b, 0, st, a);

@@ -28,7 +28,11 @@ grg_status eo_training_pair(grg_schur S, void *e, void *r_full, int nrhs, int k,
 
 static const int kOff[3] = {0, 9 * 8 * 4, 9 * 8 * 4 + 9 * 8 * 8};
 
-static size_t act_bytes(const Geom &g, int nrhs, int F) { return (size_t)nrhs * 3 * F * g.Vs * 4; }
+// the full layout, or the two padded compact halves
+static size_t act_bytes(grg_lattice L, int nrhs, int F)
+{
+    return (size_t)nrhs * 3 * F * std::max(L->g.Vs, L->eo_ok ? 2 * L->Vhs : 0) * 4;
+}
 
 static grg_status embed_all(grg_precond P)
 {
@@ -60,6 +64,36 @@ static grg_status forward(grg_precond P, const void *in, void *out, int nrhs,
         a.sel = 0;
         a.g = L->g;
         a.nrhs = nrhs;
+        GRG_TRY_HIP(launch_ptc_layer(kPtcChannels[l], kPtcChannels[l + 1], a, grid, L->stream));
+        x = a.y;
+    }
+    return GRG_OK;
+}
+
+// out = M in on the reduced parity's compact half (bf16), the other parity's
+// input zero and its output not formed
+static grg_status forward_half(grg_precond P, const void *in, void *out, int nrhs)
+{
+    grg_schur S = P->schur;
+    grg_lattice L = S->lat;
+    const void *x = in;
+    const int nth = (L->g.V / 2 + 63) / 64;
+    for (int l = 0; l < 3; ++l) {
+        PtcLayerArgs a;
+        Geom gt = L->g;
+        gt.V = 64 * nth * (l == 2 ? 1 : 2);
+        const int grid = ptc_launch_shape(0, kPtcChannels[l], kPtcChannels[l + 1], gt, nrhs, &a.rc);
+        a.x = x;
+        a.y = l == 2 ? out : P->act[l + 1];
+        a.U = L->Ueo[GRG_BF16];
+        a.A = P->A[l];
+        a.mask = l == 2 ? S->d_mask_eo : nullptr;
+        a.sel = 0;
+        a.g = L->g;
+        a.nrhs = nrhs;
+        a.Vhs = L->Vhs;
+        a.in_par = l == 0 ? S->eo_par : -1;
+        a.out_par = l == 2 ? S->eo_par : -1;
         GRG_TRY_HIP(launch_ptc_layer(kPtcChannels[l], kPtcChannels[l + 1], a, grid, L->stream));
         x = a.y;
     }
@@ -127,6 +161,18 @@ grg_status precond_apply_inner(grg_schur S, int prec, const void *r, void *p, in
     GRG_TRY(forward(P, in, P->act[3], nrhs));
     GRG_TRY_HIP(launch_axpy_convert(GRG_BF16, prec, sh, P->act[3], p, nullptr, 0, 0, nullptr,
                                     L->stream));
+    return GRG_OK;
+}
+
+// the same on the reduced parity's compact halves r and p (sh: their shape)
+grg_status precond_apply_half(grg_schur S, int prec, const BlasShape &sh, const void *r, void *p, int nrhs)
+{
+    grg_precond P = S->precond;
+    hipStream_t st = S->lat->stream;
+    if (prec == GRG_BF16) return forward_half(P, r, p, nrhs);
+    GRG_TRY_HIP(launch_axpy_convert(prec, GRG_BF16, sh, r, P->act[0], nullptr, 0, 0, nullptr, st));
+    GRG_TRY(forward_half(P, P->act[0], P->act[3], nrhs));
+    GRG_TRY_HIP(launch_axpy_convert(GRG_BF16, prec, sh, P->act[3], p, nullptr, 0, 0, nullptr, st));
     return GRG_OK;
 }
 
@@ -202,7 +248,6 @@ grg_status grg_precond_create(grg_schur S, grg_precond *out)
     if (!P) return set_error("out of host memory"), GRG_ENOMEM;
     P->schur = S;
     P->max_rhs = S->prm.max_rhs;
-    const Geom &g = S->lat->g;
     const int R = P->max_rhs;
     bool ok = true;
     auto al = [&](void **p, size_t bytes) {
@@ -220,11 +265,11 @@ grg_status grg_precond_create(grg_schur S, grg_precond *out)
         al((void **)&P->Aadj[l], sizeof(__bf16) * 16 * ptc_kp(kPtcChannels[l + 1]));
     }
     for (int k = 0; k < 4; ++k) {
-        al(&P->act[k], act_bytes(g, R, kPtcChannels[k]));
-        al(&P->dact[k], act_bytes(g, R, kPtcChannels[k]));
+        al(&P->act[k], act_bytes(S->lat, R, kPtcChannels[k]));
+        al(&P->dact[k], act_bytes(S->lat, R, kPtcChannels[k]));
     }
-    al(&P->ebuf, act_bytes(g, R, 4));
-    for (int k = 0; k < 3; ++k) al(&P->gen[k], act_bytes(g, R, 4));
+    al(&P->ebuf, act_bytes(S->lat, R, 4));
+    for (int k = 0; k < 3; ++k) al(&P->gen[k], act_bytes(S->lat, R, 4));
     al((void **)&P->wpart, sizeof(float) * (size_t)kPtcMaxGrid * 16 * ptc_np(8));
     al((void **)&P->lpart, sizeof(double) * 1024 * kMaxRhs * 2);
     al((void **)&P->lsums, sizeof(double) * kMaxRhs * 2);
@@ -242,11 +287,11 @@ grg_status grg_precond_create(grg_schur S, grg_precond *out)
     // zero everything (activations pad tiles beyond V), identity weights
     hipStream_t st = S->lat->stream;
     for (int k = 0; k < 4; ++k) {
-        GRG_TRY_HIP(launch_fill_zero(P->act[k], act_bytes(g, R, kPtcChannels[k]), st));
-        GRG_TRY_HIP(launch_fill_zero(P->dact[k], act_bytes(g, R, kPtcChannels[k]), st));
+        GRG_TRY_HIP(launch_fill_zero(P->act[k], act_bytes(S->lat, R, kPtcChannels[k]), st));
+        GRG_TRY_HIP(launch_fill_zero(P->dact[k], act_bytes(S->lat, R, kPtcChannels[k]), st));
     }
-    GRG_TRY_HIP(launch_fill_zero(P->ebuf, act_bytes(g, R, 4), st));
-    for (int k = 0; k < 3; ++k) GRG_TRY_HIP(launch_fill_zero(P->gen[k], act_bytes(g, R, 4), st));
+    GRG_TRY_HIP(launch_fill_zero(P->ebuf, act_bytes(S->lat, R, 4), st));
+    for (int k = 0; k < 3; ++k) GRG_TRY_HIP(launch_fill_zero(P->gen[k], act_bytes(S->lat, R, 4), st));
     GRG_TRY_HIP(launch_fill_zero(P->adam_m, sizeof(double) * 2 * kPtcWeights, st));
     GRG_TRY_HIP(launch_fill_zero(P->adam_v, sizeof(double) * 2 * kPtcWeights, st));
     std::vector<double> w(2 * kPtcWeights, 0.0);
@@ -367,7 +412,7 @@ grg_status grg_precond_train(grg_precond P, const grg_train_params *tp, grg_trai
         } else {
             GRG_TRY_HIP(launch_random_field(GRG_BF16, P->ebuf, S->d_mask, L->g, B, rng(), st));
             GRG_TRY(run_dslash(S, GRG_BF16, P->ebuf, r, 0, B, nullptr));
-            GRG_TRY_HIP(launch_fill_zero(x, act_bytes(L->g, B, 4), st));
+            GRG_TRY_HIP(launch_fill_zero(x, act_bytes(L, B, 4), st));
             for (int j = 0; j < k; ++j) {
                 GRG_TRY(run_dslash(S, GRG_BF16, r, q, 0, B, S->partials));
                 GRG_TRY_HIP(launch_reduce(kAlpha, S->partials, agrid, B, S->alpha, nullptr, nullptr,

@@ -24,6 +24,11 @@ struct PtcLayerArgs {
     Geom g;
     int nrhs;
     int rc;  // right-hand sides per work item (ptc_launch_shape)
+    // Vhs > 0: the compact parity halves of a lattice with even extents (Vhs
+    // padded sites each, parity 0 first in x, y, U and mask).  in_par >= 0: the
+    // input is zero on the other parity and x is this half alone; out_par >= 0:
+    // the output is wanted on this parity only and y is this half alone.
+    int Vhs = 0, in_par = -1, out_par = -1;
 };
 
 struct PtcGradArgs {
@@ -42,7 +47,7 @@ constexpr int kPtcMaxGrid = 1024;
 // right-hand sides each work item takes: as many workgroups as the device
 // holds at once (at most kPtcMaxGrid, at most one per work item) and all
 // right-hand sides per tile unless the tiles alone give a workgroup fewer
-// than about four items.
+// than about four items.  (The halves: g.V the tiles' sites.)
 int ptc_launch_shape(int kind, int fin, int fout, const Geom &g, int nrhs, int *rc);
 hipError_t launch_ptc_layer(int fin, int fout, const PtcLayerArgs &a, int grid, hipStream_t st);
 hipError_t launch_ptc_wgrad(int fin, int fout, const PtcGradArgs &a, int grid, hipStream_t st);

@@ -163,6 +163,7 @@ grg_status run_dslash(grg_schur S, int prec, const void *in, void *out, int sel,
 
 grg_status ensure_inner(grg_schur S, int prec);
 grg_status precond_apply_inner(grg_schur S, int prec, const void *r, void *p, int nrhs);
+grg_status precond_apply_half(grg_schur S, int prec, const BlasShape &sh, const void *r, void *p, int nrhs);
 
 // Largest grid any stencil or BLAS launch may use (sizes the partial sums).
 constexpr int kMaxGrid = kMaxGridValue;
@@ -1083,7 +1084,6 @@ static grg_status inner_fgcr_eo(grg_schur S, int prec, int nrhs, const double *t
     const int P = S->eo_par, Q = 1 - P;
     void **f = S->eo_f[prec];
     void *r = f[0], *x = f[1], *q = f[2], *w = f[3], *pv = f[4];
-    void *full_in = S->in_b[prec], *full_out = S->in_q[prec];
     const void *b = S->in_r[prec];
     const double d = 4.0 + S->m0;
     const int check = std::max(1, S->prm.check_every);
@@ -1113,9 +1113,7 @@ static grg_status inner_fgcr_eo(grg_schur S, int prec, int nrhs, const double *t
         // p = M^ r
         {
             PhaseTimer pt(S->prof, st, kProfPrec);
-            GRG_TRY_HIP(launch_eo_scatter(prec, g, nrhs, P, r, full_in, true, st));
-            GRG_TRY(precond_apply_inner(S, prec, full_in, full_out, nrhs));
-            GRG_TRY_HIP(launch_eo_scatter(prec, g, nrhs, P, full_out, pv, false, st));
+            GRG_TRY(precond_apply_half(S, prec, sh, r, pv, nrhs));
         }
         // q = A^ p with the sums <q, r>, |q|^2
         GRG_TRY(eo_hop(S, prec, t, pv, nullptr, w, Q, 0.0, 1.0, nrhs, nullptr, nullptr));

@@ -124,6 +124,75 @@ def test_loss_and_gradients_vs_oracle(setup):
     assert cos > 0.998
 
 
+@pytest.mark.parametrize("dims,inner,nrhs", [((4, 4, 4, 4), "bf16", 1), ((8, 4, 4, 6), "fp32", 3),
+                                             ((6, 8, 10, 4), "fp32", 4), ((8, 8, 8, 8), "fp64", 2)])
+def test_network_on_the_reduced_half(dims, inner, nrhs):
+    """The reduced solve applies the network on one parity's compact half.  Its
+    inner iterations against the same recursion (p = M r, one minimal-residual
+    step) run in FP64 with the whole network, whose input is zero on the other
+    parity: as many, to one (the rounding of r), and fewer than without the
+    network, so that a wrong neighbour would show."""
+    import torch
+
+    m0 = -0.2
+    lat = Lattice(dims, 0.5, 43)
+    grg = lat.grg
+    s = lat.schur(m0, "I", False, tol=1e-10, inner=inner, inner_tol=1e-3, max_rhs=nrhs, max_outer=1)
+    p = grg.grg_precond_create(s.h)
+    g, d = golden_gammas(), 4 + m0
+    ws = identity_weights()
+    ws[1] += ptc.random_weights(11, scale=0.01)[1]
+    for w in (ws[0], ws[2]):
+        for mu in range(4):
+            w[1 + 2 * mu, :4, :4] = 0.5 / d * (np.eye(4) - g[mu])
+            w[2 + 2 * mu, :4, :4] = 0.5 / d * (np.eye(4) + g[mu])
+    grg.grg_precond_set_weights(p, ptc.pack_weights(ws))
+    x, rmask = masked_field(lat, s, 12, nrhs)
+    c = np.unravel_index(np.arange(lat.V), dims[::-1])
+    parity = sum(c) & 1
+    red = 0 if rmask[parity == 0].sum() < rmask[parity == 1].sum() else 1
+    x[:, np.repeat(parity != red, 12)] = 0
+    b = to_dev(x)
+    keep = to_dev(np.repeat((parity == red).astype(float), 12)[None])
+
+    def steps(network):
+        r, n0 = b.clone(), torch.linalg.vector_norm(b, dim=1)
+        for k in range(1, 200):
+            z = torch.empty_like(r)
+            if network:
+                grg.grg_precond_apply(p, (r / n0[:, None]).contiguous(), z, nrhs)
+                z *= keep * n0[:, None]
+            else:
+                z.copy_(r)
+            q = torch.empty_like(r)
+            grg.grg_reduced_apply(s.h, "fp64", red, z, q, nrhs)
+            q *= keep
+            a = (q.conj() * r).sum(1) / (q.conj() * q).sum(1)
+            r = r - a[:, None] * q
+            if bool((torch.linalg.vector_norm(r, dim=1) <= 1e-3 * n0).all()):
+                return k
+        return 200
+
+    want, plain = steps(True), steps(False)
+    out = torch.empty_like(b)
+    if inner == "fp64":  # an FP64 inner solve goes to the tolerance itself
+        want = None
+    grg.grg_schur_attach_precond(s.h, p)
+    st = grg.grg_drr_solve(s.h, b, out, nrhs, allow_noconv=True)
+    grg.grg_schur_attach_precond(s.h, None)
+    st0 = grg.grg_drr_solve(s.h, b, out, nrhs, allow_noconv=True)
+    print(dims, inner, "network", want, st["iters"], "plain", plain, st0["iters"], flush=True)
+    assert st["fallbacks"] == 0
+    if want is not None:
+        assert abs(st["iters"] - want) <= 1
+        assert want < plain
+    else:
+        assert st["iters"] < st0["iters"]
+    grg.grg_precond_destroy(p)
+    s.close()
+    lat.close()
+
+
 @pytest.mark.parametrize("reduced", [False, True])
 def test_training_reduces_loss_and_iterations(reduced):
     """Pairs of D_rr itself, or of its even-odd reduced system (the inner

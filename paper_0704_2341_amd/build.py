@@ -19,7 +19,8 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgrg.so")
 SOURCES = ["kernels_dslash.hip", "kernels_blas.hip", "kernels_ptc.hip", "kernels_batch.hip", "kernels_eo.hip",
            "kernels_vcycle.hip", "kernels_coarse.hip", "kernels_approx.hip",
-           "kernels_split.hip", "kernels_small.hip", "solver.cpp", "api.cpp", "precond.cpp", "batch.cpp", "vcycle.cpp"]
+           "kernels_split.hip", "kernels_small.hip", "kernels_ring.hip",
+           "solver.cpp", "api.cpp", "precond.cpp", "batch.cpp", "vcycle.cpp"]
 ARCH = "gfx950"
 
 # Packed-FP32 instructions are disabled for every HIP translation unit.

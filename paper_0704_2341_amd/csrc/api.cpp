@@ -36,6 +36,7 @@ grg_status run_dslash(grg_schur S, int prec, const void *in, void *out, int sel,
 int partial_rows(const Geom &g, int nrhs);
 int dslash_grid(const Geom &g, int nrhs, int SB, int RG);
 DslashTune default_tune(const Geom &g, int prec, int nrhs);
+DslashTune canon_march_tune(const Geom &g, int prec, int nrhs);
 DslashTune default_lane_tune(const Geom &g, int prec, int nrhs);
 bool launch_ok(const Geom &g, int prec, int nrhs, const DslashTune &t, bool dots);
 grg_status block_apply_internal(grg_schur S, int prec, int rows, int cols, const double *in,
@@ -280,21 +281,24 @@ grg_status grg_permutation_block(const int32_t dims[4], int type, int inverse, i
 }
 
 namespace {
-// Whether D needs its input packed into internal tiles first: the smallest
-// fields are read in the canonical layout by the hop-per-wavefront form, one
-// launch for the whole call (its neighbours' reads forbid out to overlap in).
-bool dirac_staged(grg_lattice L, int precision, const double *in, const double *out, int nrhs)
+// How D runs on its canonical fields: the t-march, or a hop per wavefront on
+// fields too small for it, each one launch; both read neighbours while out is
+// written, so an out that overlaps in has its input packed into internal tiles.
+enum DiracForm { kDiracStaged, kDiracSplit, kDiracMarch };
+DiracForm dirac_form(grg_lattice L, int precision, const double *in, const double *out, int nrhs)
 {
     const size_t n = (size_t)nrhs * L->g.V * 24;
-    const bool overlap = in < out + n && out < in + n;
-    return overlap || default_tune(L->g, precision, nrhs).split != kSplitForm;
+    if (in < out + n && out < in + n) return kDiracStaged;
+    if (canon_march_tune(L->g, precision, nrhs).valid) return kDiracMarch;
+    return default_tune(L->g, precision, nrhs).split == kSplitForm ? kDiracSplit : kDiracStaged;
 }
 
-grg_status dirac_apply_launch(grg_lattice L, double m0, int precision, const double *in, double *out, int nrhs,
-                              void *stage)
+// stage: the packed input's tiles (kDiracStaged)
+grg_status dirac_apply_launch(grg_lattice L, double m0, int precision, DiracForm form, const double *in, double *out,
+                              int nrhs, void *stage)
 {
     DslashArgs a;
-    a.in = stage ? stage : (const void *)in;
+    a.in = form == kDiracStaged ? stage : (const void *)in;
     a.out = out;
     a.U = L->U[precision];
     a.mask = nullptr;
@@ -302,7 +306,9 @@ grg_status dirac_apply_launch(grg_lattice L, double m0, int precision, const dou
     a.diag = 4.0 + m0;
     a.g = L->g;
     a.nrhs = nrhs;
-    const DslashTune t = stage ? default_lane_tune(L->g, precision, nrhs) : default_tune(L->g, precision, nrhs);
+    const DslashTune t = form == kDiracStaged  ? default_lane_tune(L->g, precision, nrhs)
+                         : form == kDiracSplit ? default_tune(L->g, precision, nrhs)
+                                               : canon_march_tune(L->g, precision, nrhs);
     a.SB = t.SB;
     a.RG = t.RG;
     a.split = t.split;
@@ -311,11 +317,13 @@ grg_status dirac_apply_launch(grg_lattice L, double m0, int precision, const dou
     a.partials = nullptr;
     a.dot_with = nullptr;
     a.out_canon = 1;
-    if (stage) {
+    if (form == kDiracMarch) {
+        GRG_TRY_HIP(launch_canon_march(precision, a, t.grid, L->stream));
+    } else if (form == kDiracSplit) {
+        GRG_TRY_HIP(launch_dslash_split(precision, a, true, t.grid, L->stream));
+    } else {
         GRG_TRY_HIP(launch_pack_spinor(precision, in, stage, L->g, nrhs, L->stream));
         GRG_TRY_HIP(launch_dslash(precision, a, t.grid, L->stream));
-    } else {
-        GRG_TRY_HIP(launch_dslash_split(precision, a, true, t.grid, L->stream));
     }
     return GRG_OK;
 }
@@ -326,7 +334,8 @@ namespace grg {
 // enqueued on the lattice's stream (its device current), arguments checked
 grg_status dirac_apply_internal(grg_lattice L, double m0, int precision, const double *in, double *out, int nrhs)
 {
-    const bool staged = dirac_staged(L, precision, in, out, nrhs);
+    const DiracForm form = dirac_form(L, precision, in, out, nrhs);
+    const bool staged = form == kDiracStaged;
     const size_t bytes = spinor_elems(L->g, nrhs) * prec_bytes(precision);
     if (staged && bytes > L->tmp_bytes) {
         dfree(L->tmp_in);
@@ -334,7 +343,7 @@ grg_status dirac_apply_internal(grg_lattice L, double m0, int precision, const d
         GRG_TRY(dmalloc(&L->tmp_in, bytes, "dirac_apply scratch"));
         L->tmp_bytes = bytes;
     }
-    return dirac_apply_launch(L, m0, precision, in, out, nrhs, staged ? L->tmp_in : nullptr);
+    return dirac_apply_launch(L, m0, precision, form, in, out, nrhs, L->tmp_in);
 }
 }  // namespace grg
 }
@@ -401,8 +410,7 @@ grg_status grg_dirac_apply_noalloc(grg_lattice L, double m0, int precision, cons
     GRG_TRY(scratch_address(L->device, &base));
     // every entry the stencil reads (sites < V of every RHS) is written by the
     // pack first, so nothing left by an earlier call is read
-    GRG_TRY(dirac_apply_launch(L, m0, precision, in, out, nrhs,
-                               dirac_staged(L, precision, in, out, nrhs) ? base : nullptr));
+    GRG_TRY(dirac_apply_launch(L, m0, precision, dirac_form(L, precision, in, out, nrhs), in, out, nrhs, base));
     GRG_TRY_HIP(hipStreamSynchronize(L->stream));
     return GRG_OK;
 }

@@ -152,6 +152,10 @@ hipError_t launch_dc_update(int prec, const DcArgs &a, int grid, int SB, hipStre
 // item.  canonical (no sums): in and out are canonical complex128 fields that
 // do not overlap.
 hipError_t launch_dslash_split(int prec, const DslashArgs &a, bool canonical, int grid, hipStream_t st);
+// The t-march over canonical fields (kernels_ring.hip): every row, no sums, in and
+// out canonical complex128 fields that do not overlap; a.march slices per item,
+// grid (workgroups of one wavefront) a multiple of 8.
+hipError_t launch_canon_march(int prec, const DslashArgs &a, int grid, hipStream_t st);
 hipError_t launch_eo_split(int prec, const EoArgs &a, int grid, hipStream_t st);
 hipError_t launch_dc_split(int prec, const DcArgs &a, int grid, hipStream_t st);
 hipError_t launch_dslash_coarse(const CoarseArgs &a, hipStream_t st);

@@ -89,6 +89,40 @@ DslashTune default_tune(const Geom &g, int prec, int nrhs)
     return t;
 }
 
+// Launch of the t-march over canonical fields (valid: from 513 wavefronts' worth
+// of sites and RHS on; 8^4, 8 RHS, 512: FP64 22.1 us against 23.0 with a hop per
+// wavefront, FP32 21.6 / 21.0, BF16 22.2 / 20.4; 10^4, 4 RHS, 628: 24.5 / 27.9, 23.0 /
+// 24.6, 22.4 / 24.0).  The chip holds one of its wavefronts per SIMD in FP64
+// (registers and LDS), two in FP32 and BF16; an item is a tile of 64 sites and
+// one RHS over march slices, and its first slice costs about one more (two
+// spinors of the column before anything overlaps), so the slices are cut to the
+// fewest rounds x (slices + 1).  24^4, 12 RHS, FP64: 781 us with 8 slices, 800 with 6
+// and 809 with 12; 16^4 in FP32: 100 with 8, 115 with 4, 124 with 2.  In three
+// rounds and more of 1536 pairs of a tile and a RHS an XCD takes two tiles' RHS at
+// a time, so that all of them walk one region (32^4, 12 RHS, FP64: 2.09 ms against
+// 2.15); fewer are left contiguous (16^4: 130 us against 143).
+DslashTune canon_march_tune(const Geom &g, int prec, int nrhs)
+{
+    const long pairs = (long)((g.L[0] * g.L[1] * g.L[2] + 63) / 64) * nrhs;
+    const long res = prec == GRG_FP64 ? 1024 : 2048;
+    DslashTune t;
+    t.valid = field_waves(g, nrhs) > 512;
+    t.SB = 64;
+    t.RG = 1;
+    long best = 0;
+    for (int T = g.L[3]; T >= 1; --T) {
+        const long items = pairs * ((g.L[3] + T - 1) / T);
+        const long cost = (items + res - 1) / res * (T + 1);
+        if (best == 0 || cost < best) {
+            best = cost;
+            t.march = T;
+            t.grid = round8(std::min(items, res));
+            t.chunk = pairs >= 1536 && items >= 3 * res ? 2 * nrhs : 0;
+        }
+    }
+    return t;
+}
+
 static grg_status launch_tuned(grg_lattice L, int prec, const DslashTune &t, const void *in,
                                void *out, const uint8_t *mask, int sel, double m0, int nrhs,
                                double *partials, const void *dot_with = nullptr)

@@ -537,11 +537,12 @@ grg_status grg_schur_create(grg_lattice L, double m0, const int32_t *q, int32_t 
         set_error("hipHostMalloc failed");
         s = GRG_ENOMEM;
     }
-    if (s == GRG_OK && hipHostMalloc((void **)&S->h_buf, sizeof(double) * 12 * kMaxRhs) != hipSuccess) {
+    if (s == GRG_OK && hipHostMalloc((void **)&S->h_buf, sizeof(double) * 14 * kMaxRhs) != hipSuccess) {
         S->h_buf = nullptr;
         set_error("hipHostMalloc failed");
         s = GRG_ENOMEM;
     }
+    if (s == GRG_OK) memset(S->h_buf, 0, sizeof(double) * 14 * kMaxRhs);  // (no tag is 0)
     if (s != GRG_OK) {
         schur_free(S);
         delete S;

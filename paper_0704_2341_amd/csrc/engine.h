@@ -206,9 +206,18 @@ struct BlasShape {
 //  part (kNorm, kNorm3; optional): part[r] = thr2[r] finite (the RHS takes
 //  part in the solve; an infinite threshold marks one that does not).
 enum { kAlpha = 0, kNorm = 1, kNorm3 = 2 };
+// Where a reduction also leaves RHS r's |.|^2 for the host: pinned words 2r and
+// 2r + 1, each with tag above and half the value's bits below.  An 8-byte store is
+// whole, so a host that sees the tag in both words has the value without waiting
+// for the stream (27 us from enqueueing five short launches and a read to having
+// it, 20 so).
+struct HostNorms {
+    unsigned long long *words = nullptr;
+    unsigned tag = 0;
+};
 hipError_t launch_reduce(int mode, const double *partials, int nparts, int nrhs, double2 *alpha,
                          double *out2, const double *thr2, int *active, hipStream_t st,
-                         int *part = nullptr);
+                         int *part = nullptr, const HostNorms &host = HostNorms());
 
 // Scalars taken straight from per-workgroup partials by the vector kernels,
 // instead of by a reduction launch between: for as few rows as kFoldRows.  A
@@ -303,12 +312,14 @@ struct FoldBicg {
     int *active_out = nullptr;     // kBicgP
     const double *thr2 = nullptr;  // kBicgP
     double *rn2 = nullptr;         // kBicgP
+    HostNorms host;                // kBicgP: with rn2
 };
 hipError_t launch_bicg(int prec, int mode, const BlasShape &sh, void *x, void *r, const void *a,
                        const void *b, const void *c, const void *d, double2 *sc,
                        double *partials, hipStream_t st, const FoldBicg &fold = FoldBicg());
 hipError_t launch_bicg_reduce(int mode, const double *partials, int nparts, int nrhs, double2 *sc,
-                              double *out2, const double *thr2, int *active, hipStream_t st);
+                              double *out2, const double *thr2, int *active, hipStream_t st,
+                              const HostNorms &host = HostNorms());
 
 // V-cycle (kernels_vcycle.hip): blocked links of the next level, restriction
 // to / prolongation from the coarse sites (canonical fields), and linear

@@ -155,7 +155,9 @@ struct grg_schur_s {
     double *rn2 = nullptr, *thr2 = nullptr, *qn2 = nullptr, *bn2 = nullptr;
     int *active = nullptr;
     int *act0 = nullptr;      // RHS active when an inner solve started
-    double *h_buf = nullptr;  // pinned host staging (12 * kMaxRhs doubles: reads, uploads, flags)
+    double *h_buf = nullptr;  // pinned host staging (14 * kMaxRhs doubles: reads, uploads, flags,
+                              // and the words of HostNorms)
+    unsigned norm_tag = 0;    // the last reduction's HostNorms tag
     grg::ProfilePool prof;
     int n_dslash = 0;
     grg::DslashTune tune[3][grg::kMaxRhs + 1];    // per precision and nrhs

@@ -15,6 +15,14 @@
 
 namespace grg {
 
+__device__ __forceinline__ void host_norm(const HostNorms &h, int r, double v)
+{
+    if (h.words == nullptr) return;
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v), t = (unsigned long long)h.tag << 32;
+    __hip_atomic_store(h.words + 2 * r, t | (b & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(h.words + 2 * r + 1, t | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 constexpr int kBlasSB = 256;
 
 // items (site block, RHS rhs), RHS fastest
@@ -253,6 +261,7 @@ __global__ void __launch_bounds__(256) bicg_kernel(BlasShape sh, void *x_, void 
                     fold.rho_out[k] = rn;
                     fold.active_out[k] = sums[2] > fold.thr2[k] ? 1 : 0;
                     fold.rn2[k] = sums[2];
+                    host_norm(fold.host, k, sums[2]);
                 }
             }
         } else {
@@ -344,7 +353,7 @@ __global__ void __launch_bounds__(256) bicg_kernel(BlasShape sh, void *x_, void 
 // with the same active flags).
 __global__ void __launch_bounds__(1024) bicg_reduce_kernel(int mode, const double *partials, int nparts,
                                                           int nrhs, double2 *sc, double *out2,
-                                                          const double *thr2, int *active)
+                                                          const double *thr2, int *active, HostNorms host)
 {
     const int r = blockIdx.x;
     double sums[3] = {0, 0, 0};
@@ -356,6 +365,7 @@ __global__ void __launch_bounds__(1024) bicg_reduce_kernel(int mode, const doubl
     if (mode == kBicgInit) {
         rho[r] = make_double2(sums[0], 0.0);
         out2[r] = sums[0];
+        host_norm(host, r, sums[0]);
         if (active) active[r] = sums[0] > thr2[r] ? 1 : 0;
     } else if (mode == kBicgAlpha) {
         alpha[r] = bicg_alpha(rho[r], sums, on);
@@ -364,6 +374,7 @@ __global__ void __launch_bounds__(1024) bicg_reduce_kernel(int mode, const doubl
         beta[r] = bicg_beta(rn, rho[r], alpha[r], omega[r], on);
         rho[r] = rn;
         out2[r] = sums[2];
+        host_norm(host, r, sums[2]);
         if (active) active[r] = sums[2] > thr2[r] ? 1 : 0;
     }
 }
@@ -662,7 +673,7 @@ __global__ void __launch_bounds__(256) orthogonalise_kernel(BlasShape sh, const 
 // ------------------------------------------------------------------ reductions
 __global__ void __launch_bounds__(1024) reduce_kernel(int mode, const double *partials, int nparts,
                                                      int nrhs, double2 *alpha, double *out2,
-                                                     const double *thr2, int *active, int *part)
+                                                     const double *thr2, int *active, int *part, HostNorms host)
 {
     const int r = blockIdx.x;
     double sums[3] = {0, 0, 0};
@@ -675,6 +686,7 @@ __global__ void __launch_bounds__(1024) reduce_kernel(int mode, const double *pa
         } else {
             const double n2 = sums[mode == kNorm3 ? 2 : 0];
             out2[r] = n2;
+            host_norm(host, r, n2);
             if (active) active[r] = n2 > thr2[r] ? 1 : 0;
             if (part) part[r] = isinf(thr2[r]) ? 0 : 1;
         }
@@ -726,10 +738,11 @@ static bool shape_ok(const BlasShape &sh)
 }
 
 hipError_t launch_reduce(int mode, const double *partials, int nparts, int nrhs, double2 *alpha,
-                         double *out2, const double *thr2, int *active, hipStream_t st, int *part)
+                         double *out2, const double *thr2, int *active, hipStream_t st, int *part,
+                         const HostNorms &host)
 {
     hipLaunchKernelGGL(reduce_kernel, dim3(nrhs), dim3(reduce_threads(nparts)), 0, st, mode, partials, nparts, nrhs,
-                       alpha, out2, thr2, active, part);
+                       alpha, out2, thr2, active, part, host);
     return hipGetLastError();
 }
 
@@ -786,11 +799,11 @@ hipError_t launch_bicg(int prec, int mode, const BlasShape &sh, void *x, void *r
 }
 
 hipError_t launch_bicg_reduce(int mode, const double *partials, int nparts, int nrhs, double2 *sc,
-                              double *out2, const double *thr2, int *active, hipStream_t st)
+                              double *out2, const double *thr2, int *active, hipStream_t st, const HostNorms &host)
 {
     if (nrhs < 1 || nrhs > kMaxRhs || mode < kBicgInit || mode > kBicgBeta) return hipErrorInvalidValue;
     hipLaunchKernelGGL(bicg_reduce_kernel, dim3(nrhs), dim3(reduce_threads(nparts)), 0, st, mode, partials, nparts, nrhs, sc,
-                       out2, thr2, active);
+                       out2, thr2, active, host);
     return hipGetLastError();
 }
 

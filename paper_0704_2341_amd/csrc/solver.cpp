@@ -23,6 +23,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 
 #include "handles.h"
 
@@ -504,12 +505,38 @@ grg_status tune_dc(grg_schur S, int prec, int nrhs, int reps)
     return GRG_OK;
 }
 
+// for the reduction whose norms read_norms reads next
+static HostNorms host_norms(grg_schur S)
+{
+    HostNorms h;
+    h.words = (unsigned long long *)(S->h_buf + 12 * kMaxRhs);
+    if (++S->norm_tag == 0) S->norm_tag = 1;
+    h.tag = S->norm_tag;
+    return h;
+}
+
+// The norms of the last reduction that was given host_norms.  What the host has
+// enqueued before that reduction is done when they are here, as after a wait for
+// the stream; after 2 ms the stream is waited for (which also reports an error).
 static grg_status read_norms(grg_schur S, int nrhs, double *host)
 {
-    GRG_TRY_HIP(hipMemcpyAsync(S->h_buf, S->rn2, sizeof(double) * nrhs, hipMemcpyDeviceToHost,
-                               S->lat->stream));
-    GRG_TRY_HIP(hipStreamSynchronize(S->lat->stream));
-    memcpy(host, S->h_buf, sizeof(double) * nrhs);
+    const volatile unsigned long long *w = (const unsigned long long *)(S->h_buf + 12 * kMaxRhs);
+    const auto t0 = std::chrono::steady_clock::now();
+    bool waited = false;
+    for (int r = 0; r < nrhs; ++r)
+        for (unsigned n = 1;; ++n) {
+            const unsigned long long lo = w[2 * r], hi = w[2 * r + 1];
+            if ((unsigned)(lo >> 32) == S->norm_tag && (unsigned)(hi >> 32) == S->norm_tag) {
+                const unsigned long long b = (lo & 0xffffffffull) | (hi << 32);
+                memcpy(&host[r], &b, sizeof b);
+                break;
+            }
+            if (waited) return set_error("a reduction's result did not reach the host"), GRG_EHIP;
+            if (n % 256 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) {
+                GRG_TRY_HIP(hipStreamSynchronize(S->lat->stream));
+                waited = true;
+            }
+        }
     return GRG_OK;
 }
 
@@ -569,7 +596,7 @@ static grg_status inner_gcr(grg_schur S, int prec, int nrhs, const double *thr, 
     GRG_TRY_HIP(launch_fill_zero(x, vbytes, st));
     GRG_TRY_HIP(launch_norm2(prec, sh, r, S->partials, st));
     GRG_TRY_HIP(launch_reduce(kNorm, S->partials, sh.grid, nrhs, nullptr, S->rn2, S->thr2,
-                              S->active, st));
+                              S->active, st, nullptr, host_norms(S)));
     double h[kMaxRhs];
     GRG_TRY(read_norms(S, nrhs, h));
     auto all_done = [&](const double *n2) {
@@ -620,7 +647,7 @@ static grg_status inner_gcr(grg_schur S, int prec, int nrhs, const double *thr, 
         {
             PhaseTimer pt(S->prof, st, kProfBlas);
             GRG_TRY_HIP(launch_reduce(kNorm, S->partials, sh.grid, nrhs, nullptr, S->rn2, S->thr2,
-                                      S->active, st));
+                                      S->active, st, nullptr, host_norms(S)));
         }
         ++it;
         if (it % check == 0 || it == maxit) {
@@ -1026,7 +1053,7 @@ static grg_status inner_mr_eo(grg_schur S, int prec, int nrhs, const double *thr
     // reduced right-hand side already meets its threshold takes no step,
     // x_P = 0, but its correction z_Q = b_Q / d is not zero.
     GRG_TRY_HIP(launch_reduce(kNorm3, S->partials, pgrid, nrhs, nullptr, S->rn2, S->thr2, S->active, st,
-                              S->act0));
+                              S->act0, host_norms(S)));
     double h[kMaxRhs];
     auto all_done = [&](const double *n2) {
         for (int k = 0; k < nrhs; ++k) {
@@ -1073,7 +1100,8 @@ static grg_status inner_mr_eo(grg_schur S, int prec, int nrhs, const double *thr
             // x starts at zero: the first step writes x = alpha r without reading it
             GRG_TRY_HIP(launch_mr_update(prec, sh, x, r, q, nullptr, S->alpha, norms, st, it == 0, f));
             if (!fold || read)
-                GRG_TRY_HIP(launch_reduce(kNorm, norms, sh.grid, nrhs, nullptr, S->rn2, S->thr2, S->active, st));
+                GRG_TRY_HIP(launch_reduce(kNorm, norms, sh.grid, nrhs, nullptr, S->rn2, S->thr2, S->active, st, nullptr,
+                                          host_norms(S)));
         }
         ++it;
         if (read) {
@@ -1126,7 +1154,8 @@ static grg_status inner_fgcr_eo(grg_schur S, int prec, int nrhs, const double *t
     GRG_TRY(eo_hop(S, prec, t, b, b, r, P, 1.0, -1.0 / d, nrhs, S->partials, nullptr, nullptr, 1, 1, nullptr,
                    &pgrid));
     GRG_TRY_HIP(launch_fill_zero(x, vbytes, st));
-    GRG_TRY_HIP(launch_reduce(kNorm3, S->partials, pgrid, nrhs, nullptr, S->rn2, S->thr2, S->active, st));
+    GRG_TRY_HIP(launch_reduce(kNorm3, S->partials, pgrid, nrhs, nullptr, S->rn2, S->thr2, S->active, st, nullptr,
+                              host_norms(S)));
     double h[kMaxRhs];
     GRG_TRY(read_norms(S, nrhs, h));
     {
@@ -1158,7 +1187,7 @@ static grg_status inner_fgcr_eo(grg_schur S, int prec, int nrhs, const double *t
                                       S->active, st));
             GRG_TRY_HIP(launch_mr_update(prec, sh, x, r, q, pv, S->alpha, S->partials, st));
             GRG_TRY_HIP(launch_reduce(kNorm, S->partials, sh.grid, nrhs, nullptr, S->rn2, S->thr2,
-                                      S->active, st));
+                                      S->active, st, nullptr, host_norms(S)));
         }
         ++it;
         if (it % check == 0 || it == maxit) {
@@ -1243,7 +1272,7 @@ static grg_status inner_bicgstab(grg_schur S, int prec, int nrhs, const double *
     GRG_TRY_HIP(launch_fill_zero(x, vbytes, st));
     GRG_TRY_HIP(launch_norm2(prec, sh, r, S->partials, st));
     GRG_TRY_HIP(launch_bicg_reduce(kBicgInit, S->partials, sh.grid, nrhs, sc, S->rn2, S->thr2, S->active,
-                                   st));
+                                   st, host_norms(S)));
     GRG_TRY_HIP(launch_copy(prec, sh, r, r0, st));
     GRG_TRY_HIP(launch_copy(prec, sh, r, pv, st));
     double h[kMaxRhs];
@@ -1291,6 +1320,7 @@ static grg_status inner_bicgstab(grg_schur S, int prec, int nrhs, const double *
             f.active_out = act[1 - now];
             f.thr2 = S->thr2;
             f.rn2 = S->rn2;
+            f.host = host_norms(S);
             GRG_TRY_HIP(launch_bicg(prec, kBicgP, sh, nullptr, pv, r, v, nullptr, nullptr, sc, nullptr, st, f));
         } else {
             {
@@ -1305,7 +1335,7 @@ static grg_status inner_bicgstab(grg_schur S, int prec, int nrhs, const double *
                                       S->active, st));
             GRG_TRY_HIP(launch_bicg(prec, kBicgUpd, sh, x, r, pv, sv, tv, r0, sc, S->partials, st));
             GRG_TRY_HIP(launch_bicg_reduce(kBicgBeta, S->partials, sh.grid, nrhs, sc, S->rn2, S->thr2,
-                                           S->active, st));
+                                           S->active, st, host_norms(S)));
             GRG_TRY_HIP(launch_bicg(prec, kBicgP, sh, nullptr, pv, r, v, nullptr, nullptr, sc, nullptr, st));
         }
         ++it;
@@ -1454,11 +1484,9 @@ grg_status drr_solve_internal(grg_schur S, int nrhs, grg_solver_stats *stats, co
     // |b|^2: from the partial sums the producer of b left (bn2_parts > 0), or a pass over b
     if (bn2_parts <= 0) GRG_TRY_HIP(launch_norm2(GRG_FP64, sh, S->b64, S->partials, st));
     GRG_TRY_HIP(launch_reduce(kNorm, S->partials, bn2_parts > 0 ? bn2_parts : sh.grid, nrhs, nullptr, S->bn2,
-                              nullptr, nullptr, st));
+                              nullptr, nullptr, st, nullptr, host_norms(S)));
     double bn2[kMaxRhs], rn2[kMaxRhs], sc[kMaxRhs], scn[kMaxRhs], ih[kMaxRhs];
-    GRG_TRY_HIP(hipMemcpyAsync(S->h_buf, S->bn2, sizeof(double) * nrhs, hipMemcpyDeviceToHost, st));
-    GRG_TRY_HIP(hipStreamSynchronize(st));
-    memcpy(bn2, S->h_buf, sizeof(double) * nrhs);
+    GRG_TRY(read_norms(S, nrhs, bn2));
     memcpy(rn2, bn2, sizeof(double) * nrhs);
     for (int k = 0; k < nrhs; ++k) sc[k] = bn2[k] > 0 && isfinite(bn2[k]) ? 1.0 / sqrt(bn2[k]) : 1.0;
     // rhs_pair: the producer of b also wrote it unscaled (s = 1) into the
@@ -1552,7 +1580,7 @@ grg_status drr_solve_internal(grg_schur S, int nrhs, grg_solver_stats *stats, co
             GRG_TRY(run_dslash(S, GRG_FP64, S->x64, S->t64, 0, nrhs, nullptr));
             GRG_TRY_HIP(launch_sub_norm(sh, S->b64, S->t64, S->r64, S->partials, st));
             GRG_TRY_HIP(launch_reduce(kNorm, S->partials, sh.grid, nrhs, nullptr, S->rn2, nullptr,
-                                      nullptr, st));
+                                      nullptr, st, nullptr, host_norms(S)));
             GRG_TRY(read_norms(S, nrhs, rn2));
             for (int k = 0; k < nrhs; ++k)
                 if (best_n[k] == ncorr) best[k] = rn2[k];
@@ -1682,7 +1710,7 @@ grg_status drr_solve_internal(grg_schur S, int nrhs, grg_solver_stats *stats, co
             PhaseTimer pt(S->prof, st, kProfDc);
             GRG_TRY_HIP(launch_dc_update(prec, d, dct.grid, dct.SB, st));
             GRG_TRY_HIP(launch_reduce(kNorm, S->partials, dct.grid, nrhs, nullptr, S->rn2, nullptr,
-                                      nullptr, st));
+                                      nullptr, st, nullptr, host_norms(S)));
         }
         for (int k = 0; k < kMaxRhs; ++k) S->h_fk[npool * kMaxRhs + k] = k < nrhs ? f[k] : 0.0;
         ++npool;

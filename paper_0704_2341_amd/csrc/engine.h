@@ -196,6 +196,7 @@ struct BlasShape {
     Geom g;
     int nrhs;
     int grid;   // workgroups, multiple of 8
+    int half = 0;  // a compact parity half (hidx) instead of a full field (fidx)
 };
 
 // partials -> per-RHS reductions (fixed-order tree, deterministic)

@@ -11,6 +11,7 @@
 // point atomics anywhere, so every reduction is bitwise reproducible.
 #include "common.h"
 #include "engine.h"
+#include "eo_site.h"
 #include "reduce.h"
 
 namespace grg {
@@ -135,6 +136,20 @@ struct VecIO<GRG_FP64> {
 // X0: x is taken as zero (not read): the first update of a solve started
 // from x = 0.
 constexpr int kUnitVecs = 3;
+// the lane (first of N) whose elements 16-byte vector i of a (tile, RHS) holds: in
+// the FP32 halves two components of one lane lie together
+template <int P>
+__device__ __forceinline__ int unit_lane(const BlasShape &sh, int i)
+{
+    if (P == GRG_FP32 && sh.half) return i & 63;
+    return (i * VecIO<P>::N) & 63;
+}
+// element (s, r, c) of a field of the shape
+template <class S>
+__device__ __forceinline__ size_t bidx(const BlasShape &sh, int s, int r, int c)
+{
+    return sh.half ? hidx<S>(s, r, c, sh.nrhs) : fidx(s, r, c, sh.nrhs);
+}
 // FOLD: alpha from the stencil's partials (see FoldMr).
 template <int P, bool HAS_P, bool X0 = false, bool FOLD = false>
 __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, void *r_,
@@ -178,7 +193,7 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
         // (a unit starts at a whole component, so its lanes' sites do not depend on it)
 #pragma unroll
         for (int v = 0; v < kUnitVecs; ++v) {
-            const int site = tile * 64 + (((v * 64 + lane) * N) & 63);
+            const int site = tile * 64 + unit_lane<P>(sh, v * 64 + lane);
             if (site < sh.g.V) {
                 const size_t i = base + v * 64 + lane;
                 const uint4 xv = X0 ? make_uint4(0, 0, 0, 0) : x[i], rv = r[i], qv = q[i];
@@ -274,7 +289,7 @@ __global__ void __launch_bounds__(256) bicg_kernel(BlasShape sh, void *x_, void 
         R sre = 0, sim = 0, srr = 0;
 #pragma unroll
         for (int v = 0; v < kUnitVecs; ++v) {
-            const int site = tile * 64 + (((v * 64 + lane) * N) & 63);
+            const int site = tile * 64 + unit_lane<P>(sh, v * 64 + lane);
             if (site >= sh.g.V) continue;
             const size_t i = base + v * 64 + lane;
             cpx<R> ac[N], bc[N];
@@ -393,7 +408,7 @@ __global__ void __launch_bounds__(256) norm2_kernel(BlasShape sh, const void *v_
     if (valid) {
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-            const cpx<R> a = ldc(v, fidx(s, k, c, sh.nrhs));
+            const cpx<R> a = ldc(v, bidx<S>(sh, s, k, c));
             t += (double)a.re * a.re + (double)a.im * a.im;
         }
     }
@@ -460,15 +475,15 @@ __global__ void __launch_bounds__(256) axpy_convert_kernel(BlasShape sh, const v
         const RO fo = (RO)f;
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-            const size_t i = fidx(s, k, c, sh.nrhs);
-            const cpx<RI> a = ldc(x, i);
+            const size_t i = bidx<SO>(sh, s, k, c);
+            const cpx<RI> a = ldc(x, bidx<SI>(sh, s, k, c));
             cpx<RO> o = {fo * (RO)a.re, fo * (RO)a.im};
             if (beta) {
                 const cpx<RO> yo = ldc(y, i);
                 o.re += yo.re;
                 o.im += yo.im;
             }
-            stc(y, y_half ? ybase + fidx(s >> 1, k, c, sh.nrhs) : i, o);
+            stc(y, y_half ? ybase + hidx<SO>(s >> 1, k, c, sh.nrhs) : i, o);
         }
     }
     SITE_LOOP_END
@@ -560,7 +575,7 @@ __global__ void __launch_bounds__(256) copy_kernel(BlasShape sh, const void *x_,
     if (valid) {
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-            const size_t i = fidx(s, k, c, sh.nrhs);
+            const size_t i = bidx<S>(sh, s, k, c);
             y[i] = x[i];
         }
     }

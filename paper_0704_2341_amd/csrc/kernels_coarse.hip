@@ -10,6 +10,7 @@
 
 #include "common.h"
 #include "engine.h"
+#include "eo_site.h"
 #include "split.h"
 #include "stencil.h"
 
@@ -91,10 +92,10 @@ __global__ void __launch_bounds__(256) rb_apply_kernel(Geom g, const double2 *__
                 typedef typename Store<PP>::S SP;
                 typedef typename Store<PP>::R RP;
                 const SiteGeo q = site_geo(s, g);
-                const size_t base =
-                    (((q.c[0] + q.c[1] + q.c[2] + q.c[3]) & 1) == first ? 0 : half) + fidx(s >> 1, r, 0, nrhs);
+                SP *o = (SP *)pair + (((q.c[0] + q.c[1] + q.c[2] + q.c[3]) & 1) == first ? 0 : half);
 #pragma unroll
-                for (int c = 0; c < 12; ++c) stc((SP *)pair, base + 64 * c, cpx<RP>{(RP)acc[c].re, (RP)acc[c].im});
+                for (int c = 0; c < 12; ++c)
+                    stc(o, hidx<SP>(s >> 1, r, c, nrhs), cpx<RP>{(RP)acc[c].re, (RP)acc[c].im});
             }
         }
         n2 = wave_sum(n2);  // every lane of the wavefront takes part

@@ -208,7 +208,7 @@ struct DcEpi {
                 const double2 rv = dc_load_r(a, r_in, i);
                 const double2 d = make_double2(rv.x - f * acc[c].re, rv.y - f * acc[c].im);
                 dc_store_r(a, r_out, i, d);
-                if (r_next) stc(r_next, nx.at(i, r, c, a.nrhs), cpx<RN>{(RN)(sn * d.x), (RN)(sn * d.y)});
+                if (r_next) stc(r_next, nx.at(r_next, i, r, c, a.nrhs), cpx<RN>{(RN)(sn * d.x), (RN)(sn * d.y)});
                 nrm[0] += d.x * d.x + d.y * d.y;
                 if (x_out) {
                     const cpx<double> ev = ldr<double>(e, i);
@@ -218,7 +218,7 @@ struct DcEpi {
             } else {
                 dc_store_r(a, r_out, i, make_double2(0.0, 0.0));
                 if (x_out) x_out[i] = make_double2(0.0, 0.0);
-                if (r_next) stc(r_next, nx.at(i, r, c, a.nrhs), cpx<RN>{0, 0});
+                if (r_next) stc(r_next, nx.at(r_next, i, r, c, a.nrhs), cpx<RN>{0, 0});
             }
         }
     }
@@ -623,7 +623,7 @@ __global__ void __launch_bounds__(256) dc_update_kernel(DcArgs a)
                 const double2 rv = dc_load_r(a, r_in, i);
                 const double2 d = make_double2(rv.x - f * acc[c].re, rv.y - f * acc[c].im);
                 dc_store_r(a, r_out, i, d);
-                if (r_next) stc(r_next, nx.at(i, r, c, a.nrhs), cpx<R>{(R)(sn * d.x), (R)(sn * d.y)});
+                if (r_next) stc(r_next, nx.at(r_next, i, r, c, a.nrhs), cpx<R>{(R)(sn * d.x), (R)(sn * d.y)});
                 nrm += d.x * d.x + d.y * d.y;
                 if (x_out) {
                     const cpx<double> ev = ldr<double>(e, i);
@@ -638,7 +638,7 @@ __global__ void __launch_bounds__(256) dc_update_kernel(DcArgs a)
                 const size_t i = fidx(s, r, c, a.nrhs);
                 dc_store_r(a, r_out, i, make_double2(0.0, 0.0));
                 if (x_out) x_out[i] = make_double2(0.0, 0.0);
-                if (r_next) stc(r_next, nx.at(i, r, c, a.nrhs), cpx<R>{0, 0});
+                if (r_next) stc(r_next, nx.at(r_next, i, r, c, a.nrhs), cpx<R>{0, 0});
             }
         }
         nrm = wave_sum(nrm);

@@ -48,15 +48,26 @@ __device__ __forceinline__ void eo_load_hop(int k, typename OP::T (&p)[12], type
     nbr(s, mu, q, g, sp, sm);
     const int n = (k & 1) ? sm : sp;
     const int hn = n >> 1;
-    const int ni = in_full ? n : hn;
+    if constexpr (sizeof(S) == 8) {
+        typedef float R;
+        if (in_full) {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) p[c] = OP::load(in, fidx(ni, r, c, nrhs));
-    if (k & 1) {
-#pragma unroll
-        for (int e = 0; e < 9; ++e) u[e] = OP::load(Ui, lidx(hn, mu, e));
+            for (int c = 0; c < 12; ++c) p[c] = OP::load(in, fidx(n, r, c, nrhs));
+        } else {
+            load_half<S, R>(p, in, hn, r, nrhs);
+        }
+        load_half_link<S, R>(u, (k & 1) ? Ui : Uo, (k & 1) ? hn : h, mu);
     } else {
+        const int ni = in_full ? n : hn;
 #pragma unroll
-        for (int e = 0; e < 9; ++e) u[e] = OP::load(Uo, lidx(h, mu, e));
+        for (int c = 0; c < 12; ++c) p[c] = OP::load(in, fidx(ni, r, c, nrhs));
+        if (k & 1) {
+#pragma unroll
+            for (int e = 0; e < 9; ++e) u[e] = OP::load(Ui, lidx(hn, mu, e));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 9; ++e) u[e] = OP::load(Uo, lidx(h, mu, e));
+        }
     }
 }
 
@@ -497,7 +508,51 @@ __global__ void __launch_bounds__(256) eo_hop_kernel(EoArgs a)
             }
             R sre = 0, sim = 0, sqq = 0;
             const bool act = a.active == nullptr || a.active[r] != 0;
-            if (valid) {
+            if (valid && sizeof(S) == 8) {
+                // two components to 16 bytes (hidx): the fields' streams as they lie
+                cpx<R> o[12], v2[12];
+#pragma unroll
+                for (int c = 0; c < 12; ++c) o[c] = {0, 0};
+                if (on && act) {
+#pragma unroll
+                    for (int c = 0; c < 12; ++c) o[c] = {be * acc[c].re, be * acc[c].im};
+                    if (in2) {
+                        if (in2_full) {
+#pragma unroll
+                            for (int c = 0; c < 12; ++c) v2[c] = ldr<R>(in2, fidx(s, r, c, a.nrhs));
+                        } else {
+                            load_half_vals<S, R>(v2, in2, h, r, a.nrhs);
+                        }
+#pragma unroll
+                        for (int c = 0; c < 12; ++c) {
+                            o[c].re = fma(al, v2[c].re, o[c].re);
+                            o[c].im = fma(al, v2[c].im, o[c].im);
+                        }
+                    }
+                }
+                if (out_full) {
+                    cpx<R> pv[12];
+                    load_half_vals<S, R>(pv, (const S *)a.partner, h, r, a.nrhs);
+#pragma unroll
+                    for (int c = 0; c < 12; ++c) {
+                        stc(out, fidx(s, r, c, a.nrhs), o[c]);
+                        stc(out, fidx(s ^ 1, r, c, a.nrhs), pv[c]);
+                    }
+                } else {
+                    store_half<S, R>(out, o, h, r, a.nrhs);
+                }
+                if (dots && on) {
+                    cpx<R> v[12];
+                    if (a.dot_with) load_half_vals<S, R>(v, (const S *)a.dot_with, h, r, a.nrhs);
+#pragma unroll
+                    for (int c = 0; c < 12; ++c) {
+                        const cpx<R> w = a.dot_with ? v[c] : cpx<R>{0, 0};
+                        sre = fma(o[c].re, w.re, fma(o[c].im, w.im, sre));
+                        sim = fma(o[c].re, w.im, fma(-o[c].im, w.re, sim));
+                        sqq = fma(o[c].re, o[c].re, fma(o[c].im, o[c].im, sqq));
+                    }
+                }
+            } else if (valid) {
 #pragma unroll
                 for (int c = 0; c < 12; ++c) {
                     const size_t i = fidx(h, r, c, a.nrhs);
@@ -856,12 +911,12 @@ __global__ void __launch_bounds__(256) eo_scatter_kernel(Geom g, int nrhs, int p
                 const bool mine = site_parity(i, g) == par;
 #pragma unroll
                 for (int c = 0; c < 12; ++c)
-                    dst[fidx(i, r, c, nrhs)] = mine ? src[fidx(i >> 1, r, c, nrhs)] : S{};
+                    dst[fidx(i, r, c, nrhs)] = mine ? src[hidx<S>(i >> 1, r, c, nrhs)] : S{};
             } else {
                 SiteGeo q;
                 const int s = eo_site(i, par, g, q);
 #pragma unroll
-                for (int c = 0; c < 12; ++c) dst[fidx(i, r, c, nrhs)] = src[fidx(s, r, c, nrhs)];
+                for (int c = 0; c < 12; ++c) dst[hidx<S>(i, r, c, nrhs)] = src[fidx(s, r, c, nrhs)];
             }
         }
     }
@@ -876,7 +931,7 @@ __global__ void __launch_bounds__(256) eo_pack_links_kernel(Geom g, int Vhs, con
         const int h = s >> 1;
         for (int mu = 0; mu < 4; ++mu)
 #pragma unroll
-            for (int e = 0; e < 9; ++e) dst[lidx(h, mu, e)] = U[lidx(s, mu, e)];
+            for (int e = 0; e < 9; ++e) dst[hlidx<S>(h, mu, e)] = U[lidx(s, mu, e)];
     }
 }
 

@@ -217,15 +217,13 @@ __global__ void __launch_bounds__(kSplitThreads) eo_split_kernel(EoArgs a)
             const int n = (k & 1) ? sm : sp, hn = n >> 1;
             PT p[12], u[9];
             cpx<R> w[6];
+            if (a.in_full) {
 #pragma unroll
-            for (int c = 0; c < 12; ++c) p[c] = OP::load(in, fidx(a.in_full ? n : hn, r, c, a.nrhs));
-            if (k & 1) {
-#pragma unroll
-                for (int e = 0; e < 9; ++e) u[e] = OP::load(Ui, lidx(hn, k >> 1, e));
+                for (int c = 0; c < 12; ++c) p[c] = OP::load(in, fidx(n, r, c, a.nrhs));
             } else {
-#pragma unroll
-                for (int e = 0; e < 9; ++e) u[e] = OP::load(Uo, lidx(h, k >> 1, e));
+                load_half<S, R>(p, in, hn, r, a.nrhs);
             }
+            load_half_link<S, R>(u, (k & 1) ? Ui : Uo, (k & 1) ? hn : h, k >> 1);
             hop_w_k(k, w, p, u);
             hs.put(k, lane, w);
         }
@@ -244,7 +242,7 @@ __global__ void __launch_bounds__(kSplitThreads) eo_split_kernel(EoArgs a)
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const int c = c0 + 3 * j;
-                    const size_t i = fidx(h, r, c, a.nrhs);
+                    const size_t i = hidx<S>(h, r, c, a.nrhs);
                     cpx<R> o = {0, 0};
                     if (on && act) {
                         o = {be * acc[j].re, be * acc[j].im};
@@ -348,7 +346,7 @@ __global__ void __launch_bounds__(kSplitThreads) dc_split_kernel(DcArgs a)
                         nrm[0] += d.x * d.x + d.y * d.y;
                     }
                     dc_store_r(a, r_out, i, d);
-                    if (r_next) stc(r_next, nx.at(i, r, c, a.nrhs), cpx<RN>{(RN)(sn * d.x), (RN)(sn * d.y)});
+                    if (r_next) stc(r_next, nx.at(r_next, i, r, c, a.nrhs), cpx<RN>{(RN)(sn * d.x), (RN)(sn * d.y)});
                     if (x_out) {
                         const double2 xv = on && x_in ? x_in[i] : make_double2(0.0, 0.0);
                         x_out[i] = on ? make_double2(xv.x + f * ev[j].re, xv.y + f * ev[j].im)

@@ -674,17 +674,24 @@ static Geom half_geom(grg_lattice L)
     return gh;
 }
 
+static BlasShape half_shape(const Geom &gh, int nrhs)
+{
+    BlasShape sh = blas_shape(gh, nrhs);
+    sh.half = 1;
+    return sh;
+}
+
 // Default half-stencil: the plane form where it is valid with planes of at
 // least 256 columns (BF16, 32^4: 0.29 / 0.106 / 0.046 ms with 12 / 4 / 1 RHS
 // against 0.43 / 0.149 / 0.047 for the best other form; with 16^4's planes of
-// 128 columns it gains nothing).  Otherwise one RHS per item (FP32, 16^4, 8
-// RHS: 38 us against 48 with RG 3), workgroups of one wavefront until the
+// 128 columns it gains nothing).  Otherwise one RHS per item (FP32, 16^4, 8 RHS
+// and 8-byte loads: 38 us against 48 with RG 3; 27 with the halves' 16-byte loads), workgroups of one wavefront until the
 // field gives 4096 of them; BF16 double-buffers the hops until occupancy pays
 // more than a hop's latency (24^4, 4 RHS: 53 us double-buffered against 49; 12^4,
 // 1 RHS: 11.3 against 12.8).  The smallest fields take a hop per wavefront (8^4,
-// 1 RHS: FP64 9.0 us against 12.5, FP32 7.6 against 12.5, BF16 7.7 against 10.9)
+// 1 RHS: FP64 9.0 us against 12.5, FP32 8.3 against 10.7, BF16 7.7 against 10.9)
 // until the forms meet: FP64 at 512 wavefronts (13.8 / 16.0 us; 19.0 / 17.6 at
-// 648), FP32 at 2048 (21.7 / 22.8; 40 / 38 at 4096), BF16 at 1024 (11.9 / 12.4;
+// 648), FP32 there too (11.9 / 12.4; 14.8 / 13.2), BF16 at 1024 (11.9 / 12.4;
 // 17.3 / 16.8 at 1944).
 bool eo_launch_ok(const Geom &gh, int prec, int nrhs, const DslashTune &t);
 DslashTune default_eo_tune(const Geom &gh, int prec, int nrhs)
@@ -702,7 +709,7 @@ DslashTune default_eo_tune(const Geom &gh, int prec, int nrhs)
         t.march = 0;
     }
     const long waves = field_waves(gh, nrhs);
-    if (waves <= (prec == GRG_FP64 ? 512 : prec == GRG_FP32 ? 2048 : 1024)) {
+    if (waves <= (prec == GRG_BF16 ? 1024 : 512)) {
         t.SB = kSplitSites;
         t.split = kSplitForm;
         t.grid = dslash_grid(gh, nrhs, 64, 1);
@@ -1028,7 +1035,7 @@ static grg_status inner_mr_eo(grg_schur S, int prec, int nrhs, const double *thr
     const Geom &g = L->g;
     GRG_TRY(ensure_eo(S, prec));
     const Geom gh = half_geom(L);
-    const BlasShape sh = blas_shape(gh, nrhs);
+    const BlasShape sh = half_shape(gh, nrhs);
     const size_t vbytes = spinor_elems(gh, nrhs) * prec_bytes(prec);
     const DslashTune t = S->eotune[prec][nrhs].valid ? S->eotune[prec][nrhs]
                                                      : default_eo_tune(gh, prec, nrhs);
@@ -1139,7 +1146,7 @@ static grg_status inner_fgcr_eo(grg_schur S, int prec, int nrhs, const double *t
     const Geom &g = L->g;
     GRG_TRY(ensure_eo(S, prec));
     const Geom gh = half_geom(L);
-    const BlasShape sh = blas_shape(gh, nrhs);
+    const BlasShape sh = half_shape(gh, nrhs);
     const size_t vbytes = spinor_elems(gh, nrhs) * prec_bytes(prec);
     const DslashTune t = S->eotune[prec][nrhs].valid ? S->eotune[prec][nrhs]
                                                      : default_eo_tune(gh, prec, nrhs);
@@ -1255,7 +1262,7 @@ static grg_status inner_bicgstab(grg_schur S, int prec, int nrhs, const double *
         r = S->in_r[prec];
         x = xdst;
     }
-    const BlasShape sh = blas_shape(gv, nrhs);
+    const BlasShape sh = reduce ? half_shape(gv, nrhs) : blas_shape(gv, nrhs);
     const size_t vbytes = spinor_elems(gv, nrhs) * prec_bytes(prec);
     const int check = std::max(1, S->prm.check_every);
     double2 *sc = S->bicg_sc;
@@ -1370,7 +1377,7 @@ grg_status eo_training_pair(grg_schur S, void *e, void *r_full, int nrhs, int k,
     const int prec = GRG_BF16;
     GRG_TRY(ensure_eo(S, prec));
     const Geom gh = half_geom(L);
-    const BlasShape sh = blas_shape(gh, nrhs);
+    const BlasShape sh = half_shape(gh, nrhs);
     const DslashTune t = S->eotune[prec][nrhs].valid ? S->eotune[prec][nrhs]
                                                      : default_eo_tune(gh, prec, nrhs);
     const int P = S->eo_par, Q = 1 - P;

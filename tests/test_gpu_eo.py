@@ -300,3 +300,23 @@ def test_march_full_layout_steps(method, kind, inv, launch):
     s1.close()
     s0.close()
     lat.close()
+
+
+@pytest.mark.parametrize("method,dims", [(0, (6, 6, 6, 6)), (1, (6, 6, 6, 6)), (0, (12, 12, 10, 6)), (1, (12, 12, 10, 6))])
+def test_fp32_halves_ragged_tiles(method, dims):
+    """FP32 halves (two components of a lane together) whose last tile is ragged,
+    below and above the size at which the half-steps change form, with 4, 1 and
+    3 RHS in turn on one handle, so that what one call leaves beyond the sites of
+    the next must not count; both inner methods, each to the FP64 tolerance
+    1e-11, so the solutions are within 1e-9 of the FP64 solve's."""
+    lat = Lattice(dims, 0.5, 91)
+    s = lat.schur(-0.2, "I", False, tol=1e-11, inner="fp32", inner_tol=1e-5, max_rhs=4, method=method)
+    ref = lat.schur(-0.2, "I", False, tol=1e-12, inner="fp64", max_rhs=4)
+    b = gaussian_vectors(12 * lat.V, 4, 92)
+    for n in (4, 1, 3):
+        got, st = s.drr_solve(b[:n])
+        want, _ = ref.drr_solve(b[:n])
+        assert st["converged"] and rel_err(got, want) < 1e-9, n
+    s.close()
+    ref.close()
+    lat.close()

@@ -152,44 +152,21 @@ __global__ void __launch_bounds__(256) boundary_source_kernel(Geom g, const doub
                                                               double diag, double inv_d, double2 *__restrict__ t,
                                                               double2 *__restrict__ p, int nrhs)
 {
+    __shared__ double2 lds[4][64 * kSpinorRow];
     const int nsb = (nbnd + 255) >> 8;
     const ItemRange it = xcd_items(nsb * nrhs);
     for (int w = it.begin; w < it.end; w += it.step) {
         const int sb = w / nrhs, r = w - sb * nrhs;
         const int j = sb * 256 + (int)threadIdx.x;
-        if (j >= nbnd) continue;
-        const int s = site[j];
+        const bool in = j < nbnd;
+        const int s = in ? site[j] : 0;
         const SiteGeo q = site_geo(s, g);
+        const double2 *x = xb + (size_t)r * nb * 12;
         cpx<double> acc[12];
 #pragma unroll
         for (int c = 0; c < 12; ++c) acc[c] = {0, 0};
-#pragma unroll 1
-        for (int k = 0; k < 8; ++k) {
-            const int mu = k >> 1;
-            int sp, sm;
-            nbr(s, mu, q, g, sp, sm);
-            const int kb = bidx[(k & 1) ? sm : sp];
-            if (kb < 0) continue;
-            cpx<double> v[12], u[9];
-            const double2 *x = xb + ((size_t)r * nb + kb) * 12;
-#pragma unroll
-            for (int c = 0; c < 12; ++c) v[c] = {x[c].x, x[c].y};
-#pragma unroll
-            for (int e = 0; e < 9; ++e) {
-                const double2 l = U[lidx((k & 1) ? sm : s, mu, e)];
-                u[e] = {l.x, l.y};
-            }
-            switch (k) {
-            case 0: hop_math<0, true>(acc, v, u); break;
-            case 1: hop_math<0, false>(acc, v, u); break;
-            case 2: hop_math<1, true>(acc, v, u); break;
-            case 3: hop_math<1, false>(acc, v, u); break;
-            case 4: hop_math<2, true>(acc, v, u); break;
-            case 5: hop_math<2, false>(acc, v, u); break;
-            case 6: hop_math<3, true>(acc, v, u); break;
-            default: hop_math<3, false>(acc, v, u); break;
-            }
-        }
+        coarse_hops(acc, x, bidx, U, s, in, q, g, lds[threadIdx.x >> 6]);
+        if (!in) continue;
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             const size_t i = fidx(j, r, c, nrhs);

@@ -85,7 +85,10 @@ __global__ void __launch_bounds__(256) rb_apply_kernel(Geom g, const double2 *__
             }
 #pragma unroll
             for (int c = 0; c < 12; ++c) {
-                out[fidx(s, r, c, nrhs)] = make_double2(acc[c].re, acc[c].im);
+                // (past the caches, which keep x_b: 32^4, 12 RHS, BF16 pair: 0.93 ms against
+                // 1.00; its writes, 3 GB, bound it)
+                typedef double v2d __attribute__((ext_vector_type(2)));
+                __builtin_nontemporal_store(v2d{acc[c].re, acc[c].im}, (v2d *)(out + fidx(s, r, c, nrhs)));
                 n2 += acc[c].re * acc[c].re + acc[c].im * acc[c].im;
             }
             if constexpr (PP >= 0) {

@@ -334,6 +334,81 @@ __device__ __forceinline__ void nbr(int s, int mu, const SiteGeo &q, const Geom 
     sm = x == 0 ? s + (L - 1) * st : s - st;
 }
 
+// The canonical spinors base[n][12] at the lanes' indices n, through the
+// wavefront's LDS (kSpinorRow elements per spinor, so that the lanes' reads meet
+// no bank twice): four lanes read 64 bytes, so a load touches 16 lines, where a
+// lane per spinor touches 64 and the L1 does not hold its lines until the last
+// of the twelve loads.  Every lane of the wavefront takes part.
+constexpr int kSpinorRow = 13;
+__device__ __forceinline__ void gather_spinors(cpx<double> (&p)[12], const double2 *__restrict__ base, int n,
+                                               double2 *lds)
+{
+    const int lane = threadIdx.x & 63, q4 = lane & 3, l4 = lane >> 2;
+    double2 v[12];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const double2 *x = base + (size_t)__shfl(n, l4 + 16 * i) * 12 + q4;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[3 * i + k] = x[4 * k];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) lds[(l4 + 16 * i) * kSpinorRow + q4 + 4 * k] = v[3 * i + k];
+    asm volatile("" ::: "memory");  // (same-wavefront LDS accesses keep their order)
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        const double2 w = lds[lane * kSpinorRow + c];
+        p[c] = {w.x, w.y};
+    }
+    asm volatile("" ::: "memory");
+}
+
+// acc += the hops of site s from its coarse neighbours, x their canonical spinors
+// by coarse index, for the lanes with `in`; lds as gather_spinors'.  Which
+// neighbours are coarse is asked for all eight together: one after the other
+// they are a chain of eight round trips (the boundary sites of 32^4, 12 RHS: 433 us
+// so, 427 with the spinors gathered, 361 with both).
+template <int K>
+__device__ __forceinline__ void coarse_hop(cpx<double> (&acc)[12], const double2 *__restrict__ x, int kb,
+                                           const double2 *__restrict__ U, int s, const SiteGeo &q, const Geom &g,
+                                           double2 *lds)
+{
+    if (!__any(kb >= 0)) return;
+    int sp, sm;
+    nbr(s, K >> 1, q, g, sp, sm);
+    cpx<double> p[12], u[9];
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+        const double2 l = U[lidx((K & 1) ? sm : s, K >> 1, e)];
+        u[e] = {l.x, l.y};
+    }
+    gather_spinors(p, x, max(kb, 0), lds);
+    if (kb >= 0) hop_math<(K >> 1), (K & 1) == 0>(acc, p, u);
+}
+__device__ __forceinline__ void coarse_hops(cpx<double> (&acc)[12], const double2 *__restrict__ x,
+                                            const int32_t *__restrict__ bidx, const double2 *__restrict__ U, int s,
+                                            bool in, const SiteGeo &q, const Geom &g, double2 *lds)
+{
+    int kn[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        int sp, sm;
+        nbr(s, k >> 1, q, g, sp, sm);
+        kn[k] = bidx[(k & 1) ? sm : sp];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) kn[k] = in ? kn[k] : -1;
+    coarse_hop<0>(acc, x, kn[0], U, s, q, g, lds);
+    coarse_hop<1>(acc, x, kn[1], U, s, q, g, lds);
+    coarse_hop<2>(acc, x, kn[2], U, s, q, g, lds);
+    coarse_hop<3>(acc, x, kn[3], U, s, q, g, lds);
+    coarse_hop<4>(acc, x, kn[4], U, s, q, g, lds);
+    coarse_hop<5>(acc, x, kn[5], U, s, q, g, lds);
+    coarse_hop<6>(acc, x, kn[6], U, s, q, g, lds);
+    coarse_hop<7>(acc, x, kn[7], U, s, q, g, lds);
+}
+
 // Operands of hop h (0..7 = +x, -x, +y, -y, +z, -z, +t, -t) of site s.
 template <class OP, class OU, class S, class SU>
 __device__ __forceinline__ void load_hop(int h, typename OP::T (&p)[12], typename OU::T (&u)[9],

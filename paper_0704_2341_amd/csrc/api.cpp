@@ -672,7 +672,7 @@ grg_status grg_drr_solve(grg_schur S, const double *rhs, double *x, int nrhs, gr
     S->n_dslash = 0;
     S->fallbacks = 0;
     grg_lattice L = S->lat;
-    GRG_TRY_HIP(launch_pack_masked(rhs, S->b64, S->d_mask, 0, L->g, nrhs, L->stream));
+    GRG_TRY_HIP(launch_pack_spinor(GRG_FP64, rhs, S->b64, L->g, nrhs, L->stream, S->d_mask, 0));
     grg_status st = drr_solve_internal(S, nrhs, stats);
     if (st == GRG_OK || st == GRG_ENOCONV)
         GRG_TRY_HIP(launch_unpack_spinor(GRG_FP64, S->x64, x, L->g, nrhs, L->stream));

@@ -185,8 +185,6 @@ hipError_t launch_pack_spinor(int prec, const double *src, void *dst, const Geom
                               hipStream_t st, const uint8_t *mask = nullptr, int keep = 0);
 hipError_t launch_unpack_spinor(int prec, const void *src, double *dst, const Geom &g, int nrhs,
                                 hipStream_t st);
-hipError_t launch_pack_masked(const double *src, void *dst, const uint8_t *mask, int keep,
-                              const Geom &g, int nrhs, hipStream_t st);
 hipError_t launch_scatter_coarse(const double *xb, void *dst, const int32_t *bidx, int nb,
                                  const Geom &g, int nrhs, hipStream_t st);
 

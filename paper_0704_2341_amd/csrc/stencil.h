@@ -364,6 +364,25 @@ __device__ __forceinline__ void gather_spinors(cpx<double> (&p)[12], const doubl
     asm volatile("" ::: "memory");
 }
 
+// The lanes' spinors p to the canonical base[lane][12], lanes below n, the same way
+__device__ __forceinline__ void scatter_spinors(const cpx<double> (&p)[12], double2 *__restrict__ base, int n,
+                                                double2 *lds)
+{
+    const int lane = threadIdx.x & 63, q4 = lane & 3, l4 = lane >> 2;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) lds[lane * kSpinorRow + c] = make_double2(p[c].re, p[c].im);
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int l = l4 + 16 * i;
+        if (l < n) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) base[(size_t)l * 12 + q4 + 4 * k] = lds[l * kSpinorRow + q4 + 4 * k];
+        }
+    }
+    asm volatile("" ::: "memory");
+}
+
 // acc += the hops of site s from its coarse neighbours, x their canonical spinors
 // by coarse index, for the lanes with `in`; lds as gather_spinors'.  Which
 // neighbours are coarse is asked for all eight together: one after the other

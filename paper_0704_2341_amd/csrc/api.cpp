@@ -516,7 +516,7 @@ grg_status grg_schur_create(grg_lattice L, double m0, const int32_t *q, int32_t 
     ALLOC(S->u64, f64);
     S->partials_elems = (size_t)partial_rows(g, prm.max_rhs) * prm.max_rhs * std::max(3, 2 * kMaxRhs);
     ALLOC(S->partials, S->partials_elems * sizeof(double));
-    ALLOC(S->alpha, sizeof(double2) * kMaxRhs);
+    ALLOC(S->alpha, sizeof(double2) * 2 * kMaxRhs);  // a step's, and the one's before
     ALLOC(S->bicg_sc, sizeof(double2) * 5 * kMaxRhs);  // rho, alpha, omega, beta, and rho's other place
     ALLOC(S->beta, sizeof(double2) * kMaxRhs * kMaxRhs);
     ALLOC(S->rn2, sizeof(double) * kMaxRhs);

@@ -233,11 +233,21 @@ struct FoldMr {
     const double *thr2 = nullptr; // with nrm: a RHS at or below it takes no step
     const int *active = nullptr;
 };
+// One x update for two minimal-residual steps (p = r, alpha given): with r_out the
+// step leaves x alone and writes its new r there; the next one, given that
+// step's r and alpha as r_prev and alpha_prev, updates x with both.
+struct MrLazy {
+    void *r_out = nullptr;
+    const void *r_prev = nullptr;
+    const double2 *alpha_prev = nullptr;
+};
+enum MrX { kMrXAdd, kMrXZero, kMrXLater, kMrXPair, kMrXPairZero };
 // x += alpha r ; r -= alpha q ; partial |r|^2     (one MR/GCR step; x_zero:
 // x is taken as zero and not read, the first step from x = 0)
 hipError_t launch_mr_update(int prec, const BlasShape &sh, void *x, void *r, const void *q,
                             const void *p, const double2 *alpha, double *partials,
-                            hipStream_t st, bool x_zero = false, const FoldMr &fold = FoldMr());
+                            hipStream_t st, bool x_zero = false, const FoldMr &fold = FoldMr(),
+                            const MrLazy &lazy = MrLazy());
 // partial |v|^2
 hipError_t launch_norm2(int prec, const BlasShape &sh, const void *v, double *partials,
                         hipStream_t st);

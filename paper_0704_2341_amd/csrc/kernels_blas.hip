@@ -133,8 +133,14 @@ struct VecIO<GRG_FP64> {
 // four times the wavefronts.  Every load and store instruction of the wavefront
 // moves 1 KB of consecutive memory, and alpha and the norm of a unit belong to
 // one RHS.  Units are walked in tile order, XCD-aware.
-// X0: x is taken as zero (not read): the first update of a solve started
-// from x = 0.
+// XM says what becomes of x (enum MrX): added to; written without being read
+// (the first step from x = 0); left for the next step, r going to r_out; or
+// given that step and this one together, alpha_prev r_prev first.  The two
+// terms are rounded one after the other as two steps would, so x has the same
+// bits, and two steps move 9 vectors instead of 10 (8 instead of 9 from x = 0):
+// the kernel runs at the rate of a copy, so the bytes are what it costs (S_bb at
+// 32^4 x 12, BF16, 20 steps in pairs: 32.0 -> 31.3 ms; 16^4 x 8, FP32: 2149 ->
+// 2112 us).
 constexpr int kUnitVecs = 3;
 // the lane (first of N) whose elements 16-byte vector i of a (tile, RHS) holds: in
 // the FP32 halves two components of one lane lie together
@@ -151,11 +157,14 @@ __device__ __forceinline__ size_t bidx(const BlasShape &sh, int s, int r, int c)
     return sh.half ? hidx<S>(s, r, c, sh.nrhs) : fidx(s, r, c, sh.nrhs);
 }
 // FOLD: alpha from the stencil's partials (see FoldMr).
-template <int P, bool HAS_P, bool X0 = false, bool FOLD = false>
+template <int P, bool HAS_P, int XM = kMrXAdd, bool FOLD = false>
 __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, void *r_,
                                                         const void *q_, const void *p_,
-                                                        const double2 *alpha, double *partials, FoldMr fold)
+                                                        const double2 *alpha, double *partials, FoldMr fold,
+                                                        MrLazy lazy)
 {
+    constexpr bool SKIP = XM == kMrXLater, PAIR = XM == kMrXPair || XM == kMrXPairZero;
+    constexpr bool X0 = XM == kMrXZero || XM == kMrXPairZero;
     typedef VecIO<P> IO;
     typedef typename IO::R R;
     constexpr int N = IO::N;
@@ -164,8 +173,8 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
     __shared__ double red[4][kMaxRhs];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int i = lane; i < sh.nrhs; i += 64) red[wave][i] = 0.0;
-    uint4 *x = (uint4 *)x_, *r = (uint4 *)r_;
-    const uint4 *q = (const uint4 *)q_, *p = (const uint4 *)p_;
+    uint4 *x = (uint4 *)x_, *r = (uint4 *)r_, *ro_ = SKIP ? (uint4 *)lazy.r_out : r;
+    const uint4 *q = (const uint4 *)q_, *p = (const uint4 *)p_, *rp = (const uint4 *)lazy.r_prev;
     const int ntiles = (sh.g.V + 63) >> 6;
     const int nunits = ntiles * sh.nrhs * PARTS;
     const ItemRange it = xcd_items((nunits + 3) >> 2);
@@ -188,6 +197,8 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
             a2 = alpha[k];
         }
         const cpx<R> a = {(R)a2.x, (R)a2.y}, na = {-a.re, -a.im};
+        cpx<R> ap = {0, 0};
+        if constexpr (PAIR) ap = {(R)lazy.alpha_prev[k].x, (R)lazy.alpha_prev[k].y};
         const size_t base = (size_t)u * UV;
         R rr = 0;
         // (a unit starts at a whole component, so its lanes' sites do not depend on it)
@@ -196,20 +207,26 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
             const int site = tile * 64 + unit_lane<P>(sh, v * 64 + lane);
             if (site < sh.g.V) {
                 const size_t i = base + v * 64 + lane;
-                const uint4 xv = X0 ? make_uint4(0, 0, 0, 0) : x[i], rv = r[i], qv = q[i];
+                const uint4 xv = X0 || SKIP ? make_uint4(0, 0, 0, 0) : x[i], rv = r[i], qv = q[i];
                 cpx<R> xc[N], rc[N], qc[N], pc[N];
                 IO::get(xv, xc);
+                if constexpr (PAIR) {
+                    IO::get(rp[i], pc);
+#pragma unroll
+                    for (int e = 0; e < N; ++e) cmac(xc[e], ap, pc[e]);
+                    IO::get(IO::put(xc), xc);  // as the step before would have stored it
+                }
                 IO::get(rv, rc);
                 IO::get(qv, qc);
                 if (HAS_P) IO::get(p[i], pc);
 #pragma unroll
                 for (int e = 0; e < N; ++e) {
-                    cmac(xc[e], a, HAS_P ? pc[e] : rc[e]);
+                    if constexpr (!SKIP) cmac(xc[e], a, HAS_P ? pc[e] : rc[e]);
                     cmac(rc[e], na, qc[e]);
                 }
                 const uint4 ro = IO::put(rc);
-                x[i] = IO::put(xc);
-                r[i] = ro;
+                if constexpr (!SKIP) x[i] = IO::put(xc);
+                ro_[i] = ro;
                 IO::get(ro, rc);  // the norm of the values as stored
 #pragma unroll
                 for (int e = 0; e < N; ++e) rr = fma(rc[e].re, rc[e].re, fma(rc[e].im, rc[e].im, rr));
@@ -763,18 +780,24 @@ hipError_t launch_reduce(int mode, const double *partials, int nparts, int nrhs,
 
 hipError_t launch_mr_update(int prec, const BlasShape &sh, void *x, void *r, const void *q,
                             const void *p, const double2 *alpha, double *partials,
-                            hipStream_t st, bool x_zero, const FoldMr &fold)
+                            hipStream_t st, bool x_zero, const FoldMr &fold, const MrLazy &lazy)
 {
     if (!shape_ok(sh) || (p && fold.dot)) return hipErrorInvalidValue;
+    const bool later = lazy.r_out != nullptr, pair = lazy.r_prev != nullptr;
+    if ((later || pair) && (p || fold.dot || (later && pair) || (pair && !lazy.alpha_prev)))
+        return hipErrorInvalidValue;
     dim3 g(sh.grid), b(kBlasSB);
 #define MRK(PP, HP, X, F) \
-    hipLaunchKernelGGL((mr_update_kernel<PP, HP, X, F>), g, b, 0, st, sh, x, r, q, p, alpha, partials, fold)
+    hipLaunchKernelGGL((mr_update_kernel<PP, HP, X, F>), g, b, 0, st, sh, x, r, q, p, alpha, partials, fold, lazy)
 #define MRU(PP)                                     \
-    if (p) MRK(PP, true, false, false);             \
-    else if (fold.dot && x_zero) MRK(PP, false, true, true);   \
-    else if (fold.dot) MRK(PP, false, false, true); \
-    else if (x_zero) MRK(PP, false, true, false);   \
-    else MRK(PP, false, false, false);
+    if (p) MRK(PP, true, kMrXAdd, false);           \
+    else if (fold.dot && x_zero) MRK(PP, false, kMrXZero, true); \
+    else if (fold.dot) MRK(PP, false, kMrXAdd, true); \
+    else if (later) MRK(PP, false, kMrXLater, false); \
+    else if (pair && x_zero) MRK(PP, false, kMrXPairZero, false); \
+    else if (pair) MRK(PP, false, kMrXPair, false); \
+    else if (x_zero) MRK(PP, false, kMrXZero, false); \
+    else MRK(PP, false, kMrXAdd, false);
     switch (prec) {
     case GRG_FP64: MRU(GRG_FP64) break;
     case GRG_FP32: MRU(GRG_FP32) break;

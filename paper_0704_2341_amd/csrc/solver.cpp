@@ -1081,6 +1081,10 @@ static grg_status inner_mr_eo(grg_schur S, int prec, int nrhs, const double *thr
     // itself (the norms' rows alternate between two places), and the norms are
     // reduced where the host reads them
     const bool fold = t.grid <= kFoldRows && sh.grid <= kFoldRows;
+    // otherwise, a step that another is sure to follow leaves x to it
+    void *r_next = f[4];
+    const void *r_prev = nullptr;  // of the step that left x, with its alpha
+    bool x_zero = true;
     while (done == 0 && it < maxit) {
         // q = (d - H_PQ H_QP / d) r, with the sums for alpha
         GRG_TRY(eo_hop(S, prec, t, r, nullptr, w, Q, 0.0, 1.0, nrhs, nullptr, nullptr));
@@ -1089,7 +1093,9 @@ static grg_status inner_mr_eo(grg_schur S, int prec, int nrhs, const double *thr
         {
             PhaseTimer pt(S->prof, st, kProfBlas);
             double *norms = S->partials;
+            double2 *alpha = S->alpha + (it & 1) * kMaxRhs;
             FoldMr f;
+            MrLazy lazy;
             if (fold) {
                 norms = partial_rows_at(S, 1 + (it & 1));
                 f.dot = S->partials;
@@ -1101,11 +1107,24 @@ static grg_status inner_mr_eo(grg_schur S, int prec, int nrhs, const double *thr
                     f.thr2 = S->thr2;
                 }
             } else {
-                GRG_TRY_HIP(launch_reduce(kAlpha, S->partials, t.grid, nrhs, S->alpha, nullptr, nullptr,
+                GRG_TRY_HIP(launch_reduce(kAlpha, S->partials, t.grid, nrhs, alpha, nullptr, nullptr,
                                           S->active, st));
+                if (r_prev) {
+                    lazy.r_prev = r_prev;
+                    lazy.alpha_prev = S->alpha + ((it - 1) & 1) * kMaxRhs;
+                } else if (!read) {
+                    lazy.r_out = r_next;
+                }
             }
-            // x starts at zero: the first step writes x = alpha r without reading it
-            GRG_TRY_HIP(launch_mr_update(prec, sh, x, r, q, nullptr, S->alpha, norms, st, it == 0, f));
+            // x starts at zero: the first update writes it without reading it
+            GRG_TRY_HIP(launch_mr_update(prec, sh, x, r, q, nullptr, alpha, norms, st, x_zero, f, lazy));
+            r_prev = nullptr;
+            if (lazy.r_out) {
+                r_prev = r;
+                std::swap(r, r_next);
+            } else {
+                x_zero = false;
+            }
             if (!fold || read)
                 GRG_TRY_HIP(launch_reduce(kNorm, norms, sh.grid, nrhs, nullptr, S->rn2, S->thr2, S->active, st, nullptr,
                                           host_norms(S)));

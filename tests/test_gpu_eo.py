@@ -320,3 +320,28 @@ def test_fp32_halves_ragged_tiles(method, dims):
     s.close()
     ref.close()
     lat.close()
+
+
+@pytest.mark.parametrize("inner", ["fp64", "fp32", "bf16"])
+def test_two_steps_one_solution_update(inner):
+    """Minimal-residual steps between two looks at the norms update the solution
+    two at a time, with the bits of one at a time: a fixed number of steps (one to
+    six, so that the last is alone or second) with a look after every step, every
+    second and every fourth, on a field with a ragged last tile and more rows than
+    the scalars are folded for, one RHS zero (it takes no step)."""
+    dims, nrhs = (14, 10, 12, 10), 8
+    lat = Lattice(dims, 0.5, 33)
+    b = gaussian_vectors(12 * lat.V, nrhs, 34)
+    b[2] = 0
+    for steps in (1, 2, 3, 5, 6):
+        want = None
+        for check in (1, 2, 4):
+            s = lat.schur(-0.2, "I", False, tol=1e-12, inner=inner, inner_tol=1e-6, max_rhs=nrhs,
+                          max_iter=steps, check_every=check)
+            x, st = s.drr_solve(b, allow_noconv=True)
+            s.close()
+            assert st["iters"] == steps and np.any(x[0]) and not np.any(x[2]), (steps, check)
+            if want is None:
+                want = x
+            assert np.array_equal(x, want), (steps, check)
+    lat.close()

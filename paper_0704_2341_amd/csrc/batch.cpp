@@ -70,7 +70,8 @@ struct grg_batch_s {
     double *coef = nullptr;
     void *hx = nullptr, *hr = nullptr, *hq = nullptr, *hw = nullptr, *hbq = nullptr, *heq = nullptr;
     double *partials = nullptr;
-    double2 *alpha = nullptr;
+    double2 *alpha = nullptr;  // [2][nsys]: a step's and, of a pair's second, its own
+    int *pend = nullptr;       // systems that a pair's first step took
     double *thr2 = nullptr, *fr2 = nullptr, *rn2i = nullptr;
     // one block read back at once: FP64 |r|^2, |b|^2 per system, then the
     // counters [inner iterations, outer steps] and the inner flags
@@ -224,19 +225,32 @@ static grg_status ctl(grg_batch B, bool init)
 }
 
 // one inner minimal-residual iteration for the systems whose inner flag is
-// set (a no-op launch sequence once none is)
-static grg_status inner_step(grg_batch B, int prec)
+// set (a no-op launch sequence once none is); in the reduced solve, the first
+// of two that are enqueued together leaves x to the second (48 lattices, 4 RHS,
+// FP32: 21.9 -> 21.3 ms)
+enum StepX { kStepAlone, kStepFirst, kStepSecond };
+static grg_status inner_step(grg_batch B, int prec, StepX sx)
 {
     BatchBlasArgs a = B->eo ? blas_h(B) : blas(B);
     a.act = B->active;
     a.ctr = B->ctr;
     if (B->eo) {
         // q = (d - H_pq H_qp / d) r on the reduced parity, with <q, r>, |q|^2
-        GRG_TRY(eo_half(B, prec, B->hr, nullptr, B->hw, 1, kC0, kC1, false, B->active));
-        GRG_TRY(eo_half(B, prec, B->hw, B->hr, B->hq, 0, kCd, kCminv, true, B->active));
-        GRG_TRY_HIP(launch_batch_reduce(kAlpha, B->partials, egrid(B), B->nsys, B->alpha, nullptr, nullptr,
+        // (r in heq, free until the reconstruction, between the two steps of a pair)
+        void *r = sx == kStepSecond ? B->heq : B->hr;
+        double2 *alpha = B->alpha + (sx == kStepSecond ? B->nsys : 0);
+        GRG_TRY(eo_half(B, prec, r, nullptr, B->hw, 1, kC0, kC1, false, B->active));
+        GRG_TRY(eo_half(B, prec, B->hw, r, B->hq, 0, kCd, kCminv, true, B->active));
+        GRG_TRY_HIP(launch_batch_reduce(kAlpha, B->partials, egrid(B), B->nsys, alpha, nullptr, nullptr,
                                         B->active, nullptr, B->st));
-        GRG_TRY_HIP(launch_batch_mr_update(prec, a, B->hx, B->hr, B->hq, B->st));
+        a.alpha = alpha;
+        a.pend = B->pend;
+        if (sx == kStepFirst) a.r_later = B->heq;
+        if (sx == kStepSecond) {
+            a.r_prev = B->hr;
+            a.alpha_prev = B->alpha;
+        }
+        GRG_TRY_HIP(launch_batch_mr_update(prec, a, B->hx, r, B->hq, B->st));
         GRG_TRY_HIP(launch_batch_reduce(kNorm, B->partials, a.grid, B->nsys, nullptr, B->rn2i, B->thr2,
                                         B->active, B->active, B->st));
         return GRG_OK;
@@ -247,6 +261,13 @@ static grg_status inner_step(grg_batch B, int prec)
     GRG_TRY_HIP(launch_batch_mr_update(prec, a, B->in_x, B->in_r, B->in_q, B->st));
     GRG_TRY_HIP(launch_batch_reduce(kNorm, B->partials, a.grid, B->nsys, nullptr, B->rn2i, B->thr2, B->active,
                                     B->active, B->st));
+    return GRG_OK;
+}
+
+static grg_status inner_steps(grg_batch B, int prec, int n)
+{
+    for (int k = 0; k < n; ++k)
+        GRG_TRY(inner_step(B, prec, k & 1 ? kStepSecond : k + 1 < n ? kStepFirst : kStepAlone));
     return GRG_OK;
 }
 
@@ -282,14 +303,16 @@ static grg_status outer_step(grg_batch B, int prec, const void *r_src, const voi
         for (int k = 0; k < B->nsys; ++k) any = any || h_active(B)[k];
         const int c0 = h_ctr(B)[0];
         while (any && it < n_inner) {
-            for (int k = 0; k < chunk && it < n_inner; ++k, ++it) GRG_TRY(inner_step(B, prec));
+            const int n = std::min(chunk, n_inner - it);
+            GRG_TRY(inner_steps(B, prec, n));
+            it += n;
             GRG_TRY(read_back(B));
             any = false;
             for (int k = 0; k < B->nsys; ++k) any = any || h_active(B)[k];
         }
         if (taken) *taken = h_ctr(B)[0] - c0;
     } else {
-        for (int k = 0; k < n_inner; ++k) GRG_TRY(inner_step(B, prec));
+        GRG_TRY(inner_steps(B, prec, n_inner));
     }
     if (B->eo) {
         // the other parity of the correction, e_q = (b_q - H_qp e_p) / d, and
@@ -554,6 +577,7 @@ static void batch_free(grg_batch B)
     for (void *p : {B->hx, B->hr, B->hq, B->hw, B->hbq, B->heq}) f(p);
     f(B->partials);
     f(B->alpha);
+    f(B->pend);
     f(B->dsc);  // rn2, bn2, the counters and the inner flags
     f(B->thr2);
     f(B->fr2);
@@ -751,7 +775,8 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
         al(&B->Uh, (size_t)2 * 36 * Vh * prec_bytes(prm.inner));
     }
     al((void **)&B->partials, sizeof(double) * kBatchMaxGrid * B->nsys * 3);
-    al((void **)&B->alpha, sizeof(double2) * B->nsys);
+    al((void **)&B->alpha, sizeof(double2) * 2 * B->nsys);
+    al((void **)&B->pend, sizeof(int) * B->nsys);
     for (double **p : {&B->thr2, &B->fr2, &B->rn2i}) al((void **)p, sizeof(double) * B->nsys);
     al((void **)&B->oact, sizeof(int) * B->nsys);
     B->dsc_bytes = sizeof(double) * 2 * B->nsys + sizeof(int) * (4 + B->nsys);

@@ -38,6 +38,12 @@ struct BatchBlasArgs {
     double *partials;      // [grid][nlat * nrhs]
     const int *act;        // per-system flags as in BatchDslashArgs, or nullptr
     int *ctr;              // counter incremented once by a launch that ran (mr update), or nullptr
+    // One x update for two MR steps (see batch_mr_update_kernel): the first writes
+    // its new r to r_later and the systems it stepped to pend; the second has the
+    // first's r and alpha in r_prev and alpha_prev, and writes r there.
+    void *r_later = nullptr, *r_prev = nullptr;
+    const double2 *alpha_prev = nullptr;
+    int *pend = nullptr;
 };
 
 struct BatchDcArgs {

@@ -154,40 +154,78 @@ __global__ void __launch_bounds__(256) dslash_batch_kernel(BatchDslashArgs a)
     if (dots) part.flush(a.partials);
 }
 
-// x += alpha r ; r -= alpha q ; partial |r|^2  (per system)
-template <int P>
+// x += alpha r ; r -= alpha q ; partial |r|^2  (per system).  XM: x as that
+// says (kMrXAdd), left to the next step (kMrXLater), or given the step before
+// and this one together (kMrXPair); the two terms are rounded one after the
+// other as two steps would.  A system that converged in between still gets the
+// first term: pend holds the systems that the first step took, written also by
+// one that had none.
+template <int P, int XM>
 __global__ void __launch_bounds__(256) batch_mr_update_kernel(BatchBlasArgs a, void *x_, void *r_,
                                                               const void *q_)
 {
     typedef typename Store<P>::S S;
     typedef typename Store<P>::R R;
+    constexpr bool LATER = XM == kMrXLater, PAIR = XM == kMrXPair;
     extern __shared__ double smem[];
-    if (a.act && !any_set(a.act, a.bt.nlat * a.nrhs)) return;
-    if (a.ctr && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(a.ctr, 1);
+    const int nsys = a.bt.nlat * a.nrhs;
+    if (LATER && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < nsys; i += blockDim.x) a.pend[i] = a.act[i];
+    const bool any = a.act == nullptr || any_set(a.act, nsys);
+    if (!any && !(PAIR && any_set(a.pend, nsys))) return;
+    if (any && a.ctr && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(a.ctr, 1);
     SysPartial<1> part;
-    part.init(smem, a.bt.nlat * a.nrhs);
-    S *x = (S *)x_, *r = (S *)r_;
-    const S *q = (const S *)q_;
+    part.init(smem, nsys);
+    S *x = (S *)x_, *r = (S *)r_, *r_out = LATER ? (S *)a.r_later : PAIR ? (S *)a.r_prev : r;
+    const S *q = (const S *)q_, *r_prev = (const S *)a.r_prev;
     const ItemRange it = xcd_items(a.Vtot / 256);
     for (int w = it.begin; w < it.end; w += it.step) {
         const int s = w * 256 + threadIdx.x;
         const int l = a.bt.tile_lat[s >> 6];
         for (int k = 0; k < a.nrhs; ++k) {
             const int sys = l * a.nrhs + k;
-            if (a.act && !a.act[sys]) continue;  // converged: x and r stay
+            const bool on = !a.act || a.act[sys];
+            if (PAIR ? !a.pend[sys] : !on) continue;  // converged: x and r stay
+            if constexpr (PAIR) {
+                if (!on) {  // converged by the step before
+                    const double2 p2 = a.alpha_prev[sys];
+                    const cpx<R> ap = {(R)p2.x, (R)p2.y};
+#pragma unroll
+                    for (int c = 0; c < 12; ++c) {
+                        const size_t i = fidx(s, k, c, a.nrhs);
+                        cpx<R> xv = ldc(x, i);
+                        cmac(xv, ap, ldc(r_prev, i));
+                        stc(x, i, xv);
+                    }
+                    continue;
+                }
+            }
             const double2 a2 = a.alpha[sys];
             const cpx<R> al = {(R)a2.x, (R)a2.y}, na = {(R)-a2.x, (R)-a2.y};
+            cpx<R> ap = {0, 0};
+            if constexpr (PAIR) ap = {(R)a.alpha_prev[sys].x, (R)a.alpha_prev[sys].y};
             R rr = 0;
 #pragma unroll
             for (int c = 0; c < 12; ++c) {
                 const size_t i = fidx(s, k, c, a.nrhs);
-                cpx<R> xv = ldc(x, i), rv = ldc(r, i);
+                cpx<R> rv = ldc(r, i);
                 const cpx<R> qv = ldc(q, i);
-                cmac(xv, al, rv);
+                if constexpr (!LATER) {
+                    cpx<R> xv = ldc(x, i);
+                    if constexpr (PAIR) {
+                        cmac(xv, ap, ldc(r_prev, i));
+                        S t;
+                        stc(&t, 0, xv);  // as the step before would have stored it
+                        xv = ldc(&t, 0);
+                    }
+                    cmac(xv, al, rv);
+                    stc(x, i, xv);
+                }
                 cmac(rv, na, qv);
-                stc(x, i, xv);
-                stc(r, i, rv);
-                const cpx<R> rs = ldc(r, i);
+                S ro;
+                stc(&ro, 0, rv);
+                r_out[i] = ro;
+                const cpx<R> rs = ldc(&ro, 0);
                 rr = fma(rs.re, rs.re, fma(rs.im, rs.im, rr));
             }
             const double v[1] = {(double)rr};
@@ -775,7 +813,25 @@ hipError_t launch_dslash_batch(int prec, const BatchDslashArgs &a, int grid, int
 hipError_t launch_batch_mr_update(int prec, const BatchBlasArgs &a, void *x, void *r, const void *q,
                                   hipStream_t st)
 {
-    BDISP(prec, batch_mr_update_kernel, lds_sys(a.bt.nlat * a.nrhs, 1), a, x, r, q);
+    const size_t lds = lds_sys(a.bt.nlat * a.nrhs, 1);
+    const bool later = a.r_later != nullptr, pair = a.r_prev != nullptr;
+    if ((later || pair) && (later == pair || !a.act || !a.pend || (pair && !a.alpha_prev)))
+        return hipErrorInvalidValue;
+    switch (prec) {
+#define BMR(PP, XM) \
+    hipLaunchKernelGGL((batch_mr_update_kernel<PP, XM>), dim3(a.grid), dim3(256), lds, st, a, x, r, q)
+#define BMU(PP)                          \
+    if (later) BMR(PP, kMrXLater);       \
+    else if (pair) BMR(PP, kMrXPair);    \
+    else BMR(PP, kMrXAdd);               \
+    break;
+    case GRG_FP64: BMU(GRG_FP64)
+    case GRG_FP32: BMU(GRG_FP32)
+    case GRG_BF16: BMU(GRG_BF16)
+#undef BMU
+#undef BMR
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

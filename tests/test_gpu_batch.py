@@ -245,3 +245,37 @@ def test_bicgstab_is_rejected():
     p = grg.grg_solver_params_default(tol=1e-10, inner="fp32", inner_tol=1e-5, method="bicgstab")
     with pytest.raises(grg.GrgError):
         grg.grg_batch_create(ms, 2, p)
+
+
+@pytest.mark.parametrize("inner,inner_tol", [("fp32", 1e-5), ("bf16", 1e-2), ("fp64", 1e-6)])
+def test_two_steps_one_solution_update(inner, inner_tol):
+    """Inner steps that are enqueued together update the solution two at a time:
+    one step between two looks at the flags (each alone), two, three and five, and
+    the graph, give the same bits, since each system stops at its own threshold
+    whatever the look; masses, permutations and sizes apart, and a zero system, so
+    that systems stop after the first and after the second step of a pair."""
+    import torch
+    import paper_0704_2341_amd as grg
+
+    ensure_built()
+    descs = [dict(dims=(8, 8, 8, 8), m0=-0.3, seed=4101), dict(dims=(4, 4, 4, 4), m0=0.6, seed=4102),
+             dict(dims=(8, 8, 4, 8), m0=-0.1, seed=4103), dict(dims=(4, 8, 8, 4), m0=0.2, seed=4104)]
+    ms = members(descs, [(1, False), (2, True), (1, True), (2, False)])
+    nrhs = 3
+    want = None
+    for check, graph in ((1, False), (2, False), (3, False), (5, False), (2, True), (1, True)):
+        p = grg.grg_solver_params_default(tol=1e-11, inner=inner, inner_tol=inner_tol, check_every=check, eo=1)
+        b = grg.grg_batch_create(ms, nrhs, p)
+        x = batch_inputs(b, ms, nrhs, 51)
+        x[: 12 * ms[0]["n_coarse"]] = 0  # the first system
+        xd = to_dev(x)
+        yd = torch.empty_like(xd)
+        for _ in range(3 if graph else 1):  # the first apply of a graph runs eagerly
+            yd.zero_()
+            st = grg.grg_batch_apply(b, xd, yd, use_graph=graph)
+            assert st["converged"]
+        y = to_host(yd)
+        grg.grg_batch_destroy(b)
+        if want is None:
+            want = y
+        assert np.isfinite(y).all() and np.array_equal(y, want), (check, graph)

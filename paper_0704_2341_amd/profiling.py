@@ -32,7 +32,7 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = [os.path.join(PKG, "csrc", f)
-                  for f in ("kernels_dslash.hip", "kernels_eo.hip", "stencil.h", "common.h")]
+                  for f in ("kernels_dslash.hip", "kernels_eo.hip", "stencil.h", "eo_site.h", "common.h")]
 TRAFFIC_FILE = os.path.join(os.path.dirname(PKG), "profiles", "dslash_traffic.json")
 COPY_KERNEL = "neg_kernel"  # torch's negation: reads N bytes, writes N bytes
 
@@ -104,12 +104,18 @@ def _grid_size(r) -> int:
     return int(r["Grid_Size_X"]) * int(r["Grid_Size_Y"]) * int(r["Grid_Size_Z"])
 
 
+def _named(symbols, name):
+    """Whether a kernel's name is one of the symbols: a symbol's template
+    arguments may be the first of the kernel's (later ones at their defaults)."""
+    return any(x in name or (x.endswith(">") and x[:-1].rstrip() + ", " in name) for x in symbols)
+
+
 def _select(rows, launch, key_id="Dispatch_Id"):
     """The last `launches` dispatches of the dominant launch (its symbol may
     name several kernel instances joined by ' + ', launched alternately)."""
     syms = [x.strip() for x in launch["symbol"].split(" + ")]
     gs, n = int(launch["grid_size"]), int(launch["launches"])
-    hit = [r for r in rows if any(x in r["Kernel_Name"] for x in syms) and _grid_size(r) == gs]
+    hit = [r for r in rows if _named(syms, r["Kernel_Name"]) and _grid_size(r) == gs]
     hit.sort(key=lambda r: int(r[key_id]))
     if not hit:
         raise SystemExit(f"no dispatch of {launch['symbol']} with {gs} work-items")
@@ -247,7 +253,7 @@ def _window_avg(rows, launch, counter, after):
     syms = [x.strip() for x in launch["symbol"].split(" + ")]
     gs, n = int(launch["grid_size"]), int(launch["launches"])
     hit = sorted((r for r in rows if r["Counter_Name"] == counter and int(r["Dispatch_Id"]) > after
-                  and any(x in r["Kernel_Name"] for x in syms) and _grid_size(r) == gs),
+                  and _named(syms, r["Kernel_Name"]) and _grid_size(r) == gs),
                  key=lambda r: int(r["Dispatch_Id"]))[1:n + 1]
     if len(hit) < n:
         raise SystemExit(f"only {len(hit)} dispatches of {launch['symbol']} ({gs} work-items) after {after}")

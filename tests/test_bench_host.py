@@ -86,3 +86,19 @@ def test_traffic_lookup_by_shape_and_sources(tmp_path):
                                 "kernels": {key: {"hbm_bytes_per_launch": 1.5e9}}}))
     assert P.measured_traffic(key, str(path)) is None  # taken on other sources
     assert P.measured_traffic(key, str(tmp_path / "missing.json")) is None
+
+
+@pytest.mark.parametrize("symbol,name,same", [
+    ("dslash_kernel<0, 0>", "void grg::dslash_kernel<0, 0, false>(grg::DslashArgs)", True),
+    ("dslash_kernel<0, 1>", "void grg::dslash_kernel<0, 0, false>(grg::DslashArgs)", False),
+    ("dslash_kernel<0, 1>", "void grg::dslash_kernel<0, 10>(grg::DslashArgs)", False),
+    ("eo_plane_kernel<0, 2, 1>", "void grg::eo_plane_kernel<0, 2, 1>(grg::EoArgs)", True),
+    ("march_kernel<grg::StoreEpi<2> >", "void grg::march_kernel<grg::StoreEpi<2> >(grg::StoreEpi<2>::Args)", True),
+    ("march_kernel<grg::StoreEpi<2> >", "void grg::march_kernel<grg::DcEpi<2> >(grg::DcEpi<2>::Args)", False),
+])
+def test_profiler_names_match_symbols(symbol, name, same):
+    """A launch's symbol names the kernel whose further template arguments are
+    left out, and no other."""
+    from paper_0704_2341_amd import profiling as P
+
+    assert P._named([symbol], name) is same

@@ -234,6 +234,7 @@ static grg_status inner_step(grg_batch B, int prec, StepX sx)
     BatchBlasArgs a = B->eo ? blas_h(B) : blas(B);
     a.act = B->active;
     a.ctr = B->ctr;
+    a.grid = round8(std::min<long>((long)a.Vtot / 256 * B->nrhs, kBatchMaxGrid));
     if (B->eo) {
         // q = (d - H_pq H_qp / d) r on the reduced parity, with <q, r>, |q|^2
         // (r in heq, free until the reconstruction, between the two steps of a pair)

@@ -13,6 +13,7 @@
 #include "engine.h"
 #include "eo_site.h"
 #include "reduce.h"
+#include "vec16.h"
 
 namespace grg {
 
@@ -73,55 +74,6 @@ struct Partial {
 };
 
 // ------------------------------------------------------------------ MR / GCR step
-// 16-byte vectors of a field: 4 complex in BF16, 2 in FP32, 1 in FP64.
-template <int P>
-struct VecIO;
-template <>
-struct VecIO<GRG_BF16> {
-    static constexpr int N = 4;
-    typedef float R;
-    __device__ static void get(const uint4 &v, cpx<float> (&c)[N])
-    {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < N; ++e) c[e] = {__uint_as_float(w[e] << 16), __uint_as_float(w[e] & 0xffff0000u)};
-    }
-    __device__ static uint4 put(const cpx<float> (&c)[N])
-    {
-        return make_uint4(pack_bf16(c[0].re, c[0].im), pack_bf16(c[1].re, c[1].im),
-                          pack_bf16(c[2].re, c[2].im), pack_bf16(c[3].re, c[3].im));
-    }
-};
-template <>
-struct VecIO<GRG_FP32> {
-    static constexpr int N = 2;
-    typedef float R;
-    __device__ static void get(const uint4 &v, cpx<float> (&c)[N])
-    {
-        c[0] = {__uint_as_float(v.x), __uint_as_float(v.y)};
-        c[1] = {__uint_as_float(v.z), __uint_as_float(v.w)};
-    }
-    __device__ static uint4 put(const cpx<float> (&c)[N])
-    {
-        return make_uint4(__float_as_uint(c[0].re), __float_as_uint(c[0].im), __float_as_uint(c[1].re),
-                          __float_as_uint(c[1].im));
-    }
-};
-template <>
-struct VecIO<GRG_FP64> {
-    static constexpr int N = 1;
-    typedef double R;
-    __device__ static void get(const uint4 &v, cpx<double> (&c)[N])
-    {
-        c[0] = {__hiloint2double((int)v.y, (int)v.x), __hiloint2double((int)v.w, (int)v.z)};
-    }
-    __device__ static uint4 put(const cpx<double> (&c)[N])
-    {
-        const long long a = __double_as_longlong(c[0].re), b = __double_as_longlong(c[0].im);
-        return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
-    }
-};
-
 // x += alpha_k p, r -= alpha_k q, and the partial sums of |r|^2 (of the values
 // as stored) per RHS.  HAS_P = false: p is r itself (minimal residual).
 //
@@ -141,7 +93,6 @@ struct VecIO<GRG_FP64> {
 // the kernel runs at the rate of a copy, so the bytes are what it costs (S_bb at
 // 32^4 x 12, BF16, 20 steps in pairs: 32.0 -> 31.3 ms; 16^4 x 8, FP32: 2149 ->
 // 2112 us).
-constexpr int kUnitVecs = 3;
 // the lane (first of N) whose elements 16-byte vector i of a (tile, RHS) holds: in
 // the FP32 halves two components of one lane lie together
 template <int P>

@@ -166,7 +166,8 @@ __global__ void __launch_bounds__(256) dslash_batch_kernel(BatchDslashArgs a)
 // vectors per lane of one (tile, RHS), as mr_update_kernel does.  With a site
 // per lane, 8 bytes of each component and the RHS one after the other it ran at
 // 4.3 TB/s of the copy's 6.2 (48 lattices, 4 RHS, FP32, a single step: 0.277 ->
-// 0.236 ms, 5.0 TB/s; the whole apply 21.3 -> 21.1 ms).
+// 0.236 ms, 5.0 TB/s; the whole apply 21.3 -> 21.1 ms, and 20.5 with the streams
+// read past L2).
 template <int P, int XM>
 __global__ void __launch_bounds__(256) batch_mr_update_kernel(BatchBlasArgs a, void *x_, void *r_,
                                                               const void *q_)
@@ -217,22 +218,22 @@ __global__ void __launch_bounds__(256) batch_mr_update_kernel(BatchBlasArgs a, v
 #pragma unroll
         for (int v = 0; v < kUnitVecs; ++v) {
             const size_t i = base + v * 64;
-            const uint4 rv = r[i], qv = q[i];
+            const uint4 rv = stream_load(r + i), qv = stream_load(q + i);
             cpx<R> xc[N], rc[N], qc[N];
             IO::get(rv, rc);
             IO::get(qv, qc);
             if constexpr (!LATER) {
-                IO::get(x[i], xc);
+                IO::get(stream_load(x + i), xc);
                 if constexpr (PAIR) {
                     cpx<R> pc[N];
-                    IO::get(r_prev[i], pc);
+                    IO::get(stream_load(r_prev + i), pc);
 #pragma unroll
                     for (int e = 0; e < N; ++e) cmac(xc[e], ap, pc[e]);
                     IO::get(IO::put(xc), xc);  // as the step before would have stored it
                 }
 #pragma unroll
                 for (int e = 0; e < N; ++e) cmac(xc[e], al, rc[e]);
-                x[i] = IO::put(xc);
+                stream_store(x + i, IO::put(xc));
             }
 #pragma unroll
             for (int e = 0; e < N; ++e) cmac(rc[e], na, qc[e]);

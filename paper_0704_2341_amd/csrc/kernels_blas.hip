@@ -92,7 +92,8 @@ struct Partial {
 // bits, and two steps move 9 vectors instead of 10 (8 instead of 9 from x = 0):
 // the kernel runs at the rate of a copy, so the bytes are what it costs (S_bb at
 // 32^4 x 12, BF16, 20 steps in pairs: 32.0 -> 31.3 ms; 16^4 x 8, FP32: 2149 ->
-// 2112 us).
+// 2112 us).  x, q and the step before's r go past L2, which the half-steps around
+// find their inputs in then (31.3 -> 31.05 ms; r too: no difference).
 // the lane (first of N) whose elements 16-byte vector i of a (tile, RHS) holds: in
 // the FP32 halves two components of one lane lie together
 template <int P>
@@ -158,11 +159,11 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
             const int site = tile * 64 + unit_lane<P>(sh, v * 64 + lane);
             if (site < sh.g.V) {
                 const size_t i = base + v * 64 + lane;
-                const uint4 xv = X0 || SKIP ? make_uint4(0, 0, 0, 0) : x[i], rv = r[i], qv = q[i];
+                const uint4 xv = X0 || SKIP ? make_uint4(0, 0, 0, 0) : stream_load(x + i), rv = r[i], qv = stream_load(q + i);
                 cpx<R> xc[N], rc[N], qc[N], pc[N];
                 IO::get(xv, xc);
                 if constexpr (PAIR) {
-                    IO::get(rp[i], pc);
+                    IO::get(stream_load(rp + i), pc);
 #pragma unroll
                     for (int e = 0; e < N; ++e) cmac(xc[e], ap, pc[e]);
                     IO::get(IO::put(xc), xc);  // as the step before would have stored it
@@ -176,7 +177,7 @@ __global__ void __launch_bounds__(256) mr_update_kernel(BlasShape sh, void *x_, 
                     cmac(rc[e], na, qc[e]);
                 }
                 const uint4 ro = IO::put(rc);
-                if constexpr (!SKIP) x[i] = IO::put(xc);
+                if constexpr (!SKIP) stream_store(x + i, IO::put(xc));
                 ro_[i] = ro;
                 IO::get(ro, rc);  // the norm of the values as stored
 #pragma unroll

@@ -55,6 +55,18 @@ struct VecIO<GRG_FP64> {
     }
 };
 
+// Loads and stores past L2, for a stream that nothing near reads again.
+typedef uint32_t vec16_u4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 stream_load(const uint4 *p)
+{
+    const vec16_u4 v = __builtin_nontemporal_load((const vec16_u4 *)p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void stream_store(uint4 *p, uint4 v)
+{
+    __builtin_nontemporal_store((vec16_u4){v.x, v.y, v.z, v.w}, (vec16_u4 *)p);
+}
+
 // Vectors per lane and stream of a wavefront's unit of one (64-site tile, RHS):
 // all of it in BF16, a half in FP32, a quarter in FP64.
 constexpr int kUnitVecs = 3;

@@ -166,8 +166,8 @@ __global__ void __launch_bounds__(256) dslash_batch_kernel(BatchDslashArgs a)
 // vectors per lane of one (tile, RHS), as mr_update_kernel does.  With a site
 // per lane, 8 bytes of each component and the RHS one after the other it ran at
 // 4.3 TB/s of the copy's 6.2 (48 lattices, 4 RHS, FP32, a single step: 0.277 ->
-// 0.236 ms, 5.0 TB/s; the whole apply 21.3 -> 21.1 ms, and 20.5 with the streams
-// read past L2).
+// 0.236 ms; the whole apply 21.3 -> 21.1 ms), and with the streams read past L2
+// 0.193 ms, 6.1 TB/s, and 20.5 ms.
 template <int P, int XM>
 __global__ void __launch_bounds__(256) batch_mr_update_kernel(BatchBlasArgs a, void *x_, void *r_,
                                                               const void *q_)

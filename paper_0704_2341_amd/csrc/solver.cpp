@@ -1472,6 +1472,18 @@ static grg_status pool_slot(grg_schur S, int prec, int k, void **out)
     return GRG_OK;
 }
 
+// For the kernels that read x_b at neighbouring coarse sites while they write
+// y_b: an x_b that overlaps y_b copied into u64 (free then) and read from there.
+static grg_status unoverlapped_xb(grg_schur S, const double **xb, const double *yb, int nrhs)
+{
+    const size_t n = (size_t)nrhs * S->nb * 24;
+    if (*xb < yb + n && yb < *xb + n) {
+        GRG_TRY_HIP(hipMemcpyAsync(S->u64, *xb, n * sizeof(double), hipMemcpyDeviceToDevice, S->lat->stream));
+        *xb = (const double *)S->u64;
+    }
+    return GRG_OK;
+}
+
 // b64 (internal FP64, zero on coarse sites) -> x64 = D_rr^{-1} b64, or with
 // u_minus set, x64 = u_minus - D_rr^{-1} b64 (what S_bb needs next).
 //
@@ -1769,6 +1781,7 @@ grg_status drr_solve_internal(grg_schur S, int nrhs, grg_solver_stats *stats, co
     }
     if (xb && yb && fused && u_minus && !have_x) {
         // y_b = [D (u - sum_j f_j e_j)]_b straight from the corrections
+        GRG_TRY(unoverlapped_xb(S, &xb, yb, nrhs));
         CombineArgs c;
         for (int j = 0; j < kCorrPool; ++j) c.e[j] = j < npool ? S->epool[prec][j] : nullptr;
         c.f = S->d_fk;
@@ -1943,16 +1956,10 @@ static grg_status ensure_boundary(grg_schur S)
     return GRG_OK;
 }
 
-// (x_b and y_b may overlap: the last kernel reads x_b at neighbouring coarse
-// sites while it writes y_b, so an overlapping x_b is copied first)
 static grg_status approx_args(grg_schur S, const double *xb, double *yb, int nrhs, const void *rows, ApproxArgs &a)
 {
     grg_lattice L = S->lat;
-    const size_t n = (size_t)nrhs * S->nb * 24;
-    if (xb < yb + n && yb < xb + n) {
-        GRG_TRY_HIP(hipMemcpyAsync(S->u64, xb, n * sizeof(double), hipMemcpyDeviceToDevice, L->stream));
-        xb = (const double *)S->u64;
-    }
+    GRG_TRY(unoverlapped_xb(S, &xb, yb, nrhs));
     a.g = L->g;
     a.xb = xb;
     a.yb = yb;

@@ -212,3 +212,36 @@ def test_tuned_launch_same_result(inner):
     assert st["converged"] and rel_err(y1, y0) < 1e-11
     s.close()
     lat.close()
+
+
+@pytest.mark.parametrize("order", ["I^-1", "II^-1", "arbitrary"])
+@pytest.mark.parametrize("nrhs", [1, 5])
+def test_apply_in_place(order, nrhs):
+    """x_b and y_b that overlap, where coarse sites are neighbours: the last step
+    reads x_b there while y_b is written.  Same bits as out of place."""
+    import torch
+
+    dims, m0 = (8, 8, 8, 8), -0.2
+    lat = Lattice(dims, 0.5, 61)
+    grg = lat.grg
+    if order == "arbitrary":
+        q, nb = np.random.default_rng(61).permutation(lat.V).astype(np.int32), lat.V // 3
+    else:
+        q, nb = grg.grg_permutation_block(dims, 1 if order == "I^-1" else 2, True)
+    n = 12 * nb * nrhs
+    room = torch.empty(n + 120, dtype=torch.complex128, device="cuda")
+    x = to_dev(gaussian_vectors(12 * nb, nrhs, 61))
+    y = torch.empty_like(x)
+    for inner in ("fp64", "bf16"):
+        for verify in (0, 1):
+            h = grg.grg_schur_create(lat.h, m0, q, nb, grg.grg_solver_params_default(
+                tol=1e-10, inner=inner, inner_tol=1e-2, max_rhs=nrhs, verify=verify))
+            grg.grg_schur_apply(h, x, y, nrhs)
+            for shift in (0, 120):  # the same memory, and memory ten sites on
+                print(f"in place {order} x {nrhs} {inner} verify {verify} shift {shift}", flush=True)
+                xin, yout = room[:n].view_as(x), room[shift:shift + n].view_as(x)
+                xin.copy_(x)
+                grg.grg_schur_apply(h, xin, yout, nrhs)
+                assert torch.equal(yout, y), (inner, verify, shift)
+            grg.grg_schur_destroy(h)
+    lat.close()

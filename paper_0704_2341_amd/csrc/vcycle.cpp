@@ -159,7 +159,7 @@ grg_status check_flags(grg_vcycle_s *v)
     return GRG_OK;
 }
 
-grg_status cycle(grg_vcycle_s *v, int k, int nrhs, const double *f, double *x);
+grg_status cycle(grg_vcycle_s *v, int k, int nrhs, const double *f, double *x, bool report = false);
 
 inline double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
 inline double2 cdiv(double2 a, double2 b)
@@ -222,6 +222,7 @@ grg_status bicgstab(grg_vcycle_s *v, int k, int set, bool pre, double tol, int n
         }
         GRG_TRY(apply_level(v, k, nrhs, sin_, t));
         GRG_TRY(dots(v, k, nrhs, s, t, tmp, tt));  // <s, t> and |t|^2 in one pass; <t, s> = conj <s, t>
+        if (pre) GRG_TRY(check_flags(v));
         for (int i = 0; i < nrhs; ++i)
             omega[i] = act[i] && tt[i] > 0 ? make_double2(tmp[i].x / tt[i], -tmp[i].y / tt[i]) : make_double2(0, 0);
         // x += alpha p^ + omega s^ ; r = s - omega t
@@ -261,8 +262,9 @@ grg_status bicgstab(grg_vcycle_s *v, int k, int set, bool pre, double tol, int n
     return GRG_OK;
 }
 
-// x = cycle(k) f on level k (canonical fields of lattice k)
-grg_status cycle(grg_vcycle_s *v, int k, int nrhs, const double *f, double *x)
+// x = cycle(k) f on level k (canonical fields of lattice k).  report: what the
+// small levels' solves reported is returned before x is written.
+grg_status cycle(grg_vcycle_s *v, int k, int nrhs, const double *f, double *x, bool report)
 {
     hipStream_t st = v->lat[0]->stream;
     double2 one[kMaxRhs], ic[kMaxRhs], mc[kMaxRhs];
@@ -303,6 +305,10 @@ grg_status cycle(grg_vcycle_s *v, int k, int nrhs, const double *f, double *x)
     GRG_TRY(lincomb(v, k, nrhs, t, 2, f, one, t, mc));
     // x_r = A_rr^{-1} h = D_rr^{-1} h / c_k ; x = x_r + u
     GRG_TRY(drr(t, y));
+    if (report) {
+        if (small) GRG_TRY_HIP(hipStreamSynchronize(st));  // (grg_drr_solve has waited)
+        GRG_TRY(check_flags(v));
+    }
     GRG_TRY(lincomb(v, k, nrhs, x, 2, y, ic, u, one));
     return GRG_OK;
 }
@@ -489,9 +495,9 @@ grg_status grg_vcycle_apply(grg_vcycle v, const double *f, double *x, int nrhs)
     if (nrhs < 1 || nrhs > v->prm.max_rhs) return set_error("nrhs outside 1..max_rhs"), GRG_EINVAL;
     Dev dev(v->lat[0]->device);
     clear_flags(v);
-    const grg_status s = cycle(v, 0, nrhs, f, x);
+    const grg_status s = cycle(v, 0, nrhs, f, x, true);
     GRG_TRY_HIP(hipStreamSynchronize(v->lat[0]->stream));
-    return s == GRG_OK ? check_flags(v) : s;
+    return s;
 }
 
 grg_status grg_vcycle_solve(grg_vcycle v, int precondition, double tol, const double *f, double *x, int nrhs,

@@ -110,6 +110,72 @@ def test_small_level_stops(lat):
     grg.grg_vcycle_destroy(v)
 
 
+@pytest.mark.parametrize("dims,levels", [((8, 8, 8, 8), 3), ((4, 4, 4, 4), 2)])
+def test_failed_cycle_leaves_x(dims, levels):
+    """A cycle whose top level misses top_tol is reported and x left as it was,
+    with a level below the top solved step by step and with one solved in one launch."""
+    import torch
+
+    lt = Lattice(dims, 0.5, 51)
+    grg = lt.grg
+    v = grg.grg_vcycle_create(lt.h, M0, grg.grg_vcycle_params_default(levels=levels, max_rhs=2, max_iter=1))
+    f = to_dev(gaussian_vectors(12 * lt.V, 2, 51))
+    x = torch.full_like(f, 7.0)
+    print(f"failed cycle {dims} {levels}", flush=True)
+    with pytest.raises(grg.GrgError) as e:
+        grg.grg_vcycle_apply(v, f, x, 2)
+    assert e.value.status == grg.GRG_ENOCONV
+    assert bool((x == 7.0).all())
+    grg.grg_vcycle_destroy(v)
+    lt.close()
+
+
+def test_last_cycle_of_a_solve_is_reported(lat):
+    """The top level's solve may miss top_tol in the second cycle of the outer
+    iteration that converges: the solve is refused all the same.  Looked for over
+    right-hand sides: a tolerance that two iterations of the first cycle's top level
+    (on f) just reach and two of the second's (on s = f - alpha A M f) do not."""
+    import torch
+
+    grg = lat.grg
+
+    def handle(tol):
+        return grg.grg_vcycle_create(lat.h, M0, grg.grg_vcycle_params_default(levels=3, max_rhs=1, max_iter=2,
+                                                                              top_tol=tol))
+
+    def cycle(tol, b):
+        v, x = handle(tol), torch.empty_like(b)
+        try:
+            grg.grg_vcycle_apply(v, b, x, 1)
+        except grg.GrgError as e:
+            assert e.status == grg.GRG_ENOCONV
+            x = None
+        grg.grg_vcycle_destroy(v)
+        return x
+
+    for seed in range(52, 64):
+        f = to_dev(gaussian_vectors(12 * lat.V, 1, seed))
+        missed, reached = 1e-13, 0.9
+        while reached > 1.02 * missed:
+            tol = np.sqrt(missed * reached)
+            if cycle(tol, f) is None:
+                missed = tol
+            else:
+                reached = tol
+        mf, af = cycle(reached, f), torch.empty_like(f)
+        grg.grg_dirac_apply(lat.h, M0, "fp64", mf, af, 1)
+        s = f - (torch.linalg.norm(f) ** 2 / torch.sum(f.conj() * af)) * af
+        if cycle(1.02 * reached, s) is None:
+            print(f"seed {seed}, top_tol {reached:.2e}: the second cycle misses", flush=True)
+            v = handle(reached)
+            with pytest.raises(grg.GrgError) as e:
+                grg.grg_vcycle_solve(v, f, torch.empty_like(f), 1, tol=0.9, precondition=True)
+            assert e.value.status == grg.GRG_ENOCONV
+            grg.grg_vcycle_destroy(v)
+            return
+    pytest.fail("no such right-hand side")
+
+
 def test_preconditioned_solve(lat):
     import torch
 

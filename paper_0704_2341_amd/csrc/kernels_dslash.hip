@@ -758,8 +758,8 @@ hipError_t launch_dslash(int prec, const DslashArgs &a, int grid, hipStream_t st
 {
     if (a.nrhs < 1 || a.nrhs > kMaxRhs || a.RG < 1) return hipErrorInvalidValue;
     if (grid < 8 || grid % 8) return hipErrorInvalidValue;
-    if (a.split == kSplitForm) {
-        if (a.RG != 1 || a.SB != kSplitSites || a.march > 0) return hipErrorInvalidValue;
+    if (a.split == kSplitForm && a.march == 0) {
+        if (a.RG != 1 || a.SB != kSplitSites) return hipErrorInvalidValue;
         return launch_dslash_split(prec, a, false, grid, st);
     }
     if (a.out_canon && (a.march > 0 || a.partials)) return hipErrorInvalidValue;

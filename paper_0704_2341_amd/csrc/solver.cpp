@@ -152,7 +152,7 @@ static grg_status launch_tuned(grg_lattice L, int prec, const DslashTune &t, con
 bool launch_ok(const Geom &g, int prec, int nrhs, const DslashTune &t, bool)
 {
     if (t.grid < 8 || t.grid % 8 || t.grid > kMaxGridValue || t.chunk < 0 || t.march < 0) return false;
-    if (t.march > 0) {
+    if (t.march > 0) {  // (whatever the split)
         return t.march <= g.L[3] && t.RG >= 1 && t.RG <= nrhs &&
                64 * t.RG <= (prec == GRG_FP64 ? 512 : 768);
     }
@@ -1821,7 +1821,7 @@ grg_status block_apply_internal(grg_schur S, int prec, int rows, int cols, const
     const size_t n = (size_t)nrhs * L->g.V * 24;
     const DslashTune &tt = S->tune[prec][nrhs];
     const DslashTune t = tt.valid ? tt : default_tune(L->g, prec, nrhs);
-    if (t.split == kSplitForm && !(in < out + n && out < in + n)) {
+    if (t.split == kSplitForm && t.march == 0 && !(in < out + n && out < in + n)) {
         // the hop-per-wavefront form reads and writes the canonical fields
         DslashArgs a;
         a.in = in;

@@ -114,3 +114,32 @@ def test_canonical_march(dims, nrhs):
             assert torch.equal(y, z), (prec, apply)
             assert bool((room[:256] == 3.0).all()) and bool((room[-256:] == 3.0).all())
     lat.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+def test_marching_launch_ignores_split(prec):
+    """A marching launch runs as such whatever its split (8 names the hop-per-wavefront
+    form only where march is 0): the sub-blocks and a solve, to the bits of split 0."""
+    import torch
+
+    dims, nrhs = (8, 8, 8, 8), 3
+    lat = Lattice(dims, 0.5, 74)
+    grg = lat.grg
+    s = lat.schur(-0.2, "I", False, tol=1e-8, inner=prec, inner_tol=1e-2, eo=0, max_rhs=nrhs)
+    x = to_dev(gaussian_vectors(12 * lat.V, nrhs, 74))
+    outs = []
+    for split in (0, 8):
+        print(f"march 4, split {split}, {prec}", flush=True)
+        grg.grg_schur_set_launch(s.h, prec, nrhs, [64, 1, split, 64, 0, 4])
+        y, z = torch.empty_like(x), torch.empty_like(x)
+        grg.grg_block_apply(s.h, prec, 0, -1, x, y, nrhs)
+        st = grg.grg_drr_solve(s.h, x, z, nrhs)
+        assert st["converged"]
+        outs.append((y, z))
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+    for bad in ([128, 1, 8, 64, 0, 0], [64, 3, 8, 64, 0, 0], [64, 1, 8, 60, 0, 0]):
+        with pytest.raises(grg.GrgError) as e:
+            grg.grg_schur_set_launch(s.h, prec, nrhs, bad)
+        assert e.value.status == grg.GRG_EINVAL
+    s.close()
+    lat.close()

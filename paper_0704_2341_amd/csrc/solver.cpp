@@ -395,6 +395,72 @@ static void dc_fill_launch(DcArgs &d, const DslashTune &t)
     d.grp_first = (t.split & 2) != 0;
 }
 
+// The launches that tune_dc times (out: cap of them; returns their number):
+// the default's, the site-parallel step, a hop per wavefront, and the marching
+// forms with divisors of nrhs.
+int dc_candidates(const Geom &g, int prec, int nrhs, DslashTune *out, int cap)
+{
+    int n = 0;
+    auto add = [&](const DslashTune &t) {
+        if (n < cap && dc_launch_ok(g, prec, nrhs, t)) out[n++] = t;
+    };
+    add(default_dc_tune(g, prec, nrhs));
+    for (int sb : {64, 128, 256}) {
+        DslashTune t;
+        t.SB = sb;
+        t.RG = 1;
+        t.grid = round8(std::min<long>((long)((g.V + sb - 1) / sb) * nrhs, 2048));
+        add(t);
+    }
+    {
+        DslashTune t;  // a hop per wavefront
+        t.SB = kSplitSites;
+        t.RG = 1;
+        t.split = kSplitForm;
+        t.grid = dslash_grid(g, nrhs, 64, 1);
+        add(t);
+    }
+    const int nb3 = (g.L[0] * g.L[1] * g.L[2] + 63) / 64;
+    for (int rg = std::min(nrhs, 8); rg >= 1; --rg) {
+        if (nrhs % rg) continue;
+        for (int T = 2; T <= g.L[3]; T *= 2) {
+            for (int ch : {0, 8, nb3 / 8, nb3 / 4, nb3 / 2}) {
+                DslashTune t;
+                t.march = T;
+                t.SB = 64;
+                t.RG = rg;
+                t.chunk = ch;
+                const long items = (long)nb3 * ((g.L[3] + T - 1) / T) * (nrhs / rg);
+                if (ch > 0 && ch * 8 >= items) continue;
+                t.grid = round8(std::min<long>(items, 2048));
+                add(t);
+                t.split = 1;  // the LDS-ring form (where valid)
+                if (ch <= 8) add(t);
+                // the ring form with the RHS groups of a tile together
+                // (chunks: an eighth per XCD, or whole z-planes of tiles)
+                t.split = 3;
+                if (ch == 0 || ch == 8) add(t);
+            }
+            if (nrhs / rg > 1) {
+                const int plane = (g.L[0] * g.L[1] + 63) / 64 * (nrhs / rg);
+                for (int ch : {plane, 2 * plane}) {
+                    DslashTune t;
+                    t.march = T;
+                    t.SB = 64;
+                    t.RG = rg;
+                    t.chunk = ch;
+                    t.split = 3;
+                    const long items = (long)nb3 * ((g.L[3] + T - 1) / T) * (nrhs / rg);
+                    if (ch * 8 >= items) continue;
+                    t.grid = round8(std::min<long>(items, 2048));
+                    add(t);
+                }
+            }
+        }
+    }
+    return n;
+}
+
 // Autotuner of the defect-correction step (inner precision prec), timed on
 // the handle's workspaces; every candidate computes the same sums in the
 // same order per site.
@@ -445,58 +511,9 @@ grg_status tune_dc(grg_schur S, int prec, int nrhs, int reps)
         t.ms = ms / reps;
         if (t.ms < best.ms) best = t;
     };
-    for (int sb : {64, 128, 256}) {
-        DslashTune t = default_dc_tune(g, prec, nrhs);
-        t.SB = sb;
-        t.grid = round8(std::min<long>((long)((g.V + sb - 1) / sb) * nrhs, 2048));
-        timeit(t);
-    }
-    {
-        DslashTune t;  // a hop per wavefront
-        t.SB = kSplitSites;
-        t.RG = 1;
-        t.split = kSplitForm;
-        t.grid = dslash_grid(g, nrhs, 64, 1);
-        timeit(t);
-    }
-    const int nb3 = (g.L[0] * g.L[1] * g.L[2] + 63) / 64;
-    for (int rg = std::min(nrhs, 8); rg >= 1; --rg) {
-        if (nrhs % rg) continue;
-        for (int T = 2; T <= g.L[3]; T *= 2) {
-            for (int ch : {0, 8, nb3 / 8, nb3 / 4, nb3 / 2}) {
-                DslashTune t;
-                t.march = T;
-                t.SB = 64;
-                t.RG = rg;
-                t.chunk = ch;
-                const long items = (long)nb3 * ((g.L[3] + T - 1) / T) * (nrhs / rg);
-                if (ch > 0 && ch * 8 >= items) continue;
-                t.grid = round8(std::min<long>(items, 2048));
-                timeit(t);
-                t.split = 1;  // the LDS-ring form (where valid)
-                if (ch <= 8) timeit(t);
-                // the ring form with the RHS groups of a tile together
-                // (chunks: an eighth per XCD, or whole z-planes of tiles)
-                t.split = 3;
-                if (ch == 0 || ch == 8) timeit(t);
-            }
-            if (nrhs / rg > 1) {
-                const int plane = (g.L[0] * g.L[1] + 63) / 64 * (nrhs / rg);
-                for (int ch : {plane, 2 * plane}) {
-                    DslashTune t;
-                    t.march = T;
-                    t.SB = 64;
-                    t.RG = rg;
-                    t.chunk = ch;
-                    t.split = 3;
-                    const long items = (long)nb3 * ((g.L[3] + T - 1) / T) * (nrhs / rg);
-                    if (ch * 8 >= items) continue;
-                    t.grid = round8(std::min<long>(items, 2048));
-                    timeit(t);
-                }
-            }
-        }
-    }
+    std::vector<DslashTune> cands(4096);
+    cands.resize(dc_candidates(g, prec, nrhs, cands.data(), (int)cands.size()));
+    for (const DslashTune &t : cands) timeit(t);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (status != GRG_OK) return status;

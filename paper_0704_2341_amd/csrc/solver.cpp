@@ -90,10 +90,22 @@ DslashTune default_tune(const Geom &g, int prec, int nrhs)
     return t;
 }
 
+// Whether the x-y-z slices, cut into tiles of 64 sites, fill at least `eighths` of
+// the tiles' lanes: what the marching forms, whose tiles lie within a slice, lose
+// against those whose tiles run on through the lattice.
+static bool slices_fill(const Geom &g, int eighths)
+{
+    const long V3 = (long)g.L[0] * g.L[1] * g.L[2];
+    return V3 >= (V3 + 63) / 64 * 8 * eighths;
+}
+
 // Launch of the t-march over canonical fields (valid: from 513 wavefronts' worth
 // of sites and RHS on; 8^4, 8 RHS, 512: FP64 22.1 us against 23.0 with a hop per
 // wavefront, FP32 21.6 / 21.0, BF16 22.2 / 20.4; 10^4, 4 RHS, 628: 24.5 / 27.9, 23.0 /
-// 24.6, 22.4 / 24.0).  The chip holds one of its wavefronts per SIMD in FP64
+// 24.6, 22.4 / 24.0; and where the slices fill three quarters of their tiles'
+// lanes: FP64, 5 RHS, 5000 wavefronts, time against the other forms' 0.76 with
+// slices of 64 sites, 0.98 with 48, 1.08 with 40, 1.29 with 32, 3.7 with 8).
+// The chip holds one of its wavefronts per SIMD in FP64
 // (registers and LDS), two in FP32 and BF16; an item is a tile of 64 sites and
 // one RHS over march slices, and its first slice costs about one more (two
 // spinors of the column before anything overlaps), so the slices are cut to the
@@ -107,16 +119,21 @@ DslashTune canon_march_tune(const Geom &g, int prec, int nrhs)
     const long pairs = (long)((g.L[0] * g.L[1] * g.L[2] + 63) / 64) * nrhs;
     const long res = prec == GRG_FP64 ? 1024 : 2048;
     DslashTune t;
-    t.valid = field_waves(g, nrhs) > 512;
+    t.valid = field_waves(g, nrhs) > 512 && slices_fill(g, 6);
+    if (!t.valid) return t;
     t.SB = 64;
     t.RG = 1;
+    // cuts into n chunks, of the fewest slices for that n, until n chunks in
+    // even the fewest rounds, pairs n / res, cannot cost less
+    const long Lt = g.L[3];
     long best = 0;
-    for (int T = g.L[3]; T >= 1; --T) {
-        const long items = pairs * ((g.L[3] + T - 1) / T);
+    for (long n = 1; n <= Lt && (best == 0 || pairs * (Lt + n) < best * res); ++n) {
+        const long T = (Lt + n - 1) / n;
+        const long items = pairs * ((Lt + T - 1) / T);
         const long cost = (items + res - 1) / res * (T + 1);
         if (best == 0 || cost < best) {
             best = cost;
-            t.march = T;
+            t.march = (int)T;
             t.grid = round8(std::min(items, res));
             t.chunk = pairs >= 1536 && items >= 3 * res ? 2 * nrhs : 0;
         }
@@ -338,7 +355,10 @@ grg_status tune_dslash(grg_schur S, int prec, int nrhs, int reps)
 // least four RHS, four of them in a t-marching workgroup (32^4, 12 RHS: FP64
 // 3.40 ms against 4.18, FP32 2.49 against 2.81), in its LDS-ring form where
 // that is valid (BF16: 2.07 ms against 2.34; without it the site-parallel
-// kernel is the faster one, 0.76 ms against 0.80 at 24^4).  The smallest fields
+// kernel is the faster one, 0.76 ms against 0.80 at 24^4) and the slices fill
+// seven eighths of their tiles' lanes (36000 wavefronts, 16 RHS, FP32: 0.97 of the
+// site-parallel kernel's time with slices of 64 sites, 1.07 with 105 in two tiles,
+// 1.38 with 32, 4.3 with 8).  The smallest fields
 // take a hop per wavefront (8^4, 1 RHS: 11.8 us against 17.7; at 768 wavefronts
 // the forms meet, at 1024 it is 31 against 27).
 bool dc_launch_ok(const Geom &g, int prec, int nrhs, const DslashTune &t);
@@ -353,7 +373,7 @@ DslashTune default_dc_tune(const Geom &g, int prec, int nrhs)
         return t;
     }
     t.SB = 64;
-    if (field_waves(g, nrhs) > 32768 && nrhs >= 4) {
+    if (field_waves(g, nrhs) > 32768 && nrhs >= 4 && slices_fill(g, 7)) {
         t.RG = 4;
         t.march = std::min(8, g.L[3]);
         t.split = prec == GRG_BF16 ? 3 : 0;

@@ -4,6 +4,7 @@ checked without a GPU."""
 import ctypes as C
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -97,3 +98,41 @@ def test_dc_tuning_candidates(lib, dims, nrhs, prec):
     assert all(t.SB == 64 for t in out[:n] if t.march > 0)
     assert all(t.grid >= 8 and t.grid % 8 == 0 for t in out[:n])
     assert f(C.byref(g), prec, nrhs, out, 2) == 2  # no more than there is room for
+
+
+def _march_tune(lib, dims, prec, nrhs):
+    f = lib._ZN3grg16canon_march_tuneERKNS_4GeomEii
+    f.restype, f.argtypes = _Tune, [C.POINTER(_Geom), C.c_int, C.c_int]
+    return f(C.byref(_geom(dims)), prec, nrhs)
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_march_rule(lib, prec):
+    """The t-march of D runs where its slices fill their tiles of 64 sites, with the
+    chunks of the fewest rounds x (slices + 1), the longest among equals; the rule
+    itself takes no time that grows with Lt.  The defect correction's marching
+    default as well needs slices that fill their tiles."""
+    rng = np.random.default_rng(75)
+    for _ in range(300):
+        dims = [int(d) for d in np.exp(rng.uniform(0, np.log(33), 4))]
+        nrhs = int(rng.integers(1, 17))
+        t = _march_tune(lib, dims, prec, nrhs)
+        v3 = dims[0] * dims[1] * dims[2]
+        tiles = -(-v3 // 64)
+        waves = -(-v3 * dims[3] // 64) * nrhs
+        assert bool(t.valid) == (waves > 512 and 4 * v3 >= 3 * 64 * tiles), (dims, nrhs)
+        if t.valid:
+            pairs, res = tiles * nrhs, 1024 if prec == 0 else 2048
+            cost = {T: -(-pairs * -(-dims[3] // T) // res) * (T + 1) for T in range(1, dims[3] + 1)}
+            best = max(T for T in cost if cost[T] == min(cost.values()))
+            assert t.march == best, (dims, nrhs)
+            assert t.grid == max(8, -(-min(pairs * -(-dims[3] // best), res) // 8) * 8)
+    for dims in ((1, 1, 1, 1 << 27), (2, 2, 2, 8192), (3, 3, 3, 4096), (5, 13, 1, 4096)):
+        assert not _march_tune(lib, dims, prec, 12).valid
+        d = lib._ZN3grg15default_dc_tuneERKNS_4GeomEii
+        d.restype, d.argtypes = _Tune, [C.POINTER(_Geom), C.c_int, C.c_int]
+        assert d(C.byref(_geom(dims)), prec, 12).march == 0
+    t0 = time.perf_counter()
+    for _ in range(100):
+        assert _march_tune(lib, (4, 4, 4, 1 << 21), prec, 1).valid
+    assert time.perf_counter() - t0 < 0.1  # (a walk over every T: over a second)

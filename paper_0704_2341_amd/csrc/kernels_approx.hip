@@ -131,11 +131,26 @@ __device__ __forceinline__ cpx<double> row_divide(double2 a, double2 b)
     return {(a.x * b.x + a.y * b.y) / den, (a.y * b.x - a.x * b.y) / den};
 }
 
+// -w = (y - z) / d + t, in the formula's order: where z is close to y (row sums
+// close to d), y / d + t - z / d has up to three times its rounding error
+__device__ __forceinline__ double minus_w(double y, double z, double t, double inv_d)
+{
+    return (y - z) * inv_d + t;
+}
+
+// c v, rounded (not fused into what it is subtracted from): the bits of a z that is
+// formed in a pass of its own
+__device__ __forceinline__ cpx<double> scaled(double c, cpx<double> v)
+{
+#pragma clang fp contract(off)
+    return {c * v.re, c * v.im};
+}
+
 // ------------------------------------------------------------------ the fields
 // Boundary site j, RHS r: y = (D x)_j from its coarse neighbours, then p = -w
-// or what is known of it:
+// or what it is formed from:
 //   kNoRows   p = y / d                                  (S0_bb)
-//   kTwoPass  p = y / d + t, and t for boundary_apply_kernel to subtract z / d
+//   kTwoPass  p = y, and t, from which boundary_apply_kernel forms z and -w
 //   kOnePass  p = (y - z) / d + t with z = d t: no neighbour carries a t (the
 //             all-even coarse set, where this saves writing t and three more
 //             passes over the boundary: S~_bb at 32^4 with 12 RHS 1.18 ms in
@@ -170,15 +185,15 @@ __global__ void __launch_bounds__(256) boundary_source_kernel(Geom g, const doub
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             const size_t i = fidx(j, r, c, nrhs);
-            cpx<double> pv = {acc[c].re * inv_d, acc[c].im * inv_d};
-            if constexpr (MODE != kNoRows) {
+            cpx<double> pv = acc[c];
+            if constexpr (MODE == kNoRows) {
+                pv = {acc[c].re * inv_d, acc[c].im * inv_d};
+            } else {
                 const cpx<double> tv = row_divide(make_double2(acc[c].re, acc[c].im), rows[fidx(s, 0, c, 1)]);
                 if constexpr (MODE == kTwoPass) t[i] = make_double2(tv.re, tv.im);
-                pv.re += tv.re;
-                pv.im += tv.im;
                 if constexpr (MODE == kOnePass) {
-                    pv.re -= diag * tv.re * inv_d;
-                    pv.im -= diag * tv.im * inv_d;
+                    const cpx<double> z = scaled(diag, tv);
+                    pv = {minus_w(acc[c].re, z.re, tv.re, inv_d), minus_w(acc[c].im, z.im, tv.im, inv_d)};
                 }
             }
             p[i] = make_double2(pv.re, pv.im);
@@ -186,7 +201,7 @@ __global__ void __launch_bounds__(256) boundary_source_kernel(Geom g, const doub
     }
 }
 
-// p <- -w = p - z / d on the boundary, z = D_rr t from the neighbours on it
+// p (y) <- -w on the boundary, z = D_rr t from the neighbours on it
 // (t = 0 off it, but for the kBadRow sites)
 __global__ void __launch_bounds__(256) boundary_apply_kernel(Geom g, const double2 *__restrict__ U,
                                                              const double2 *__restrict__ rows,
@@ -247,8 +262,8 @@ __global__ void __launch_bounds__(256) boundary_apply_kernel(Geom g, const doubl
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             const size_t i = fidx(j, r, c, nrhs);
-            const double2 v = p[i];
-            p[i] = make_double2(v.x - acc[c].re * inv_d, v.y - acc[c].im * inv_d);
+            const double2 y = p[i], tv = t[i];
+            p[i] = make_double2(minus_w(y.x, acc[c].re, tv.x, inv_d), minus_w(y.y, acc[c].im, tv.y, inv_d));
         }
     }
 }

@@ -206,3 +206,56 @@ def test_zero_row_sums():
     assert bool(torch.isfinite(torch.view_as_real(y)).all())
     s.close()
     lat.close()
+
+
+@pytest.mark.parametrize("linked", [False, True])
+def test_formula_order(linked):
+    """(y - z) / d + t where the row sums equal d, so that z is y up to rounding:
+    links 1 along x in the rows of coarse sites and 0 elsewhere, and a source of whole
+    numbers on the sites x = 0, whose image on x = 2 and 6 is -1/2 (1 -/+ g_x) x / d.
+    In units of u = 2^-53: t = y d / d^2 errs by at most 3 u, z = d t by 4, y - z is
+    exact and takes t's error out again, which leaves z's rounding and the last sum's,
+    and the hop to the coarse site adds two equal terms, exactly: 2 u and the second
+    order.  (y / d + t first and z / d off afterwards reaches 2.9 u.)  With `linked`, a
+    coarse site more whose neighbours lie next to the boundary's (z formed in a pass
+    of its own)."""
+    import torch
+
+    dims, m0, nrhs = (8, 4, 4, 4), -0.45, 5
+    V, d = int(np.prod(dims)), 4.0 + m0
+    c = np.array([[(s // int(np.prod(dims[:mu]))) % dims[mu] for mu in range(4)] for s in range(V)])
+    row = (c[:, 1:] % 2 == 0).all(axis=1)
+    links = np.zeros((V, 4, 3, 3), complex)
+    links[row, 0] = np.eye(3)
+    coarse = row & (c[:, 0] % 2 == 0)
+    if linked:
+        coarse |= (c == (1, 1, 1, 0)).all(axis=1)
+    q = np.concatenate([np.flatnonzero(coarse), np.flatnonzero(~coarse)]).astype(np.int32)
+    nb = int(coarse.sum())
+    lat = Lattice(dims, 0.0, 0, bc=(1, 1, 1, 1), links=links)
+    h = lat.grg.grg_schur_create(lat.h, m0, q, nb, lat.grg.grg_solver_params_default(max_rhs=nrhs))
+    cc = c[q[:nb]]
+    src = np.flatnonzero(row[q[:nb]] & (cc[:, 0] == 0))
+    rng = np.random.default_rng(76)
+    up = rng.integers(1, 1 << 20, (nrhs, len(src), 2, 3, 2)).astype(float)  # spins 0 and 1
+    xb = np.zeros((nrhs, nb, 4, 3), complex)
+    xb[:, src, :2] = up[..., 0] + 1j * up[..., 1]
+    x = to_dev(xb.reshape(nrhs, -1))
+    y = torch.empty_like(x)
+    lat.grg.grg_reusken_apply(h, x, y, nrhs)
+    got = to_host(y).reshape(nrhs, nb, 4, 3)
+    u0, u1 = xb[:, src, 0], xb[:, src, 1]
+    checked = 0
+    for xs, sg in ((2, 1), (6, -1)):
+        # from x = 0 on to x + 2: -1/2 (1 + g_x) x; back to x - 2: -1/2 (1 - g_x) x
+        at = np.flatnonzero(row[q[:nb]] & (cc[:, 0] == xs))
+        assert (cc[at, 1:] == cc[src, 1:]).all()
+        num = np.stack([u0, u1, sg * -1j * u1, sg * -1j * u0], axis=2)
+        for part in (np.real, np.imag):
+            want = part(num).astype(np.longdouble) * np.longdouble(-0.5) / np.longdouble(d)
+            err = np.abs(part(got[:, at]).astype(np.longdouble) - want) / np.abs(want)
+            assert float(err.max()) <= 2.0 * 2.0 ** -53 * (1 + 1e-3), float(err.max()) * 2.0 ** 53
+            checked += err.size
+    assert checked == nrhs * len(src) * 2 * 24
+    lat.grg.grg_schur_destroy(h)
+    lat.close()

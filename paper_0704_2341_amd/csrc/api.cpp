@@ -434,8 +434,6 @@ static void schur_free(grg_schur S)
     dfree((void *&)S->cb_in);
     dfree((void *&)S->cb_out);
     dfree(S->dt64);
-    dfree((void *&)S->bnd_site);
-    dfree((void *&)S->bnd_map);
     dfree((void *&)S->d_mask_eo);
     dfree((void *&)S->d_mask_par);
     for (int p = 0; p < 3; ++p) {
@@ -508,7 +506,15 @@ grg_status grg_schur_create(grg_lattice L, double m0, const int32_t *q, int32_t 
     if (s == GRG_OK) s = dmalloc((void **)&(ptr), (bytes), #ptr)
     ALLOC(S->d_mask, V);
     ALLOC(S->d_q, sizeof(int32_t) * n_coarse);
-    ALLOC(S->d_bidx, sizeof(int32_t) * V);
+    // behind the coarse indices, the boundary's tables (at most 8 sites per coarse one)
+    S->bnd_most = (int)std::min<long>(8L * n_coarse, (long)V - n_coarse);
+    ALLOC(S->d_bidx, sizeof(int32_t) * (2 * (size_t)V + S->bnd_most + 2 + boundary_blocks(g)));
+    if (S->d_bidx) {
+        S->bnd_map = S->d_bidx + V;
+        S->bnd_site = S->bnd_map + V;
+        S->bnd_info = S->bnd_site + S->bnd_most;
+        S->bnd_count = S->bnd_info + 2;
+    }
     ALLOC(S->b64, f64);
     ALLOC(S->x64, f64);
     ALLOC(S->r64, f64);
@@ -537,12 +543,15 @@ grg_status grg_schur_create(grg_lattice L, double m0, const int32_t *q, int32_t 
         set_error("hipHostMalloc failed");
         s = GRG_ENOMEM;
     }
-    if (s == GRG_OK && hipHostMalloc((void **)&S->h_buf, sizeof(double) * 14 * kMaxRhs) != hipSuccess) {
+    if (s == GRG_OK && hipHostMalloc((void **)&S->h_buf, sizeof(double) * (14 * kMaxRhs + 1)) != hipSuccess) {
         S->h_buf = nullptr;
         set_error("hipHostMalloc failed");
         s = GRG_ENOMEM;
     }
-    if (s == GRG_OK) memset(S->h_buf, 0, sizeof(double) * 14 * kMaxRhs);  // (no tag is 0)
+    if (s == GRG_OK) {
+        memset(S->h_buf, 0, sizeof(double) * (14 * kMaxRhs + 1));  // (no tag is 0)
+        S->h_bnd = (int *)(S->h_buf + 14 * kMaxRhs);
+    }
     if (s != GRG_OK) {
         schur_free(S);
         delete S;

@@ -263,13 +263,12 @@ hipError_t launch_axpy_convert(int prec_in, int prec_out, const BlasShape &sh, c
                                const int *active, hipStream_t st, size_t y_half = 0, int y_first = 0);
 // y = x - y (FP64), used for u - z
 hipError_t launch_xmy(const BlasShape &sh, const void *x, void *y, hipStream_t st);
-// the rest-site ones field (the row sums' input)
-hipError_t launch_rest_ones(const Geom &g, const uint8_t *mask, void *o, hipStream_t st);
 hipError_t launch_combine(int prec, const BlasShape &sh, const CombineArgs &a, hipStream_t st);
 // Schur complement approximations of section 3 on the boundary, the rest
-// sites next to a coarse site (kernels_approx.hip).  count: boundary_blocks + 1
-// ints; site: the boundary's sites in lattice order (count's last entry of
-// them), map: site -> index in it, or negative.
+// sites next to a coarse site (kernels_approx.hip).  site: the boundary's sites
+// in lattice order, map: site -> index in it, or negative; count: scratch of
+// boundary_blocks ints; info[0]: the boundary sites' number, info[1]: the stamp
+// of the rows with which a boundary site has a neighbour whose t is not zero.
 struct ApproxArgs {
     Geom g;
     const double *xb;     // canonical coarse vector
@@ -277,20 +276,24 @@ struct ApproxArgs {
     const int32_t *q, *bidx;
     int nb;
     const int32_t *site, *map;
-    int nbnd;
+    int nbnd;             // the boundary sites' number, or with info set at least that
     const void *U;        // FP64 links
     const void *rows;     // row sums of D_rr (one FP64 field), nullptr: couplings inside D_rr ignored
-    int linked;           // a boundary site has a neighbour whose t is not zero
+    int linked;           // a boundary site has, or may have, a neighbour whose t is not zero
     double diag;          // 4 + m0
     void *t, *p;          // compact FP64 fields over the boundary, internal tiles
     int nrhs;
+    // info set: what the host does not know yet.  launch_boundary_coarse leaves
+    // host[0] = info[0] + 1 and, with stamp > 0 the rows' one, host[1] = stamp or
+    // -stamp, as such a neighbour exists or not (pinned words, each whole).
+    const int *info;
+    int *host, stamp;
 };
 int boundary_blocks(const Geom &g);
 hipError_t launch_boundary_build(const Geom &g, const int32_t *bidx, int *count, int32_t *site, int32_t *map,
-                                 hipStream_t st);
-hipError_t launch_boundary_rows(const Geom &g, const int32_t *bidx, const void *rows, int32_t *map, hipStream_t st);
-hipError_t launch_boundary_links(const Geom &g, const int32_t *site, int nbnd, const int32_t *map, int *linked,
-                                 hipStream_t st);
+                                 int *info, hipStream_t st);
+hipError_t launch_boundary_rows(const Geom &g, const int32_t *bidx, const void *U, double diag, void *rows,
+                                int32_t *map, int *info, int stamp, hipStream_t st);
 hipError_t launch_boundary_source(const ApproxArgs &a, hipStream_t st);
 hipError_t launch_boundary_apply(const ApproxArgs &a, hipStream_t st);
 hipError_t launch_boundary_coarse(const ApproxArgs &a, hipStream_t st);

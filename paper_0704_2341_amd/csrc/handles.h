@@ -97,7 +97,7 @@ struct grg_schur_s {
     std::vector<int32_t> q_host;
     uint8_t *d_mask = nullptr;    // 1 on coarse sites
     int32_t *d_q = nullptr;       // coarse index -> site
-    int32_t *d_bidx = nullptr;    // site -> coarse index or -1
+    int32_t *d_bidx = nullptr;    // site -> coarse index or -1 (and the boundary's tables behind it)
     // FP64 outer fields, [max_rhs][12][Vs] each
     void *b64 = nullptr, *x64 = nullptr, *r64 = nullptr, *t64 = nullptr, *u64 = nullptr;
     // the defect correction's residual in FP32 once it is small ([max_rhs][12][Vs]
@@ -117,11 +117,14 @@ struct grg_schur_s {
     // the lattice's gauge_version they were computed from (-1: not yet)
     void *dt64 = nullptr;
     int dt_version = -1;
-    // the rest sites next to a coarse site, in lattice order, and the map from
-    // sites into that list (negative off it; allocated on first use)
+    // the rest sites next to a coarse site, in lattice order, the map from sites
+    // into that list (negative off it), and their scratch and device words (see
+    // ApproxArgs; behind d_bidx, made on first use), and the words that a call
+    // leaves for the host
     int32_t *bnd_site = nullptr, *bnd_map = nullptr;
-    int n_bnd = -1;
-    int bnd_linked = 1;  // with the rows of dt_version: a boundary site has a neighbour whose t is not zero
+    int bnd_most = 0;  // room for the list
+    int *bnd_count = nullptr, *bnd_info = nullptr, *h_bnd = nullptr;
+    bool bnd_built = false;
     // even-odd reduced inner solve: mask per parity ([2][Vhs]), the parity of
     // the reduced system, and compact fields per inner precision: r, x, q
     // (reduced parity), w (other parity) and the preconditioned direction p
@@ -156,7 +159,7 @@ struct grg_schur_s {
     int *active = nullptr;
     int *act0 = nullptr;      // RHS active when an inner solve started
     double *h_buf = nullptr;  // pinned host staging (14 * kMaxRhs doubles: reads, uploads, flags,
-                              // and the words of HostNorms)
+                              // and the words of HostNorms; then h_bnd's)
     unsigned norm_tag = 0;    // the last reduction's HostNorms tag
     grg::ProfilePool prof;
     int n_dslash = 0;

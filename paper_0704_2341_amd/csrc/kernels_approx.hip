@@ -38,90 +38,109 @@ __device__ __forceinline__ bool on_boundary(int s, const Geom &g, const int32_t 
     return b;
 }
 
-// per block of 256 sites, the boundary sites' number
-__global__ void __launch_bounds__(256) boundary_count_kernel(Geom g, const int32_t *__restrict__ bidx, int *count)
+// A first call makes the tables in two launches and, with rows, a third; nothing is
+// read back: the kernels after them take the number of boundary sites from info[0],
+// and the last one of the call leaves what later calls want in pinned words.  (List,
+// map and counts allocated by themselves and three waits for the host: first
+// S~_bb on 8^4, 1 RHS, 97 us against 78 over the whole lattice.)
+constexpr int kBoundaryBlock = 1024;
+
+// per block of sites, the boundary sites' number
+__global__ void __launch_bounds__(kBoundaryBlock) boundary_count_kernel(Geom g, const int32_t *__restrict__ bidx,
+                                                                        int *count, int *info)
 {
-    __shared__ int n[4];
-    const int s = blockIdx.x * 256 + threadIdx.x;
+    __shared__ int n[16];
+    const int s = blockIdx.x * kBoundaryBlock + threadIdx.x;
     const unsigned long long m = __ballot(on_boundary(s, g, bidx));
     if ((threadIdx.x & 63) == 0) n[threadIdx.x >> 6] = __popcll(m);
     __syncthreads();
-    if (threadIdx.x == 0) count[blockIdx.x] = n[0] + n[1] + n[2] + n[3];
-}
-
-// count[i] -> the sum of the counts before i; count[n] the total (one workgroup)
-__global__ void __launch_bounds__(1024) boundary_scan_kernel(int *count, int n)
-{
-    __shared__ int sm[1024];
-    int base = 0;
-    for (int i0 = 0; i0 < n; i0 += 1024) {
-        const int i = i0 + (int)threadIdx.x;
-        const int v = i < n ? count[i] : 0;
-        sm[threadIdx.x] = v;
-        __syncthreads();
-        for (int o = 1; o < 1024; o <<= 1) {
-            const int a = (int)threadIdx.x >= o ? sm[threadIdx.x - o] : 0;
-            __syncthreads();
-            sm[threadIdx.x] += a;
-            __syncthreads();
-        }
-        if (i < n) count[i] = base + sm[threadIdx.x] - v;
-        base += sm[1023];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        int t = 0;
+        for (int w = 0; w < 16; ++w) t += n[w];
+        count[blockIdx.x] = t;
+        if (blockIdx.x == 0) info[1] = 0;
     }
-    if (threadIdx.x == 0) count[n] = base;
 }
 
-// site[j] = the j-th boundary site in lattice order, map[s] = its j, or -1
-__global__ void __launch_bounds__(256) boundary_fill_kernel(Geom g, const int32_t *__restrict__ bidx,
-                                                            const int *__restrict__ first, int32_t *site,
-                                                            int32_t *map)
+// site[j] = the j-th boundary site in lattice order, map[s] = its j, or -1;
+// info[0] the sites' number.  Each block adds the counts before it itself.
+__global__ void __launch_bounds__(kBoundaryBlock) boundary_fill_kernel(Geom g, const int32_t *__restrict__ bidx,
+                                                                       const int *__restrict__ count, int32_t *site,
+                                                                       int32_t *map, int *info)
 {
-    __shared__ int n[4];
-    const int s = blockIdx.x * 256 + threadIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ int n[16], before[16];
+    const int s = blockIdx.x * kBoundaryBlock + threadIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int sum = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kBoundaryBlock) sum += count[i];
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
     const bool b = on_boundary(s, g, bidx);
     const unsigned long long m = __ballot(b);
-    if (lane == 0) n[wave] = __popcll(m);
+    if (lane == 0) {
+        n[wave] = __popcll(m);
+        before[wave] = sum;
+    }
     __syncthreads();
-    int j = first[blockIdx.x] + __popcll(m & ((1ull << lane) - 1));
-    for (int w = 0; w < wave; ++w) j += n[w];
+    int j = __popcll(m & ((1ull << lane) - 1));
+    for (int w = 0; w < 16; ++w) j += before[w] + (w < wave ? n[w] : 0);
     if (b) site[j] = s;
     if (s < g.V) map[s] = b ? j : -1;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kBoundaryBlock - 1) info[0] = j + (b ? 1 : 0);
 }
 
-// rest sites off the boundary: kBadRow where a row sum's 0 / d~ is not zero
+// The row sums d~ = D_rr 1 of the rest sites (the sums of the stencil on a field
+// that is 1 there); rest sites off the boundary: kBadRow where a row sum's 0 / d~
+// is not zero; info[1] = stamp if a boundary site has a neighbour with t != 0 (one
+// on the boundary, or a kBadRow site).
 __global__ void __launch_bounds__(256) boundary_rows_kernel(Geom g, const int32_t *__restrict__ bidx,
-                                                            const double2 *__restrict__ rows, int32_t *map)
+                                                            const double2 *__restrict__ U, double diag,
+                                                            double2 *__restrict__ rows, int32_t *map, int *info,
+                                                            int stamp)
 {
     const int s = blockIdx.x * 256 + threadIdx.x;
-    if (s >= g.V || bidx[s] >= 0 || map[s] >= 0) return;
-    bool bad = false;
-#pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        const double2 b = rows[fidx(s, 0, c, 1)];
-        const double den = b.x * b.x + b.y * b.y;
-        bad = bad || !(den > 0.0 && isfinite(den));
-    }
-    map[s] = bad ? kBadRow : -1;
-}
-
-// *linked = 1 if a boundary site has a neighbour with t != 0: one on the
-// boundary, or a kBadRow site
-__global__ void __launch_bounds__(256) boundary_links_kernel(Geom g, const int32_t *__restrict__ site, int nbnd,
-                                                             const int32_t *__restrict__ map, int *linked)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= nbnd) return;
-    const int s = site[j];
+    if (s >= g.V || bidx[s] >= 0) return;
     const SiteGeo q = site_geo(s, g);
-    bool b = false;
+    cpx<double> acc[12];
 #pragma unroll
+    for (int c = 0; c < 12; ++c) acc[c] = {diag, 0.0};
+    bool near = false;  // a neighbour is on the boundary
+#pragma unroll 1
     for (int mu = 0; mu < 4; ++mu) {
         int sp, sm;
         nbr(s, mu, q, g, sp, sm);
-        b = b || map[sp] != -1 || map[sm] != -1;
+        cpx<double> uf[9], ub[9], pf[12], pb[12];
+#pragma unroll
+        for (int e = 0; e < 9; ++e) {
+            const double2 f = U[lidx(s, mu, e)], w = U[lidx(sm, mu, e)];
+            uf[e] = {f.x, f.y};
+            ub[e] = {w.x, w.y};
+        }
+        const double vf = bidx[sp] < 0 ? 1.0 : 0.0, vb = bidx[sm] < 0 ? 1.0 : 0.0;
+        // (a neighbour's entry may be changing between its negative values)
+        near = near || map[sp] >= 0 || map[sm] >= 0;
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            pf[c] = {vf, 0.0};
+            pb[c] = {vb, 0.0};
+        }
+        switch (mu) {
+        case 0: hop_math<0, true>(acc, pf, uf); hop_math<0, false>(acc, pb, ub); break;
+        case 1: hop_math<1, true>(acc, pf, uf); hop_math<1, false>(acc, pb, ub); break;
+        case 2: hop_math<2, true>(acc, pf, uf); hop_math<2, false>(acc, pb, ub); break;
+        default: hop_math<3, true>(acc, pf, uf); hop_math<3, false>(acc, pb, ub); break;
+        }
     }
-    if (b) *linked = 1;
+    bool t_set = map[s] >= 0;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) rows[fidx(s, 0, c, 1)] = make_double2(acc[c].re, acc[c].im);
+    if (!t_set) {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const double den = acc[c].re * acc[c].re + acc[c].im * acc[c].im;
+            t_set = t_set || !(den > 0.0 && isfinite(den));
+        }
+        map[s] = t_set ? kBadRow : -1;
+    }
+    if (t_set && near) info[1] = stamp;
 }
 
 // t = a / b as the formula divides
@@ -163,11 +182,13 @@ __global__ void __launch_bounds__(256) boundary_source_kernel(Geom g, const doub
                                                               const int32_t *__restrict__ bidx, int nb,
                                                               const double2 *__restrict__ U,
                                                               const double2 *__restrict__ rows,
-                                                              const int32_t *__restrict__ site, int nbnd,
-                                                              double diag, double inv_d, double2 *__restrict__ t,
+                                                              const int32_t *__restrict__ site, int most,
+                                                              const int *__restrict__ info, double diag,
+                                                              double inv_d, double2 *__restrict__ t,
                                                               double2 *__restrict__ p, int nrhs)
 {
     __shared__ double2 lds[4][64 * kSpinorRow];
+    const int nbnd = info ? info[0] : most;
     const int nsb = (nbnd + 255) >> 8;
     const ItemRange it = xcd_items(nsb * nrhs);
     for (int w = it.begin; w < it.end; w += it.step) {
@@ -206,10 +227,11 @@ __global__ void __launch_bounds__(256) boundary_source_kernel(Geom g, const doub
 __global__ void __launch_bounds__(256) boundary_apply_kernel(Geom g, const double2 *__restrict__ U,
                                                              const double2 *__restrict__ rows,
                                                              const int32_t *__restrict__ site,
-                                                             const int32_t *__restrict__ map, int nbnd,
-                                                             double diag, double inv_d,
+                                                             const int32_t *__restrict__ map, int most,
+                                                             const int *__restrict__ info, double diag, double inv_d,
                                                              const double2 *__restrict__ t, double2 *p, int nrhs)
 {
+    const int nbnd = info ? info[0] : most;
     const int nsb = (nbnd + 255) >> 8;
     const ItemRange it = xcd_items(nsb * nrhs);
     for (int w = it.begin; w < it.end; w += it.step) {
@@ -270,16 +292,25 @@ __global__ void __launch_bounds__(256) boundary_apply_kernel(Geom g, const doubl
 
 // y_b = [D w]_b, w = x_b on the coarse sites and -p on the boundary: every
 // neighbour of a coarse site is one or the other.  64 coarse sites and one RHS
-// per workgroup, a hop per wavefront (split.h), RHS fastest.
+// per workgroup, a hop per wavefront (split.h), RHS fastest.  With info, its values
+// also go to the pinned words `host` (see ApproxArgs).
 __global__ void __launch_bounds__(kSplitThreads) boundary_coarse_kernel(Geom g, const double2 *__restrict__ xb,
                                                                         const int32_t *__restrict__ qsites,
                                                                         const int32_t *__restrict__ bidx, int nb,
                                                                         const int32_t *__restrict__ map,
                                                                         const double2 *__restrict__ U, double diag,
                                                                         const double2 *__restrict__ p,
-                                                                        double2 *__restrict__ yb, int nrhs)
+                                                                        double2 *__restrict__ yb, int nrhs,
+                                                                        const int *__restrict__ info, int *host,
+                                                                        int stamp)
 {
     __shared__ HopSums<double> sums;
+    if (info && blockIdx.x == 0 && threadIdx.x == 0) {
+        __hip_atomic_store(host, info[0] + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (stamp)
+            __hip_atomic_store(host + 1, info[1] == stamp ? stamp : -stamp, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int nkb = (nb + 63) >> 6;
     const ItemRange it = xcd_items(nkb * nrhs);
@@ -337,30 +368,23 @@ static inline int round8_grid(long n)
     return (int)std::max<long>(8, (n + 7) / 8 * 8);
 }
 
-int boundary_blocks(const Geom &g) { return (g.V + 255) / 256; }
+int boundary_blocks(const Geom &g) { return (g.V + kBoundaryBlock - 1) / kBoundaryBlock; }
 
 hipError_t launch_boundary_build(const Geom &g, const int32_t *bidx, int *count, int32_t *site, int32_t *map,
-                                 hipStream_t st)
+                                 int *info, hipStream_t st)
 {
     const int n = boundary_blocks(g);
-    hipLaunchKernelGGL(boundary_count_kernel, dim3(n), dim3(256), 0, st, g, bidx, count);
-    hipLaunchKernelGGL(boundary_scan_kernel, dim3(1), dim3(1024), 0, st, count, n);
-    hipLaunchKernelGGL(boundary_fill_kernel, dim3(n), dim3(256), 0, st, g, bidx, (const int *)count, site, map);
+    hipLaunchKernelGGL(boundary_count_kernel, dim3(n), dim3(kBoundaryBlock), 0, st, g, bidx, count, info);
+    hipLaunchKernelGGL(boundary_fill_kernel, dim3(n), dim3(kBoundaryBlock), 0, st, g, bidx, (const int *)count, site,
+                       map, info);
     return hipGetLastError();
 }
 
-hipError_t launch_boundary_rows(const Geom &g, const int32_t *bidx, const void *rows, int32_t *map, hipStream_t st)
+hipError_t launch_boundary_rows(const Geom &g, const int32_t *bidx, const void *U, double diag, void *rows,
+                                int32_t *map, int *info, int stamp, hipStream_t st)
 {
-    hipLaunchKernelGGL(boundary_rows_kernel, dim3(boundary_blocks(g)), dim3(256), 0, st, g, bidx,
-                       (const double2 *)rows, map);
-    return hipGetLastError();
-}
-
-hipError_t launch_boundary_links(const Geom &g, const int32_t *site, int nbnd, const int32_t *map, int *linked,
-                                 hipStream_t st)
-{
-    if (nbnd < 1) return hipSuccess;
-    hipLaunchKernelGGL(boundary_links_kernel, dim3((nbnd + 255) / 256), dim3(256), 0, st, g, site, nbnd, map, linked);
+    hipLaunchKernelGGL(boundary_rows_kernel, dim3((g.V + 255) / 256), dim3(256), 0, st, g, bidx, (const double2 *)U,
+                       diag, (double2 *)rows, map, info, stamp);
     return hipGetLastError();
 }
 
@@ -371,7 +395,7 @@ hipError_t launch_boundary_source(const ApproxArgs &a, hipStream_t st)
     const dim3 grd(round8_grid((long)((a.nbnd + 255) / 256) * a.nrhs)), blk(256);
 #define SRC(M)                                                                                              \
     hipLaunchKernelGGL(boundary_source_kernel<M>, grd, blk, 0, st, a.g, (const double2 *)a.xb, a.bidx, a.nb, \
-                       (const double2 *)a.U, (const double2 *)a.rows, a.site, a.nbnd, a.diag, 1.0 / a.diag, \
+                       (const double2 *)a.U, (const double2 *)a.rows, a.site, a.nbnd, a.info, a.diag, 1.0 / a.diag, \
                        (double2 *)a.t, (double2 *)a.p, a.nrhs)
     if (!a.rows) SRC(kNoRows);
     else if (a.linked) SRC(kTwoPass);
@@ -385,7 +409,7 @@ hipError_t launch_boundary_apply(const ApproxArgs &a, hipStream_t st)
     if (a.nrhs < 1 || a.nrhs > kMaxRhs || a.nbnd < 0 || !a.rows) return hipErrorInvalidValue;
     if (a.nbnd == 0 || !a.linked) return hipSuccess;
     hipLaunchKernelGGL(boundary_apply_kernel, dim3(round8_grid((long)((a.nbnd + 255) / 256) * a.nrhs)), dim3(256),
-                       0, st, a.g, (const double2 *)a.U, (const double2 *)a.rows, a.site, a.map, a.nbnd, a.diag,
+                       0, st, a.g, (const double2 *)a.U, (const double2 *)a.rows, a.site, a.map, a.nbnd, a.info, a.diag,
                        1.0 / a.diag, (const double2 *)a.t, (double2 *)a.p, a.nrhs);
     return hipGetLastError();
 }
@@ -395,7 +419,7 @@ hipError_t launch_boundary_coarse(const ApproxArgs &a, hipStream_t st)
     if (a.nrhs < 1 || a.nrhs > kMaxRhs || a.nb < 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(boundary_coarse_kernel, dim3(round8_grid((long)((a.nb + 63) / 64) * a.nrhs)),
                        dim3(kSplitThreads), 0, st, a.g, (const double2 *)a.xb, a.q, a.bidx, a.nb, a.map,
-                       (const double2 *)a.U, a.diag, (const double2 *)a.p, (double2 *)a.yb, a.nrhs);
+                       (const double2 *)a.U, a.diag, (const double2 *)a.p, (double2 *)a.yb, a.nrhs, a.info, a.host, a.stamp);
     return hipGetLastError();
 }
 

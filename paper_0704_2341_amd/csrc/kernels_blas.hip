@@ -474,18 +474,6 @@ __global__ void __launch_bounds__(256) xmy_kernel(BlasShape sh, const double2 *x
 
 static bool shape_ok(const BlasShape &sh);
 
-// 1 on every rest-site dof (one field), 0 on the coarse sites
-__global__ void __launch_bounds__(256) rest_ones_kernel(BlasShape sh, const uint8_t *mask, double2 *o)
-{
-    SITE_LOOP_BEGIN(sh)
-    if (valid) {
-        const double v = mask[s] == 0 ? 1.0 : 0.0;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) o[fidx(s, 0, c, 1)] = make_double2(v, 0.0);
-    }
-    SITE_LOOP_END
-}
-
 template <int P>
 __global__ void __launch_bounds__(256) combine_kernel(BlasShape sh, CombineArgs a)
 {
@@ -520,17 +508,6 @@ hipError_t launch_combine(int prec, const BlasShape &sh, const CombineArgs &a, h
     case GRG_BF16: hipLaunchKernelGGL(combine_kernel<GRG_BF16>, dim3(sh.grid), dim3(kBlasSB), 0, st, sh, a); break;
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_rest_ones(const Geom &g, const uint8_t *mask, void *o, hipStream_t st)
-{
-    BlasShape sh;
-    sh.g = g;
-    sh.nrhs = 1;
-    const int blocks = (g.V + 255) / 256;
-    sh.grid = blocks < 8 ? 8 : blocks > 2048 ? 2048 : (blocks + 7) / 8 * 8;
-    hipLaunchKernelGGL(rest_ones_kernel, dim3(sh.grid), dim3(kBlasSB), 0, st, sh, mask, (double2 *)o);
     return hipGetLastError();
 }
 

@@ -1955,48 +1955,26 @@ grg_status schur_apply_internal(grg_schur S, const double *xb, double *yb, int n
 namespace grg {
 
 // The boundary of the partition (the rest sites next to a coarse site), on
-// first use.  At most 8 sites per coarse one.
+// first use.
 static grg_status ensure_boundary(grg_schur S)
 {
-    if (S->n_bnd >= 0) return GRG_OK;
-    grg_lattice L = S->lat;
-    const Geom &g = L->g;
-    const int nblk = boundary_blocks(g);
-    const size_t most = (size_t)std::min<long>(8L * S->nb, (long)g.V - S->nb);
-    int *count = nullptr;
-    auto give_up = [&](grg_status e) {
-        if (count) (void)hipFree(count);
-        if (S->bnd_site) (void)hipFree(S->bnd_site);
-        if (S->bnd_map) (void)hipFree(S->bnd_map);
-        S->bnd_site = S->bnd_map = nullptr;
-        return e;
-    };
-    if (hipMalloc(&S->bnd_site, sizeof(int32_t) * most) != hipSuccess) {
-        S->bnd_site = nullptr;
-        return set_error("boundary list: hipMalloc failed"), GRG_ENOMEM;
-    }
-    if (hipMalloc(&S->bnd_map, sizeof(int32_t) * g.V) != hipSuccess) {
-        S->bnd_map = nullptr;
-        return set_error("boundary map: hipMalloc failed"), give_up(GRG_ENOMEM);
-    }
-    if (hipMalloc(&count, sizeof(int) * (nblk + 1)) != hipSuccess) {
-        count = nullptr;
-        return set_error("boundary count: hipMalloc failed"), give_up(GRG_ENOMEM);
-    }
-    int n = 0;
-    hipError_t e = launch_boundary_build(g, S->d_bidx, count, S->bnd_site, S->bnd_map, L->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&n, count + nblk, sizeof(int), hipMemcpyDeviceToHost, L->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-    if (e != hipSuccess) return set_error("boundary list: %s", hipGetErrorString(e)), give_up(GRG_EHIP);
-    (void)hipFree(count);
-    S->n_bnd = n;
+    if (S->bnd_built) return GRG_OK;
+    GRG_TRY_HIP(launch_boundary_build(S->lat->g, S->d_bidx, S->bnd_count, S->bnd_site, S->bnd_map, S->bnd_info,
+                                      S->lat->stream));
+    S->bnd_built = true;
     return GRG_OK;
 }
 
-static grg_status approx_args(grg_schur S, const double *xb, double *yb, int nrhs, const void *rows, ApproxArgs &a)
+// stamp: the rows' (with rows)
+static grg_status approx_args(grg_schur S, const double *xb, double *yb, int nrhs, const void *rows, int stamp,
+                              ApproxArgs &a)
 {
     grg_lattice L = S->lat;
     GRG_TRY(unoverlapped_xb(S, &xb, yb, nrhs));
+    // what an earlier call's words say, whole or not there yet
+    const volatile int *w = S->h_bnd;
+    const int count = w[0] - 1, link = w[1];
+    const bool known = count >= 0 && (!rows || link == stamp || link == -stamp);
     a.g = L->g;
     a.xb = xb;
     a.yb = yb;
@@ -2005,14 +1983,17 @@ static grg_status approx_args(grg_schur S, const double *xb, double *yb, int nrh
     a.nb = S->nb;
     a.site = S->bnd_site;
     a.map = S->bnd_map;
-    a.nbnd = S->n_bnd;
+    a.nbnd = known ? count : S->bnd_most;
     a.U = L->U[GRG_FP64];
     a.rows = rows;
-    a.linked = S->bnd_linked;
+    a.linked = rows && link == -stamp ? 0 : 1;
     a.diag = 4.0 + S->m0;
     a.t = S->t64;  // V sites' room; the boundary has fewer
     a.p = S->x64;
     a.nrhs = nrhs;
+    a.info = known ? nullptr : S->bnd_info;
+    a.host = S->h_bnd;
+    a.stamp = rows ? stamp : 0;
     return GRG_OK;
 }
 
@@ -2024,7 +2005,7 @@ grg_status diag_schur_apply_internal(grg_schur S, const double *xb, double *yb, 
     hipStream_t st = S->lat->stream;
     GRG_TRY(ensure_boundary(S));
     ApproxArgs a;
-    GRG_TRY(approx_args(S, xb, yb, nrhs, nullptr, a));
+    GRG_TRY(approx_args(S, xb, yb, nrhs, nullptr, 0, a));
     GRG_TRY_HIP(launch_boundary_source(a, st));
     GRG_TRY_HIP(launch_boundary_coarse(a, st));
     return GRG_OK;
@@ -2047,20 +2028,15 @@ grg_status reusken_apply_internal(grg_schur S, const double *xb, double *yb, int
         return GRG_ENOMEM;
     }
     GRG_TRY(ensure_boundary(S));
+    const int stamp = L->gauge_version + 1;
     if (S->dt_version != L->gauge_version) {
-        GRG_TRY_HIP(launch_rest_ones(g, S->d_mask, S->t64, st));
-        GRG_TRY(run_dslash(S, GRG_FP64, S->t64, S->dt64, 0, 1, nullptr));
-        GRG_TRY_HIP(launch_boundary_rows(g, S->d_bidx, S->dt64, S->bnd_map, st));
-        int *linked = S->active;  // (set by every solve before it is read)
-        GRG_TRY_HIP(launch_fill_zero(linked, sizeof(int), st));
-        GRG_TRY_HIP(launch_boundary_links(g, S->bnd_site, S->n_bnd, S->bnd_map, linked, st));
-        GRG_TRY_HIP(hipMemcpyAsync(S->h_buf, linked, sizeof(int), hipMemcpyDeviceToHost, st));
-        GRG_TRY_HIP(hipStreamSynchronize(st));
-        memcpy(&S->bnd_linked, S->h_buf, sizeof(int));
+        StencilTimer ev(S, GRG_FP64);
+        GRG_TRY_HIP(launch_boundary_rows(g, S->d_bidx, L->U[GRG_FP64], 4.0 + S->m0, S->dt64, S->bnd_map, S->bnd_info,
+                                         stamp, st));
         S->dt_version = L->gauge_version;
     }
     ApproxArgs a;
-    GRG_TRY(approx_args(S, xb, yb, nrhs, S->dt64, a));
+    GRG_TRY(approx_args(S, xb, yb, nrhs, S->dt64, stamp, a));
     GRG_TRY_HIP(launch_boundary_source(a, st));
     GRG_TRY_HIP(launch_boundary_apply(a, st));
     GRG_TRY_HIP(launch_boundary_coarse(a, st));

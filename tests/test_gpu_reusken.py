@@ -7,7 +7,7 @@ with its free-field spectrum in closed form."""
 import numpy as np
 import pytest
 
-from grg_inputs import gaussian_vectors
+from grg_inputs import gaussian_vectors, su3_links
 from oracle import dense, matfree
 
 from gpu_support import Lattice, rel_err, to_dev, to_host
@@ -258,4 +258,71 @@ def test_formula_order(linked):
             checked += err.size
     assert checked == nrhs * len(src) * 2 * 24
     lat.grg.grg_schur_destroy(h)
+    lat.close()
+
+
+@pytest.mark.parametrize("dims,kind,inv", [((8, 8, 8, 8), "I", False), ((8, 6, 4, 10), "II", True),
+                                           ((16, 16, 16, 16), "I", False), ((2, 4, 2, 2), "I", True)])
+def test_first_calls(dims, kind, inv):
+    """A handle's first call and the first on a new gauge field (whose row sums may
+    couple sites that the last one's did not) do not know yet how many boundary sites
+    there are, nor whether any are linked: to the bits of a call that does."""
+    import torch
+
+    lat = Lattice(dims, 0.5, 77)
+    grg, nrhs = lat.grg, 3
+    q, nb = grg.grg_permutation_block(dims, 1 if kind == "I" else 2, inv)
+    x = to_dev(gaussian_vectors(12 * nb, nrhs, 77))
+    links2 = su3_links(dims, 0.5, 78)
+    applies = (grg.grg_reusken_apply, grg.grg_diag_schur_apply)
+
+    def twice(h, apply):
+        ys = []
+        for _ in range(2):
+            y = torch.empty_like(x)
+            apply(h, x, y, nrhs)
+            ys.append(y)
+        assert torch.equal(ys[0], ys[1])
+        return ys[0]
+
+    seen = {}
+    for order in (applies, applies[::-1]):
+        grg.grg_gauge_set(lat.h, lat.links)
+        h = grg.grg_schur_create(lat.h, -0.2, q, nb, grg.grg_solver_params_default(max_rhs=nrhs))
+        for field in (0, 1):
+            if field:
+                grg.grg_gauge_set(lat.h, links2)
+            for apply in order:
+                print(f"first call {dims} {kind} {inv} {apply.__name__} field {field}", flush=True)
+                y = twice(h, apply)
+                assert torch.equal(seen.setdefault((apply, field), y), y)
+        grg.grg_schur_destroy(h)
+    sample = to_host(x)
+    for field, links in ((0, lat.links), (1, links2)):
+        want = matfree.reusken_apply(links, dims, -0.2, q, nb, sample)
+        assert rel_err(to_host(seen[applies[0], field]), want) < 1e-12
+    lat.close()
+
+
+def test_first_calls_allocate_no_tables():
+    """The boundary's tables lie in the handle's own memory: the first call without
+    row sums allocates nothing on the device, the first one with them that field alone."""
+    import torch
+
+    dims = (24, 24, 24, 24)
+    lat = Lattice(dims, 0.5, 79)
+    grg = lat.grg
+    q, nb = grg.grg_permutation_block(dims, 1, False)
+    h = grg.grg_schur_create(lat.h, -0.2, q, nb, grg.grg_solver_params_default(max_rhs=1))
+    x = to_dev(gaussian_vectors(12 * nb, 1, 79))
+    y = torch.empty_like(x)
+    torch.cuda.synchronize()
+    free = [torch.cuda.mem_get_info()[0]]
+    for apply in (grg.grg_diag_schur_apply, grg.grg_reusken_apply):
+        apply(h, x, y, 1)
+        free.append(torch.cuda.mem_get_info()[0])
+    assert free[1] == free[0]
+    rows = lat.V * 12 * 16
+    assert rows <= free[1] - free[2] < rows + (1 << 21)  # (2 MiB: the allocator's unit)
+    grg.grg_schur_destroy(h)
     lat.close()

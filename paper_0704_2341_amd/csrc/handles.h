@@ -125,6 +125,7 @@ struct grg_schur_s {
     int bnd_most = 0;  // room for the list
     int *bnd_count = nullptr, *bnd_info = nullptr, *h_bnd = nullptr;
     bool bnd_built = false;
+    int n_bnd = -1, bnd_link = 0;  // those words as last read
     // even-odd reduced inner solve: mask per parity ([2][Vhs]), the parity of
     // the reduced system, and compact fields per inner precision: r, x, q
     // (reduced parity), w (other parity) and the preconditioned direction p

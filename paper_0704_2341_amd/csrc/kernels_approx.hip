@@ -174,21 +174,24 @@ __device__ __forceinline__ cpx<double> scaled(double c, cpx<double> v)
 //             all-even coarse set, where this saves writing t and three more
 //             passes over the boundary: S~_bb at 32^4 with 12 RHS 1.18 ms in
 //             two passes)
+// FIRST: the number of sites, and which of the last two forms, from info (a variant
+// of its own: looking there costs every call 0.3 us).
 // Work items (256 boundary sites, RHS), RHS fastest: the RHS share the links
 // in L2.
 enum { kNoRows = 0, kTwoPass = 1, kOnePass = 2 };
-template <int MODE>
+template <int MODE, bool FIRST>
 __global__ void __launch_bounds__(256) boundary_source_kernel(Geom g, const double2 *__restrict__ xb,
                                                               const int32_t *__restrict__ bidx, int nb,
                                                               const double2 *__restrict__ U,
                                                               const double2 *__restrict__ rows,
                                                               const int32_t *__restrict__ site, int most,
-                                                              const int *__restrict__ info, double diag,
+                                                              const int *__restrict__ info, int stamp, double diag,
                                                               double inv_d, double2 *__restrict__ t,
                                                               double2 *__restrict__ p, int nrhs)
 {
     __shared__ double2 lds[4][64 * kSpinorRow];
-    const int nbnd = info ? info[0] : most;
+    const int nbnd = FIRST ? info[0] : most;
+    const bool two = MODE == kTwoPass && (!FIRST || info[1] == stamp);
     const int nsb = (nbnd + 255) >> 8;
     const ItemRange it = xcd_items(nsb * nrhs);
     for (int w = it.begin; w < it.end; w += it.step) {
@@ -211,8 +214,9 @@ __global__ void __launch_bounds__(256) boundary_source_kernel(Geom g, const doub
                 pv = {acc[c].re * inv_d, acc[c].im * inv_d};
             } else {
                 const cpx<double> tv = row_divide(make_double2(acc[c].re, acc[c].im), rows[fidx(s, 0, c, 1)]);
-                if constexpr (MODE == kTwoPass) t[i] = make_double2(tv.re, tv.im);
-                if constexpr (MODE == kOnePass) {
+                if (two) {
+                    t[i] = make_double2(tv.re, tv.im);
+                } else {
                     const cpx<double> z = scaled(diag, tv);
                     pv = {minus_w(acc[c].re, z.re, tv.re, inv_d), minus_w(acc[c].im, z.im, tv.im, inv_d)};
                 }
@@ -224,14 +228,22 @@ __global__ void __launch_bounds__(256) boundary_source_kernel(Geom g, const doub
 
 // p (y) <- -w on the boundary, z = D_rr t from the neighbours on it
 // (t = 0 off it, but for the kBadRow sites)
+template <bool FIRST>
 __global__ void __launch_bounds__(256) boundary_apply_kernel(Geom g, const double2 *__restrict__ U,
                                                              const double2 *__restrict__ rows,
                                                              const int32_t *__restrict__ site,
                                                              const int32_t *__restrict__ map, int most,
-                                                             const int *__restrict__ info, double diag, double inv_d,
+                                                             const int *__restrict__ info, int stamp, double diag,
+                                                             double inv_d,
                                                              const double2 *__restrict__ t, double2 *p, int nrhs)
 {
-    const int nbnd = info ? info[0] : most;
+    // this site's t, wanted again at the end (read twice, 762 -> 808 us for the whole
+    // S~_bb on the inverse Type II ordering at 32^4, 12 RHS; it does not fit the
+    // registers), and its neighbours, asked for all together
+    __shared__ double2 own[12][256];
+    __shared__ int nbj[8][256];
+    if (FIRST && info[1] != stamp) return;  // p is -w already
+    const int nbnd = FIRST ? info[0] : most;
     const int nsb = (nbnd + 255) >> 8;
     const ItemRange it = xcd_items(nsb * nrhs);
     for (int w = it.begin; w < it.end; w += it.step) {
@@ -241,19 +253,30 @@ __global__ void __launch_bounds__(256) boundary_apply_kernel(Geom g, const doubl
         const int s = site[j];
         const SiteGeo q = site_geo(s, g);
         cpx<double> acc[12];
+        int jk[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            int sp, sm;
+            nbr(s, k >> 1, q, g, sp, sm);
+            jk[k] = map[(k & 1) ? sm : sp];
+        }
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             const double2 v = t[fidx(j, r, c, nrhs)];
             acc[c] = {diag * v.x, diag * v.y};
+            own[c][threadIdx.x] = v;
         }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) nbj[k][threadIdx.x] = jk[k];
+        asm volatile("" ::: "memory");
 #pragma unroll 1
         for (int k = 0; k < 8; ++k) {
             const int mu = k >> 1;
+            const int jn = nbj[k][threadIdx.x];
+            if (jn == -1) continue;  // coarse, or t = 0
             int sp, sm;
             nbr(s, mu, q, g, sp, sm);
             const int n = (k & 1) ? sm : sp;
-            const int jn = map[n];
-            if (jn == -1) continue;  // coarse, or t = 0
             cpx<double> v[12], u[9];
             if (jn >= 0) {
 #pragma unroll
@@ -284,7 +307,7 @@ __global__ void __launch_bounds__(256) boundary_apply_kernel(Geom g, const doubl
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             const size_t i = fidx(j, r, c, nrhs);
-            const double2 y = p[i], tv = t[i];
+            const double2 y = p[i], tv = own[c][threadIdx.x];
             p[i] = make_double2(minus_w(y.x, acc[c].re, tv.x, inv_d), minus_w(y.y, acc[c].im, tv.y, inv_d));
         }
     }
@@ -292,8 +315,9 @@ __global__ void __launch_bounds__(256) boundary_apply_kernel(Geom g, const doubl
 
 // y_b = [D w]_b, w = x_b on the coarse sites and -p on the boundary: every
 // neighbour of a coarse site is one or the other.  64 coarse sites and one RHS
-// per workgroup, a hop per wavefront (split.h), RHS fastest.  With info, its values
-// also go to the pinned words `host` (see ApproxArgs).
+// per workgroup, a hop per wavefront (split.h), RHS fastest.  FIRST: the values of
+// info also go to the pinned words `host` (see ApproxArgs).
+template <bool FIRST>
 __global__ void __launch_bounds__(kSplitThreads) boundary_coarse_kernel(Geom g, const double2 *__restrict__ xb,
                                                                         const int32_t *__restrict__ qsites,
                                                                         const int32_t *__restrict__ bidx, int nb,
@@ -305,7 +329,7 @@ __global__ void __launch_bounds__(kSplitThreads) boundary_coarse_kernel(Geom g, 
                                                                         int stamp)
 {
     __shared__ HopSums<double> sums;
-    if (info && blockIdx.x == 0 && threadIdx.x == 0) {
+    if (FIRST && blockIdx.x == 0 && threadIdx.x == 0) {
         __hip_atomic_store(host, info[0] + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         if (stamp)
             __hip_atomic_store(host + 1, info[1] == stamp ? stamp : -stamp, __ATOMIC_RELAXED,
@@ -393,13 +417,15 @@ hipError_t launch_boundary_source(const ApproxArgs &a, hipStream_t st)
     if (a.nrhs < 1 || a.nrhs > kMaxRhs || a.nb < 1 || a.nbnd < 0) return hipErrorInvalidValue;
     if (a.nbnd == 0) return hipSuccess;
     const dim3 grd(round8_grid((long)((a.nbnd + 255) / 256) * a.nrhs)), blk(256);
-#define SRC(M)                                                                                              \
-    hipLaunchKernelGGL(boundary_source_kernel<M>, grd, blk, 0, st, a.g, (const double2 *)a.xb, a.bidx, a.nb, \
-                       (const double2 *)a.U, (const double2 *)a.rows, a.site, a.nbnd, a.info, a.diag, 1.0 / a.diag, \
-                       (double2 *)a.t, (double2 *)a.p, a.nrhs)
-    if (!a.rows) SRC(kNoRows);
-    else if (a.linked) SRC(kTwoPass);
-    else SRC(kOnePass);
+#define SRC(M, F)                                                                                              \
+    hipLaunchKernelGGL((boundary_source_kernel<M, F>), grd, blk, 0, st, a.g, (const double2 *)a.xb, a.bidx, a.nb, \
+                       (const double2 *)a.U, (const double2 *)a.rows, a.site, a.nbnd, a.info, a.stamp, a.diag, \
+                       1.0 / a.diag, (double2 *)a.t, (double2 *)a.p, a.nrhs)
+    if (!a.rows && a.info) SRC(kNoRows, true);
+    else if (!a.rows) SRC(kNoRows, false);
+    else if (a.info) SRC(kTwoPass, true);
+    else if (a.linked) SRC(kTwoPass, false);
+    else SRC(kOnePass, false);
 #undef SRC
     return hipGetLastError();
 }
@@ -408,18 +434,28 @@ hipError_t launch_boundary_apply(const ApproxArgs &a, hipStream_t st)
 {
     if (a.nrhs < 1 || a.nrhs > kMaxRhs || a.nbnd < 0 || !a.rows) return hipErrorInvalidValue;
     if (a.nbnd == 0 || !a.linked) return hipSuccess;
-    hipLaunchKernelGGL(boundary_apply_kernel, dim3(round8_grid((long)((a.nbnd + 255) / 256) * a.nrhs)), dim3(256),
-                       0, st, a.g, (const double2 *)a.U, (const double2 *)a.rows, a.site, a.map, a.nbnd, a.info, a.diag,
-                       1.0 / a.diag, (const double2 *)a.t, (double2 *)a.p, a.nrhs);
+    const dim3 grd(round8_grid((long)((a.nbnd + 255) / 256) * a.nrhs)), blk(256);
+#define APP(F)                                                                                              \
+    hipLaunchKernelGGL(boundary_apply_kernel<F>, grd, blk, 0, st, a.g, (const double2 *)a.U, (const double2 *)a.rows, \
+                       a.site, a.map, a.nbnd, a.info, a.stamp, a.diag, 1.0 / a.diag, (const double2 *)a.t,     \
+                       (double2 *)a.p, a.nrhs)
+    if (a.info) APP(true);
+    else APP(false);
+#undef APP
     return hipGetLastError();
 }
 
 hipError_t launch_boundary_coarse(const ApproxArgs &a, hipStream_t st)
 {
     if (a.nrhs < 1 || a.nrhs > kMaxRhs || a.nb < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(boundary_coarse_kernel, dim3(round8_grid((long)((a.nb + 63) / 64) * a.nrhs)),
-                       dim3(kSplitThreads), 0, st, a.g, (const double2 *)a.xb, a.q, a.bidx, a.nb, a.map,
-                       (const double2 *)a.U, a.diag, (const double2 *)a.p, (double2 *)a.yb, a.nrhs, a.info, a.host, a.stamp);
+    const dim3 grd(round8_grid((long)((a.nb + 63) / 64) * a.nrhs)), blk(kSplitThreads);
+#define COARSE(F)                                                                                           \
+    hipLaunchKernelGGL(boundary_coarse_kernel<F>, grd, blk, 0, st, a.g, (const double2 *)a.xb, a.q, a.bidx, a.nb, \
+                       a.map, (const double2 *)a.U, a.diag, (const double2 *)a.p, (double2 *)a.yb, a.nrhs, a.info, \
+                       a.host, a.stamp)
+    if (a.info) COARSE(true);
+    else COARSE(false);
+#undef COARSE
     return hipGetLastError();
 }
 

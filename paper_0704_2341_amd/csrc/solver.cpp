@@ -1971,10 +1971,13 @@ static grg_status approx_args(grg_schur S, const double *xb, double *yb, int nrh
 {
     grg_lattice L = S->lat;
     GRG_TRY(unoverlapped_xb(S, &xb, yb, nrhs));
-    // what an earlier call's words say, whole or not there yet
-    const volatile int *w = S->h_bnd;
-    const int count = w[0] - 1, link = w[1];
-    const bool known = count >= 0 && (!rows || link == stamp || link == -stamp);
+    if (S->n_bnd < 0 || (rows && S->bnd_link != stamp && S->bnd_link != -stamp)) {
+        // what an earlier call has left, whole or not there yet
+        const volatile int *w = S->h_bnd;
+        S->n_bnd = w[0] - 1;
+        S->bnd_link = w[1];
+    }
+    const bool known = S->n_bnd >= 0 && (!rows || S->bnd_link == stamp || S->bnd_link == -stamp);
     a.g = L->g;
     a.xb = xb;
     a.yb = yb;
@@ -1983,10 +1986,10 @@ static grg_status approx_args(grg_schur S, const double *xb, double *yb, int nrh
     a.nb = S->nb;
     a.site = S->bnd_site;
     a.map = S->bnd_map;
-    a.nbnd = known ? count : S->bnd_most;
+    a.nbnd = known ? S->n_bnd : S->bnd_most;
     a.U = L->U[GRG_FP64];
     a.rows = rows;
-    a.linked = rows && link == -stamp ? 0 : 1;
+    a.linked = rows && S->bnd_link == -stamp ? 0 : 1;
     a.diag = 4.0 + S->m0;
     a.t = S->t64;  // V sites' room; the boundary has fewer
     a.p = S->x64;

@@ -466,6 +466,26 @@ static void schur_free(grg_schur S)
     S->prof.stop.clear();
 }
 
+// Whether coarse sites have two coarse neighbours or more on average (of at most
+// 1024 of them, evenly spaced: the inverse orderings have about five, the others none).
+static bool coarse_adjacent(const Geom &g, const int32_t *q, int nb, const std::vector<int32_t> &bidx)
+{
+    const int n = std::min(nb, 1024);
+    long sum = 0;
+    for (int i = 0; i < n; ++i) {
+        const int s = q[(long)i * nb / n];
+        int st = 1, c = s;
+        for (int mu = 0; mu < 4; ++mu) {
+            const int x = c % g.L[mu];
+            sum += bidx[x + 1 == g.L[mu] ? s - x * st : s + st] >= 0;
+            sum += bidx[x == 0 ? s + (g.L[mu] - 1) * st : s - st] >= 0;
+            c /= g.L[mu];
+            st *= g.L[mu];
+        }
+    }
+    return sum >= 2L * n;
+}
+
 grg_status grg_schur_create(grg_lattice L, double m0, const int32_t *q, int32_t n_coarse,
                             const grg_solver_params *params, grg_schur *out)
 {
@@ -492,11 +512,13 @@ grg_status grg_schur_create(grg_lattice L, double m0, const int32_t *q, int32_t 
         mask[q[k]] = 1;
     }
     DeviceGuard dg(L->device);
+    const bool adjacent = coarse_adjacent(L->g, q, n_coarse, bidx);
     grg_schur S = new (std::nothrow) grg_schur_s();
     if (!S) return set_error("out of host memory"), GRG_ENOMEM;
     S->lat = L;
     S->m0 = m0;
     S->nb = n_coarse;
+    S->coarse_adjacent = adjacent;
     S->prm = prm;
     S->q_host.assign(q, q + V);
     const Geom &g = L->g;

@@ -172,7 +172,8 @@ int rb_apply_grid(const Geom &g);
 // kept corrections (inner precision prec) at the coarse sites' neighbours
 hipError_t launch_coarse_combine_apply(int prec, const Geom &g, const double *xb, const int32_t *qsites,
                                        const int32_t *bidx, int nb, const void *U64, double diag,
-                                       const CombineArgs &a, double *yb, int nrhs, hipStream_t st);
+                                       const CombineArgs &a, double *yb, int nrhs, hipStream_t st,
+                                       bool adjacent);
 hipError_t launch_eo_hop(int prec, const EoArgs &a, int grid, hipStream_t st);
 // compact field of parity par <-> full field (zero off that parity)
 hipError_t launch_eo_scatter(int prec, const Geom &g, int nrhs, int par, const void *src, void *dst,

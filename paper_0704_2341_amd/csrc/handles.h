@@ -117,6 +117,7 @@ struct grg_schur_s {
     // the lattice's gauge_version they were computed from (-1: not yet)
     void *dt64 = nullptr;
     int dt_version = -1;
+    bool coarse_adjacent = false;  // most coarse sites have coarse neighbours
     // the rest sites next to a coarse site, in lattice order, the map from sites
     // into that list (negative off it), and their scratch and device words (see
     // ApproxArgs; behind d_bidx, made on first use), and the words that a call

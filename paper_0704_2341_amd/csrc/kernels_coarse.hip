@@ -188,7 +188,8 @@ __device__ __forceinline__ void coarse_w(cpx<double> (&w)[12], int n, const doub
 // 64 coarse sites and one RHS per workgroup, a hop per wavefront (split.h):
 // each wavefront gathers one neighbour's corrections, so a site's eight
 // gathers wait together instead of one after the other.  RHS fastest, one
-// contiguous range per XCD: the RHS of a block share their links in L2.
+// contiguous range per XCD: the RHS of a block share their links in L2.  (Large
+// fields: coarse_combine_lane_kernel.)
 template <int P>
 __global__ void __launch_bounds__(kSplitThreads) coarse_combine_apply_kernel(Geom g, const double2 *__restrict__ xb,
                                                                              const int32_t *__restrict__ qsites,
@@ -234,16 +235,85 @@ __global__ void __launch_bounds__(kSplitThreads) coarse_combine_apply_kernel(Geo
     }
 }
 
+// The same with a lane per coarse site, its hops one after the other (to the same
+// bits), for fields that give enough wavefronts to wait with.
+template <int P>
+__global__ void __launch_bounds__(256) coarse_combine_lane_kernel(Geom g, const double2 *__restrict__ xb,
+                                                                  const int32_t *__restrict__ qsites,
+                                                                  const int32_t *__restrict__ bidx, int nb,
+                                                                  const double2 *__restrict__ U, double diag,
+                                                                  CombineArgs a, double2 *__restrict__ yb, int nrhs)
+{
+    const int nkb = (nb + 255) >> 8;
+    const ItemRange it = xcd_items(nkb * nrhs);
+    for (int wi = it.begin; wi < it.end; wi += it.step) {
+        const int kb = wi / nrhs, r = wi - kb * nrhs;
+        const int k = kb * 256 + (int)threadIdx.x;
+        if (k >= nb) continue;
+        const int s = qsites[k];
+        const SiteGeo q = site_geo(s, g);
+        cpx<double> acc[12];
+        const double2 *v = xb + ((size_t)r * nb + k) * 12;
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = {diag * v[c].x, diag * v[c].y};
+        // one hop per iteration (+x, -x, ..., -t): the FP64 operands of a hop
+        // are 84 registers, so the hops are not unrolled
+#pragma unroll 1
+        for (int h = 0; h < 8; ++h) {
+            const int mu = h >> 1;
+            int sp, sm;
+            nbr(s, mu, q, g, sp, sm);
+            cpx<double> w[12], u[9];
+            coarse_w<P>(w, (h & 1) ? sm : sp, xb, bidx, nb, r, nrhs, a);
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                const double2 x = U[lidx((h & 1) ? sm : s, mu, e)];
+                u[e] = {x.x, x.y};
+            }
+            switch (h) {
+            case 0: hop_math<0, true>(acc, w, u); break;
+            case 1: hop_math<0, false>(acc, w, u); break;
+            case 2: hop_math<1, true>(acc, w, u); break;
+            case 3: hop_math<1, false>(acc, w, u); break;
+            case 4: hop_math<2, true>(acc, w, u); break;
+            case 5: hop_math<2, false>(acc, w, u); break;
+            case 6: hop_math<3, true>(acc, w, u); break;
+            default: hop_math<3, false>(acc, w, u); break;
+            }
+        }
+        double2 *o = yb + ((size_t)r * nb + k) * 12;
+#pragma unroll
+        for (int c = 0; c < 12; ++c) o[c] = make_double2(acc[c].re, acc[c].im);
+    }
+}
+
+// A lane per coarse site where it is the faster form: by the wavefronts it gives,
+// and by whether most coarse sites are neighbours of others (their x_b is read, and
+// by several, which the eight wavefronts of a hop each would fetch anew).  BF16, us,
+// lane / hop per wavefront: neighbours (inverse orderings) 35 / 32 at 768 wavefronts,
+// 40 / 45 at 1024, 118 / 155 at 3888, 328 / 454 at 12288; none 78 / 54, 82 / 76, 367 /
+// 324, 660 / 701 (FP32 at 12288: 634 / 633 and 620 / 580).
+static bool coarse_lane_form(int prec, long waves, bool adjacent)
+{
+    return adjacent ? waves > 896 : prec == GRG_BF16 && waves > 8192;
+}
+
 hipError_t launch_coarse_combine_apply(int prec, const Geom &g, const double *xb, const int32_t *qsites,
                                        const int32_t *bidx, int nb, const void *U64, double diag,
-                                       const CombineArgs &a, double *yb, int nrhs, hipStream_t st)
+                                       const CombineArgs &a, double *yb, int nrhs, hipStream_t st, bool adjacent)
 {
     if (nrhs < 1 || nrhs > kMaxRhs || nb < 1 || a.n < 0 || a.n > kCorrPool) return hipErrorInvalidValue;
-    const long items = (long)(nb + 63) / 64 * nrhs;
-    dim3 grd((unsigned)std::max<long>(8, (std::min<long>(items, 2048) + 7) / 8 * 8)), blk(kSplitThreads);
+    const long waves = (long)(nb + 63) / 64 * nrhs;  // with a site per lane
+    const bool lane = coarse_lane_form(prec, waves, adjacent);
+    const long items = lane ? (long)(nb + 255) / 256 * nrhs : waves;
+    dim3 grd((unsigned)std::max<long>(8, (std::min<long>(items, 2048) + 7) / 8 * 8)), blk(lane ? 256 : kSplitThreads);
 #define CCA(PP)                                                                                        \
-    hipLaunchKernelGGL(coarse_combine_apply_kernel<PP>, grd, blk, 0, st, g, (const double2 *)xb, qsites, bidx, nb, \
-                       (const double2 *)U64, diag, a, (double2 *)yb, nrhs)
+    if (lane)                                                                                          \
+        hipLaunchKernelGGL(coarse_combine_lane_kernel<PP>, grd, blk, 0, st, g, (const double2 *)xb, qsites, bidx, nb, \
+                           (const double2 *)U64, diag, a, (double2 *)yb, nrhs);                        \
+    else                                                                                               \
+        hipLaunchKernelGGL(coarse_combine_apply_kernel<PP>, grd, blk, 0, st, g, (const double2 *)xb, qsites, bidx, nb, \
+                           (const double2 *)U64, diag, a, (double2 *)yb, nrhs)
     switch (prec) {
     case GRG_FP64: CCA(GRG_FP64); break;
     case GRG_FP32: CCA(GRG_FP32); break;

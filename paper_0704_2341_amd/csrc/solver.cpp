@@ -1831,7 +1831,7 @@ grg_status drr_solve_internal(grg_schur S, int nrhs, grg_solver_stats *stats, co
             GRG_TRY_HIP(hipMemcpyAsync(S->d_fk, S->h_fk, sizeof(double) * kCorrPool * kMaxRhs,
                                        hipMemcpyHostToDevice, st));
         GRG_TRY_HIP(launch_coarse_combine_apply(prec, g, xb, S->d_q, S->d_bidx, S->nb, L->U[GRG_FP64],
-                                                4.0 + S->m0, c, yb, nrhs, st));
+                                                4.0 + S->m0, c, yb, nrhs, st, S->coarse_adjacent));
         if (npool > 0) GRG_TRY_HIP(hipStreamSynchronize(st));  // h_fk is reused next
         *fused = true;
     } else {

@@ -245,3 +245,24 @@ def test_apply_in_place(order, nrhs):
                 assert torch.equal(yout, y), (inner, verify, shift)
             grg.grg_schur_destroy(h)
     lat.close()
+
+
+@pytest.mark.parametrize("inner", ["fp64", "fp32", "bf16"])
+def test_last_step_forms(inner):
+    """The apply's last step on the inverse orderings, whose coarse sites are
+    neighbours: 13 right-hand sides of 4032 coarse sites give 819 wavefronts and
+    take a hop per wavefront, 16 give 1008 and take a lane per site, with a ragged
+    last workgroup in either."""
+    dims = (14, 16, 18, 16)
+    lat = Lattice(dims, 0.5, 62)
+    s = lat.schur(-0.2, "II", True, tol=1e-12, inner=inner, inner_tol=1e-2 if inner == "bf16" else 1e-5, max_rhs=16)
+    xb = gaussian_vectors(12 * s.nb, 16, 62)
+    sample = [0, 12]
+    want, _, _ = matfree.schur_apply(lat.links, dims, -0.2, s.q, s.nb, xb[sample], restart=8, tol=1e-13)
+    for n in (13, 16):
+        print(f"last step {n} right-hand sides, {inner}", flush=True)
+        y, st = s.apply(xb[:n])
+        assert st["converged"]
+        assert rel_err(y[sample], want) < 1e-10, n
+    s.close()
+    lat.close()

@@ -54,9 +54,9 @@ struct grg_batch_s {
     int4 *dims = nullptr;
     double *diag = nullptr;
     long long *coff = nullptr;
-    void *b64 = nullptr, *x64 = nullptr, *r64 = nullptr, *t64 = nullptr;
+    void *b64 = nullptr, *x64 = nullptr, *r64 = nullptr;
     void *Uh = nullptr;  // the inner precision's links by side (reduced solve)
-    void *in_b = nullptr, *in_x = nullptr, *in_r = nullptr, *in_q = nullptr;
+    void *in_x = nullptr, *in_r = nullptr, *in_q = nullptr;  // (in_r, in_q: without the reduced solve)
     // the even-odd reduced inner solve (every extent even, params.eo) on compact
     // half-lattice fields (BatchHalf): per lattice the parity with fewer rest
     // sites carries the reduced system; coef holds per lattice [1, 0, d, 1 / d,
@@ -564,9 +564,7 @@ static void batch_free(grg_batch B)
     f(B->b64);
     f(B->x64);
     f(B->r64);
-    f(B->t64);
     f(B->Uh);
-    f(B->in_b);
     f(B->in_x);
     f(B->in_r);
     f(B->in_q);
@@ -761,8 +759,10 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
     al((void **)&B->dims, sizeof(int4) * count);
     al((void **)&B->diag, sizeof(double) * count);
     al((void **)&B->coff, sizeof(long long) * count);
-    for (void **p : {&B->b64, &B->x64, &B->r64, &B->t64}) al(p, f64);
-    for (void **p : {&B->in_b, &B->in_x, &B->in_r, &B->in_q}) al(p, fin);
+    for (void **p : {&B->b64, &B->x64, &B->r64}) al(p, f64);
+    al(&B->in_x, fin);
+    if (!eo)
+        for (void **p : {&B->in_r, &B->in_q}) al(p, fin);
     B->eo = eo;
     B->Vh = (int)Vh;
     const size_t fh = (size_t)Vh * nrhs * 12 * prec_bytes(prm.inner);
@@ -825,8 +825,9 @@ grg_status grg_batch_create(const grg_batch_member *m, int count, int nrhs,
     }
     GRG_TRY_HIP(hipStreamSynchronize(st));
 #undef UP
-    for (void *p : {B->b64, B->x64, B->r64, B->t64}) GRG_TRY_HIP(launch_fill_zero(p, f64, st));
-    for (void *p : {B->in_b, B->in_x, B->in_r, B->in_q}) GRG_TRY_HIP(launch_fill_zero(p, fin, st));
+    for (void *p : {B->b64, B->x64, B->r64}) GRG_TRY_HIP(launch_fill_zero(p, f64, st));
+    for (void *p : {B->in_x, B->in_r, B->in_q})
+        if (p) GRG_TRY_HIP(launch_fill_zero(p, fin, st));
     for (void *p : {B->hx, B->hr, B->hq, B->hw, B->hbq, B->heq})
         if (p) GRG_TRY_HIP(launch_fill_zero(p, fh, st));
     GRG_TRY_HIP(launch_fill_zero(B->dsc, B->dsc_bytes, st));
@@ -939,7 +940,8 @@ grg_status grg_batch_tune(grg_batch B)
     const int precs[2] = {GRG_FP64, B->prm.inner};
     for (int pi = 0; pi < (B->prm.inner == GRG_FP64 ? 1 : 2); ++pi) {
         const int prec = precs[pi];
-        void *in = prec == GRG_FP64 ? B->b64 : B->in_b, *out = prec == GRG_FP64 ? B->t64 : B->in_q;
+        // (b64, x64, r64 and in_x are written by every apply before they are read)
+        void *in = prec == GRG_FP64 ? B->b64 : B->in_x, *out = prec == GRG_FP64 ? B->r64 : B->x64;
         float best = 1e30f;
         int bsb = 64, brg = 1, bgrid = 0;
         for (int sb : {64, 128, 256}) {

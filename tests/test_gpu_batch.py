@@ -279,3 +279,36 @@ def test_two_steps_one_solution_update(inner, inner_tol):
         if want is None:
             want = y
         assert np.isfinite(y).all() and np.array_equal(y, want), (check, graph)
+
+
+@pytest.mark.parametrize("eo", [1, 0])
+def test_device_memory(eo):
+    """A batch holds the fields that its applies use, and tuning it uses those too:
+    three in FP64 and the inner correction, then the six halves of the reduced solve
+    or the residual and product of the full one; links in three precisions, those of
+    the reduced solve once more by side; and the partial sums."""
+    import torch
+    import paper_0704_2341_amd as grg
+
+    ensure_built()
+    dims, nrhs = (16, 16, 16, 16), 12
+    V = int(np.prod(dims))
+    ms = members([dict(dims=dims, m0=-0.1, seed=4100)], [(1, False)])
+    p = grg.grg_solver_params_default(tol=1e-9, inner="fp32", inner_tol=1e-4, check_every=2, eo=eo)
+    total = 12 * ms[0]["n_coarse"] * nrhs
+    xd = to_dev(gaussian_vectors(total, 1, 4101))
+    yd, zd = torch.empty_like(xd), torch.empty_like(xd)
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    b = grg.grg_batch_create(ms, nrhs, p)
+    grg.grg_batch_apply(b, xd, yd, use_graph=False)
+    held = free0 - torch.cuda.mem_get_info()[0]
+    field = V * 12 * nrhs
+    want = 3 * 16 * field + (8 + 6 * 4 if eo else 3 * 8) * field + 36 * V * (16 + 8 + 4 + (8 if eo else 0))
+    want += 2048 * nrhs * 3 * 8 + 2 * 16 * total
+    assert held <= want + (32 << 20), (held, want)  # (2 MiB units of some twenty allocations)
+    grg.grg_batch_tune(b)
+    assert free0 - torch.cuda.mem_get_info()[0] <= held + (2 << 20)
+    st = grg.grg_batch_apply(b, xd, zd, use_graph=False)
+    assert st["converged"] and rel_err(to_host(zd), to_host(yd)) < 1e-8
+    grg.grg_batch_destroy(b)

@@ -37,6 +37,8 @@ int partial_rows(const Geom &g, int nrhs);
 int dslash_grid(const Geom &g, int nrhs, int SB, int RG);
 DslashTune default_tune(const Geom &g, int prec, int nrhs);
 DslashTune canon_march_tune(const Geom &g, int prec, int nrhs);
+DslashTune split_tune(const Geom &g, int nrhs);
+bool canon_split_form(const Geom &g, int prec, int nrhs);
 DslashTune default_lane_tune(const Geom &g, int prec, int nrhs);
 bool launch_ok(const Geom &g, int prec, int nrhs, const DslashTune &t, bool dots);
 grg_status block_apply_internal(grg_schur S, int prec, int rows, int cols, const double *in,
@@ -290,7 +292,7 @@ DiracForm dirac_form(grg_lattice L, int precision, const double *in, const doubl
     const size_t n = (size_t)nrhs * L->g.V * 24;
     if (in < out + n && out < in + n) return kDiracStaged;
     if (canon_march_tune(L->g, precision, nrhs).valid) return kDiracMarch;
-    return default_tune(L->g, precision, nrhs).split == kSplitForm ? kDiracSplit : kDiracStaged;
+    return canon_split_form(L->g, precision, nrhs) ? kDiracSplit : kDiracStaged;
 }
 
 // stage: the packed input's tiles (kDiracStaged)
@@ -307,7 +309,7 @@ grg_status dirac_apply_launch(grg_lattice L, double m0, int precision, DiracForm
     a.g = L->g;
     a.nrhs = nrhs;
     const DslashTune t = form == kDiracStaged  ? default_lane_tune(L->g, precision, nrhs)
-                         : form == kDiracSplit ? default_tune(L->g, precision, nrhs)
+                         : form == kDiracSplit ? split_tune(L->g, nrhs)
                                                : canon_march_tune(L->g, precision, nrhs);
     a.SB = t.SB;
     a.RG = t.RG;

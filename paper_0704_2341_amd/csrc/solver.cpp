@@ -73,21 +73,39 @@ DslashTune default_lane_tune(const Geom &g, int prec, int nrhs)
     return t;
 }
 
-// The smallest fields run a hop per wavefront instead (8^4, 1 RHS: FP64 8.0 us
-// against 10.7, BF16 6.6 against 9.3), up to where the one-lane-per-site form
-// has as many wavefronts to wait with (FP64 22.5 / 23.5 us at 1296 wavefronts,
-// 49.2 / 49.5 at 4096; FP32 34.4 / 35.5 at 4096, 71 / 65 at 8192; BF16 13.4 /
-// 13.5 at 1296, 19.8 / 17.2 at 2592).
-DslashTune default_tune(const Geom &g, int prec, int nrhs)
+// 64 sites of one RHS per workgroup, a hop per wavefront.
+DslashTune split_tune(const Geom &g, int nrhs)
 {
-    const long waves = field_waves(g, nrhs);
-    if (waves > (prec == GRG_FP64 ? 640 : prec == GRG_FP32 ? 4096 : 1024)) return default_lane_tune(g, prec, nrhs);
     DslashTune t;
     t.SB = kSplitSites;
     t.RG = 1;
     t.split = kSplitForm;
     t.grid = dslash_grid(g, nrhs, 64, 1);
     return t;
+}
+
+// The smallest fields run a hop per wavefront instead (8^4, 1 RHS: FP64 8.0 us
+// against 10.7, BF16 6.6 against 9.3), up to where the one-lane-per-site form
+// has as many wavefronts to wait with in the solves, with their fused sums
+// (BiCGstab on D_rr, us, a hop per wavefront / a lane per site: FP64 1716 / 1818 at
+// 512 wavefronts, 2048 / 1898 at 628, 2542 / 2371 at 948; FP32 2474 / 2536 at 1024,
+// 2655 / 2617 at 1296, 6650 / 5889 at 4096; BF16 1672 / 1736 at 628, 2040 / 1987 at 948,
+// 2241 / 2040 at 1024).
+DslashTune default_tune(const Geom &g, int prec, int nrhs)
+{
+    const long waves = field_waves(g, nrhs);
+    if (waves > (prec == GRG_FP64 ? 576 : prec == GRG_FP32 ? 1152 : 896)) return default_lane_tune(g, prec, nrhs);
+    return split_tune(g, nrhs);
+}
+
+// Whether an operator apply between canonical fields, without sums, takes the
+// hop-per-wavefront form, one launch, and not a lane per site between packing
+// and unpacking (D_rr, us, one launch / three: FP64 38.0 / 40.4 at 948
+// wavefronts, 47.6 / 49.1 at 1296, 62.1 / 58.9 at 2048; FP32 38.5 / 41.7 at 1296, 49.1 /
+// 47.8 at 2048, 76.3 / 69.0 at 4096; BF16 30.9 / 31.3 at 948, 37.6 / 36.1 at 1296).
+bool canon_split_form(const Geom &g, int prec, int nrhs)
+{
+    return field_waves(g, nrhs) <= (prec == GRG_BF16 ? 1024 : 1536);
 }
 
 // Whether the x-y-z slices, cut into tiles of 64 sites, fill at least `eighths` of
@@ -1857,8 +1875,9 @@ grg_status block_apply_internal(grg_schur S, int prec, int rows, int cols, const
     grg_lattice L = S->lat;
     const size_t n = (size_t)nrhs * L->g.V * 24;
     const DslashTune &tt = S->tune[prec][nrhs];
-    const DslashTune t = tt.valid ? tt : default_tune(L->g, prec, nrhs);
-    if (t.split == kSplitForm && t.march == 0 && !(in < out + n && out < in + n)) {
+    const bool split = tt.valid ? tt.split == kSplitForm && tt.march == 0 : canon_split_form(L->g, prec, nrhs);
+    if (split && !(in < out + n && out < in + n)) {
+        const DslashTune t = tt.valid ? tt : split_tune(L->g, nrhs);
         // the hop-per-wavefront form reads and writes the canonical fields
         DslashArgs a;
         a.in = in;

@@ -143,3 +143,34 @@ def test_marching_launch_ignores_split(prec):
         assert e.value.status == grg.GRG_EINVAL
     s.close()
     lat.close()
+
+
+@pytest.mark.parametrize("dims,nrhs", [((8, 8, 8, 9), 8), ((8, 8, 8, 8), 15), ((8, 8, 8, 18), 8), ((12, 16, 8, 16), 4)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_either_side_of_the_forms(dims, nrhs):
+    """576, 960, 1152 and 1536 wavefronts, and a RHS more: 576 and 1152 are the last that
+    the solves give a hop per wavefront in FP64 and FP32, 1536 (and 1024 in BF16) the
+    last that the applies between canonical fields do.  Sub-blocks to the bits of the
+    plain launch, and a solve whose residual meets its tolerance."""
+    import torch
+
+    lat = Lattice(dims, 0.5, 80)
+    grg = lat.grg
+    for n in (nrhs, nrhs + 1):
+        x = to_dev(gaussian_vectors(12 * lat.V, n, 80))
+        y, z = torch.empty_like(x), torch.empty_like(x)
+        order = np.arange(lat.V, dtype=np.int32)
+        coarse = order % 16 == 0
+        q, nb = np.concatenate([order[coarse], order[~coarse]]), int(coarse.sum())
+        for prec in ("fp64", "fp32", "bf16"):
+            print(f"{dims} x {n} {prec}", flush=True)
+            h = grg.grg_schur_create(lat.h, -0.2, q, nb, grg.grg_solver_params_default(
+                tol=1e-8, inner=prec, inner_tol=1e-2, method="bicgstab", eo=0, max_rhs=n))
+            st = grg.grg_drr_solve(h, x, z, n)
+            assert st["converged"] and st["true_rel_resid"] <= 1e-8
+            grg.grg_block_apply(h, prec, 0, -1, x, y, n)
+            grg.grg_schur_set_launch(h, prec, n, [64, 1, 0, 64, 0, 0])
+            grg.grg_block_apply(h, prec, 0, -1, x, z, n)
+            assert torch.equal(y, z), (prec, n)
+            grg.grg_schur_destroy(h)
+    lat.close()

@@ -189,9 +189,11 @@ grg_status grg_permutation_block(const int32_t dims[4], int type, int inverse, i
  * Figure 2 shows before and after blocking.  Computed in the given precision:
  * inputs and links are rounded to it (BF16 through FP32, round to nearest
  * even), the arithmetic is FP64, FP32 or FP32 on BF16 operands, and the result
- * is widened to FP64.  Uses a grow-only scratch of the lattice handle (one
- * field of nrhs in that precision, allocated on the first call that needs
- * more; the smallest fields need none).  GRG_EINVAL: null pointer, nrhs outside 1..16, bad precision, gauge
+ * is widened to FP64.  Runs on the canonical fields directly, or (in and out
+ * that overlap, lattices whose x-y-z slices leave many lanes of a 64-site tile
+ * empty) from a grow-only scratch of the lattice handle: one field of nrhs in
+ * that precision, allocated on the first call that needs more.
+ * GRG_EINVAL: null pointer, nrhs outside 1..16, bad precision, gauge
  * field not set, m0 not finite. */
 grg_status grg_dirac_apply(grg_lattice lat, double m0, int precision, const double *in,
                            double *out, int nrhs);
@@ -202,7 +204,7 @@ grg_status grg_dirac_apply(grg_lattice lat, double m0, int precision, const doub
  * its internal staging lives in a fixed scratch array of
  * GRG_NOALLOC_SCRATCH_BYTES per GPU that the library holds until the process
  * ends, so the call itself allocates nothing (the first call on a device
- * looks up that device's array once).  Needs
+ * looks up that device's array once).  Needs, whatever of it a call stages,
  *     2 * ceil256(12 * Vs * nrhs * b) <= GRG_NOALLOC_SCRATCH_BYTES,
  * b = 16, 8, 4 bytes for FP64, FP32, BF16 and Vs = V rounded up to a multiple
  * of 256 (e.g. 8^4 with 16 RHS in FP64, 16^4 with 1 RHS); larger requests

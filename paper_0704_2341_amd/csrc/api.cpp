@@ -365,7 +365,7 @@ grg_status grg_dirac_apply(grg_lattice L, double m0, int precision, const double
 }
 
 // ------------------------------------------------------------------ no-alloc D apply
-// The staging fields of grg_dirac_apply_noalloc live in this fixed array, one
+// The staging field of grg_dirac_apply_noalloc lives in this fixed array, one
 // copy per GPU, held until the process ends.  In host code `scratch` is only
 // the shadow of the device symbol; its device address is taken once per
 // device with hipGetSymbolAddress and only that address is passed on.
@@ -401,7 +401,9 @@ grg_status grg_dirac_apply_noalloc(grg_lattice L, double m0, int precision, cons
     if (precision < GRG_FP64 || precision > GRG_BF16) return set_error("bad precision"), GRG_EINVAL;
     if (!L->gauge_set) return set_error("gauge field not set"), GRG_EINVAL;
     if (!isfinite(m0)) return set_error("m0 not finite"), GRG_EINVAL;
-    // two fields, each starting on a 256-byte boundary
+    // the documented limit: two fields on 256-byte boundaries, though a call stages its
+    // input at most (in and out that overlap, or D not on the canonical fields): one
+    // limit whatever the form that a call takes
     const size_t bytes = (spinor_elems(L->g, nrhs) * prec_bytes(precision) + 255) & ~(size_t)255;
     if (2 * bytes > (size_t)GRG_NOALLOC_SCRATCH_BYTES)
         return set_error("dirac_apply_noalloc: %zu bytes of staging for %d RHS exceed the %u-byte scratch",
@@ -410,8 +412,8 @@ grg_status grg_dirac_apply_noalloc(grg_lattice L, double m0, int precision, cons
     DeviceGuard dg(L->device);
     void *base = nullptr;
     GRG_TRY(scratch_address(L->device, &base));
-    // every entry the stencil reads (sites < V of every RHS) is written by the
-    // pack first, so nothing left by an earlier call is read
+    // every entry of the array that the stencil reads (sites < V of every RHS) is
+    // written by the pack first, so nothing left by an earlier call is read
     GRG_TRY(dirac_apply_launch(L, m0, precision, dirac_form(L, precision, in, out, nrhs), in, out, nrhs, base));
     GRG_TRY_HIP(hipStreamSynchronize(L->stream));
     return GRG_OK;

@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(256) rb_apply_kernel(Geom g, const double2 *__
 #pragma unroll
             for (int c = 0; c < 12; ++c) {
                 // (past the caches, which keep x_b: 32^4, 12 RHS, BF16 pair: 0.93 ms against
-                // 1.00; its writes, 3 GB, bound it)
+                // 1.00, 4.2 TB/s of its 3.0 GB written and 0.9 fetched)
                 typedef double v2d __attribute__((ext_vector_type(2)));
                 __builtin_nontemporal_store(v2d{acc[c].re, acc[c].im}, (v2d *)(out + fidx(s, r, c, nrhs)));
                 n2 += acc[c].re * acc[c].re + acc[c].im * acc[c].im;

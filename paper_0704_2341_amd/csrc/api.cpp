@@ -471,10 +471,10 @@ static void schur_free(grg_schur S)
 }
 
 // Whether coarse sites have two coarse neighbours or more on average (of at most
-// 1024 of them, evenly spaced: the inverse orderings have about five, the others none).
+// 256 of them, evenly spaced: the inverse orderings have about five, the others none).
 static bool coarse_adjacent(const Geom &g, const int32_t *q, int nb, const std::vector<int32_t> &bidx)
 {
-    const int n = std::min(nb, 1024);
+    const int n = std::min(nb, 256);
     long sum = 0;
     for (int i = 0; i < n; ++i) {
         const int s = q[(long)i * nb / n];
